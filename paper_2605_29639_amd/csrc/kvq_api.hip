@@ -72,6 +72,34 @@ int ilog2(int x) {
   return s;
 }
 
+// Pieces the many-row kernel cuts every (sequence, kv head)'s walk over the context into, given how
+// many the workspace has room for.  Without a split a call launches `walks` workgroups of 128 query
+// rows, and one sequence's chunk of a prompt leaves most of the chip idle (512 tokens of 32 / 8
+// heads: 128 workgroups, where two run on each of 256 compute units).  The estimate below is in
+// microseconds, from measurements at head_dim 128: 2.6 per 64-token group and workgroup with two
+// of them on a compute unit, 0.6 of that with one, about 3 until a workgroup's first group is
+// consumed; splitting adds the second launch and writes and reads 64 KB per workgroup.  One
+// sequence's 512 tokens over 16384 cached ones (fp8, 32 / 8 heads): 427 us in one piece, 178 in
+// four with the merge; eight such chunks over 4096 (1024 workgroups, two full rounds) stay whole.
+int context_splits(int64_t walks, int64_t groups, int64_t room) {
+  const int64_t slots = auto_waves() / 4;
+  if (walks >= 4 * slots) return 1;
+  int best = 1;
+  double best_us = 0.0;
+  for (int64_t c = 1; c <= room && c <= kvq::kMaxContextSplits && (c == 1 || c * 2 <= groups); ++c) {
+    const int64_t n = walks * c, rest = n % slots;
+    if (c > 1 && n > 4 * slots) break;
+    const double rounds = (double)(n / slots) + (rest == 0 ? 0.0 : 2 * rest <= slots ? 0.6 : 1.0);
+    const double us = rounds * (3.0 + 2.6 * (double)((groups + c - 1) / c)) +
+                      (c > 1 ? 6.0 + 0.025 * (double)n : 0.0);
+    if (c == 1 || us < best_us) {
+      best = (int)c;
+      best_us = us;
+    }
+  }
+  return best;
+}
+
 // Everything the launch needs that depends only on host-side arguments.
 bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t num_q_heads,
                int32_t max_seq_len, int32_t chunk_tokens, int32_t shared_prefix_tokens,
@@ -145,6 +173,16 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
   plan->acc_floats = slot_rows * d->head_dim;
   plan->ml_floats = slot_rows * 2;
   plan->prefix_ints = ((size_t)batch + 2 + 3) & ~(size_t)3;  // prefix sums, prefix length
+  // A many-row call has the same workspace as if it went through the streaming kernel; the pieces
+  // of a split context beyond the first (whose rows go to `out`) use it, row by row of `out`.
+  plan->context_splits = 1;
+  if (batch > 0 && kvq::prefill_applies(rows, d->mode)) {
+    const int64_t out_rows = (int64_t)batch * q_len * num_q_heads;
+    const int64_t walks = (int64_t)batch * d->num_kv_heads *
+                          ((rows + kvq::kRowsPerWorkgroup - 1) / kvq::kRowsPerWorkgroup);
+    plan->context_splits = context_splits(walks, ((int64_t)max_seq_len + 63) / 64,
+                                          (int64_t)slot_rows / out_rows + 1);
+  }
   return true;
 }
 
@@ -400,6 +438,7 @@ int attn_call(const void* q, const void* cache, const float* scales,
   a.wave_clock = nullptr;
   a.shared_groups = plan.shared_groups;
   a.prefix_chunks = plan.prefix_chunks;
+  a.context_splits = plan.context_splits;
   const hipError_t e = kvq::launch_attn(a, (hipStream_t)stream);
   return e == hipSuccess ? KVQ_OK : KVQ_E_HIP;
 }

@@ -935,7 +935,7 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t stream) {
 #else
   constexpr bool stream_only = false, many_rows_kernel = true;
 #endif
-  if (many_rows_kernel && prefill_applies(a)) return launch_prefill(a, stream);
+  if (many_rows_kernel && prefill_applies(a.rows, a.mode)) return launch_prefill(a, stream);
   hipError_t e;
   if (a.shared_groups > 0 && !stream_only) {  // the shared prefix, read once for many sequences
 #ifdef KVQ_PROFILE

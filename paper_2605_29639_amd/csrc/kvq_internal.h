@@ -77,6 +77,8 @@ __host__ __device__ inline uint8_t stored_byte(uint8_t code, int mode) {
 }
 
 constexpr int kMaxPrefixChunks = 8;  // pieces a shared prefix is cut into at most
+constexpr int kRowsPerWorkgroup = 128;    // query rows a workgroup of the many-row kernel owns
+constexpr int kMaxContextSplits = 64;     // pieces that kernel's walk over the context is cut into at most
 
 struct AttnPlan {
   int32_t rows;            // (num_q_heads / num_kv_heads) * q_len query rows per kv head
@@ -90,6 +92,7 @@ struct AttnPlan {
   size_t prefix_ints;      // workspace: groups before each sequence and the prefix length (batch + 2, padded to 4)
   int32_t shared_groups;   // shared prefix in 64-token groups, 0 where the prefix kernel is not used
   int32_t prefix_chunks;   // pieces the prefix kernel cuts it into (>= 1)
+  int32_t context_splits;  // many-row kernel: pieces its walk over the context is cut into (>= 1)
 };
 
 struct AttnArgs {
@@ -111,6 +114,7 @@ struct AttnArgs {
   int32_t shared_groups;  // leading 64-token groups that all sequences' tables map to the same
                           // blocks (0: none, or a call the prefix kernel does not serve)
   int32_t prefix_chunks;  // pieces the prefix kernel cuts those groups into: one partial each
+  int32_t context_splits; // pieces the many-row kernel cuts a (sequence, kv head)'s groups into
   unsigned long long* wave_clock;  // measurement build: 8 clock readings per wavefront; else null
 };
 
@@ -119,7 +123,11 @@ hipError_t launch_write(const void* k, const void* v, const int64_t* slot_mappin
                         const kvq_cache_desc_t& desc, hipStream_t stream);
 hipError_t launch_attn(const AttnArgs& a, hipStream_t stream);
 // the kernel for 128 and more query rows per kv head (kvq_prefill.hip)
-bool prefill_applies(const AttnArgs& a);
+inline bool prefill_applies(int64_t rows, int mode) {
+  // (the group-scaled int4 format has no many-row kernel: its row groups go through the
+  // streaming kernel)
+  return rows >= kRowsPerWorkgroup && mode != KVQ_INT4_GROUP32;
+}
 hipError_t launch_prefill(const AttnArgs& a, hipStream_t stream);
 // the same kernel over a prefix all sequences share, rows of all sequences stacked; leaves
 // partials for the reduce (a.shared_groups > 0, a.prefix_chunks >= 1)

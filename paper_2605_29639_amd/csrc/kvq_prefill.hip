@@ -5,7 +5,8 @@
 // has to be shared is the dequantization: the streaming kernel converts a group's codes once
 // per 32 rows, this kernel once per 128.  A workgroup of four wavefronts owns 128 query rows of
 // one (sequence, kv head) and walks the context from position 0 to the last position any of its
-// rows may see (no split over the context, so no partials and no merge).  Per 64-token group
+// rows may see, or one of p.context_splits pieces of it where the call has too few such
+// workgroups to fill the chip (see merge_kernel below).  Per 64-token group
 // each wavefront loads a quarter of the K and V codes, converts them to f16 and puts them in
 // LDS in the order the matrix instruction wants its A operand (one 16-byte read per lane and
 // instruction, no bank conflicts); after a barrier every wavefront runs QK^T, the online
@@ -23,7 +24,7 @@ namespace kvq {
 namespace {
 
 constexpr int kWavesPerGroup = 4;
-constexpr int kRowsPerWorkgroup = kWavesPerGroup * 32;
+static_assert(kRowsPerWorkgroup == kWavesPerGroup * 32, "a wavefront owns two 16-row tiles");
 
 // minimum over the wavefront
 __device__ inline int wave_min_int(int v) {
@@ -80,9 +81,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
   // the eight XCDs in turn, each with an L2 of its own, and the row blocks of one (sequence,
   // kv head) read the same codes: they are placed on one XCD (workgroups x, x + 8, x + 16, ...)
   // so that the codes leave HBM once, not once per XCD.
-  int pair, rb;  // PREFIX: pair = (piece of the prefix, kv head)
+  int pair, rb;  // pair = (sequence, piece of its context, kv head); PREFIX: (piece of the prefix, kv head)
   {
-    const int pairs = (PREFIX ? p.prefix_chunks : p.batch) * H, id = blockIdx.x;
+    const int pairs = (PREFIX ? p.prefix_chunks : p.batch * p.context_splits) * H, id = blockIdx.x;
     if (pairs % 8 == 0) {
       const int x = id & 7, k = id >> 3;
       pair = x + 8 * (k / row_blocks);
@@ -106,11 +107,16 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
     n_min = 0;  // (set below, from the rows' own causal lengths)
   } else {
     b = pair / H;
+    if (p.context_splits > 1) {
+      chunk = b % p.context_splits;
+      b /= p.context_splits;
+    }
     L = p.seq_lens[b];
     const int r_last = min(p.rows, (rb + 1) * kRowsPerWorkgroup) - 1;
     const int n_max = L - p.q_len + r_last / G + 1;
-    g0 = 0;
-    ng = (n_max + 63) >> 6;
+    const int all = (n_max + 63) >> 6;
+    g0 = (int)((long long)chunk * all / p.context_splits);
+    ng = (int)((long long)(chunk + 1) * all / p.context_splits);
     n_min = wave_live ? L - p.q_len + r0 / G + 1 : L;  // shortest causal length here
   }
 
@@ -352,15 +358,15 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
   // ---- the walk: group g is consumed from half g % 2 while group g + 1 is converted into the
   // other half and group g + 2 is requested (indices past the end repeat the last group) ----
   Entries e_next, e_after;
-  {
+  if (g0 < ng) {  // (a context shorter than its number of pieces leaves some of them empty)
     Entries e0;
     fetch_entries(g0, e0);
     fetch_entries(min(g0 + 1, ng - 1), e_next);
     issue_loads(g0, e0);
+    publish(g0, 0);
+    issue_loads(min(g0 + 1, ng - 1), e_next);
+    fetch_entries(min(g0 + 2, ng - 1), e_after);
   }
-  publish(g0, 0);
-  issue_loads(min(g0 + 1, ng - 1), e_next);
-  fetch_entries(min(g0 + 2, ng - 1), e_after);
   __syncthreads();
   for (int g = g0; g < ng; ++g) {
     const int half = (g - g0) & 1;
@@ -401,27 +407,71 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
     }
     return;
   }
-  // ---- normalised rows ----
+  // ---- normalised rows: the first piece's (the only one's, without a split) go to `out`, the
+  // others' to the workspace, which holds rows in the order of `out`, one such array per piece ----
+  const size_t out_rows = (size_t)p.batch * p.q_len * p.num_q_heads;
+  float* dst = chunk == 0 ? p.out : p.ws_acc + (size_t)(chunk - 1) * out_rows * D;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     const float l = xor16_sum(l_run[nt]);
     const int r = r0 + nt * 16 + m16;
     if (r >= p.rows) continue;
     const int j = r / G, gi = r - j * G;
-    float* orow = p.out + (((size_t)b * p.q_len + j) * p.num_q_heads + (size_t)h * G + gi) * D;
-    const float inv = 1.0f / l;
+    const size_t row = ((size_t)b * p.q_len + j) * p.num_q_heads + (size_t)h * G + gi;
+    float* orow = dst + row * D;
+    float inv = 1.0f / l;
+    if (p.context_splits > 1) {  // a row may see nothing of a piece
+      inv = l > 0.0f ? inv : 0.0f;
+      if (g4 == 0)
+        p.ws_ml[(size_t)chunk * out_rows + row] =
+            l > 0.0f ? m_run[nt] + __builtin_amdgcn_logf(l) : -INFINITY;
+    }
 #pragma unroll
     for (int tt = 0; tt < DT; ++tt) *(floatx4*)(orow + 16 * tt + 4 * g4) = acc[nt][tt] * inv;
   }
 }
 
-}  // namespace
-
-bool prefill_applies(const AttnArgs& a) {
-  // (the group-scaled int4 format has no many-row kernel: its row groups go through the
-  // streaming kernel)
-  return a.rows >= kRowsPerWorkgroup && a.mode != KVQ_INT4_GROUP32;
+// ---- the pieces of a split context put together: out = sum_c w_c out_c / sum_c w_c with
+// w_c = 2^(lse_c), lse_c the base-2 logarithm of piece c's softmax denominator.  A thread owns four
+// channels of a row.  Memory-bound (every piece's rows read once, `out` written once), all loads of
+// up to four pieces in flight together. ----
+__global__ __launch_bounds__(256) void merge_kernel(float* __restrict__ out,
+                                                    const float* __restrict__ acc,
+                                                    const float* __restrict__ lse, int64_t rows,
+                                                    int quads_shift, int splits) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;  // (row, four channels)
+  const int64_t row = i >> quads_shift;
+  if (row >= rows) return;
+  const size_t stride = (size_t)rows << quads_shift;  // floatx4s per piece
+  const floatx4* __restrict__ pieces = (const floatx4*)acc + i;
+  floatx4 sum = ((const floatx4*)out)[i];
+  float M = lse[row], den = 1.0f;
+  for (int c0 = 1; c0 < splits; c0 += 4) {
+    floatx4 a[4];
+    float e[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int c = min(c0 + k, splits - 1);
+      a[k] = pieces[(size_t)(c - 1) * stride];
+      e[k] = c0 + k < splits ? lse[(size_t)c * rows + row] : -INFINITY;
+    }
+    const float top = fmaxf(fmaxf(fmaxf(e[0], e[1]), fmaxf(e[2], e[3])), M);
+    const float safe = top == -INFINITY ? 0.0f : top;
+    const float keep = __builtin_amdgcn_exp2f(M - safe);
+    sum *= keep;
+    den *= keep;
+    M = top;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float w = __builtin_amdgcn_exp2f(e[k] - safe);
+      sum += w * a[k];
+      den += w;
+    }
+  }
+  ((floatx4*)out)[i] = sum * (1.0f / den);
 }
+
+}  // namespace
 
 template <bool PREFIX>
 hipError_t launch_many_rows(const AttnArgs& a, int all_rows, int walks, hipStream_t stream) {
@@ -450,7 +500,14 @@ hipError_t launch_many_rows(const AttnArgs& a, int all_rows, int walks, hipStrea
 }
 
 hipError_t launch_prefill(const AttnArgs& a, hipStream_t stream) {
-  return launch_many_rows<false>(a, a.rows, a.batch, stream);
+  const hipError_t e = launch_many_rows<false>(a, a.rows, a.batch * a.context_splits, stream);
+  if (e != hipSuccess || a.context_splits == 1) return e;
+  const int64_t rows = (int64_t)a.batch * a.q_len * a.num_q_heads;
+  const int quads_shift = a.head_dim == 128 ? 5 : 4;
+  const int64_t blocks = ((rows << quads_shift) + 255) / 256;
+  hipLaunchKernelGGL(merge_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, a.out, a.ws_acc,
+                     a.ws_ml, rows, quads_shift, (int)a.context_splits);
+  return hipGetLastError();
 }
 
 // the shared groups of a decode or verification batch (a.shared_groups > 0), ahead of the

@@ -303,3 +303,18 @@ def test_shared_prefix_is_read_through_stacked_rows(mode, q_len, lens):
             else:
                 assert attn_err(hinted, want) <= TOL, (chunk, hint)
                 assert attn_err(hinted, plain.astype(np.float64)) <= 2e-4, (chunk, hint)
+
+
+@pytest.mark.parametrize("mode,D", [(m, 128) for m in MODES if m != W.MODE_INT4_GROUP] +
+                         [(W.MODE_INT8, 64), (W.MODE_FP8, 64)])
+@pytest.mark.parametrize("lens,q_len", [([2000, 41, 700], 40), ([64, 65, 128, 1], 33), ([5000], 130),
+                                        ([8191, 300], 64)])
+def test_many_query_rows_over_a_split_context(mode, D, lens, q_len):
+    """Calls of the many-row kernel with too few row blocks to fill the chip walk the context in
+    pieces that a second launch merges: contexts shorter than their number of pieces (empty
+    pieces), pieces a row sees nothing of, lengths around a group's edge, row blocks that are not
+    full.  The bound is the checker's; f16 probabilities give 1e-4 or less."""
+    lens = [max(l, q_len) for l in lens]
+    wl = W.custom("split", mode, lens, q_len, 8, 2, D, 16, seed=len(lens) + mode)
+    errs = check(wl)
+    assert max(errs) <= 5e-4
