@@ -986,6 +986,111 @@ __global__ __launch_bounds__(kWaves * 64) void write_int4_bulk_kernel(
 }
 
 // ---- unquantized cache: the rows are copied to their slots ---------------------------------
+// The copy is a transpose for V (a channel's eight tokens are 16 adjacent bytes), so a wavefront
+// takes a 16-token sub-block at a time: lane (c = lane % 16, g = lane / 16) loads the D / 16 channels
+// from c D / 16 on of four tokens.  K (tokens 4 i + g): the loaded piece goes out as it came, and a
+// store instruction fills a whole quad.  V (tokens 4 g + i): the four tokens of a channel become two
+// words, and one v_permlane16_swap_b32 per word pairs them with the neighbour row's four tokens, so
+// that every store is a whole 16-byte half-row.
+// Bound by memory: 30 k tokens of 8 heads x 128 (246 MB in and out) take 54 us, 4.5 TB/s; a wavefront
+// per (token, head) with 2-byte stores, the form a decode step's single tokens keep, took 153.
+
+// exchanges the odd rows of 16 lanes of a with the even rows of b
+__device__ inline void swap_rows(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+
+// Rows r_lo .. r_hi - 1 of the sub-block at block offset `base`; `src` is row r_lo's token.
+template <int D>
+__device__ inline void plain_subblock(const uint16_t* __restrict__ src, size_t tstride,
+                                      uint16_t* __restrict__ tile, int kv, int base, int r_lo,
+                                      int r_hi, int lane) {
+  constexpr int CH = D / 16;   // channels per lane
+  constexpr int W = CH / 2;    // words per lane and token
+  typedef uint32_t words __attribute__((ext_vector_type(W)));
+  const int c = lane & 15, g = lane >> 4;
+  words raw[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = kv ? 4 * g + i : 4 * i + g;
+    raw[i] = (r >= r_lo && r < r_hi)
+                 ? *(const words*)(src + (ptrdiff_t)(r - r_lo) * (ptrdiff_t)tstride + CH * c)
+                 : words{};
+  }
+  if (kv == 0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 4 * i + g;
+      if (r >= r_lo && r < r_hi) *(words*)(tile + k_elem16(base + r, CH * c, D)) = raw[i];
+    }
+    return;
+  }
+  // channel e's tokens 4 g, 4 g + 1 and 4 g + 2, 4 g + 3
+  uint32_t lo[CH], hi[CH];
+#pragma unroll
+  for (int e = 0; e < CH; ++e) {
+    const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;  // the halves the channel sits in
+    lo[e] = __builtin_amdgcn_perm(raw[1][e >> 1], raw[0][e >> 1], sel);
+    hi[e] = __builtin_amdgcn_perm(raw[3][e >> 1], raw[2][e >> 1], sel);
+  }
+  // even g: channels e of the first half of CH with tokens 0-7 of the half-row, odd g: the second
+#pragma unroll
+  for (int e = 0; e < CH / 2; ++e) {
+    swap_rows(lo[e], lo[e + CH / 2]);
+    swap_rows(hi[e], hi[e + CH / 2]);
+    const int first = 8 * (g >> 1);  // the half-row's first token
+    const int d = CH * c + (CH / 2) * (g & 1) + e;
+    uint16_t* half = tile + v_elem16(base + first, d, D);
+    const uint4 piece = make_uint4(lo[e], hi[e], lo[e + CH / 2], hi[e + CH / 2]);
+    if (first >= r_lo && first + 8 <= r_hi) {
+      *(uint4*)half = piece;
+    } else {  // the other slots keep their contents
+      const uint32_t w[4] = {piece.x, piece.y, piece.z, piece.w};
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+        if (first + t >= r_lo && first + t < r_hi) half[t] = (uint16_t)(w[t >> 1] >> (16 * (t & 1)));
+    }
+  }
+}
+
+// unit = (window of 16 consecutive tokens of the call, kv head, K|V): every run that starts in it
+template <int D>
+__global__ __launch_bounds__(kWaves * 64) void write_plain_bulk_kernel(
+    const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const int64_t* __restrict__ slot_mapping, int32_t num_tokens, uint16_t* __restrict__ cache,
+    int32_t H, int32_t bs) {
+  const int lane = threadIdx.x & 63;
+  const int64_t unit = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
+  const int windows = (num_tokens + 15) >> 4;
+  if (unit >= (int64_t)windows * H * 2) return;
+  const int kv = (int)(unit & 1);
+  const int h = (int)((unit >> 1) % H);
+  const int w0 = (int)((unit >> 1) / H) * 16;
+  bool first = false;
+  {
+    const int t = w0 + lane;
+    if (lane < 16 && t < num_tokens) {
+      const int64_t slot = slot_mapping[t];
+      if (slot >= 0) first = !(t > 0 && (slot & 15) > 0 && slot_mapping[t - 1] == slot - 1);
+    }
+  }
+  uint32_t starts = (uint32_t)__ballot(first);
+  while (starts) {
+    const int t0 = w0 + __builtin_ctz(starts);
+    starts &= starts - 1;
+    const int64_t slot0 = slot_mapping[t0];
+    const int so = (int)(slot0 & 15);
+    const bool cont = lane < 16 - so && t0 + lane < num_tokens && slot_mapping[t0 + lane] == slot0 + lane;
+    const int run = __builtin_ctz(~(uint32_t)__ballot(cont));
+    const int64_t blk = slot0 >> __builtin_ctz(bs);
+    plain_subblock<D>((kv ? v : k) + ((size_t)t0 * H + h) * D, (size_t)H * D,
+                      cache + tile_offset(blk, kv, h, H, bs, D), kv, (int)(slot0 & (bs - 1)) - so, so,
+                      so + run, lane);
+  }
+}
+
 // unit = (token, kv head, K|V); a lane moves D/64 adjacent channels.
 template <int D>
 __global__ __launch_bounds__(kWaves * 64) void write_plain_kernel(
@@ -1048,6 +1153,13 @@ hipError_t launch_write(const void* k, const void* v, const int64_t* slot_mappin
     else
       hipLaunchKernelGGL(write_int4_kernel<false>, dim3(grid), block, 0, stream, kk, vv, slot_mapping,
                          num_tokens, c, scales, desc.num_kv_heads, desc.block_size);
+  } else if (desc.mode == KVQ_BF16_PLAIN && bulk) {
+    if (desc.head_dim == 128)
+      hipLaunchKernelGGL((write_plain_bulk_kernel<128>), dim3(grid), block, 0, stream, kk, vv, slot_mapping,
+                         num_tokens, (uint16_t*)cache, desc.num_kv_heads, desc.block_size);
+    else
+      hipLaunchKernelGGL((write_plain_bulk_kernel<64>), dim3(grid), block, 0, stream, kk, vv, slot_mapping,
+                         num_tokens, (uint16_t*)cache, desc.num_kv_heads, desc.block_size);
   } else if (desc.mode == KVQ_BF16_PLAIN) {
     const unsigned g = (unsigned)(((int64_t)num_tokens * desc.num_kv_heads * 2 + kWaves - 1) / kWaves);
     if (desc.head_dim == 128)

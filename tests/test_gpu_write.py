@@ -352,3 +352,36 @@ def test_tokens_in_any_order_with_skips_anywhere(mode, num_tokens, bs):
                        cache, scales, desc)
     torch.cuda.synchronize()
     assert_pool_equal(None, fetch(cache, scales, desc), (oc, osc))
+
+
+@pytest.mark.parametrize("mode", ALL_MODES)
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("bs", [16, 32])
+@pytest.mark.parametrize("repeats", [1, 2])     # 816 tokens: per-run kernels; 1632: prefill kernels
+def test_every_run_of_a_sub_block(mode, D, bs, repeats):
+    """A run of every (start, length) a 16-token sub-block can hold, each in a block of its own over
+    a stale pool: whole and partial rows of the transposed V store, slots around the run kept, and
+    (block-scaled fp8) scales that grow over older codes."""
+    import torch
+    from paper_2605_29639_amd import kvq
+    skip_unsupported(mode, D)
+    H = 3
+    rng = np.random.default_rng(mode + 10 * D + bs + repeats)
+    runs = [(so, n) for so in range(16) for n in range(1, 17 - so)] * repeats
+    base = [i * bs + 16 * int(rng.integers(0, bs // 16)) for i in range(len(runs))]
+    slots = np.concatenate([b + so + np.arange(n) for b, (so, n) in zip(base, runs)]).astype(np.int64)
+    x = (rng.standard_normal((2, len(slots), H, D), dtype=np.float32) *
+         rng.choice([0.01, 1.0, 30.0], size=(2, len(slots), H, 1)).astype(np.float32))
+    k, v = W.to_bf16_bits(x[0]), W.to_bf16_bits(x[1])
+    desc = kvq.make_desc(mode, len(runs), bs, H, D)
+    oc, osc = oracle.alloc_cache(mode, len(runs), bs, H, D)
+    oc[:] = 0x5A
+    osc[:] = (0.07, 0.11) if mode == W.MODE_FP8_TENSOR else rng.choice([1e-3, 0.01, 3.0], size=osc.shape)
+    canon = torch.from_numpy(oc.view(np.int16) if oc.dtype == np.uint16 else oc).cuda()
+    cache = kvq.cache_from_canonical(canon, desc)
+    scales = torch.from_numpy(osc).cuda()
+    oracle.kv_quant_write(k, v, slots, oc, osc, mode)
+    kvq.kv_quant_write(bits_to_bf16_tensor(k), bits_to_bf16_tensor(v), torch.from_numpy(slots).cuda(),
+                       cache, scales, desc)
+    torch.cuda.synchronize()
+    assert_pool_equal(None, fetch(cache, scales, desc), (oc, osc))
