@@ -385,3 +385,97 @@ def test_every_run_of_a_sub_block(mode, D, bs, repeats):
                        cache, scales, desc)
     torch.cuda.synchronize()
     assert_pool_equal(None, fetch(cache, scales, desc), (oc, osc))
+
+
+@pytest.mark.parametrize("mode,D", [(W.MODE_INT8, 64), (W.MODE_INT4, 128), (W.MODE_FP8, 64)])
+def test_the_scale_of_every_bf16_absmax(mode, D):
+    """absmax / 127 (7, 448) rounded once to fp32, for every finite bf16 magnitude, through the
+    prefill kernel; every 40th one through the kernel of small calls as well."""
+    import torch
+    from paper_2605_29639_amd import kvq
+    amax = np.arange(0x7F80, dtype=np.uint16)
+    rows = np.zeros((len(amax), 1, D), dtype=np.uint16)
+    rows[:, 0, 5] = amax
+    rows[:, 0, 9] = 0x8000 | (amax // 2)
+    desc = kvq.make_desc(mode, len(amax), 16, 1, D)
+    slots = np.arange(len(amax), dtype=np.int64) * 16        # a block of its own for every row
+    oc, osc = oracle.alloc_cache(mode, len(amax), 16, 1, D)
+    oracle.kv_quant_write(rows, rows, slots, oc, osc, mode)
+    for some in (slice(None), slice(0, None, 40)):
+        cache, scales = kvq.alloc_cache(desc)
+        kvq.kv_quant_write(bits_to_bf16_tensor(rows[some]), bits_to_bf16_tensor(rows[some]),
+                           torch.from_numpy(slots[some]).cuda(), cache, scales, desc)
+        torch.cuda.synchronize()
+        got_c, got_s = fetch(cache, scales, desc)
+        assert_pool_equal(None, (got_c[some], got_s[some]), (oc[some], osc[some]))
+
+
+@pytest.mark.parametrize("mode,D", [(W.MODE_INT8, 128), (W.MODE_INT8, 64), (W.MODE_INT4, 128),
+                                    (W.MODE_INT4_GROUP, 128), (W.MODE_FP8, 128), (W.MODE_FP8, 64)])
+@pytest.mark.parametrize("some", [None, 60])     # prefill kernel, kernel of small calls
+def test_rounding_of_every_pair_of_mantissas(mode, D, some):
+    """x / s for every 8-bit mantissa of x under an absmax of every 8-bit mantissa and down to 2^-15 of
+    it: all the exact ties of absmax / 127 (7, 448) in a format, on whichever side the rounding of the
+    scale puts them, both signs; every row (int4 groups: every 32 channels; fp8: every block) has one
+    absmax."""
+    import torch
+    from paper_2605_29639_amd import kvq
+    G = 31 if mode == W.MODE_INT4_GROUP else D - 1          # values beside the absmax per scale
+    rows = []
+    for ma in range(128):
+        amax = 0x4080 + ma                                   # exponent of 4.0
+        x = [(0x4080 - 128 * e + m) | (0x8000 if (m + e) % 3 == 0 else 0)
+             for e in range(16) for m in range(128) if 0x4080 - 128 * e + m <= amax]
+        x += [0] * (-len(x) % (16 * G))                      # whole blocks of 16 tokens (fp8)
+        x = np.array(x, dtype=np.uint16).reshape(-1, G)
+        rows.append(np.concatenate([np.full((len(x), 1), amax, dtype=np.uint16), x], axis=1))
+    x = np.concatenate(rows)
+    if mode == W.MODE_INT4_GROUP:
+        x = x[: len(x) // 64 * 64].reshape(-1, 128)
+    T = len(x) // 16 * 16
+    x = np.ascontiguousarray(x[:T].reshape(T, 1, D))
+    if some:
+        pick = np.random.default_rng(mode).permutation(T // 16)[:some]
+        x = np.ascontiguousarray(x.reshape(-1, 16, 1, D)[pick].reshape(-1, 1, D))
+    T = len(x)
+    desc = kvq.make_desc(mode, T // 16, 16, 1, D)
+    slots = np.arange(T, dtype=np.int64)
+    oc, osc = oracle.alloc_cache(mode, T // 16, 16, 1, D)
+    oracle.kv_quant_write(x, x, slots, oc, osc, mode)
+    cache, scales = kvq.alloc_cache(desc)
+    for part in np.split(slots, range(960, T, 960)) if some else [slots]:
+        kvq.kv_quant_write(bits_to_bf16_tensor(x[part]), bits_to_bf16_tensor(x[part]),
+                           torch.from_numpy(part).cuda(), cache, scales, desc)
+    torch.cuda.synchronize()
+    assert_pool_equal(None, fetch(cache, scales, desc), (oc, osc))
+
+
+@pytest.mark.parametrize("D,bs", [(128, 16), (64, 32)])
+@pytest.mark.parametrize("scales_kv", [(0.25, 0.0125), (7.0 / 448, 8.75 / 448), (0.07, 1.0 / 3),
+                                       (0.75, 0.3359375), (1e-28, 2.0 ** -130), (1e37, 0.0)])
+def test_static_scales_of_every_kind(D, bs, scales_kv):
+    """Static scales that are powers of two, round decimals (many quotients just beside a tie), a bf16
+    number over 448 (rounded or not), short fractions (exact ties), near one third of a bf16 number, below
+    the normal range, huge and zero."""
+    import torch
+    from paper_2605_29639_amd import kvq
+    rng = np.random.default_rng(5)
+    T, mode = 1100, W.MODE_FP8_TENSOR
+    x = np.stack([rng.standard_normal((T, 2, D)) * min(max(s, 2.0 ** -130), 1e35) * rng.choice([0.003, 1.0, 90.0, 600.0], size=(T, 2, 1))
+                  for s in scales_kv]).astype(np.float32)
+    x = np.clip(x, -3e38, 3e38)
+    k, v = W.to_bf16_bits(x[0]), W.to_bf16_bits(x[1])
+    nblk = T // bs + 1
+    slots = np.arange(T, dtype=np.int64)
+    oc, osc = oracle.alloc_cache(mode, nblk, bs, 2, D)
+    osc[:] = np.array(scales_kv, dtype=np.float32)
+    oracle.kv_quant_write(k, v, slots, oc, osc, mode)
+    for n in (T, 500):                                       # prefill kernel, kernel of small calls
+        desc = kvq.make_desc(mode, nblk, bs, 2, D)
+        cache, scales = kvq.alloc_cache(desc)
+        scales.copy_(torch.from_numpy(osc))
+        for lo in range(0, T, n):
+            kvq.kv_quant_write(bits_to_bf16_tensor(k[lo:lo + n]), bits_to_bf16_tensor(v[lo:lo + n]),
+                               torch.from_numpy(slots[lo:lo + n]).cuda(), cache, scales, desc)
+        torch.cuda.synchronize()
+        assert_pool_equal(None, fetch(cache, scales, desc), (oc, osc))
