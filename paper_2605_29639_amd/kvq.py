@@ -130,20 +130,41 @@ def strerror(code):
     return lib().kvq_strerror(int(code)).decode()
 
 
+# A decode step makes two calls of a few microseconds of GPU work each, so what the marshalling below
+# costs counts: one token of one sequence took 26 us a step with a stream object looked up and an
+# argument object made for every tensor, now 18, of which 11.6 are the library's own calls and kernels.
+_torch_module = None
+
+
+def _torch():
+    """The torch module, imported by the first call that needs it."""
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
+
+
 def _stream(stream):
+    """The stream's handle: the given one, or that of the current stream of the current device."""
     if stream is not None:
-        return C.c_void_p(int(stream))
-    import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+        return int(stream)
+    c = _torch()._C
+    if hasattr(c, "_cuda_getCurrentRawStream"):   # (the stream object costs 3 us)
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    return _torch().cuda.current_stream().cuda_stream
 
 
 def _dev(t, dtype, name):
-    import torch
-    if t is not None and t.numel() == 0 and t.dtype == dtype:
-        return C.c_void_p(None)  # an empty tensor has no storage to point at
-    if not isinstance(t, torch.Tensor) or not t.is_cuda or t.dtype != dtype or not t.is_contiguous():
-        raise TypeError("%s must be a contiguous device tensor of %s" % (name, dtype))
-    return C.c_void_p(t.data_ptr())
+    """The address of a contiguous device tensor (None, a null pointer, for an empty tensor, which has no
+    storage to point at)."""
+    if isinstance(t, _torch().Tensor):
+        if t.dtype == dtype:
+            if t.numel() == 0:
+                return None
+            if t.is_cuda and t.is_contiguous():
+                return t.data_ptr()
+    raise TypeError("%s must be a contiguous device tensor of %s" % (name, dtype))
 
 
 def make_desc(mode, num_blocks, block_size, num_kv_heads, head_dim):
@@ -166,13 +187,13 @@ def alloc_cache(desc, device="cuda", zero=True):
     return cache, scales
 
 
-_pool_sizes = {}   # descriptor fields -> (cache bytes, scales bytes), as the library reports them
+_pool_sizes = {}   # a descriptor's bytes -> (cache bytes, scales bytes), as the library reports them
 
 
 def _check_pool(cache, scales, desc):
     """The cache and scales tensors have the sizes the library reports for the descriptor: a
     smaller buffer would be overrun on the device, which checks nothing."""
-    key = (desc.mode, desc.num_blocks, desc.block_size, desc.num_kv_heads, desc.head_dim)
+    key = bytes(desc)
     sizes = _pool_sizes.get(key)
     if sizes is None:
         sizes = _pool_sizes[key] = (lib().kvq_cache_bytes(desc), lib().kvq_scales_bytes(desc))
@@ -186,16 +207,17 @@ def _check_pool(cache, scales, desc):
 
 
 def kv_quant_write(k, v, slot_mapping, cache, scales, desc, stream=None, L=None):
-    import torch
-    rows = (k.shape[0], desc.num_kv_heads, desc.head_dim)
-    if tuple(k.shape) != rows or tuple(v.shape) != rows:
+    torch = _torch()
+    num_tokens = k.shape[0]
+    rows = (num_tokens, desc.num_kv_heads, desc.head_dim)
+    if k.shape != rows or v.shape != rows:
         raise ValueError("k and v must be [num_tokens, %d, %d], not %s and %s"
                          % (rows[1], rows[2], tuple(k.shape), tuple(v.shape)))
-    if tuple(slot_mapping.shape) != (k.shape[0],):
-        raise ValueError("slot_mapping must be [num_tokens] = [%d]" % k.shape[0])
+    if slot_mapping.shape != (num_tokens,):
+        raise ValueError("slot_mapping must be [num_tokens] = [%d]" % num_tokens)
     _check_pool(cache, scales, desc)
     rc = (L or lib()).kv_quant_write(_dev(k, torch.bfloat16, "k"), _dev(v, torch.bfloat16, "v"),
-                              _dev(slot_mapping, torch.int64, "slot_mapping"), k.shape[0],
+                              _dev(slot_mapping, torch.int64, "slot_mapping"), num_tokens,
                               _dev(cache, torch.uint8, "cache"),
                               _dev(scales, torch.float32, "scales"), C.byref(desc),
                               _stream(stream))
@@ -208,10 +230,11 @@ def _check_attn_shapes(q, cache, scales, desc, block_tables, seq_lens, q_len, ou
     if seq_lens.dim() != 1:
         raise ValueError("seq_lens must be [batch]")
     batch = seq_lens.shape[0]
-    if q.dim() != 3 or q.shape[0] != batch * q_len or q.shape[2] != desc.head_dim:
+    shape = q.shape
+    if len(shape) != 3 or shape[0] != batch * q_len or shape[2] != desc.head_dim:
         raise ValueError("q must be [batch * q_len, num_q_heads, %d] = [%d, *, %d], not %s"
                          % (desc.head_dim, batch * q_len, desc.head_dim, tuple(q.shape)))
-    if tuple(out.shape) != tuple(q.shape):
+    if out.shape != shape:
         raise ValueError("out must have q's shape %s, not %s" % (tuple(q.shape), tuple(out.shape)))
     if block_tables.dim() != 2 or block_tables.shape[0] != batch:
         raise ValueError("block_tables must be [batch, max_blocks_per_seq] with batch = %d" % batch)
@@ -242,33 +265,28 @@ def paged_decode_attn(q, cache, scales, desc, block_tables, seq_lens, q_len, max
                       sm_scale, out, workspace, chunk_tokens=0, stream=None, L=None,
                       shared_prefix_tokens=0):
     """paged_decode_attn, or paged_decode_attn_prefix when shared_prefix_tokens is given."""
-    import torch
+    torch = _torch()
     batch = _check_attn_shapes(q, cache, scales, desc, block_tables, seq_lens, q_len, out)
-    need = workspace_bytes(desc, batch, q_len, q.shape[1], max_seq_len, chunk_tokens,
+    num_q_heads, held = q.shape[1], workspace.numel() * workspace.element_size()
+    need = workspace_bytes(desc, batch, q_len, num_q_heads, max_seq_len, chunk_tokens,
                            shared_prefix_tokens)
-    if batch > 0 and workspace.numel() * workspace.element_size() < need:
+    if batch > 0 and held < need:
         raise ValueError("workspace holds %d bytes, the call needs %d" % (workspace.numel(), need))
-    if shared_prefix_tokens:
-        rc = (L or lib()).paged_decode_attn_prefix(
-            _dev(q, torch.bfloat16, "q"), _dev(cache, torch.uint8, "cache"),
+    L, what = L or lib(), "paged_decode_attn"
+    args = (_dev(q, torch.bfloat16, "q"), _dev(cache, torch.uint8, "cache"),
             _dev(scales, torch.float32, "scales"), C.byref(desc),
             _dev(block_tables, torch.int32, "block_tables"), block_tables.shape[1],
-            _dev(seq_lens, torch.int32, "seq_lens"), batch, q_len, q.shape[1], max_seq_len,
-            float(sm_scale), chunk_tokens, int(shared_prefix_tokens),
-            _dev(out, torch.float32, "out"), _dev(workspace, torch.uint8, "workspace"),
-            workspace.numel(), _stream(stream))
-        if rc != OK:
-            raise KvqError(rc, "paged_decode_attn_prefix")
-        return
-    rc = (L or lib()).paged_decode_attn(
-        _dev(q, torch.bfloat16, "q"), _dev(cache, torch.uint8, "cache"),
-        _dev(scales, torch.float32, "scales"), C.byref(desc),
-        _dev(block_tables, torch.int32, "block_tables"), block_tables.shape[1],
-        _dev(seq_lens, torch.int32, "seq_lens"), batch, q_len, q.shape[1], max_seq_len,
-        float(sm_scale), chunk_tokens, _dev(out, torch.float32, "out"),
-        _dev(workspace, torch.uint8, "workspace"), workspace.numel(), _stream(stream))
+            _dev(seq_lens, torch.int32, "seq_lens"), batch, q_len, num_q_heads, max_seq_len,
+            float(sm_scale), chunk_tokens)
+    rest = (_dev(out, torch.float32, "out"), _dev(workspace, torch.uint8, "workspace"),
+            held, _stream(stream))
+    if shared_prefix_tokens:
+        what = "paged_decode_attn_prefix"
+        rc = L.paged_decode_attn_prefix(*args, int(shared_prefix_tokens), *rest)
+    else:
+        rc = L.paged_decode_attn(*args, *rest)
     if rc != OK:
-        raise KvqError(rc, "paged_decode_attn")
+        raise KvqError(rc, what)
 
 
 STATIC_WORKSPACE_BYTES = 64 << 20   # KVQ_STATIC_WORKSPACE_BYTES
@@ -277,7 +295,7 @@ STATIC_WORKSPACE_BYTES = 64 << 20   # KVQ_STATIC_WORKSPACE_BYTES
 def paged_decode_attn_static(q, cache, scales, desc, block_tables, seq_lens, q_len, max_seq_len,
                              sm_scale, out, chunk_tokens=0, stream=None):
     """paged_decode_attn on the library's own static scratch buffer (no workspace argument)."""
-    import torch
+    torch = _torch()
     batch = _check_attn_shapes(q, cache, scales, desc, block_tables, seq_lens, q_len, out)
     rc = lib().paged_decode_attn_static(
         _dev(q, torch.bfloat16, "q"), _dev(cache, torch.uint8, "cache"),
@@ -293,11 +311,11 @@ def _any(t, dtype, name):
     """Device tensor, or pinned host tensor the GPU can address."""
     import torch
     if t is not None and t.numel() == 0 and t.dtype == dtype:
-        return C.c_void_p(None)
+        return None
     if not isinstance(t, torch.Tensor) or t.dtype != dtype or not t.is_contiguous() or \
             not (t.is_cuda or t.is_pinned()):
         raise TypeError("%s must be a contiguous device or pinned host tensor of %s" % (name, dtype))
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def packed_sizes(desc, num):
