@@ -67,24 +67,9 @@ __device__ inline int wave_incl_scan(int v) {
 __device__ inline int lane_value(int v, int lane_index) {  // lane_index wave-uniform
   return __builtin_amdgcn_readlane(v, lane_index);
 }
-__device__ inline float lane_value(float v, int lane_index) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane_index));
-}
 __device__ inline int wave_sum(int v) { return lane_value(wave_incl_scan(v), 63); }
 __device__ inline int wave_min(int v) {
   return lane_value(dpp_scan_bits(v, 0x7FFFFFFF, [](int a, int b) { return a < b ? a : b; }), 63);
-}
-__device__ inline float wave_sum_f(float v) {
-  const int r = dpp_scan_bits(__float_as_int(v), 0, [](int a, int b) {
-    return __float_as_int(__int_as_float(a) + __int_as_float(b));
-  });
-  return __int_as_float(__builtin_amdgcn_readlane(r, 63));
-}
-__device__ inline float wave_max_f(float v) {
-  const int r = dpp_scan_bits(__float_as_int(v), __float_as_int(-INFINITY), [](int a, int b) {
-    return __float_as_int(fmaxf(__int_as_float(a), __int_as_float(b)));
-  });
-  return __int_as_float(__builtin_amdgcn_readlane(r, 63));
 }
 
 // How the flat list of `flat` groups is cut into wavefront ranges.  With a caller-given granule
@@ -754,115 +739,113 @@ attn_stream_kernel(const AttnArgs p) {
   if constexpr (CEIL) p.ws_acc[(size_t)w * 64 + lane] = __uint_as_float(ceil_x & 0x3FFFFFFFu);
 }
 
-// ---- log-sum-exp merge of a pair's partials: one wavefront per (sequence, query head) and
-// slice of the sequence's query tokens (blockIdx.y; up to 64 slices, so a handful of tokens get
-// a wavefront each), each lane owning D/64 channels.  The kernel is a chain of memory round
-// trips behind a launch, so it is written to keep that chain short: where the pair lies in the
-// flat list comes from the prefix sums the streaming kernel's first wavefront left in the
-// workspace (one round trip; a scan of seq_lens in every one of these wavefronts would cost
-// batch^2 * heads loads); which wavefront ranges cover it is 32-bit arithmetic; then the (max,
-// sum) pairs of up to 64 covering ranges, one per lane, and the first eight ranges' accumulator
-// rows are requested together (one more round trip for a pair cut into at most eight pieces);
-// further rows follow eight at a time. ----
+// ---- log-sum-exp merge of a pair's partials: a workgroup per pair and slice of its rows (blockIdx.y).
+// D/4 lanes (a "unit") own a row, four channels each; where a row has many partials, several units
+// share it and take every so many of them, and their results meet in LDS.  The kernel is a chain of memory round
+// trips behind a launch, so it is written to keep that chain short: where the pair lies in the flat
+// list comes from the prefix sums the streaming kernel's first wavefront left in the workspace (one
+// round trip; a scan of seq_lens in every workgroup would cost batch^2 * heads loads); which
+// wavefront ranges cover it is 32-bit arithmetic on scalars, once for all its rows; then a unit requests
+// (max, sum) and accumulator of eight partials at once, and the launch gives a row enough units for that
+// to be all of them, as a rule.  A wavefront per (sequence, query head) with its query tokens one after
+// the other, the earlier form, took 28 us for 32 query rows x 512 pairs of three partials each, now 16;
+// 16 us for 16 rows x 128 pairs of 17, now 11; 10 us for 4 rows x 1024 pairs of three, now 6.
+constexpr int kReduceBatch = 8;      // partials a unit requests at once
+constexpr int kReduceThreads = 512;  // at most (1024 would leave 128 registers, and spills)
 template <int D>
-__global__ __launch_bounds__(64) void attn_reduce_kernel(const AttnArgs p) {
-  constexpr int E = D / 64;
-  constexpr int NB = 8;  // accumulator rows requested at once
-  typedef float floatE __attribute__((ext_vector_type(E)));
+__global__ __launch_bounds__(kReduceThreads) void attn_reduce_kernel(const AttnArgs p) {
+  constexpr int LR = D / 4;  // lanes per unit
   typedef float float2v __attribute__((ext_vector_type(2)));
-  const int hq = blockIdx.x % p.num_q_heads;
-  const int b = blockIdx.x / p.num_q_heads;
-  const int lane = threadIdx.x;
+  __shared__ floatx4 sh_acc[kReduceThreads];
+  __shared__ float2v sh_ml[kReduceThreads / LR];
+  const int unit = threadIdx.x / LR, lane = threadIdx.x % LR, units = blockDim.x / LR;
   // where the sequence lies in the flat list: the prefix sums the streaming kernel left, and
   // the length P (in groups) of the shared prefix it left to the prefix kernel (0: none)
+  const int Hp = p.pairs_per_seq, pair = blockIdx.x;
+  const int b = pair / Hp, pr = pair - b * Hp;
   const int before = p.ws_prefix[b], next = p.ws_prefix[b + 1], total = p.ws_prefix[p.batch];
   const int P = p.ws_prefix[p.batch + 1];
-  const int Hp = p.pairs_per_seq;
-  const int all_pairs = p.batch * Hp;
-  const Split split = make_split(p.range_groups, (total - p.batch * P) * Hp, p.num_waves);
-  const int rt = 16 * p.row_tiles;
-  const int h = hq / p.group;
   const int ng = next - before;
   const int na = P > 0 ? p.prefix_chunks : 0;  // partials the prefix kernel left for this pair
-  const float* __restrict__ ws_acc = p.ws_acc + lane * E;
-  const float2v* __restrict__ ws_ml = (const float2v*)p.ws_ml;
+  const Split split = make_split(p.range_groups, (total - p.batch * P) * Hp, p.num_waves);
+  int wb = 0, nb = 0;  // the wavefront ranges that cover the pair's listed groups
+  if (ng > P) {
+    const int start = (before - b * P) * Hp + pr * (ng - P);
+    wb = range_of(split, start);
+    nb = range_of(split, start + (ng - P) - 1) - wb + 1;
+  }
+  if (na == 0 && nb == 1) return;  // the streaming kernel already wrote the final rows
   // a range between two non-empty ones can be empty only if the list is shorter than the grid
   const bool sparse = split.requested == 0 && split.q == 0;
-  int rg_known = -1, wb = 0, nb = 0;
-  // (the wavefront takes the query tokens j = y, y + Y, ... one after the other: their rows
-  // mostly lie in one row group, whose place in the list is then worked out once)
-  for (int j = blockIdx.y; j < p.q_len; j += gridDim.y) {
-    const int r = j * p.group + (hq - h * p.group);
-    const int rg = r / rt, rl = r - rg * rt;
-    const int pr = h * p.num_row_groups + rg;
-    const int pair = b * Hp + pr;
-    // the wavefront ranges that cover the pair's listed groups
-    if (rg != rg_known && ng > P) {
-      const int start = (before - b * P) * Hp + pr * (ng - P);
-      wb = range_of(split, start);
-      nb = range_of(split, start + (ng - P) - 1) - wb + 1;
-      rg_known = rg;
-    }
-    if (na == 0 && nb == 1) continue;  // the streaming kernel already wrote the final rows
-    const int n = na + nb;
-    // the e-th partial of the pair: the prefix kernel's (one per chunk of the prefix, in slots
-    // behind the streaming kernel's), then one per covering wavefront range
-    auto row_of = [&](int e) {
-      const size_t slot = e < na ? (size_t)p.num_waves + (size_t)(e + 1) * all_pairs + pair
-                                 : (size_t)(wb + (e - na)) + pair;
-      return slot * rt + rl;
-    };
-    // its (max, sum), or (-inf, 0) past the last one and for a range that is empty and left
-    // no partial
-    auto max_sum = [&](int e) {
-      const int w = wb + (e - na);
-      const bool live =
-          e < n && (e < na || !sparse || range_begin(split, w) < range_begin(split, w + 1));
-      return live ? ws_ml[row_of(e)] : float2v{-INFINITY, 0.0f};
-    };
-    auto load_rows = [&](floatE (&a)[NB], int e0, int count) {
+  const int n = na + nb;
+  const int rt = 16 * p.row_tiles, all_pairs = p.batch * Hp;
+  const int h = pr / p.num_row_groups, rg = pr - h * p.num_row_groups;
+  // this workgroup's rows, and the units that share one
+  const int per = (min(rt, p.rows) + (int)gridDim.y - 1) / (int)gridDim.y;
+  const int r0 = (int)blockIdx.y * per, rows = min(per, p.rows - rg * rt - r0);
+  const int slices = units / per;  // (the launch makes units a multiple of per at least)
+  const int rl = r0 + unit % per, slice = unit / per;
+  const bool live = unit % per < rows && slice < slices;
+  const floatx4* __restrict__ ws_acc = (const floatx4*)p.ws_acc;
+  const float2v* __restrict__ ws_ml = (const float2v*)p.ws_ml;
+  float M = -INFINITY, den = 0.0f;
+  floatx4 num = {0.f, 0.f, 0.f, 0.f};
+  for (int e0 = live ? slice : n; e0 < n; e0 += kReduceBatch * slices) {
+    floatx4 a[kReduceBatch];
+    float2v ml[kReduceBatch];
 #pragma unroll
-      for (int k = 0; k < NB; ++k)
-        if (k < count) a[k] = *(const floatE*)(ws_acc + row_of(e0 + k) * D);
-    };
-    floatE a_first[NB];
-    load_rows(a_first, 0, n);
-
-    // pass 1: the maximum over all partials
-    const float2v ml_first = max_sum(lane);
-    float M = ml_first[0];
-    for (int e0 = 64; e0 < n; e0 += 64) M = fmaxf(M, max_sum(e0 + lane)[0]);
-    M = wave_max_f(M);
-
-    // pass 2: weights, denominator and the weighted sum of the accumulators
-    floatE num = {};
-    float den = 0.0f;
-    for (int e0 = 0; e0 < n; e0 += 64) {
-      const float2v ml = e0 == 0 ? ml_first : max_sum(e0 + lane);
-      const float wgt = __builtin_amdgcn_exp2f(ml[0] - M);  // 0 for an empty range
-      den += wgt * ml[1];
-      const int count = min(64, n - e0);
-      for (int k0 = 0; k0 < count; k0 += NB) {
-        floatE a[NB];
-        if (e0 == 0 && k0 == 0) {
-#pragma unroll
-          for (int k = 0; k < NB; ++k) a[k] = a_first[k];
-        } else {
-          load_rows(a, e0 + k0, count - k0);
-        }
-#pragma unroll
-        for (int k = 0; k < NB; ++k) {
-          if (k0 + k >= count) break;
-          const float wk = lane_value(wgt, k0 + k);
-          // (an empty range's row was never written: it must not enter even with weight 0)
-          if (wk != 0.0f) num += wk * a[k];
-        }
+    for (int k = 0; k < kReduceBatch; ++k) {
+      // the e-th partial of the pair: the prefix kernel's (one per chunk of the prefix, in slots
+      // behind the streaming kernel's), then one per covering wavefront range
+      const int e = e0 + k * slices, w = wb + (e - na);
+      ml[k] = float2v{-INFINITY, 0.0f};
+      // (an empty range left no partial: it must not enter even with weight 0)
+      a[k] = floatx4{0.f, 0.f, 0.f, 0.f};
+      if (e < n && (e < na || !sparse || range_begin(split, w) < range_begin(split, w + 1))) {
+        const size_t slot = e < na ? (size_t)p.num_waves + (size_t)(e + 1) * all_pairs + pair
+                                   : (size_t)w + pair;
+        const size_t row = slot * rt + rl;
+        ml[k] = ws_ml[row];
+        a[k] = ws_acc[row * LR + lane];
       }
     }
-    den = wave_sum_f(den);
-    float* o = p.out + (((size_t)b * p.q_len + j) * p.num_q_heads + hq) * D + lane * E;
-    *(floatE*)o = num * (1.0f / den);
+    float top = M;
+#pragma unroll
+    for (int k = 0; k < kReduceBatch; ++k) top = fmaxf(top, ml[k][0]);
+    const float safe = top == -INFINITY ? 0.0f : top;
+    const float keep = __builtin_amdgcn_exp2f(M - safe);
+    M = top;
+    num *= keep;
+    den *= keep;
+#pragma unroll
+    for (int k = 0; k < kReduceBatch; ++k) {
+      const float w = __builtin_amdgcn_exp2f(ml[k][0] - safe);
+      num += w * a[k];
+      den += w * ml[k][1];
+    }
   }
+  if (slices > 1) {
+    sh_acc[threadIdx.x] = num;
+    if (lane == 0) sh_ml[unit] = float2v{M, den};
+    __syncthreads();
+    if (!live || slice != 0) return;
+    float top = M;
+    for (int k = 1; k < slices; ++k) top = fmaxf(top, sh_ml[unit + k * per][0]);
+    const float safe = top == -INFINITY ? 0.0f : top;
+    const float keep = __builtin_amdgcn_exp2f(M - safe);
+    num *= keep;
+    den *= keep;
+    for (int k = 1; k < slices; ++k) {
+      const int u = unit + k * per;
+      const float w = __builtin_amdgcn_exp2f(sh_ml[u][0] - safe);
+      num += w * sh_acc[u * LR + lane];
+      den += w * sh_ml[u][1];
+    }
+  }
+  if (!live) return;
+  const int r = rg * rt + rl, j = r / p.group, gi = r - j * p.group;
+  float* o = p.out + (((size_t)b * p.q_len + j) * p.num_q_heads + (size_t)h * p.group + gi) * D;
+  ((floatx4*)o)[lane] = num * (1.0f / den);
 }
 
 #ifdef KVQ_PROFILE
@@ -961,13 +944,21 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t stream) {
     e = a.head_dim == 128 ? launch_stream<KVQ_BF16_PLAIN, 128>(a, stream)
                           : launch_stream<KVQ_BF16_PLAIN, 64>(a, stream);
   if (e != hipSuccess || stream_only) return e;
-  // (a wavefront per (sequence, query head) and four query tokens, 64 per query head at most)
-  const int per_head = (a.q_len + 3) / 4;
-  const dim3 rgrid((unsigned)((size_t)a.batch * a.num_q_heads), (unsigned)(per_head < 64 ? per_head : 64));
+  // a unit of head_dim / 4 lanes for each row, or for every eight of a row's partials where it has more
+  // than that on average (a shared prefix does not count: a prefix that is dropped on the device
+  // leaves the call paged_decode_attn's bit for bit); as many rows to a workgroup as its threads hold
+  const int64_t pairs = (int64_t)a.batch * a.pairs_per_seq;
+  const int units = kReduceThreads / (a.head_dim / 4);
+  const int rows = a.rows < 16 * a.row_tiles ? a.rows : 16 * a.row_tiles;
+  const int64_t wanted = (a.num_waves / pairs + 2 + kReduceBatch - 1) / kReduceBatch;
+  const int slices = (int)(wanted < units ? wanted : units);
+  const int most = units / slices, parts = (rows + most - 1) / most, per = (rows + parts - 1) / parts;
+  const dim3 rgrid((unsigned)pairs, (unsigned)parts);
+  const dim3 threads((unsigned)(per * slices * (a.head_dim / 4) + 63) / 64 * 64);
   if (a.head_dim == 128)
-    hipLaunchKernelGGL((attn_reduce_kernel<128>), rgrid, dim3(64), 0, stream, a);
+    hipLaunchKernelGGL((attn_reduce_kernel<128>), rgrid, threads, 0, stream, a);
   else
-    hipLaunchKernelGGL((attn_reduce_kernel<64>), rgrid, dim3(64), 0, stream, a);
+    hipLaunchKernelGGL((attn_reduce_kernel<64>), rgrid, threads, 0, stream, a);
   return hipGetLastError();
 }
 
