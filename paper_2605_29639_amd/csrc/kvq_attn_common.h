@@ -36,13 +36,22 @@ __device__ inline float row_bcast(float x) {
       float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x150 + I, 0xF, 0xF, true));
 }
 
+// Over the four lanes that share lane % 16: v_permlane32_swap_b32 and v_permlane16_swap_b32 of a value with
+// itself leave it beside the value 32 (16) lanes away, without the round trip through LDS of a shuffle,
+// which nothing hides where one or two wavefronts run on a SIMD.
+template <class Op>
+__device__ inline float xor16_reduce(float v, Op op) {
+  const uint32_t u = __float_as_uint(v);
+  const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  const uint32_t w = __float_as_uint(op(__uint_as_float(h[0]), __uint_as_float(h[1])));
+  const auto r = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+  return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 __device__ inline float xor16_max(float v) {
-  v = fmaxf(v, __shfl_xor(v, 16, 64));
-  return fmaxf(v, __shfl_xor(v, 32, 64));
+  return xor16_reduce(v, [](float a, float b) { return fmaxf(a, b); });
 }
 __device__ inline float xor16_sum(float v) {
-  v += __shfl_xor(v, 16, 64);
-  return v + __shfl_xor(v, 32, 64);
+  return xor16_reduce(v, [](float a, float b) { return a + b; });
 }
 
 // Four stored code bytes (one dword) -> four f16, in byte order.
@@ -181,6 +190,128 @@ __device__ inline void online_softmax(floatx4 (&S)[NT][4], float skp, float lsv,
     }
     if constexpr (FP8) lsum = lsum * rsv;  // one scale per lane
     l_run[nt] = l_run[nt] * alpha[nt] + lsum;
+  }
+  // (per 16-row tile: a tile none of whose rows' maxima moved keeps its accumulators as they are)
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    if (__any(alpha[nt] != 1.0f)) {
+#pragma unroll
+      for (int tt = 0; tt < DT; ++tt) acc[nt][tt] *= alpha[nt];
+    }
+  }
+}
+
+// The same for the many-row kernel, whose token scales lie in LDS: `scales` points at the lane's 16
+// tokens' logit factors, then log2 V scales, then reciprocal V scales, each array `pitch` floatx4s long
+// (token-scaled formats only; the others have one skp, lsv, rsv per lane).  The 16 lanes of a row read
+// the same address, a broadcast, so a logit costs one multiply-add where the row broadcasts of
+// online_softmax take a multiply and an add at the slower rate of DPP instructions.  With one scale per
+// lane the maximum is taken of the raw contractions and the exponent is one multiply-add too.
+template <int MODE, int NT, int DT, bool TAIL, class Operand, int NP>
+__device__ inline void online_softmax_rows(floatx4 (&S)[NT][4], const floatx4* scales, int pitch,
+                                           float skp, float lsv, float rsv, int pos_lane,
+                                           const int (&nrow)[NT], float (&m_run)[NT],
+                                           float (&l_run)[NT], floatx4 (&acc)[NT][DT],
+                                           Operand (&pb)[NT][NP]) {
+  constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN;
+  constexpr bool FP8 = MODE == KVQ_FP8E4M3_BLOCK_HEAD || MODE == KVQ_FP8E4M3_TENSOR;
+  constexpr bool TOKEN_SCALE = MODE == KVQ_INT8_TOKEN_HEAD || MODE == KVQ_INT4_TOKEN_HEAD;
+  constexpr bool RAW = !TOKEN_SCALE && !TAIL;  // S stays the raw contraction, its factor >= 0
+  float mx[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) mx[nt] = -INFINITY;
+  if constexpr (RAW) {
+    if (__any(skp < 0.0f)) {  // (a negative softmax scale, or static scale)
+      const float sign = skp < 0.0f ? -1.0f : 1.0f;
+      skp *= sign;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) S[nt][u] *= sign;
+    }
+  }
+  // (the next four tokens' scales are requested while these are used, and no earlier: registers)
+  [[maybe_unused]] floatx4 k4[2], l4[2];
+  if constexpr (TOKEN_SCALE) {
+    k4[0] = scales[0];
+    l4[0] = scales[pitch];
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if constexpr (TOKEN_SCALE) {
+      if (u < 3) {
+        k4[(u + 1) & 1] = scales[u + 1];
+        l4[(u + 1) & 1] = scales[pitch + u + 1];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float z = S[nt][u][i];
+        if constexpr (TOKEN_SCALE) z = __builtin_fmaf(z, k4[u & 1][i], l4[u & 1][i]);
+        else if constexpr (TAIL) z = __builtin_fmaf(z, skp, lsv);
+        if constexpr (TAIL) z = (pos_lane + 4 * u + i < nrow[nt]) ? z : -INFINITY;
+        if constexpr (!RAW) S[nt][u][i] = z;
+        mx[nt] = fmaxf(mx[nt], z);
+      }
+    if constexpr (TOKEN_SCALE) __builtin_amdgcn_sched_barrier(0);
+  }
+  float alpha[NT], msub[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    const float m_here = RAW ? __builtin_fmaf(mx[nt], skp, lsv) : mx[nt];
+    const float m_new = fmaxf(m_run[nt], xor16_max(m_here));
+    const float m_safe = (m_new == -INFINITY) ? 0.0f : m_new;
+    alpha[nt] = __builtin_amdgcn_exp2f(m_run[nt] - m_safe);
+    m_run[nt] = m_new;
+    msub[nt] = RAW ? lsv - (m_safe - kPOffset) : m_safe - kPOffset;
+  }
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    float lsum = 0.0f;
+    [[maybe_unused]] uint32_t hi_bits[16], lo_bits[16];
+    [[maybe_unused]] floatx4 r4[2];
+    if constexpr (TOKEN_SCALE) r4[0] = scales[2 * pitch];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if constexpr (TOKEN_SCALE) {
+        if (u < 3) r4[(u + 1) & 1] = scales[2 * pitch + u + 1];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int tix = 4 * u + i;
+        const float pr = __builtin_amdgcn_exp2f(RAW ? __builtin_fmaf(S[nt][u][i], skp, msub[nt])
+                                                    : S[nt][u][i] - msub[nt]);
+        if constexpr (TOKEN_SCALE) lsum = __builtin_fmaf(pr, r4[u & 1][i], lsum);
+        else lsum += pr;
+        if constexpr (PLAIN) {  // two bf16 terms, see online_softmax
+          hi_bits[tix] = __float_as_uint(pr) & 0xFFFF0000u;
+          lo_bits[tix] = __float_as_uint(pr - __uint_as_float(hi_bits[tix]));
+        } else {
+          pb[nt][tix >> 3][tix & 7] = (_Float16)pr;
+        }
+      }
+      if constexpr (TOKEN_SCALE) __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (PLAIN) {
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        uintx4 ph, pl;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int t = 8 * hf + 2 * e;
+          ph[e] = __builtin_amdgcn_perm(hi_bits[t + 1], hi_bits[t], 0x07060302u);
+          pl[e] = __builtin_amdgcn_perm(lo_bits[t + 1], lo_bits[t], 0x07060302u);
+        }
+        pb[nt][hf] = __builtin_bit_cast(bf16x8, ph);
+        pb[nt][2 + hf] = __builtin_bit_cast(bf16x8, pl);
+      }
+    }
+    if constexpr (FP8) lsum *= rsv;  // one scale per lane
+    l_run[nt] = __builtin_fmaf(l_run[nt], alpha[nt], lsum);
   }
   // (per 16-row tile: a tile none of whose rows' maxima moved keeps its accumulators as they are)
 #pragma unroll

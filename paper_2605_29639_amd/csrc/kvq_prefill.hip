@@ -61,10 +61,11 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
   using Operand = std::conditional_t<PLAIN, bf16x8, half8>;
   __shared__ half8 k_ops[2][4][KS][64];    // [half][quad of the sub-block][step][lane]
   __shared__ half8 v_ops[2][DT][2][64];    // [half][channel tile][tokens 0-7 | 8-15][lane]
-  __shared__ floatx4 s_ops[2][64];         // [half][token]: K scale * log2e / sqrt(D), log2 and
-                                           // reciprocal of the V scale
+  // [half]: K scale * log2e / sqrt(D), log2 and reciprocal of the V scale of the 64 tokens
+  __shared__ __align__(16) float s_ops[2][3][64];
 
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wv = threadIdx.x >> 6;
   const int m16 = lane & 15, g4 = lane >> 4;
   const int H = p.num_kv_heads, G = p.group, bs = p.block_size, bs_shift = p.bs_shift;
   // rows a (kv head) has in this kernel: one sequence's, or all sequences' stacked
@@ -92,6 +93,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
       pair = id / row_blocks;
       rb = id - pair * row_blocks;
     }
+    rb = row_blocks - 1 - rb;  // the later a chunk's rows, the longer their walk: the longest start first
   }
   const int h = pair % H;
   // this wavefront's rows, and the groups [g0, ng) the workgroup has to walk
@@ -173,22 +175,24 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
   if constexpr (PREFIX) n_min = wave_min_int(min(nrow[0], nrow[1]));
 
   // ---- producer side: this wavefront's quarter of a group's codes ----
+  // (a group's table entries come with the lane's offsets inside their blocks: the position that
+  // gives the one gives the other)
   struct Entries {
-    int k, v;
+    uint32_t k, v, k_at, v_at;
   };
+  const uint32_t k_fixed = (uint32_t)h * tile_bytes + k_lane, v_fixed = (uint32_t)h * tile_bytes + v_lane;
   auto fetch_entries = [&](int g, Entries& e) {  // g is clamped by the caller
-    const int pos0 = g << 6;
-    e.k = table[min(pos0 + 16 * sbk, last_sb) >> bs_shift];
-    e.v = table[min(pos0 + 16 * g4, last_sb) >> bs_shift];
+    const uint32_t tk = (uint32_t)min((g << 6) + 16 * sbk, last_sb), tv = (uint32_t)min((g << 6) + 16 * g4, last_sb);
+    e.k = (uint32_t)table[tk >> bs_shift];
+    e.v = (uint32_t)table[tv >> bs_shift];
+    e.k_at = (tk & (uint32_t)(bs - 1)) * RB + k_fixed;
+    e.v_at = tv & (uint32_t)(bs - 1);
   };
   uintx4 rk[KJ], rv[VP];
   float sk_next = 0.0f, sv_next = 0.0f;
-  auto issue_loads = [&](int g, const Entries& e) {
-    const int pos0 = g << 6;
-    const uint32_t off_k = (uint32_t)(min(pos0 + 16 * sbk, last_sb) & (bs - 1));
-    const uint32_t off_v = (uint32_t)(min(pos0 + 16 * g4, last_sb) & (bs - 1));
-    const uint8_t* kbase = cache + (size_t)e.k * block_stride + (h * tile_bytes + off_k * RB + k_lane);
-    const uint8_t* vbase = cache + (size_t)e.v * block_stride + (h * tile_bytes + off_v * RB + v_lane);
+  auto issue_loads = [&](const Entries& e) {
+    const uint8_t* kbase = cache + ((uint64_t)e.k * block_stride + e.k_at);
+    const uint8_t* vbase = cache + ((uint64_t)e.v * block_stride + (e.v_at * RB + v_fixed));
 #pragma unroll
     for (int j = 0; j < KJ; ++j) rk[j] = *(const uintx4*)(kbase + 256 * j);
     // (unquantized: piece 2 t + hf is channel tile t, tokens 8 hf .. 8 hf + 7)
@@ -196,8 +200,8 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
     for (int x = 0; x < VP; ++x)
       rv[x] = *(const uintx4*)(vbase + (PLAIN ? (x & 1) * (16 * D) + 256 * (x >> 1) : 256 * x));
     if (!PLAIN && wv == 0) {  // the scales of the group's 64 tokens, lane = token
-      const uint32_t s_lane = TOKEN_SCALE ? h * bs + m16 + off_v : (MODE == KVQ_FP8E4M3_TENSOR ? 0u : (uint32_t)h);
-      const float* sp = scales + (size_t)e.v * s_block_stride + s_lane;
+      const uint32_t s_lane = TOKEN_SCALE ? (uint32_t)(h * bs + m16) + e.v_at : (MODE == KVQ_FP8E4M3_TENSOR ? 0u : (uint32_t)h);
+      const float* sp = scales + ((uint64_t)e.v * s_block_stride + s_lane);
       sk_next = sp[0];
       sv_next = sp[s_kv];
     }
@@ -237,22 +241,20 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
         k_ops[half][wv][2 * j][lane] = cvt8<MODE>(rk[j][0], rk[j][1]);
         k_ops[half][wv][2 * j + 1][lane] = cvt8<MODE>(rk[j][2], rk[j][3]);
       }
-      uint32_t keep[4] = {~0u, ~0u, ~0u, ~0u};
       if (FP8 && (g << 6) + 64 > L) {  // V bytes of missing tokens: an e4m3 NaN times 0 is NaN
         const int live = L - ((g << 6) + 16 * g4);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int n = min(max(live - 4 * e, 0), 4);
-          keep[e] = n == 4 ? ~0u : (1u << (8 * n)) - 1u;
+          const uint32_t keep = n == 4 ? ~0u : (1u << (8 * n)) - 1u;
+#pragma unroll
+          for (int t = 0; t < VT; ++t) rv[t][e] &= keep;
         }
       }
 #pragma unroll
       for (int t = 0; t < VT; ++t) {
-        uintx4 raw = rv[t];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) raw[e] &= keep[e];
-        v_ops[half][wv * VT + t][0][lane] = cvt8<MODE>(raw[0], raw[1]);
-        v_ops[half][wv * VT + t][1][lane] = cvt8<MODE>(raw[2], raw[3]);
+        v_ops[half][wv * VT + t][0][lane] = cvt8<MODE>(rv[t][0], rv[t][1]);
+        v_ops[half][wv * VT + t][1][lane] = cvt8<MODE>(rv[t][2], rv[t][3]);
       }
     }
     // The scales go the same way: held in registers from the load to the softmax two iterations
@@ -267,7 +269,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
         lsv = 0.0f;
         rsv = 0.0f;
       }
-      s_ops[half][lane] = floatx4{skp, lsv, rsv, 0.0f};
+      s_ops[half][0][lane] = skp;
+      s_ops[half][1][lane] = lsv;
+      s_ops[half][2][lane] = rsv;
     }
   };
 
@@ -314,13 +318,13 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
     constexpr bool TAIL = decltype(TAILC)::value;
     const int pos0 = g << 6;
     float skp = p.scale_log2, lsv = 0.0f, rsv = 1.0f;
-    if constexpr (!PLAIN) {
-      const floatx4 sc = s_ops[half][lane];
-      skp = sc[0];
-      lsv = sc[1];
-      rsv = sc[2];
+    if constexpr (FP8) {
+      skp = s_ops[half][0][lane];
+      lsv = s_ops[half][1][lane];
+      rsv = s_ops[half][2][lane];
     }
-    online_softmax<MODE, NT, DT, TAIL>(S, skp, lsv, rsv, pos0 + 16 * g4, nrow, m_run, l_run, acc, pb);
+    online_softmax_rows<MODE, NT, DT, TAIL>(S, (const floatx4*)&s_ops[half][0][16 * g4], 16, skp, lsv, rsv,
+                                            pos0 + 16 * g4, nrow, m_run, l_run, acc, pb);
   };
   auto pv = [&](int half) {
     // two channel tiles at a time: their four operands are read while the previous pair's
@@ -362,9 +366,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
     Entries e0;
     fetch_entries(g0, e0);
     fetch_entries(min(g0 + 1, ng - 1), e_next);
-    issue_loads(g0, e0);
+    issue_loads(e0);
     publish(g0, 0);
-    issue_loads(min(g0 + 1, ng - 1), e_next);
+    issue_loads(e_next);
     fetch_entries(min(g0 + 2, ng - 1), e_after);
   }
   __syncthreads();
@@ -378,7 +382,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
     }
     // group g + 1 (requested one iteration ago) into the other half; request group g + 2
     publish(min(g + 1, ng - 1), half ^ 1);
-    issue_loads(min(g + 2, ng - 1), e_after);
+    issue_loads(e_after);
     fetch_entries(min(g + 3, ng - 1), e_after);
     __syncthreads();
   }
