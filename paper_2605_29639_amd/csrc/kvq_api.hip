@@ -134,13 +134,21 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
   if (chunk_tokens == 0) {
     // even split over as many wavefronts as an MI355X keeps resident at this kernel's
     // register footprint: 256 CUs x 4 SIMDs x 2 (one 16-row tile, or two at head_dim 64) or
-    // x 1 (two tiles at head_dim 128)
-    // (an unquantized cache needs twice the registers per group: one wavefront per SIMD; so
-    // does the group-scaled int4 cache, for its four accumulators per logit)
+    // x 1 (two tiles at head_dim 128; an unquantized cache, which needs twice the registers per
+    // group)
     const int64_t waves = auto_waves();
-    const bool two_per_simd = (plan->row_tiles == 1 || d->head_dim == 64) &&
-                              d->mode != KVQ_BF16_PLAIN && d->mode != KVQ_INT4_GROUP32;
-    const int64_t resident = two_per_simd ? waves : waves / 2;
+    const bool two_per_simd =
+        (plan->row_tiles == 1 || d->head_dim == 64) && d->mode != KVQ_BF16_PLAIN;
+    int64_t resident = two_per_simd ? waves : waves / 2;
+    // (the group-scaled int4 kernel did with one per SIMD, and half the partials: a call whose
+    // partials would no longer fit the static scratch buffer gets as many wavefronts as do, and no
+    // fewer than then)
+    if (d->mode == KVQ_INT4_GROUP32) {
+      const int64_t slot_bytes = 16 * (d->head_dim + 2) * (int64_t)sizeof(float);
+      const int64_t room = ((int64_t)KVQ_STATIC_WORKSPACE_BYTES - ((int64_t)batch + 8) * 4) / slot_bytes -
+                           (int64_t)batch * pairs;
+      resident = room < waves / 2 ? waves / 2 : room < waves ? room : waves;
+    }
     plan->range_groups = 0;
     plan->num_waves = (int32_t)(flat_max < resident ? flat_max : resident);
   } else {

@@ -112,12 +112,14 @@ __device__ inline int range_of(const Split& s, int f) {
 //   pipeline, but the arithmetic replaced by an XOR of the loaded words (one dword per lane is
 //   stored so that the loads stay);
 //   CLOCK = true: the kernel itself, every wavefront also storing clock readings at fixed points.
-// (The second launch bound, two wavefronts per SIMD, for the quantized one-tile kernels: they
+// (The second launch bound, two wavefronts per SIMD, for the quantized one-tile kernels (the group-scaled
+// int4 one among them, since its scales come from LDS: 218 registers where row broadcasts took 268,
+// and 56 -> 49 us a call for 195 MB): they
 // fit either way, but told so the compiler keeps everything in 200-224 VGPRs instead of parking
 // values in AGPRs and copying them back, 1-2 % faster.  At head_dim 64 the two-tile kernels,
 // double buffers included, fit 256 registers as well and run two per SIMD too.)
 template <int MODE, int D, int NT, bool CEIL, int DEPTH, bool CLOCK>
-__global__ __launch_bounds__(64, ((NT == 1 || D == 64) && MODE != KVQ_BF16_PLAIN && MODE != KVQ_INT4_GROUP32) ? 2 : 1) void
+__global__ __launch_bounds__(64, ((NT == 1 || D == 64) && MODE != KVQ_BF16_PLAIN) ? 2 : 1) void
 attn_stream_kernel(const AttnArgs p) {
   constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN;  // unquantized cache: 2-byte elements
   // e4m3 codes, one scale per lane and group: the block's, or the whole layer's
@@ -156,6 +158,15 @@ attn_stream_kernel(const AttnArgs p) {
       if (lane == 0) p.wave_clock[(size_t)w * 16 + k] = t;
     }
   };
+  // The even split counts on its wavefronts being spread evenly, two (or one) to every SIMD.  Where the
+  // registers would let a third share a SIMD (int4, head_dim 64) the dispatcher sometimes puts it there
+  // and leaves another SIMD with one, depending on what ran before: int4, 163 MB, 37 or 47 us with the
+  // same code.  Naming a register claims all below it, and caps the SIMD at the plan's number (the
+  // kernels not named here need that many anyway).
+  constexpr bool kTwoPerSimd =
+      (NT == 1 || D == 64) && MODE != KVQ_BF16_PLAIN;
+  if constexpr (kTwoPerSimd) asm volatile("" ::: "v175");
+  else if constexpr (PLAIN && D == 64) asm volatile("" ::: "v255", "a7");
   stamp(6);
   stamp(0);
   const int32_t* __restrict__ seq_lens = p.seq_lens;
@@ -453,67 +464,85 @@ attn_stream_kernel(const AttnArgs p) {
       }
   };
 
+  // ---- the scales of a group, lane = token: what the softmax multiplies and shifts by.  Token scales go
+  // through LDS (the wavefront's own, in order: no barrier), from where the softmax reads four
+  // tokens' at a time; called ahead of QK^T, whose time covers the way there and back. ----
+  __shared__ __align__(16) float sh_scales[TOKEN_SCALE ? 3 : 1][64];  // skp, log2 and 1 / of the V scale
+  __shared__ floatx4 sh_group[GROUPED ? 2 : 1][GROUPED ? 64 : 1];     // K scales; V scales relative to the token's largest
+  float skp_lane = 0.0f, lsv_lane = 0.0f, rsv_lane = 0.0f;
+  auto stage_scales = [&](ScaleT sk, ScaleT sv, const Cursor& c) {
+    if constexpr (CEIL) return;
+    // a slot that was never written: its scales are not data
+    const bool dead = TOKEN_SCALE && (c.g << 6) + lane >= c.L;
+    if constexpr (GROUPED) {
+      const float sv_max = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
+      lsv_lane = dead ? 0.0f : __builtin_amdgcn_logf(fmaxf(sv_max, kMinVScale));
+      rsv_lane = dead ? 0.0f : __builtin_amdgcn_exp2f(-lsv_lane);
+      floatx4 k, ratio;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        k[g] = dead ? 0.0f : sk[g] * p.scale_log2;
+        ratio[g] = dead ? 0.0f : sv[g] * rsv_lane;
+      }
+      sh_group[0][lane] = k;
+      sh_group[1][lane] = ratio;
+    } else {
+      skp_lane = dead ? 0.0f : sk * p.scale_log2;
+      lsv_lane = PLAIN || dead ? 0.0f : __builtin_amdgcn_logf(fmaxf(sv, kMinVScale));
+      rsv_lane = PLAIN ? 1.0f : dead ? 0.0f : __builtin_amdgcn_exp2f(-lsv_lane);
+    }
+    if constexpr (TOKEN_SCALE) {
+      sh_scales[0][lane] = skp_lane;
+      sh_scales[1][lane] = lsv_lane;
+      sh_scales[2][lane] = rsv_lane;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+  };
+
   // ---- online softmax of a group: S (logits) -> pb (f16 probabilities x V scale); the body is
   // online_softmax in kvq_attn_common.h, shared with the many-row kernel.
   // TAIL = some row's causal length ends inside the group: positions past a row's length are
-  // masked and scales of never-written slots are ignored. ----
-  auto softmax_impl = [&](auto TAILC, floatx4 (&S)[NT][4], ScaleT sk, ScaleT sv, const Cursor& c,
-                          Operand (&pb)[NT][2 * EB]) {
+  // masked. ----
+  auto softmax_impl = [&](auto TAILC, floatx4 (&S)[NT][4], const Cursor& c, Operand (&pb)[NT][2 * EB]) {
     constexpr bool TAIL = decltype(TAILC)::value;
+    const floatx4* scales = (const floatx4*)&sh_scales[0][TOKEN_SCALE ? 16 * g4 : 0];
+    if constexpr (GROUPED) {
+      // the logit (plus log2 of the V scale): the four groups' contractions weighted by the token's
+      // four K scales
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const floatx4 l4 = scales[16 + u];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const floatx4 k = sh_group[0][16 * g4 + 4 * u + i];
+          float z = __builtin_fmaf(S[0][u][i], k[0], l4[i]);
+#pragma unroll
+          for (int g = 1; g < 4; ++g) z = __builtin_fmaf(SG[g - 1][u][i], k[g], z);
+          S[0][u][i] = z;
+        }
+      }
+    }
+    online_softmax<MODE, NT, DT, TAIL>(S, scales, skp_lane, lsv_lane, rsv_lane, (c.g << 6) + 16 * g4, nrow,
+                                       m_run, l_run, acc, pb);
+    if constexpr (GROUPED) {
+      // S now holds the probabilities times the largest V scale: one B operand per group
+#pragma unroll
+      for (int t = 0; t < 16; ++t) {
+        const floatx4 ratio = sh_group[1][16 * g4 + t];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) pbg[g][t >> 3][t & 7] = (_Float16)(S[0][t >> 2][t & 3] * ratio[g]);
+      }
+    }
+  };
+  auto softmax = [&](floatx4 (&S)[NT][4], ScaleT sk, ScaleT sv, const Cursor& c, Operand (&pb)[NT][2 * EB]) {
     if constexpr (CEIL) {
       if constexpr (GROUPED) ceil_x ^= __float_as_uint(sk[0] + sk[1] + sk[2] + sk[3] + sv[0] + sv[1] + sv[2] + sv[3]);
       else ceil_x ^= __float_as_uint(sk) ^ __float_as_uint(sv);
       return;
     }
-    const int pos0 = c.g << 6, L = c.L;
-    if constexpr (GROUPED) {
-#pragma clang fp contract(off)
-      // a slot that was never written: its scales are not data
-      const bool dead = TAIL && pos0 + 16 * g4 + m16 >= L;
-      float skp[4], ratio[4];
-      const float sv_max = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
-      const float lsv = dead ? 0.0f : __builtin_amdgcn_logf(fmaxf(sv_max, kMinVScale));
-      const float rsv = dead ? 0.0f : __builtin_amdgcn_exp2f(-lsv);
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        skp[g] = dead ? 0.0f : sk[g] * p.scale_log2;
-        ratio[g] = dead ? 0.0f : sv[g] * rsv;  // this group's V scale relative to the token's largest
-      }
-      // the logit: the four groups' contractions weighted by the token's four K scales
-      static_for<16>([&](auto I) {
-        constexpr int tix = decltype(I)::value, u = tix >> 2, i = tix & 3;
-        float z = S[0][u][i] * row_bcast<tix>(skp[0]);
-#pragma unroll
-        for (int g = 1; g < 4; ++g) z = z + SG[g - 1][u][i] * row_bcast<tix>(skp[g]);
-        S[0][u][i] = z;
-      });
-      online_softmax<MODE, NT, DT, TAIL>(S, 1.0f, lsv, rsv, pos0 + 16 * g4, nrow, m_run, l_run, acc, pb);
-      // S now holds the probabilities times the largest V scale: one B operand per group
-      static_for<16>([&](auto I) {
-        constexpr int tix = decltype(I)::value, u = tix >> 2, i = tix & 3;
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          pbg[g][tix >> 3][tix & 7] = (_Float16)(S[0][u][i] * row_bcast<tix>(ratio[g]));
-      });
-    } else {
-      // this lane's scales: logit factor, log2 of the V scale and its inverse
-      float skp = sk * p.scale_log2;
-      float lsv = PLAIN ? 0.0f : __builtin_amdgcn_logf(fmaxf(sv, kMinVScale));
-      float rsv = PLAIN ? 1.0f : __builtin_amdgcn_exp2f(-lsv);
-      if (TOKEN_SCALE && TAIL && pos0 + 16 * g4 + m16 >= L) {
-        skp = 0.0f;  // a slot that was never written: its scales are not data
-        lsv = 0.0f;
-        rsv = 0.0f;
-      }
-      online_softmax<MODE, NT, DT, TAIL>(S, skp, lsv, rsv, pos0 + 16 * g4, nrow, m_run, l_run, acc, pb);
-    }
-  };
-  auto softmax = [&](floatx4 (&S)[NT][4], ScaleT sk, ScaleT sv, const Cursor& c,
-                     Operand (&pb)[NT][2 * EB]) {
-    if ((c.g << 6) + 64 > c.L - p.q_len + 1)
-      softmax_impl(std::true_type{}, S, sk, sv, c, pb);
-    else
-      softmax_impl(std::false_type{}, S, sk, sv, c, pb);
+    if ((c.g << 6) + 64 > c.L - p.q_len + 1) softmax_impl(std::true_type{}, S, c, pb);
+    else softmax_impl(std::false_type{}, S, c, pb);
   };
 
   // ---- acc^T += V^T P^T ----
@@ -642,6 +671,7 @@ attn_stream_kernel(const AttnArgs p) {
       if (i == q1) __builtin_amdgcn_s_setprio(2);
       if (i == q2) __builtin_amdgcn_s_setprio(1);
       if (i == q3) __builtin_amdgcn_s_setprio(0);
+      stage_scales(sk, sv, cur);
       qk(kt, S);
       const ScaleT sk_cur = sk, sv_cur = sv;
       load_k(kt, sk, sv, vbase, nxt, blk_k, blk_v);
@@ -659,6 +689,7 @@ attn_stream_kernel(const AttnArgs p) {
       nxt = nn;
     }
     stamp(3);
+    stage_scales(sk, sv, cur);
     qk(kt, S);  // the range's last group: nothing left to request
     softmax(S, sk, sv, cur, pb);
     pv(vt, pb, cur);
@@ -697,6 +728,7 @@ attn_stream_kernel(const AttnArgs p) {
       fetch_entries(c2, tk0, tv0);
       load_k(ktb, skb, svb, vbase, c1, tk1, tv1);
       load_v(vtb, vbase, c1);
+      stage_scales(ska, sva, cur);
       qk(kta, S);
       softmax(S, ska, sva, cur, pb);
       pv(vta, pb, cur);
@@ -705,6 +737,7 @@ attn_stream_kernel(const AttnArgs p) {
       fetch_entries(c3, tk1, tv1);
       load_k(kta, ska, sva, vbase, c2, tk0, tv0);
       load_v(vta, vbase, c2);
+      stage_scales(skb, svb, cur);
       qk(ktb, S);
       softmax(S, skb, svb, cur, pb);
       pv(vtb, pb, cur);
@@ -718,14 +751,17 @@ attn_stream_kernel(const AttnArgs p) {
     if (i + 1 < count) {
       load_k(ktb, skb, svb, vbase, c1, tk1, tv1);
       load_v(vtb, vbase, c1);
+      stage_scales(ska, sva, cur);
       qk(kta, S);
       softmax(S, ska, sva, cur, pb);
       pv(vta, pb, cur);
       leave(c1);
+      stage_scales(skb, svb, cur);
       qk(ktb, S);
       softmax(S, skb, svb, cur, pb);
       pv(vtb, pb, cur);
     } else {
+      stage_scales(ska, sva, cur);
       qk(kta, S);
       softmax(S, ska, sva, cur, pb);
       pv(vta, pb, cur);

@@ -2,8 +2,6 @@
 // types, stored codes -> f16, the cross-lane pieces of the softmax.
 #pragma once
 
-#include <utility>
-
 #include "kvq_internal.h"
 
 namespace kvq {
@@ -19,22 +17,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr float kPOffset = 10.0f;   // probabilities are scaled by 2^10 (cancels in acc / l)
 constexpr float kMinVScale = 7.888609052210118e-31f;  // 2^-100
-
-template <class F, int... Is>
-__device__ inline void static_for_impl(F&& f, std::integer_sequence<int, Is...>) {
-  (f(std::integral_constant<int, Is>{}), ...);
-}
-template <int N, class F>
-__device__ inline void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
-
-// value of lane I of the caller's 16-lane row
-template <int I>
-__device__ inline float row_bcast(float x) {
-  return __builtin_bit_cast(
-      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x150 + I, 0xF, 0xF, true));
-}
 
 // Over the four lanes that share lane % 16: v_permlane32_swap_b32 and v_permlane16_swap_b32 of a value with
 // itself leave it beside the value 32 (16) lanes away, without the round trip through LDS of a shuffle,
@@ -103,119 +85,30 @@ __device__ inline half8 cvt8(uint32_t x0, uint32_t x1) {
 
 // Online softmax of one 64-token group for NT tiles of 16 query rows, shared by the streaming
 // and the many-row kernels.  In: S, the raw contractions K.q in the accumulator layout (lane
-// (row n, sub-block g) holds the 16 tokens of sub-block g); this lane's token's scales as
-// skp = K scale * softmax scale * log2(e), lsv = log2(V scale), rsv = 1 / V scale (per token for
-// the token-scaled formats, the same in every lane otherwise); pos_lane = position of the
-// lane's first token; nrow = causal length of the lane's row per tile.  Out: pb, the
-// probabilities times the V scale as the B operand of P.V (f16 scaled by 2^10, or two bf16
-// terms for an unquantized cache) (for the group-scaled int4 format S is left holding those
-// probabilities in fp32 instead); the running maximum m_run (of logit + lsv, base 2) and sum
+// (row n, sub-block g) holds the 16 tokens of sub-block g); the scales as skp = K scale * softmax
+// scale * log2(e), lsv = log2(V scale), rsv = 1 / V scale; pos_lane = position of the lane's first
+// token; nrow = causal length of the lane's row per tile.  Token-scaled formats have them in LDS:
+// `scales` points at the lane's 16 tokens' skp, then lsv, then rsv, each array 64 floats long.  The 16
+// lanes of a row read the same address, a broadcast, so a logit costs one multiply-add (as row
+// broadcasts riding on a multiply and an add they cost two instructions of the slower DPP form: the
+// many-row kernel 406 -> 396 us int8, 351 -> 341 int4; the two-tile streaming kernel 152 -> 149).  The other formats have one skp, lsv, rsv per lane: the maximum is
+// taken of the raw contractions and the exponent is one multiply-add.  Group-scaled int4: S already
+// holds the logits (plus lsv), and is left holding the probabilities in fp32 for its caller to scale
+// once more.
+// Out: pb, the probabilities times the V scale as the B operand of P.V (f16 scaled by 2^10, or two
+// bf16 terms for an unquantized cache); the running maximum m_run (of logit + lsv, base 2) and sum
 // l_run are updated and acc is rescaled when a maximum moved.
 // TAIL: some row's causal length ends inside the group, so positions are masked.
-// The arithmetic on broadcast operands is kept as separate multiply / add so that the row
-// broadcast rides on the instruction itself (v_mul_f32_dpp, v_add_f32_dpp) instead of costing
-// moves.
 template <int MODE, int NT, int DT, bool TAIL, class Operand, int NP>
-__device__ inline void online_softmax(floatx4 (&S)[NT][4], float skp, float lsv, float rsv,
-                                      int pos_lane, const int (&nrow)[NT], float (&m_run)[NT],
-                                      float (&l_run)[NT], floatx4 (&acc)[NT][DT],
-                                      Operand (&pb)[NT][NP]) {
-#pragma clang fp contract(off)
+__device__ inline void online_softmax(floatx4 (&S)[NT][4], const floatx4* scales, float skp, float lsv,
+                                      float rsv, int pos_lane, const int (&nrow)[NT],
+                                      float (&m_run)[NT], float (&l_run)[NT],
+                                      floatx4 (&acc)[NT][DT], Operand (&pb)[NT][NP]) {
+  constexpr int pitch = 16;  // floatx4s per array of scales
   constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN;
   constexpr bool FP8 = MODE == KVQ_FP8E4M3_BLOCK_HEAD || MODE == KVQ_FP8E4M3_TENSOR;
-  constexpr bool TOKEN_SCALE = MODE == KVQ_INT8_TOKEN_HEAD || MODE == KVQ_INT4_TOKEN_HEAD ||
-                               MODE == KVQ_INT4_GROUP32;
-  // logits in base 2, shifted by log2 of the V scale; row maximum
-  float mx[NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) mx[nt] = -INFINITY;
-  static_for<16>([&](auto I) {
-    constexpr int tix = decltype(I)::value, u = tix >> 2, i = tix & 3;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      float ze;
-      if constexpr (TOKEN_SCALE) {
-        ze = S[nt][u][i] * row_bcast<tix>(skp);
-        ze = ze + row_bcast<tix>(lsv);
-      } else if constexpr (PLAIN) {
-        ze = S[nt][u][i] * skp;
-      } else {
-        ze = __builtin_fmaf(S[nt][u][i], skp, lsv);
-      }
-      if constexpr (TAIL) ze = (pos_lane + tix < nrow[nt]) ? ze : -INFINITY;
-      S[nt][u][i] = ze;
-      mx[nt] = fmaxf(mx[nt], ze);
-    }
-  });
-  float alpha[NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const float m_new = fmaxf(m_run[nt], xor16_max(mx[nt]));
-    const float m_safe = (m_new == -INFINITY) ? 0.0f : m_new;
-    alpha[nt] = __builtin_amdgcn_exp2f(m_run[nt] - m_safe);
-    m_run[nt] = m_new;
-    const float msub = m_safe - kPOffset;
-    float lsum = 0.0f;
-    [[maybe_unused]] uint32_t hi_bits[16], lo_bits[16];
-    static_for<16>([&](auto I) {
-      constexpr int tix = decltype(I)::value, u = tix >> 2, i = tix & 3;
-      const float pr = __builtin_amdgcn_exp2f(S[nt][u][i] - msub);
-      if constexpr (MODE == KVQ_INT4_GROUP32) S[nt][u][i] = pr;  // its caller scales them once more
-      if constexpr (TOKEN_SCALE) {
-        lsum = __builtin_fmaf(pr, row_bcast<tix>(rsv), lsum);  // one v_fmac_f32_dpp
-      } else {
-        lsum = lsum + pr;
-      }
-      if constexpr (PLAIN) {
-        // bf16 keeps 8 bits of a probability: it goes in as two terms, the value cut to
-        // bf16 and the (exactly representable) rest cut to bf16, 16 bits in all
-        hi_bits[tix] = __float_as_uint(pr) & 0xFFFF0000u;
-        lo_bits[tix] = __float_as_uint(pr - __uint_as_float(hi_bits[tix]));
-      } else {
-        pb[nt][tix >> 3][tix & 7] = (_Float16)pr;
-      }
-    });
-    if constexpr (PLAIN) {
-#pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {
-        uintx4 ph, pl;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {  // the upper halves of two tokens' words, packed
-          ph[e] = __builtin_amdgcn_perm(hi_bits[8 * hf + 2 * e + 1], hi_bits[8 * hf + 2 * e], 0x07060302u);
-          pl[e] = __builtin_amdgcn_perm(lo_bits[8 * hf + 2 * e + 1], lo_bits[8 * hf + 2 * e], 0x07060302u);
-        }
-        pb[nt][hf] = __builtin_bit_cast(bf16x8, ph);
-        pb[nt][2 + hf] = __builtin_bit_cast(bf16x8, pl);
-      }
-    }
-    if constexpr (FP8) lsum = lsum * rsv;  // one scale per lane
-    l_run[nt] = l_run[nt] * alpha[nt] + lsum;
-  }
-  // (per 16-row tile: a tile none of whose rows' maxima moved keeps its accumulators as they are)
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    if (__any(alpha[nt] != 1.0f)) {
-#pragma unroll
-      for (int tt = 0; tt < DT; ++tt) acc[nt][tt] *= alpha[nt];
-    }
-  }
-}
-
-// The same for the many-row kernel, whose token scales lie in LDS: `scales` points at the lane's 16
-// tokens' logit factors, then log2 V scales, then reciprocal V scales, each array `pitch` floatx4s long
-// (token-scaled formats only; the others have one skp, lsv, rsv per lane).  The 16 lanes of a row read
-// the same address, a broadcast, so a logit costs one multiply-add where the row broadcasts of
-// online_softmax take a multiply and an add at the slower rate of DPP instructions.  With one scale per
-// lane the maximum is taken of the raw contractions and the exponent is one multiply-add too.
-template <int MODE, int NT, int DT, bool TAIL, class Operand, int NP>
-__device__ inline void online_softmax_rows(floatx4 (&S)[NT][4], const floatx4* scales, int pitch,
-                                           float skp, float lsv, float rsv, int pos_lane,
-                                           const int (&nrow)[NT], float (&m_run)[NT],
-                                           float (&l_run)[NT], floatx4 (&acc)[NT][DT],
-                                           Operand (&pb)[NT][NP]) {
-  constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN;
-  constexpr bool FP8 = MODE == KVQ_FP8E4M3_BLOCK_HEAD || MODE == KVQ_FP8E4M3_TENSOR;
-  constexpr bool TOKEN_SCALE = MODE == KVQ_INT8_TOKEN_HEAD || MODE == KVQ_INT4_TOKEN_HEAD;
+  constexpr bool GROUPED = MODE == KVQ_INT4_GROUP32;
+  constexpr bool TOKEN_SCALE = MODE == KVQ_INT8_TOKEN_HEAD || MODE == KVQ_INT4_TOKEN_HEAD || GROUPED;
   constexpr bool RAW = !TOKEN_SCALE && !TAIL;  // S stays the raw contraction, its factor >= 0
   float mx[NT];
 #pragma unroll
@@ -232,13 +125,14 @@ __device__ inline void online_softmax_rows(floatx4 (&S)[NT][4], const floatx4* s
   }
   // (the next four tokens' scales are requested while these are used, and no earlier: registers)
   [[maybe_unused]] floatx4 k4[2], l4[2];
-  if constexpr (TOKEN_SCALE) {
+  constexpr bool kLogits = TOKEN_SCALE && !GROUPED;  // from S by this loop
+  if constexpr (kLogits) {
     k4[0] = scales[0];
     l4[0] = scales[pitch];
   }
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    if constexpr (TOKEN_SCALE) {
+    if constexpr (kLogits) {
       if (u < 3) {
         k4[(u + 1) & 1] = scales[u + 1];
         l4[(u + 1) & 1] = scales[pitch + u + 1];
@@ -250,13 +144,13 @@ __device__ inline void online_softmax_rows(floatx4 (&S)[NT][4], const floatx4* s
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         float z = S[nt][u][i];
-        if constexpr (TOKEN_SCALE) z = __builtin_fmaf(z, k4[u & 1][i], l4[u & 1][i]);
-        else if constexpr (TAIL) z = __builtin_fmaf(z, skp, lsv);
+        if constexpr (kLogits) z = __builtin_fmaf(z, k4[u & 1][i], l4[u & 1][i]);
+        else if constexpr (TAIL && !GROUPED) z = __builtin_fmaf(z, skp, lsv);
         if constexpr (TAIL) z = (pos_lane + 4 * u + i < nrow[nt]) ? z : -INFINITY;
         if constexpr (!RAW) S[nt][u][i] = z;
         mx[nt] = fmaxf(mx[nt], z);
       }
-    if constexpr (TOKEN_SCALE) __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kLogits) __builtin_amdgcn_sched_barrier(0);
   }
   float alpha[NT], msub[NT];
 #pragma unroll
@@ -287,9 +181,13 @@ __device__ inline void online_softmax_rows(floatx4 (&S)[NT][4], const floatx4* s
                                                     : S[nt][u][i] - msub[nt]);
         if constexpr (TOKEN_SCALE) lsum = __builtin_fmaf(pr, r4[u & 1][i], lsum);
         else lsum += pr;
-        if constexpr (PLAIN) {  // two bf16 terms, see online_softmax
+        if constexpr (PLAIN) {
+          // bf16 keeps 8 bits of a probability: it goes in as two terms, the value cut to
+          // bf16 and the (exactly representable) rest cut to bf16, 16 bits in all
           hi_bits[tix] = __float_as_uint(pr) & 0xFFFF0000u;
           lo_bits[tix] = __float_as_uint(pr - __uint_as_float(hi_bits[tix]));
+        } else if constexpr (GROUPED) {
+          S[nt][u][i] = pr;
         } else {
           pb[nt][tix >> 3][tix & 7] = (_Float16)pr;
         }
@@ -301,7 +199,7 @@ __device__ inline void online_softmax_rows(floatx4 (&S)[NT][4], const floatx4* s
       for (int hf = 0; hf < 2; ++hf) {
         uintx4 ph, pl;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
+        for (int e = 0; e < 4; ++e) {  // the upper halves of two tokens' words, packed
           const int t = 8 * hf + 2 * e;
           ph[e] = __builtin_amdgcn_perm(hi_bits[t + 1], hi_bits[t], 0x07060302u);
           pl[e] = __builtin_amdgcn_perm(lo_bits[t + 1], lo_bits[t], 0x07060302u);

@@ -323,8 +323,8 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
       lsv = s_ops[half][1][lane];
       rsv = s_ops[half][2][lane];
     }
-    online_softmax_rows<MODE, NT, DT, TAIL>(S, (const floatx4*)&s_ops[half][0][16 * g4], 16, skp, lsv, rsv,
-                                            pos0 + 16 * g4, nrow, m_run, l_run, acc, pb);
+    online_softmax<MODE, NT, DT, TAIL>(S, (const floatx4*)&s_ops[half][0][16 * g4], skp, lsv, rsv,
+                                       pos0 + 16 * g4, nrow, m_run, l_run, acc, pb);
   };
   auto pv = [&](int half) {
     // two channel tiles at a time: their four operands are read while the previous pair's
