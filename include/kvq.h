@@ -183,11 +183,11 @@ size_t paged_decode_attn_workspace_bytes(const kvq_cache_desc_t* desc, int32_t b
  * (no atomics).
  * q_len is 1 in a decode step, a handful when speculated tokens are verified, and may be
  * hundreds for a chunk of a prompt attending over its quantized prefix and itself.  With 128
- * and more query rows per kv head ((num_q_heads / num_kv_heads) * q_len)
- * the call runs a kernel of its own that walks each (sequence, kv head) without a split and
- * dequantizes every K/V tile once for 128 rows (no workspace use, no second kernel); otherwise
- * the rows are taken 32 at a time, each such group streaming the keys and values again.  Either
- * way that use is bound by arithmetic, not by HBM.
+ * and more query rows per kv head ((num_q_heads / num_kv_heads) * q_len), and with fewer where
+ * that is faster, the call runs a kernel of its own that dequantizes every K/V tile once for 128
+ * rows; calls with too few such row blocks to fill the GPU split the context and merge the pieces
+ * in a second kernel.  Otherwise the rows are taken 32 at a time, each such group streaming the
+ * keys and values again.  Many rows are bound by arithmetic, not by HBM.
  * Requires 1 <= q_len <= KVQ_MAX_Q_LEN and num_q_heads % num_kv_heads == 0. */
 int paged_decode_attn(const void* q, const void* cache, const float* scales,
                       const kvq_cache_desc_t* desc, const int32_t* block_tables,
@@ -214,7 +214,8 @@ int paged_decode_attn(const void* q, const void* cache, const float* scales,
  * The prefix is used when every sequence has at least that many tokens (decided on the device
  * from seq_lens), for every format but KVQ_INT4_GROUP32, with batch >= 2 and fewer than 128
  * query rows per kv head; otherwise, and with shared_prefix_tokens < 64, the call is
- * paged_decode_attn.  shared_prefix_tokens < 0 is KVQ_E_BAD_SHAPE.
+ * paged_decode_attn (which, where the device finds a sequence too short, stays on the streaming
+ * kernel).  shared_prefix_tokens < 0 is KVQ_E_BAD_SHAPE.
  *
  * workspace_bytes must be at least paged_decode_attn_prefix_workspace_bytes() for the same
  * arguments (more than paged_decode_attn needs: room for the first kernel's partials). */

@@ -100,6 +100,29 @@ int context_splits(int64_t walks, int64_t groups, int64_t room) {
   return best;
 }
 
+// Whether a call goes to the many-row kernel (a workgroup per 128 query rows of a kv head, keys and values
+// dequantized once for all of them) or to the streaming kernel (32 rows at a time, the keys and values
+// streamed again for each such group).  128 rows and more always do; below that the workgroup is not full,
+// and what decides is how often the streaming kernel would read the cache.  Measured streaming -> many-row,
+// us a call: 32 sequences of 2 k to 8 k tokens, 64 / 8 heads, head_dim 128, 96 rows: int8 213 -> 162,
+// int4 180 -> 160, bf16 363 -> 194; 64 rows: int8 158 -> 158, int4 126 -> 154, bf16 246 -> 184; 40 rows:
+// int8 140 -> 148, bf16 236 -> 177.  head_dim 64: int8 96 rows 125 -> 117 and, short, 43 -> 45, 120 rows
+// 77 -> 41; bf16 40 rows 117 -> 118, 96 rows 180 -> 123.  With a workgroup for every slot of the chip
+// and short contexts (little to lose to uneven lengths) 33 rows are enough: 200 sequences of up to 300
+// tokens, 48 rows, 91 -> 49; 128 of up to 2000, 48 rows, 177 -> 138; but 60 of up to 6000, 56 rows,
+// 190 -> 204.  (The group-scaled int4 format has no many-row kernel.)
+bool many_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t max_seq_len,
+               int64_t chunk_tokens, bool shared_prefix) {
+  if (d->mode == KVQ_INT4_GROUP32) return false;
+  if (rows >= kvq::kRowsPerWorkgroup) return true;
+  // (a caller's split-K granule is the streaming kernel's, and so is what follows a shared prefix)
+  if (chunk_tokens > 0 || shared_prefix) return false;
+  const int64_t passes = (rows + 31) / 32 + (d->mode == KVQ_BF16_PLAIN ? 1 : 0);
+  if (passes >= (d->head_dim == 128 ? 3 : 4)) return rows > 32;
+  return rows > 32 && d->head_dim == 128 && max_seq_len <= 2048 &&
+         batch * d->num_kv_heads >= auto_waves() / 4;
+}
+
 // Everything the launch needs that depends only on host-side arguments.
 bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t num_q_heads,
                int32_t max_seq_len, int32_t chunk_tokens, int32_t shared_prefix_tokens,
@@ -134,21 +157,14 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
   if (chunk_tokens == 0) {
     // even split over as many wavefronts as an MI355X keeps resident at this kernel's
     // register footprint: 256 CUs x 4 SIMDs x 2 (one 16-row tile, or two at head_dim 64) or
-    // x 1 (two tiles at head_dim 128; an unquantized cache, which needs twice the registers per
-    // group)
+    // x 1 (two tiles at head_dim 128)
+    // (an unquantized cache needs twice the registers per group: one wavefront per SIMD; so
+    // does the group-scaled int4 cache, for its four accumulators per logit, in the workspace; see
+    // below for its launch)
     const int64_t waves = auto_waves();
-    const bool two_per_simd =
-        (plan->row_tiles == 1 || d->head_dim == 64) && d->mode != KVQ_BF16_PLAIN;
-    int64_t resident = two_per_simd ? waves : waves / 2;
-    // (the group-scaled int4 kernel did with one per SIMD, and half the partials: a call whose
-    // partials would no longer fit the static scratch buffer gets as many wavefronts as do, and no
-    // fewer than then)
-    if (d->mode == KVQ_INT4_GROUP32) {
-      const int64_t slot_bytes = 16 * (d->head_dim + 2) * (int64_t)sizeof(float);
-      const int64_t room = ((int64_t)KVQ_STATIC_WORKSPACE_BYTES - ((int64_t)batch + 8) * 4) / slot_bytes -
-                           (int64_t)batch * pairs;
-      resident = room < waves / 2 ? waves / 2 : room < waves ? room : waves;
-    }
+    const bool two_per_simd = (plan->row_tiles == 1 || d->head_dim == 64) &&
+                              d->mode != KVQ_BF16_PLAIN && d->mode != KVQ_INT4_GROUP32;
+    const int64_t resident = two_per_simd ? waves : waves / 2;
     plan->range_groups = 0;
     plan->num_waves = (int32_t)(flat_max < resident ? flat_max : resident);
   } else {
@@ -178,13 +194,23 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
       (size_t)plan->num_waves +
       (size_t)batch * plan->pairs_per_seq * (plan->shared_groups > 0 ? 1 + plan->prefix_chunks : 1);
   const size_t slot_rows = slots * 16 * plan->row_tiles;
+  plan->slot_rows = (int32_t)(16 * plan->row_tiles);
   plan->acc_floats = slot_rows * d->head_dim;
   plan->ml_floats = slot_rows * 2;
   plan->prefix_ints = ((size_t)batch + 2 + 3) & ~(size_t)3;  // prefix sums, prefix length
+  // The group-scaled int4 kernel runs two wavefronts per SIMD as well.  Its workspace is that of one, so
+  // twice the wavefronts have room for their partials where a slot needs only eight rows; with
+  // more the call keeps to one.
+  if (d->mode == KVQ_INT4_GROUP32 && chunk_tokens == 0 && rows <= 8) {
+    plan->slot_rows = 8;
+    const int64_t waves = auto_waves();
+    plan->num_waves = (int32_t)(flat_max < 1 ? 1 : flat_max < waves ? flat_max : waves);
+  }
   // A many-row call has the same workspace as if it went through the streaming kernel; the pieces
   // of a split context beyond the first (whose rows go to `out`) use it, row by row of `out`.
   plan->context_splits = 1;
-  if (batch > 0 && kvq::prefill_applies(rows, d->mode)) {
+  plan->many_rows = batch > 0 && many_rows(d, batch, rows, max_seq_len, chunk_tokens, plan->shared_groups > 0);
+  if (plan->many_rows) {
     const int64_t out_rows = (int64_t)batch * q_len * num_q_heads;
     const int64_t walks = (int64_t)batch * d->num_kv_heads *
                           ((rows + kvq::kRowsPerWorkgroup - 1) / kvq::kRowsPerWorkgroup);
@@ -438,6 +464,7 @@ int attn_call(const void* q, const void* cache, const float* scales,
   a.head_dim = desc->head_dim;
   a.mode = desc->mode;
   a.row_tiles = plan.row_tiles;
+  a.slot_rows = plan.slot_rows;
   a.num_row_groups = plan.num_row_groups;
   a.pairs_per_seq = plan.pairs_per_seq;
   a.range_groups = plan.range_groups;
@@ -446,6 +473,7 @@ int attn_call(const void* q, const void* cache, const float* scales,
   a.wave_clock = nullptr;
   a.shared_groups = plan.shared_groups;
   a.prefix_chunks = plan.prefix_chunks;
+  a.many_rows = plan.many_rows;
   a.context_splits = plan.context_splits;
   const hipError_t e = kvq::launch_attn(a, (hipStream_t)stream);
   return e == hipSuccess ? KVQ_OK : KVQ_E_HIP;

@@ -112,15 +112,14 @@ __device__ inline int range_of(const Split& s, int f) {
 //   pipeline, but the arithmetic replaced by an XOR of the loaded words (one dword per lane is
 //   stored so that the loads stay);
 //   CLOCK = true: the kernel itself, every wavefront also storing clock readings at fixed points.
-// (The second launch bound, two wavefronts per SIMD, for the quantized one-tile kernels (the group-scaled
-// int4 one among them, since its scales come from LDS: 218 registers where row broadcasts took 268,
-// and 56 -> 49 us a call for 195 MB): they
+// (PER_SIMD, the second launch bound: two wavefronts per SIMD for the quantized one-tile kernels (the
+// group-scaled int4 one among them, since its scales come from LDS: 218 registers where row broadcasts
+// took 268, and 56 -> 49 us a call for 195 MB; one where its partials need the room): they
 // fit either way, but told so the compiler keeps everything in 200-224 VGPRs instead of parking
 // values in AGPRs and copying them back, 1-2 % faster.  At head_dim 64 the two-tile kernels,
 // double buffers included, fit 256 registers as well and run two per SIMD too.)
-template <int MODE, int D, int NT, bool CEIL, int DEPTH, bool CLOCK>
-__global__ __launch_bounds__(64, ((NT == 1 || D == 64) && MODE != KVQ_BF16_PLAIN) ? 2 : 1) void
-attn_stream_kernel(const AttnArgs p) {
+template <int MODE, int D, int NT, bool CEIL, int DEPTH, bool CLOCK, int PER_SIMD>
+__global__ __launch_bounds__(64, PER_SIMD) void attn_stream_kernel(const AttnArgs p) {
   constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN;  // unquantized cache: 2-byte elements
   // e4m3 codes, one scale per lane and group: the block's, or the whole layer's
   constexpr bool FP8 = MODE == KVQ_FP8E4M3_BLOCK_HEAD || MODE == KVQ_FP8E4M3_TENSOR;
@@ -163,10 +162,8 @@ attn_stream_kernel(const AttnArgs p) {
   // and leaves another SIMD with one, depending on what ran before: int4, 163 MB, 37 or 47 us with the
   // same code.  Naming a register claims all below it, and caps the SIMD at the plan's number (the
   // kernels not named here need that many anyway).
-  constexpr bool kTwoPerSimd =
-      (NT == 1 || D == 64) && MODE != KVQ_BF16_PLAIN;
-  if constexpr (kTwoPerSimd) asm volatile("" ::: "v175");
-  else if constexpr (PLAIN && D == 64) asm volatile("" ::: "v255", "a7");
+  if constexpr (PER_SIMD == 2) asm volatile("" ::: "v175");
+  else if constexpr ((PLAIN && D == 64) || GROUPED) asm volatile("" ::: "v255", "a7");
   stamp(6);
   stamp(0);
   const int32_t* __restrict__ seq_lens = p.seq_lens;
@@ -398,7 +395,7 @@ attn_stream_kernel(const AttnArgs p) {
 #pragma unroll
         for (int tt = 0; tt < DT; ++tt) *(floatx4*)(orow + 16 * tt + 4 * g4) = acc[nt][tt] * inv;
       } else {
-        const size_t row = slot * (NT * 16) + rl;
+        const size_t row = slot * p.slot_rows + rl;
         float* arow = p.ws_acc + row * D;
 #pragma unroll
         for (int tt = 0; tt < DT; ++tt) *(floatx4*)(arow + 16 * tt + 4 * g4) = acc[nt][tt];
@@ -840,7 +837,7 @@ __global__ __launch_bounds__(kReduceThreads) void attn_reduce_kernel(const AttnA
       if (e < n && (e < na || !sparse || range_begin(split, w) < range_begin(split, w + 1))) {
         const size_t slot = e < na ? (size_t)p.num_waves + (size_t)(e + 1) * all_pairs + pair
                                    : (size_t)w + pair;
-        const size_t row = slot * rt + rl;
+        const size_t row = slot * p.slot_rows + rl;
         ml[k] = ws_ml[row];
         a[k] = ws_acc[row * LR + lane];
       }
@@ -901,13 +898,18 @@ unsigned long long* g_wave_clock = nullptr;
 template <int MODE, int D, bool CEIL, bool CLOCK>
 void launch_variant(const AttnArgs& a, hipStream_t stream) {
   constexpr int kDepth = MODE == KVQ_BF16_PLAIN ? 1 : 2;
+  constexpr int kOneTile = MODE == KVQ_BF16_PLAIN ? 1 : 2, kTwoTiles = D == 64 ? kOneTile : 1;  // per SIMD
+  const dim3 grid(a.num_waves), block(64);
   if constexpr (MODE == KVQ_INT4_GROUP32) {  // (the plan gives this format one row tile always)
-    hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK>), dim3(a.num_waves), dim3(64), 0, stream, a);
+    if (a.slot_rows == 8)
+      hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK, 2>), grid, block, 0, stream, a);
+    else
+      hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK, 1>), grid, block, 0, stream, a);
   } else {
     if (a.row_tiles == 1)
-      hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK>), dim3(a.num_waves), dim3(64), 0, stream, a);
+      hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK, kOneTile>), grid, block, 0, stream, a);
     else
-      hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 2, CEIL, kDepth, CLOCK>), dim3(a.num_waves), dim3(64), 0, stream, a);
+      hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 2, CEIL, kDepth, CLOCK, kTwoTiles>), grid, block, 0, stream, a);
   }
 }
 
@@ -954,7 +956,7 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t stream) {
 #else
   constexpr bool stream_only = false, many_rows_kernel = true;
 #endif
-  if (many_rows_kernel && prefill_applies(a.rows, a.mode)) return launch_prefill(a, stream);
+  if (many_rows_kernel && a.many_rows) return launch_prefill(a, stream);
   hipError_t e;
   if (a.shared_groups > 0 && !stream_only) {  // the shared prefix, read once for many sequences
 #ifdef KVQ_PROFILE

@@ -84,6 +84,7 @@ struct AttnPlan {
   int32_t rows;            // (num_q_heads / num_kv_heads) * q_len query rows per kv head
   int32_t row_tiles;       // 16-row tiles handled by one wavefront (1 or 2)
   int32_t num_row_groups;  // ceil(rows / (16 * row_tiles))
+  int32_t slot_rows;       // rows a partial's slot in the workspace holds (16 * row_tiles, or fewer)
   int32_t pairs_per_seq;   // num_kv_heads * num_row_groups
   int32_t range_groups;    // 64-token groups per wavefront range; 0 = even split on the device
   int32_t num_waves;       // wavefronts launched (= grid size)
@@ -92,6 +93,7 @@ struct AttnPlan {
   size_t prefix_ints;      // workspace: groups before each sequence and the prefix length (batch + 2, padded to 4)
   int32_t shared_groups;   // shared prefix in 64-token groups, 0 where the prefix kernel is not used
   int32_t prefix_chunks;   // pieces the prefix kernel cuts it into (>= 1)
+  int32_t many_rows;       // the call goes to the many-row kernel
   int32_t context_splits;  // many-row kernel: pieces its walk over the context is cut into (>= 1)
 };
 
@@ -109,11 +111,12 @@ struct AttnArgs {
                        // by its first wavefront, read by the reduce)
   int32_t max_blocks_per_seq, batch, q_len, num_q_heads, num_kv_heads, group, rows;
   int32_t block_size, bs_shift, head_dim, mode;
-  int32_t row_tiles, num_row_groups, pairs_per_seq, range_groups, num_waves;
+  int32_t row_tiles, num_row_groups, slot_rows, pairs_per_seq, range_groups, num_waves;
   float scale_log2;  // sm_scale * log2(e)
   int32_t shared_groups;  // leading 64-token groups that all sequences' tables map to the same
                           // blocks (0: none, or a call the prefix kernel does not serve)
   int32_t prefix_chunks;  // pieces the prefix kernel cuts those groups into: one partial each
+  int32_t many_rows;      // the call goes to the many-row kernel (kvq_prefill.hip)
   int32_t context_splits; // pieces the many-row kernel cuts a (sequence, kv head)'s groups into
   unsigned long long* wave_clock;  // measurement build: 8 clock readings per wavefront; else null
 };
@@ -122,12 +125,7 @@ hipError_t launch_write(const void* k, const void* v, const int64_t* slot_mappin
                         int32_t num_tokens, void* cache, float* scales,
                         const kvq_cache_desc_t& desc, hipStream_t stream);
 hipError_t launch_attn(const AttnArgs& a, hipStream_t stream);
-// the kernel for 128 and more query rows per kv head (kvq_prefill.hip)
-inline bool prefill_applies(int64_t rows, int mode) {
-  // (the group-scaled int4 format has no many-row kernel: its row groups go through the
-  // streaming kernel)
-  return rows >= kRowsPerWorkgroup && mode != KVQ_INT4_GROUP32;
-}
+// the kernel for many query rows per kv head (kvq_prefill.hip), where the plan says so
 hipError_t launch_prefill(const AttnArgs& a, hipStream_t stream);
 // the same kernel over a prefix all sequences share, rows of all sequences stacked; leaves
 // partials for the reduce (a.shared_groups > 0, a.prefix_chunks >= 1)

@@ -318,3 +318,18 @@ def test_many_query_rows_over_a_split_context(mode, D, lens, q_len):
     wl = W.custom("split", mode, lens, q_len, 8, 2, D, 16, seed=len(lens) + mode)
     errs = check(wl)
     assert max(errs) <= 5e-4
+
+
+@pytest.mark.parametrize("mode,D,G,q_len", [(W.MODE_INT8, 128, 8, 9), (W.MODE_INT4, 128, 6, 11), (W.MODE_FP8, 128, 8, 15),
+                                            (W.MODE_FP8_TENSOR, 64, 8, 13), (W.MODE_BF16, 128, 3, 11),
+                                            (W.MODE_BF16, 64, 5, 13), (W.MODE_INT8, 128, 4, 17)])
+@pytest.mark.parametrize("lens", [[3000, 20, 64, 700], [40 + 29 * (i % 30) for i in range(300)]],
+                         ids=["few", "crowd"])
+def test_a_workgroup_of_query_rows_that_is_not_full(mode, D, G, q_len, lens):
+    """33 to 127 query rows per kv head where the many-row kernel takes them: row tiles and wavefronts of
+    its one workgroup without rows, with a split context and (many pairs) without; a split-K granule
+    keeps such calls on the streaming kernel, which must agree."""
+    lens = [max(l, q_len) for l in lens]
+    wl = W.custom("part", mode, lens, q_len, 2 * G, 2, D, 16, seed=G + q_len)
+    errs = check(wl, chunks=(0, 256))
+    assert max(errs) <= 5e-4
