@@ -1,10 +1,10 @@
 // paged_decode_attn for many query rows per kv head (a chunk of a prompt attending over its
 // quantized prefix and itself, Section 2's prefill phase fed from the Section 7.2.2 cache).
 //
-// With 128 and more query rows per kv head the work is arithmetic, not memory traffic, and what
-// has to be shared is the dequantization: the streaming kernel converts a group's codes once
-// per 32 rows, this kernel once per 128.  A workgroup of four wavefronts owns 128 query rows of
-// one (sequence, kv head) and walks the context from position 0 to the last position any of its
+// With many query rows per kv head (128 and more; from 33 on where the plan finds it faster)
+// the work is arithmetic, not memory traffic, and what has to be shared is the dequantization:
+// the streaming kernel converts a group's codes once per 32 rows, this kernel once per 128.  A
+// workgroup of four wavefronts owns 128 query rows of one (sequence, kv head) and walks the context from position 0 to the last position any of its
 // rows may see, or one of p.context_splits pieces of it where the call has too few such
 // workgroups to fill the chip (see merge_kernel below).  Per 64-token group
 // each wavefront loads a quarter of the K and V codes, converts them to f16 and puts them in
