@@ -813,9 +813,10 @@ __global__ __launch_bounds__(kReduceThreads) void attn_reduce_kernel(const AttnA
   const int n = na + nb;
   const int rt = 16 * p.row_tiles, all_pairs = p.batch * Hp;
   const int h = pr / p.num_row_groups, rg = pr - h * p.num_row_groups;
-  // this workgroup's rows, and the units that share one
+  // this workgroup's rows, and the units that share one (the parts may reach past the row group,
+  // whose next row is another pair's)
   const int per = (min(rt, p.rows) + (int)gridDim.y - 1) / (int)gridDim.y;
-  const int r0 = (int)blockIdx.y * per, rows = min(per, p.rows - rg * rt - r0);
+  const int r0 = (int)blockIdx.y * per, rows = min(per, min(rt, p.rows - rg * rt) - r0);
   const int slices = units / per;  // (the launch makes units a multiple of per at least)
   const int rl = r0 + unit % per, slice = unit / per;
   const bool live = unit % per < rows && slice < slices;

@@ -333,3 +333,15 @@ def test_a_workgroup_of_query_rows_that_is_not_full(mode, D, G, q_len, lens):
     wl = W.custom("part", mode, lens, q_len, 2 * G, 2, D, 16, seed=G + q_len)
     errs = check(wl, chunks=(0, 256))
     assert max(errs) <= 5e-4
+
+
+@pytest.mark.parametrize("mode,D,groups", [(W.MODE_BF16, 64, 33), (W.MODE_INT8, 64, 41), (W.MODE_FP8, 64, 65),
+                                           (W.MODE_BF16, 64, 74), (W.MODE_INT8, 128, 18), (W.MODE_BF16, 128, 35),
+                                           (W.MODE_INT4_GROUP, 128, 34)])
+def test_row_groups_whose_parts_reach_past_them(mode, D, groups):
+    """40 query rows, two or three row groups, and so many partials per row that the reduce cuts a row
+    group into parts that do not divide it (7 x 5 or 11 x 3 parts of 32 rows, 6 x 3 of 16): the last part
+    must stop at the group's last row, the next row is the next group's."""
+    wl = W.custom("parts", mode, [64 * groups - 9], 5, 16, 2, D, 16, seed=groups)
+    errs = check(wl, chunks=(64, 0))
+    assert max(errs) <= 5e-4
