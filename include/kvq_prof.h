@@ -38,6 +38,15 @@ void kvq_profile_skip_reduce(int on);
  * dequantization among 128 rows.  On initially.  Process-global. */
 void kvq_profile_prefill_kernel(int on);
 
+/* What paged_decode_attn (or, with shared_prefix_tokens, paged_decode_attn_prefix) would launch for
+ * these host-side arguments; batch >= 1.  Host only.  plan_out: [0] 1 if the call goes to the
+ * many-row kernel, [1] pieces that kernel may cut the context into, [2] wavefronts of the streaming
+ * kernel, [3] 64-token groups of the shared prefix that the prefix kernel takes, [4] rows of a row
+ * group, and the reduce's [5] grid in x, [6] grid in y and [7] threads per workgroup. */
+int kvq_profile_plan(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,
+                     int32_t max_seq_len, int32_t chunk_tokens, int32_t shared_prefix_tokens,
+                     int64_t plan_out[8]);
+
 /* While `buf` (device, 16 x uint64 per launched
  * wavefront, i.e. 16 * 8 * (number of wavefronts) bytes) is registered, every wavefront of the
  * streaming kernel stores in buf[16*w + k]: the shader clock at entry (k = 0), after its first

@@ -573,6 +573,22 @@ int kvq_blocks_import(const void* packed_cache, const float* packed_scales,
 }
 
 #ifdef KVQ_PROFILE  // exported by the measurement build only (include/kvq_prof.h)
+int kvq_profile_plan(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,
+                     int32_t max_seq_len, int32_t chunk_tokens, int32_t shared_prefix_tokens,
+                     int64_t plan_out[8]) {
+  kvq::AttnPlan p;
+  int err;
+  if (!make_plan(desc, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, shared_prefix_tokens, &p, &err))
+    return err;
+  if (batch == 0) return KVQ_E_BAD_SHAPE;
+  const kvq::ReduceLaunch r =
+      kvq::reduce_launch(batch, p.pairs_per_seq, p.num_waves, p.rows, p.row_tiles, desc->head_dim);
+  const int64_t values[8] = {p.many_rows, p.context_splits, p.num_waves, p.shared_groups,
+                             16 * p.row_tiles, r.pairs, r.parts, r.threads};
+  for (int i = 0; i < 8; ++i) plan_out[i] = values[i];
+  return KVQ_OK;
+}
+
 void kvq_profile_split_events(void* before, void* after) {
   kvq::set_profile_events((hipEvent_t)before, (hipEvent_t)after);
 }

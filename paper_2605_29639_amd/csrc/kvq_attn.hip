@@ -783,8 +783,6 @@ __global__ __launch_bounds__(64, PER_SIMD) void attn_stream_kernel(const AttnArg
 // to be all of them, as a rule.  A wavefront per (sequence, query head) with its query tokens one after
 // the other, the earlier form, took 28 us for 32 query rows x 512 pairs of three partials each, now 16;
 // 16 us for 16 rows x 128 pairs of 17, now 11; 10 us for 4 rows x 1024 pairs of three, now 6.
-constexpr int kReduceBatch = 8;      // partials a unit requests at once
-constexpr int kReduceThreads = 512;  // at most (1024 would leave 128 registers, and spills)
 template <int D>
 __global__ __launch_bounds__(kReduceThreads) void attn_reduce_kernel(const AttnArgs p) {
   constexpr int LR = D / 4;  // lanes per unit
@@ -983,17 +981,8 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t stream) {
     e = a.head_dim == 128 ? launch_stream<KVQ_BF16_PLAIN, 128>(a, stream)
                           : launch_stream<KVQ_BF16_PLAIN, 64>(a, stream);
   if (e != hipSuccess || stream_only) return e;
-  // a unit of head_dim / 4 lanes for each row, or for every eight of a row's partials where it has more
-  // than that on average (a shared prefix does not count: a prefix that is dropped on the device
-  // leaves the call paged_decode_attn's bit for bit); as many rows to a workgroup as its threads hold
-  const int64_t pairs = (int64_t)a.batch * a.pairs_per_seq;
-  const int units = kReduceThreads / (a.head_dim / 4);
-  const int rows = a.rows < 16 * a.row_tiles ? a.rows : 16 * a.row_tiles;
-  const int64_t wanted = (a.num_waves / pairs + 2 + kReduceBatch - 1) / kReduceBatch;
-  const int slices = (int)(wanted < units ? wanted : units);
-  const int most = units / slices, parts = (rows + most - 1) / most, per = (rows + parts - 1) / parts;
-  const dim3 rgrid((unsigned)pairs, (unsigned)parts);
-  const dim3 threads((unsigned)(per * slices * (a.head_dim / 4) + 63) / 64 * 64);
+  const ReduceLaunch r = reduce_launch(a.batch, a.pairs_per_seq, a.num_waves, a.rows, a.row_tiles, a.head_dim);
+  const dim3 rgrid((unsigned)r.pairs, (unsigned)r.parts), threads((unsigned)r.threads);
   if (a.head_dim == 128)
     hipLaunchKernelGGL((attn_reduce_kernel<128>), rgrid, threads, 0, stream, a);
   else

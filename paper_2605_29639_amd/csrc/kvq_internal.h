@@ -80,6 +80,34 @@ constexpr int kMaxPrefixChunks = 8;  // pieces a shared prefix is cut into at mo
 constexpr int kRowsPerWorkgroup = 128;    // query rows a workgroup of the many-row kernel owns
 constexpr int kMaxContextSplits = 64;     // pieces that kernel's walk over the context is cut into at most
 
+constexpr int kReduceBatch = 8;      // partials a unit of the reduce requests at once
+constexpr int kReduceThreads = 512;  // at most (1024 would leave 128 registers, and spills)
+
+// Launch of the reduce: a workgroup per (pair, part of its row group's rows).
+struct ReduceLaunch {
+  int64_t pairs;
+  int32_t parts, threads;
+};
+// A unit of head_dim / 4 lanes for each row, or for every eight of a row's partials where it has more
+// than that on average (a shared prefix does not count: a prefix that is dropped on the device
+// leaves the call as it is without one, bit for bit); as many rows to a workgroup as its threads
+// hold.  A launch has fewer than 2^32 threads in x, so very many pairs get smaller workgroups.
+inline ReduceLaunch reduce_launch(int64_t batch, int64_t pairs_per_seq, int64_t num_waves, int rows,
+                                  int row_tiles, int head_dim) {
+  ReduceLaunch l;
+  l.pairs = batch * pairs_per_seq;
+  int most_threads = kReduceThreads;
+  while (most_threads > 64 && l.pairs * most_threads > 0xFFFFFFFFll) most_threads /= 2;
+  const int lanes = head_dim / 4, units = most_threads / lanes;
+  rows = rows < 16 * row_tiles ? rows : 16 * row_tiles;
+  const int64_t wanted = (num_waves / l.pairs + 2 + kReduceBatch - 1) / kReduceBatch;
+  const int slices = (int)(wanted < units ? wanted : units), most = units / slices;
+  l.parts = (rows + most - 1) / most;
+  const int per = (rows + l.parts - 1) / l.parts;
+  l.threads = (per * slices * lanes + 63) / 64 * 64;
+  return l;
+}
+
 struct AttnPlan {
   int32_t rows;            // (num_q_heads / num_kv_heads) * q_len query rows per kv head
   int32_t row_tiles;       // 16-row tiles handled by one wavefront (1 or 2)
@@ -129,7 +157,6 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t stream);
 hipError_t launch_prefill(const AttnArgs& a, hipStream_t stream);
 // the same kernel over a prefix all sequences share, rows of all sequences stacked; leaves
 // partials for the reduce (a.shared_groups > 0, a.prefix_chunks >= 1)
-bool prefix_applies(const AttnArgs& a);
 hipError_t launch_prefix(const AttnArgs& a, hipStream_t stream);
 #ifdef KVQ_PROFILE  // the measurement build's switches (include/kvq_prof.h)
 void set_prefill_kernel(bool on);

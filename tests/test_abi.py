@@ -66,6 +66,39 @@ def test_sizes():
     assert L.kvq_cache_bytes(None) == 0
 
 
+PLAN = ("many_rows", "context_splits", "num_waves", "shared_groups", "group_rows", "pairs", "parts", "threads")
+
+
+def plan(desc, batch, q_len, hq, max_len, chunk=0, prefix=0):
+    out = (C.c_int64 * 8)()
+    rc = kvq.prof_lib().kvq_profile_plan(C.byref(desc), batch, q_len, hq, max_len, chunk, prefix, out)
+    assert rc == kvq.OK
+    return dict(zip(PLAN, out))
+
+
+@pytest.mark.parametrize("mode,D,H,G,q_len,max_len", [(5, 128, 8, 8, 512, 512), (0, 128, 8, 4, 4, 64), (0, 64, 8, 8, 4, 64),
+                                                      (0, 128, 8, 4, 1, 64), (0, 64, 1, 2, 1, 4096)])
+def test_the_reduce_of_very_many_pairs_fits_a_launch(mode, D, H, G, q_len, max_len):
+    """A grid has fewer than 2^32 threads in x, whatever the number of pairs; every row of a row group has a
+    unit of head_dim / 4 lanes in some part."""
+    for log2 in range(25):
+        batch = 1 << log2
+        groups = (max_len + 63) // 64
+        rows = G * q_len
+        row_groups = -(-rows // (16 if rows <= 16 or mode == 5 else 32))
+        desc = d(mode=mode, H=H, D=D, nblk=64)
+        need = kvq.workspace_bytes(desc, batch, q_len, H * G, max_len, 0)
+        # (stop where the call is refused, the flat list's index being 32 bits, or where no GPU could hold
+        # its partials and output)
+        if batch * groups * H * row_groups > 0x7FFFFFFF or need + batch * rows * H * D * 4 > 288 << 30:
+            break
+        p = plan(desc, batch, q_len, H * G, max_len)
+        assert p["pairs"] == batch * H * row_groups
+        assert p["pairs"] * p["threads"] < 1 << 32
+        assert 64 <= p["threads"] <= 512 and p["threads"] % 64 == 0
+        assert p["parts"] * (p["threads"] // (D // 4)) >= min(rows, p["group_rows"])
+
+
 FAKE = C.c_void_p(0x1000)  # never dereferenced: every call below fails validation first
 
 
