@@ -72,19 +72,19 @@ int ilog2(int x) {
   return s;
 }
 
-// Pieces the many-row kernel cuts every (sequence, kv head)'s walk over the context into, given how
-// many the workspace has room for.  Without a split a call launches `walks` workgroups of 128 query
-// rows, and one sequence's chunk of a prompt leaves most of the chip idle (512 tokens of 32 / 8
-// heads: 128 workgroups, where two run on each of 256 compute units).  The estimate below is in
+// Pieces the many-row kernel should cut the contexts into where all sequences have `groups` 64-token
+// groups, given how many the workspace has room for.  Without a split a call launches `walks` workgroups
+// of 128 query rows, and one sequence's chunk of a prompt leaves most of the chip idle (512 tokens of
+// 32 / 8 heads: 128 workgroups, where two run on each of 256 compute units).  The estimate below is in
 // microseconds, from measurements at head_dim 128: 2.6 per 64-token group and workgroup with two
 // of them on a compute unit, 0.6 of that with one, about 3 until a workgroup's first group is
 // consumed; splitting adds the second launch and writes and reads 64 KB per workgroup.  One
 // sequence's 512 tokens over 16384 cached ones (fp8, 32 / 8 heads): 427 us in one piece, 178 in
 // four with the merge; eight such chunks over 4096 (1024 workgroups, two full rounds) stay whole.
-int context_splits(int64_t walks, int64_t groups, int64_t room) {
+int64_t equal_pieces(int64_t walks, int64_t groups, int64_t room) {
   const int64_t slots = auto_waves() / 4;
   if (walks >= 4 * slots) return 1;
-  int best = 1;
+  int64_t best = 1;
   double best_us = 0.0;
   for (int64_t c = 1; c <= room && c <= kvq::kMaxContextSplits && (c == 1 || c * 2 <= groups); ++c) {
     const int64_t n = walks * c, rest = n % slots;
@@ -93,11 +93,37 @@ int context_splits(int64_t walks, int64_t groups, int64_t room) {
     const double us = rounds * (3.0 + 2.6 * (double)((groups + c - 1) / c)) +
                       (c > 1 ? 6.0 + 0.025 * (double)n : 0.0);
     if (c == 1 || us < best_us) {
-      best = (int)c;
+      best = c;
       best_us = us;
     }
   }
   return best;
+}
+
+// How the many-row kernel may cut the contexts: the pieces themselves are worked out on the device, from
+// the lengths (max_seq_len is only a bound on them).  With few workgroups: as many cuts as equal
+// contexts of max_seq_len would get, and pieces long enough to be worth the partials they leave (a
+// workgroup's partials cost the chip 0.025 us, its groups 1.6 us of one slot).  With enough
+// workgroups and fewer than 128 rows: one slot's worth of cuts per (kv head, row block), for contexts
+// longer than 1.5 times what a slot gets on average; the streaming kernel, which such calls would
+// otherwise take, splits any mixture of lengths evenly.  64 sequences, one of 65536 tokens and the rest
+// of 1000, 96 rows, 64 / 8 heads, int8: streaming 211 us, many-row uncut 1629, cut 109; 300 of 40 to
+// 2000 tokens: 414, 162 and 175 (the pieces are worked out, and none is needed).  A 512-token chunk
+// on its own under a bound of 32768: 21 us without leave to cut, 28 cut by the bound, 23 now (the
+// second launch finds nothing to do); over 4096 tokens, same bound: 117, 63 and 63.
+void cut_contexts(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t seq_rows,
+                  int64_t groups, int64_t slot_rows, kvq::AttnPlan* plan) {
+  const int64_t slots = auto_waves() / 4, room = slot_rows / seq_rows;
+  const int64_t per_seq = d->num_kv_heads * ((rows + kvq::kRowsPerWorkgroup - 1) / kvq::kRowsPerWorkgroup);
+  plan->piece_min = (int32_t)(per_seq < 32 ? 2 : per_seq / 16);
+  const int64_t c = equal_pieces(batch * per_seq, groups, room / batch + 1);
+  if (c > 1) {
+    plan->extra_pieces = (int32_t)(batch * (c - 1));
+  } else if (rows < kvq::kRowsPerWorkgroup && groups > 2 * plan->piece_min) {
+    const int64_t extra = (slots + per_seq - 1) / per_seq;
+    plan->extra_pieces = (int32_t)(extra < room ? extra : room);
+    plan->piece_share = 1.5f * (float)per_seq / (float)slots;
+  }
 }
 
 // Whether a call goes to the many-row kernel (a workgroup per 128 query rows of a kv head, keys and values
@@ -117,6 +143,8 @@ bool many_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t m
   if (rows >= kvq::kRowsPerWorkgroup) return true;
   // (a caller's split-K granule is the streaming kernel's, and so is what follows a shared prefix)
   if (chunk_tokens > 0 || shared_prefix) return false;
+  // (the merge's launch has 32 threads for every output row, and fewer than 2^32)
+  if (batch * d->num_kv_heads > 1 << 19) return false;
   const int64_t passes = (rows + 31) / 32 + (d->mode == KVQ_BF16_PLAIN ? 1 : 0);
   if (passes >= (d->head_dim == 128 ? 3 : 4)) return rows > 32;
   return rows > 32 && d->head_dim == 128 && max_seq_len <= 2048 &&
@@ -207,16 +235,14 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
     plan->num_waves = (int32_t)(flat_max < 1 ? 1 : flat_max < waves ? flat_max : waves);
   }
   // A many-row call has the same workspace as if it went through the streaming kernel; the pieces
-  // of a split context beyond the first (whose rows go to `out`) use it, row by row of `out`.
-  plan->context_splits = 1;
+  // of a cut context beyond the first (whose rows go to `out`) use it, a sequence's rows each.
+  plan->extra_pieces = 0;
+  plan->piece_min = 1;
+  plan->piece_share = 0.0f;
   plan->many_rows = batch > 0 && many_rows(d, batch, rows, max_seq_len, chunk_tokens, plan->shared_groups > 0);
-  if (plan->many_rows) {
-    const int64_t out_rows = (int64_t)batch * q_len * num_q_heads;
-    const int64_t walks = (int64_t)batch * d->num_kv_heads *
-                          ((rows + kvq::kRowsPerWorkgroup - 1) / kvq::kRowsPerWorkgroup);
-    plan->context_splits = context_splits(walks, ((int64_t)max_seq_len + 63) / 64,
-                                          (int64_t)slot_rows / out_rows + 1);
-  }
+  if (plan->many_rows)
+    cut_contexts(d, batch, rows, (int64_t)q_len * num_q_heads, ((int64_t)max_seq_len + 63) / 64,
+                 (int64_t)slot_rows, plan);
   return true;
 }
 
@@ -474,7 +500,9 @@ int attn_call(const void* q, const void* cache, const float* scales,
   a.shared_groups = plan.shared_groups;
   a.prefix_chunks = plan.prefix_chunks;
   a.many_rows = plan.many_rows;
-  a.context_splits = plan.context_splits;
+  a.extra_pieces = plan.extra_pieces;
+  a.piece_min = plan.piece_min;
+  a.piece_share = plan.piece_share;
   const hipError_t e = kvq::launch_attn(a, (hipStream_t)stream);
   return e == hipSuccess ? KVQ_OK : KVQ_E_HIP;
 }
@@ -583,7 +611,7 @@ int kvq_profile_plan(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len,
   if (batch == 0) return KVQ_E_BAD_SHAPE;
   const kvq::ReduceLaunch r =
       kvq::reduce_launch(batch, p.pairs_per_seq, p.num_waves, p.rows, p.row_tiles, desc->head_dim);
-  const int64_t values[8] = {p.many_rows, p.context_splits, p.num_waves, p.shared_groups,
+  const int64_t values[8] = {p.many_rows, p.extra_pieces, p.num_waves, p.shared_groups,
                              16 * p.row_tiles, r.pairs, r.parts, r.threads};
   for (int i = 0; i < 8; ++i) plan_out[i] = values[i];
   return KVQ_OK;

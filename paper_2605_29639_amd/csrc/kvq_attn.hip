@@ -44,34 +44,6 @@ struct Cursor {
   int b, pr, g, ng, L;
 };
 
-// Cross-lane scans and reductions on the DPP network (no LDS round trips): Hillis-Steele
-// inside each row of 16 lanes (row_shr 1, 2, 4, 8), then the last lane of row 0 / row 2 into
-// row 1 / row 3 (row_bcast:15) and lane 31 into rows 2 and 3 (row_bcast:31).  Lanes a step does
-// not reach receive the operation's identity.  Lane 63 ends up holding the reduction.
-template <class Op>
-__device__ inline int dpp_scan_bits(int v, int identity, Op op) {
-#define KVQ_DPP_STEP(CTRL, ROWS) \
-  v = op(v, __builtin_amdgcn_update_dpp(identity, v, CTRL, ROWS, 0xF, false))
-  KVQ_DPP_STEP(0x111, 0xF);  // row_shr:1
-  KVQ_DPP_STEP(0x112, 0xF);  // row_shr:2
-  KVQ_DPP_STEP(0x114, 0xF);  // row_shr:4
-  KVQ_DPP_STEP(0x118, 0xF);  // row_shr:8
-  KVQ_DPP_STEP(0x142, 0xA);  // row_bcast:15 into rows 1 and 3
-  KVQ_DPP_STEP(0x143, 0xC);  // row_bcast:31 into rows 2 and 3
-#undef KVQ_DPP_STEP
-  return v;
-}
-__device__ inline int wave_incl_scan(int v) {
-  return dpp_scan_bits(v, 0, [](int a, int b) { return a + b; });
-}
-__device__ inline int lane_value(int v, int lane_index) {  // lane_index wave-uniform
-  return __builtin_amdgcn_readlane(v, lane_index);
-}
-__device__ inline int wave_sum(int v) { return lane_value(wave_incl_scan(v), 63); }
-__device__ inline int wave_min(int v) {
-  return lane_value(dpp_scan_bits(v, 0x7FFFFFFF, [](int a, int b) { return a < b ? a : b; }), 63);
-}
-
 // How the flat list of `flat` groups is cut into wavefront ranges.  With a caller-given granule
 // every range has `requested` groups; otherwise the list is cut into num_waves ranges whose
 // sizes differ by at most one group, range w starting at floor(w * flat / num_waves), so that

@@ -78,7 +78,7 @@ __host__ __device__ inline uint8_t stored_byte(uint8_t code, int mode) {
 
 constexpr int kMaxPrefixChunks = 8;  // pieces a shared prefix is cut into at most
 constexpr int kRowsPerWorkgroup = 128;    // query rows a workgroup of the many-row kernel owns
-constexpr int kMaxContextSplits = 64;     // pieces that kernel's walk over the context is cut into at most
+constexpr int kMaxContextSplits = 64;     // pieces that kernel cuts contexts of one length into at most
 
 constexpr int kReduceBatch = 8;      // partials a unit of the reduce requests at once
 constexpr int kReduceThreads = 512;  // at most (1024 would leave 128 registers, and spills)
@@ -122,7 +122,10 @@ struct AttnPlan {
   int32_t shared_groups;   // shared prefix in 64-token groups, 0 where the prefix kernel is not used
   int32_t prefix_chunks;   // pieces the prefix kernel cuts it into (>= 1)
   int32_t many_rows;       // the call goes to the many-row kernel
-  int32_t context_splits;  // many-row kernel: pieces its walk over the context is cut into (>= 1)
+  // many-row kernel: pieces beyond each sequence's first that the contexts may be cut into (0: no cut),
+  // groups a piece holds at least, and the share of all groups that it holds at least
+  int32_t extra_pieces, piece_min;
+  float piece_share;
 };
 
 struct AttnArgs {
@@ -145,7 +148,8 @@ struct AttnArgs {
                           // blocks (0: none, or a call the prefix kernel does not serve)
   int32_t prefix_chunks;  // pieces the prefix kernel cuts those groups into: one partial each
   int32_t many_rows;      // the call goes to the many-row kernel (kvq_prefill.hip)
-  int32_t context_splits; // pieces the many-row kernel cuts a (sequence, kv head)'s groups into
+  int32_t extra_pieces, piece_min;  // how the many-row kernel may cut the contexts, as in AttnPlan
+  float piece_share;
   unsigned long long* wave_clock;  // measurement build: 8 clock readings per wavefront; else null
 };
 

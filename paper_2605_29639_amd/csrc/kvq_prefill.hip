@@ -4,10 +4,10 @@
 // With many query rows per kv head (128 and more; from 33 on where the plan finds it faster)
 // the work is arithmetic, not memory traffic, and what has to be shared is the dequantization:
 // the streaming kernel converts a group's codes once per 32 rows, this kernel once per 128.  A
-// workgroup of four wavefronts owns 128 query rows of one (sequence, kv head) and walks the context from position 0 to the last position any of its
-// rows may see, or one of p.context_splits pieces of it where the call has too few such
-// workgroups to fill the chip (see merge_kernel below).  Per 64-token group
-// each wavefront loads a quarter of the K and V codes, converts them to f16 and puts them in
+// workgroup of four wavefronts owns 128 query rows of one (sequence, kv head) and walks the context
+// from position 0 to the last position any of its rows may see, or a piece of it where the call has too
+// few such workgroups to fill the chip or some contexts are far longer than others (see
+// context_piece and merge_kernel below).  Per 64-token group each wavefront loads a quarter of the K and V codes, converts them to f16 and puts them in
 // LDS in the order the matrix instruction wants its A operand (one 16-byte read per lane and
 // instruction, no bank conflicts); after a barrier every wavefront runs QK^T, the online
 // softmax and P.V for its own 32 rows against the shared operands.  LDS holds two groups, so
@@ -26,11 +26,88 @@ namespace {
 constexpr int kWavesPerGroup = 4;
 static_assert(kRowsPerWorkgroup == kWavesPerGroup * 32, "a wavefront owns two 16-row tiles");
 
-// minimum over the wavefront
+// minimum over the wavefront (by shuffles: with a result the compiler knows to be uniform it makes two
+// copies of the PREFIX kernel's loop and spills)
 __device__ inline int wave_min_int(int v) {
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) v = min(v, __shfl_xor(v, d, 64));
   return v;
+}
+
+// A workgroup's place among the pieces the contexts are cut into.
+struct Piece {
+  int b, chunk, pieces;  // chunk of `pieces` of sequence b's context
+  int extra;             // pieces beyond the first ones of their sequences that come before this one
+};
+
+// The f-th piece of the batch.  Decided here, from the lengths themselves, because the host has only an
+// upper bound on them: sequences are cut into pieces of k groups, the smallest k (p.piece_min,
+// p.piece_share of all groups at least) that makes no more than p.extra_pieces cuts.  So a batch of equal
+// contexts is cut evenly, one long context among short ones is cut alone, and short ones are left
+// whole however large the declared bound.  Every wavefront works it out for itself, a round trip
+// ahead of its first code.  `leave` (wave-uniform): also store the extra pieces before every
+// sequence, for the merge.  Returns false for a piece that does not exist.
+__device__ inline bool context_piece(const AttnArgs& p, int f, bool leave, Piece& piece) {
+  const int lane = threadIdx.x & 63, B = p.batch, E = p.extra_pieces;
+  const int32_t* __restrict__ seq_lens = p.seq_lens;
+  if (B == 1) {  // (the rule below, on scalars)
+    const int g = (seq_lens[0] + 63) >> 6;
+    const int k = max(max(p.piece_min, (int)((float)g * p.piece_share)), (g + E) / (E + 1));
+    piece = Piece{0, f, g > 0 ? (g - 1) / k + 1 : 1, max(f - 1, 0)};
+    if (leave && lane < 2) p.ws_prefix[lane] = lane == 0 ? 0 : piece.pieces - 1;
+    return f < piece.pieces;
+  }
+  auto groups = [&](int i) { return i < B ? (seq_lens[i] + 63) >> 6 : 0; };
+  const int own = groups(lane);  // (up to 64 sequences: a lane each, and no further loads)
+  int total = own, top = own;
+  for (int i = lane + 64; i < B; i += 256) {
+    const int g[4] = {groups(i), groups(i + 64), groups(i + 128), groups(i + 192)};
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      total += g[n];
+      top = max(top, g[n]);
+    }
+  }
+  total = wave_sum(total);
+  top = -wave_min(-top);
+  int k = max(p.piece_min, (int)((float)total * p.piece_share));
+  if (B > 64) {
+    k = max(k, (total + E - 1) / E);  // (a sequence of g groups is cut (g - 1) / k times)
+  } else {
+    k = max(k, (total + E + B - 1) / (E + B));  // (no smaller one can do)
+    while (k < top && wave_sum(own > 0 ? (own - 1) / k : 0) > E) k += max(1, k >> 3);
+  }
+  if (k >= top) {  // nothing to cut
+    if (leave)
+      for (int i = lane; i <= B; i += 64) p.ws_prefix[i] = 0;
+    piece = Piece{f, 0, 1, 0};
+    return f < B;
+  }
+  int base = 0;
+  bool found = false;
+  for (int i0 = 0; i0 < B; i0 += 64) {
+    const int g = i0 == 0 ? own : groups(i0 + lane), cuts = g > 0 ? (g - 1) / k : 0;
+    const int incl = wave_incl_scan(cuts);  // cuts up to and including the lane's sequence
+    if (leave) {
+      if (i0 + lane < B) p.ws_prefix[i0 + lane + 1] = base + incl;
+      if (i0 == 0 && lane == 0) p.ws_prefix[0] = 0;
+    }
+    if (!found) {
+      // the sequences here whose pieces all lie before piece f
+      const int n = __popcll(__ballot(i0 + lane < B && base + incl + i0 + lane + 1 <= f));
+      if (n < 64 && i0 + n < B) {
+        found = true;
+        const int before = base + (n > 0 ? lane_value(incl, n - 1) : 0);
+        piece.b = i0 + n;
+        piece.chunk = f - before - piece.b;
+        piece.pieces = lane_value(cuts, n) + 1;
+        piece.extra = before + max(piece.chunk - 1, 0);
+      }
+    }
+    base += lane_value(incl, 63);
+    if (found && !leave) break;
+  }
+  return found;
 }
 
 // PREFIX = true is the kernel for a prefix that every sequence of a decode or verification
@@ -82,9 +159,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
   // the eight XCDs in turn, each with an L2 of its own, and the row blocks of one (sequence,
   // kv head) read the same codes: they are placed on one XCD (workgroups x, x + 8, x + 16, ...)
   // so that the codes leave HBM once, not once per XCD.
-  int pair, rb;  // pair = (sequence, piece of its context, kv head); PREFIX: (piece of the prefix, kv head)
+  int pair, rb;  // pair = (piece of the contexts, kv head); PREFIX: (piece of the prefix, kv head)
   {
-    const int pairs = (PREFIX ? p.prefix_chunks : p.batch * p.context_splits) * H, id = blockIdx.x;
+    const int pairs = (PREFIX ? p.prefix_chunks : p.batch + p.extra_pieces) * H, id = blockIdx.x;
     if (pairs % 8 == 0) {
       const int x = id & 7, k = id >> 3;
       pair = x + 8 * (k / row_blocks);
@@ -100,6 +177,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
   const int r0 = rb * kRowsPerWorkgroup + wv * 32;
   const bool wave_live = r0 < all_rows;
   int b, L, g0, ng, n_min, chunk = 0;
+  Piece piece{0, 0, 1, 0};
   if constexpr (PREFIX) {
     chunk = pair / H;
     b = rb * kRowsPerWorkgroup / p.rows;  // whose block table: the first row's sequence (all agree)
@@ -108,17 +186,17 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
     ng = (int)((long long)(chunk + 1) * P / p.prefix_chunks);
     n_min = 0;  // (set below, from the rows' own causal lengths)
   } else {
-    b = pair / H;
-    if (p.context_splits > 1) {
-      chunk = b % p.context_splits;
-      b /= p.context_splits;
-    }
+    piece.b = pair / H;
+    if (p.extra_pieces > 0 &&
+        !context_piece(p, piece.b, __builtin_amdgcn_readfirstlane((int)(blockIdx.x == 0 && wv == 0)), piece))
+      return;
+    b = piece.b;
     L = p.seq_lens[b];
     const int r_last = min(p.rows, (rb + 1) * kRowsPerWorkgroup) - 1;
     const int n_max = L - p.q_len + r_last / G + 1;
     const int all = (n_max + 63) >> 6;
-    g0 = (int)((long long)chunk * all / p.context_splits);
-    ng = (int)((long long)(chunk + 1) * all / p.context_splits);
+    g0 = (int)((long long)piece.chunk * all / piece.pieces);
+    ng = (int)((long long)(piece.chunk + 1) * all / piece.pieces);
     n_min = wave_live ? L - p.q_len + r0 / G + 1 : L;  // shortest causal length here
   }
 
@@ -362,7 +440,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
   // ---- the walk: group g is consumed from half g % 2 while group g + 1 is converted into the
   // other half and group g + 2 is requested (indices past the end repeat the last group) ----
   Entries e_next, e_after;
-  if (g0 < ng) {  // (a context shorter than its number of pieces leaves some of them empty)
+  if (g0 < ng) {  // (a chunk's first rows see fewer groups than there may be pieces)
     Entries e0;
     fetch_entries(g0, e0);
     fetch_entries(min(g0 + 1, ng - 1), e_next);
@@ -411,53 +489,58 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
     }
     return;
   }
-  // ---- normalised rows: the first piece's (the only one's, without a split) go to `out`, the
-  // others' to the workspace, which holds rows in the order of `out`, one such array per piece ----
-  const size_t out_rows = (size_t)p.batch * p.q_len * p.num_q_heads;
-  float* dst = chunk == 0 ? p.out : p.ws_acc + (size_t)(chunk - 1) * out_rows * D;
+  // ---- normalised rows: those of a sequence's first piece (mostly the only one) go to `out`, the
+  // others' to the workspace, a piece's rows in the order its sequence's have in `out`; the logarithms
+  // of the denominators likewise, those of first pieces ahead ----
+  const size_t seq_rows = (size_t)p.q_len * p.num_q_heads;
+  const size_t to = (size_t)(piece.chunk == 0 ? b : piece.extra) * seq_rows;
+  float* dst = (piece.chunk == 0 ? p.out : p.ws_acc) + to * D;
+  float* lse = p.ws_ml + ((piece.chunk == 0 ? 0 : (size_t)p.batch * seq_rows) + to);
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     const float l = xor16_sum(l_run[nt]);
     const int r = r0 + nt * 16 + m16;
     if (r >= p.rows) continue;
     const int j = r / G, gi = r - j * G;
-    const size_t row = ((size_t)b * p.q_len + j) * p.num_q_heads + (size_t)h * G + gi;
+    const size_t row = (size_t)j * p.num_q_heads + (size_t)h * G + gi;
     float* orow = dst + row * D;
     float inv = 1.0f / l;
-    if (p.context_splits > 1) {  // a row may see nothing of a piece
+    if (piece.pieces > 1) {  // a row may see nothing of a piece
       inv = l > 0.0f ? inv : 0.0f;
-      if (g4 == 0)
-        p.ws_ml[(size_t)chunk * out_rows + row] =
-            l > 0.0f ? m_run[nt] + __builtin_amdgcn_logf(l) : -INFINITY;
+      if (g4 == 0) lse[row] = l > 0.0f ? m_run[nt] + __builtin_amdgcn_logf(l) : -INFINITY;
     }
 #pragma unroll
     for (int tt = 0; tt < DT; ++tt) *(floatx4*)(orow + 16 * tt + 4 * g4) = acc[nt][tt] * inv;
   }
 }
 
-// ---- the pieces of a split context put together: out = sum_c w_c out_c / sum_c w_c with
+// ---- the pieces of cut contexts put together: out = sum_c w_c out_c / sum_c w_c with
 // w_c = 2^(lse_c), lse_c the base-2 logarithm of piece c's softmax denominator.  A thread owns four
-// channels of a row.  Memory-bound (every piece's rows read once, `out` written once), all loads of
-// up to four pieces in flight together. ----
-__global__ __launch_bounds__(256) void merge_kernel(float* __restrict__ out,
-                                                    const float* __restrict__ acc,
-                                                    const float* __restrict__ lse, int64_t rows,
-                                                    int quads_shift, int splits) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;  // (row, four channels)
-  const int64_t row = i >> quads_shift;
-  if (row >= rows) return;
-  const size_t stride = (size_t)rows << quads_shift;  // floatx4s per piece
-  const floatx4* __restrict__ pieces = (const floatx4*)acc + i;
-  floatx4 sum = ((const floatx4*)out)[i];
-  float M = lse[row], den = 1.0f;
+// channels of a row; workgroup = (sequence, 256 threads' worth of its rows), so that those of a
+// sequence that was left whole end at once.  Memory-bound (every piece's rows read once, `out`
+// written once), all loads of up to four pieces in flight together. ----
+__global__ __launch_bounds__(256) void merge_kernel(const AttnArgs p, int quads_shift, int parts) {
+  const int b = (int)(blockIdx.x / (uint32_t)parts), part = (int)(blockIdx.x - (uint32_t)b * parts);
+  const int first = p.ws_prefix[b], splits = 1 + p.ws_prefix[b + 1] - first;
+  if (splits == 1) return;
+  const size_t seq_rows = (size_t)p.q_len * p.num_q_heads;
+  const size_t i = (size_t)part * 256 + threadIdx.x, row = i >> quads_shift;  // (row, four channels)
+  if (row >= seq_rows) return;
+  const size_t quads = seq_rows << quads_shift;  // floatx4s per piece
+  floatx4* const out = (floatx4*)p.out + (size_t)b * quads + i;
+  // (piece c lies c pieces from here; the first one's rows are in `out`)
+  const floatx4* __restrict__ pieces = (const floatx4*)p.ws_acc + (size_t)first * quads + i;
+  const float* __restrict__ lse = p.ws_ml + ((size_t)p.batch + first) * seq_rows + row;
+  floatx4 sum = *out;
+  float M = p.ws_ml[(size_t)b * seq_rows + row], den = 1.0f;
   for (int c0 = 1; c0 < splits; c0 += 4) {
     floatx4 a[4];
     float e[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int c = min(c0 + k, splits - 1);
-      a[k] = pieces[(size_t)(c - 1) * stride];
-      e[k] = c0 + k < splits ? lse[(size_t)c * rows + row] : -INFINITY;
+      a[k] = pieces[(size_t)(c - 1) * quads];
+      e[k] = c0 + k < splits ? lse[(size_t)(c - 1) * seq_rows] : -INFINITY;
     }
     const float top = fmaxf(fmaxf(fmaxf(e[0], e[1]), fmaxf(e[2], e[3])), M);
     const float safe = top == -INFINITY ? 0.0f : top;
@@ -472,7 +555,7 @@ __global__ __launch_bounds__(256) void merge_kernel(float* __restrict__ out,
       den += w;
     }
   }
-  ((floatx4*)out)[i] = sum * (1.0f / den);
+  *out = sum * (1.0f / den);
 }
 
 }  // namespace
@@ -504,13 +587,12 @@ hipError_t launch_many_rows(const AttnArgs& a, int all_rows, int walks, hipStrea
 }
 
 hipError_t launch_prefill(const AttnArgs& a, hipStream_t stream) {
-  const hipError_t e = launch_many_rows<false>(a, a.rows, a.batch * a.context_splits, stream);
-  if (e != hipSuccess || a.context_splits == 1) return e;
-  const int64_t rows = (int64_t)a.batch * a.q_len * a.num_q_heads;
+  const hipError_t e = launch_many_rows<false>(a, a.rows, a.batch + a.extra_pieces, stream);
+  if (e != hipSuccess || a.extra_pieces == 0) return e;
   const int quads_shift = a.head_dim == 128 ? 5 : 4;
-  const int64_t blocks = ((rows << quads_shift) + 255) / 256;
-  hipLaunchKernelGGL(merge_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, a.out, a.ws_acc,
-                     a.ws_ml, rows, quads_shift, (int)a.context_splits);
+  const int64_t parts = ((((int64_t)a.q_len * a.num_q_heads) << quads_shift) + 255) / 256;
+  hipLaunchKernelGGL(merge_kernel, dim3((unsigned)(a.batch * parts)), dim3(256), 0, stream, a, quads_shift,
+                     (int)parts);
   return hipGetLastError();
 }
 

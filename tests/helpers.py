@@ -37,17 +37,22 @@ from paper_2605_29639_amd.fill import attn_err, bits_to_bf16_tensor, gpu_desc, g
 
 
 def gpu_attention(wl, cache, scales, desc, chunk_tokens=None, seq_lens=None, q=None, q_len=None,
-                  L=None, shared_prefix_tokens=0):
-    """Run the library's paged_decode_attn on a device cache; returns float32 numpy out."""
+                  L=None, shared_prefix_tokens=0, max_len=None):
+    """Run the library's paged_decode_attn on a device cache; returns float32 numpy out.  max_len: the
+    declared bound on the lengths, by default the longest one."""
     import torch
     from paper_2605_29639_amd import kvq
     q_len = wl.q_len if q_len is None else q_len
     seq_lens = wl.seq_lens if seq_lens is None else seq_lens
     qbits = wl.q if q is None else q
     chunk = wl.chunk_tokens if chunk_tokens is None else chunk_tokens
-    max_len = int(seq_lens.max())
+    max_len = int(seq_lens.max()) if max_len is None else max_len
+    tables = wl.block_tables
+    if tables.shape[1] * wl.block_size < max_len:   # (columns no sequence reaches)
+        more = -(-max_len // wl.block_size) - tables.shape[1]
+        tables = np.pad(tables, ((0, 0), (0, more)), constant_values=-1)
     qd = bits_to_bf16_tensor(qbits)
-    bt = torch.from_numpy(wl.block_tables).cuda()
+    bt = torch.from_numpy(tables).cuda()
     sl = torch.from_numpy(np.ascontiguousarray(seq_lens, dtype=np.int32)).cuda()
     out = torch.full((qbits.shape[0], qbits.shape[1], wl.head_dim), float("nan"),
                      dtype=torch.float32, device="cuda")

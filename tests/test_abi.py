@@ -66,7 +66,7 @@ def test_sizes():
     assert L.kvq_cache_bytes(None) == 0
 
 
-PLAN = ("many_rows", "context_splits", "num_waves", "shared_groups", "group_rows", "pairs", "parts", "threads")
+PLAN = ("many_rows", "extra_pieces", "num_waves", "shared_groups", "group_rows", "pairs", "parts", "threads")
 
 
 def plan(desc, batch, q_len, hq, max_len, chunk=0, prefix=0):
@@ -97,6 +97,25 @@ def test_the_reduce_of_very_many_pairs_fits_a_launch(mode, D, H, G, q_len, max_l
         assert p["pairs"] * p["threads"] < 1 << 32
         assert 64 <= p["threads"] <= 512 and p["threads"] % 64 == 0
         assert p["parts"] * (p["threads"] // (D // 4)) >= min(rows, p["group_rows"])
+
+
+@pytest.mark.parametrize("mode,D", [(0, 128), (1, 128), (2, 128), (4, 128), (0, 64), (2, 64), (3, 64)])
+def test_many_row_calls_may_always_cut_a_long_context(mode, D):
+    """The host knows a bound on the lengths and not their mixture: fewer than 128 query rows, which the
+    streaming kernel would split evenly, never go to the many-row kernel without leave to cut, and no call
+    may cut more than its workspace holds."""
+    desc = d(mode=mode, H=8, D=D, nblk=64)
+    for q_len in (5, 8, 12, 15, 16, 64, 512):
+        for batch in (1, 3, 64, 65, 300, 2000):
+            for max_len in (512, 2048, 32768):
+                p = plan(desc, batch, q_len, 64, max_len)
+                if not p["many_rows"]:
+                    assert q_len < 16
+                    continue
+                if q_len < 16:
+                    assert p["extra_pieces"] >= 1 or max_len <= 256, (q_len, batch, max_len)
+                held = kvq.workspace_bytes(desc, batch, q_len, 64, max_len, 0)
+                assert p["extra_pieces"] * q_len * 64 * D * 4 < held
 
 
 FAKE = C.c_void_p(0x1000)  # never dereferenced: every call below fails validation first

@@ -345,3 +345,23 @@ def test_row_groups_whose_parts_reach_past_them(mode, D, groups):
     wl = W.custom("parts", mode, [64 * groups - 9], 5, 16, 2, D, 16, seed=groups)
     errs = check(wl, chunks=(64, 0))
     assert max(errs) <= 5e-4
+
+
+@pytest.mark.parametrize("mode,D,G,q_len", [(W.MODE_INT8, 128, 8, 12), (W.MODE_BF16, 64, 8, 13), (W.MODE_INT4, 128, 4, 33),
+                                            (W.MODE_FP8, 64, 8, 20)])
+@pytest.mark.parametrize("lens", [[2900], [70, 3100] + [70 + i for i in range(20)], [64 * i + 1 for i in range(30)],
+                                  [40] * 40 + [2500] + [130] * 60, [65 + i for i in range(130)] + [3000, 1]],
+                         ids=["one", "one long", "all lengths", "one long of 101", "the last but one long"])
+def test_contexts_are_cut_by_their_lengths(mode, D, G, q_len, lens):
+    """The many-row kernel works its pieces out on the device: one long context among short ones, up to
+    64 sequences and more, whatever bound on the lengths the call declares (with a bound far above
+    them all, short contexts stay whole)."""
+    lens = [max(l, q_len) for l in lens]
+    wl = W.custom("cut", mode, lens, q_len, 2 * G, 2, D, 16, seed=len(lens) + D)
+    oc, osc = oracle_fill(wl)
+    want = oracle_out(wl, oc, osc)
+    cache, scales, desc = upload_oracle_cache(wl, oc, osc)
+    for bound in (max(lens), max(lens) + 77, 20000):
+        got = gpu_attention(wl, cache, scales, desc, chunk_tokens=0, max_len=bound)
+        assert np.isfinite(got).all(), bound
+        assert attn_err(got, want) <= 5e-4, bound

@@ -144,3 +144,44 @@ def test_a_captured_verify_step_with_a_shared_prefix_replays_like_eager_calls():
         assert torch.equal(out_g, out_e), "replay %d differs from the eager calls" % replay
         assert torch.equal(cache_g, cache_e) and torch.equal(scales_g, scales_e), replay
         assert torch.isfinite(out_g).all()
+
+
+@pytest.mark.parametrize("mode,D,q_len", [(W.MODE_INT8, 128, 40), (W.MODE_BF16, 64, 13)])
+def test_a_captured_many_row_call_cuts_the_contexts_of_each_replay(mode, D, q_len):
+    """How the contexts are cut is worked out on the device from the lengths of the moment: a graph
+    captured with one long sequence replays with another long one, with none, and with all of them
+    long, bit for bit like eager calls."""
+    import torch
+    from paper_2605_29639_amd import kvq
+    wl = W.custom("graph_cut", mode, [2500, 2300, 2400], q_len, 16, 2, D, 16, seed=9)
+    bt = torch.from_numpy(wl.block_tables).cuda()
+    cache, scales, desc = gpu_fill(wl)
+    bound = int(wl.seq_lens.max())
+    q = bits_to_bf16_tensor(wl.q)
+    ws = [kvq.alloc_workspace(desc, wl.batch, q_len, 16, bound, 0) for _ in range(2)]
+    out = [torch.zeros(q.shape, dtype=torch.float32, device="cuda") for _ in range(2)]
+    static = torch.tensor([2500, 60, 50], dtype=torch.int32, device="cuda")
+
+    def call(lens, i):
+        kvq.paged_decode_attn(q, cache, scales, desc, bt, lens, q_len, bound, wl.sm_scale, out[i], ws[i])
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        call(static, 0)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(static, 0)
+    for lens in ([2500, 60, 50], [41, 2300, 700], [64, 65, 40], [2500, 2300, 2400], [60, 40, 2400]):
+        new = torch.tensor(lens, dtype=torch.int32, device="cuda")
+        static.copy_(new)
+        ws[0].fill_(0xFF)
+        out[0].fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        call(new, 1)
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], out[1]), lens
+        assert torch.isfinite(out[0]).all()
