@@ -234,6 +234,7 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
     const int64_t waves = auto_waves();
     plan->num_waves = (int32_t)(flat_max < 1 ? 1 : flat_max < waves ? flat_max : waves);
   }
+  plan->few_waves = plan->num_waves <= auto_waves() / 2;
   // A many-row call has the same workspace as if it went through the streaming kernel; the pieces
   // of a cut context beyond the first (whose rows go to `out`) use it, a sequence's rows each.
   plan->extra_pieces = 0;
@@ -495,6 +496,7 @@ int attn_call(const void* q, const void* cache, const float* scales,
   a.pairs_per_seq = plan.pairs_per_seq;
   a.range_groups = plan.range_groups;
   a.num_waves = plan.num_waves;
+  a.few_waves = plan.few_waves;
   a.scale_log2 = sm_scale * 1.4426950408889634f;
   a.wave_clock = nullptr;
   a.shared_groups = plan.shared_groups;

@@ -90,7 +90,8 @@ __device__ inline int range_of(const Split& s, int f) {
 // fit either way, but told so the compiler keeps everything in 200-224 VGPRs instead of parking
 // values in AGPRs and copying them back, 1-2 % faster.  At head_dim 64 the two-tile kernels,
 // double buffers included, fit 256 registers as well and run two per SIMD too.)
-template <int MODE, int D, int NT, bool CEIL, int DEPTH, bool CLOCK, int PER_SIMD>
+// EVEN: the launch has no more wavefronts than are resident at PER_SIMD of them.
+template <int MODE, int D, int NT, bool CEIL, int DEPTH, bool CLOCK, int PER_SIMD, bool EVEN>
 __global__ __launch_bounds__(64, PER_SIMD) void attn_stream_kernel(const AttnArgs p) {
   constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN;  // unquantized cache: 2-byte elements
   // e4m3 codes, one scale per lane and group: the block's, or the whole layer's
@@ -133,9 +134,11 @@ __global__ __launch_bounds__(64, PER_SIMD) void attn_stream_kernel(const AttnArg
   // registers would let a third share a SIMD (int4, head_dim 64) the dispatcher sometimes puts it there
   // and leaves another SIMD with one, depending on what ran before: int4, 163 MB, 37 or 47 us with the
   // same code.  Naming a register claims all below it, and caps the SIMD at the plan's number (the
-  // kernels not named here need that many anyway).
-  if constexpr (PER_SIMD == 2) asm volatile("" ::: "v175");
-  else if constexpr ((PLAIN && D == 64) || GROUPED) asm volatile("" ::: "v255", "a7");
+  // kernels not named here need that many anyway).  A caller's granule mostly makes more wavefronts than
+  // the even split, and then whatever fits runs: capped like the even split's they take 74 us instead of
+  // 63 (bf16, head_dim 64, 64-token granules, 110k tokens), 48 instead of 43 (fp8).
+  if constexpr (EVEN && PER_SIMD == 2) asm volatile("" ::: "v175");
+  else if constexpr (EVEN && ((PLAIN && D == 64) || INT4)) asm volatile("" ::: "v255", "a7");
   stamp(6);
   stamp(0);
   const int32_t* __restrict__ seq_lens = p.seq_lens;
@@ -871,16 +874,29 @@ void launch_variant(const AttnArgs& a, hipStream_t stream) {
   constexpr int kDepth = MODE == KVQ_BF16_PLAIN ? 1 : 2;
   constexpr int kOneTile = MODE == KVQ_BF16_PLAIN ? 1 : 2, kTwoTiles = D == 64 ? kOneTile : 1;  // per SIMD
   const dim3 grid(a.num_waves), block(64);
+  // A caller's granule (range_groups > 0) can make any number of wavefronts.  Few of them, at most one
+  // for every SIMD, are kept apart under int4, whose kernels would share SIMDs and leave others idle: int4,
+  // 1024-token granules, 861 wavefronts, 37 to 56 us by what ran before, 38 to 43 kept apart;
+  // group-scaled 57, now 46.
+  const bool granule = a.range_groups > 0;
   if constexpr (MODE == KVQ_INT4_GROUP32) {  // (the plan gives this format one row tile always)
-    if (a.slot_rows == 8)
-      hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK, 2>), grid, block, 0, stream, a);
+    if (granule ? !a.few_waves : a.slot_rows == 8)
+      hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK, 2, true>), grid, block, 0, stream, a);
     else
-      hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK, 1>), grid, block, 0, stream, a);
+      hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK, 1, true>), grid, block, 0, stream, a);
+  } else if (a.row_tiles == 2) {
+    hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 2, CEIL, kDepth, CLOCK, kTwoTiles, true>), grid, block, 0, stream, a);
+  } else if constexpr (MODE == KVQ_INT4_TOKEN_HEAD) {
+    if (!granule)
+      hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK, 2, true>), grid, block, 0, stream, a);
+    else if (a.few_waves)
+      hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK, 1, true>), grid, block, 0, stream, a);
+    else
+      hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK, 2, false>), grid, block, 0, stream, a);
+  } else if (D == 64 && granule) {
+    hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK, kOneTile, D != 64>), grid, block, 0, stream, a);
   } else {
-    if (a.row_tiles == 1)
-      hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK, kOneTile>), grid, block, 0, stream, a);
-    else
-      hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 2, CEIL, kDepth, CLOCK, kTwoTiles>), grid, block, 0, stream, a);
+    hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK, kOneTile, true>), grid, block, 0, stream, a);
   }
 }
 

@@ -116,6 +116,7 @@ struct AttnPlan {
   int32_t pairs_per_seq;   // num_kv_heads * num_row_groups
   int32_t range_groups;    // 64-token groups per wavefront range; 0 = even split on the device
   int32_t num_waves;       // wavefronts launched (= grid size)
+  int32_t few_waves;       // no more of them than the GPU has SIMDs
   size_t acc_floats;       // workspace: accumulators
   size_t ml_floats;        // workspace: (max, sum) pairs
   size_t prefix_ints;      // workspace: groups before each sequence and the prefix length (batch + 2, padded to 4)
@@ -143,6 +144,7 @@ struct AttnArgs {
   int32_t max_blocks_per_seq, batch, q_len, num_q_heads, num_kv_heads, group, rows;
   int32_t block_size, bs_shift, head_dim, mode;
   int32_t row_tiles, num_row_groups, slot_rows, pairs_per_seq, range_groups, num_waves;
+  int32_t few_waves;  // num_waves is at most the number of SIMDs
   float scale_log2;  // sm_scale * log2(e)
   int32_t shared_groups;  // leading 64-token groups that all sequences' tables map to the same
                           // blocks (0: none, or a call the prefix kernel does not serve)

@@ -365,3 +365,14 @@ def test_contexts_are_cut_by_their_lengths(mode, D, G, q_len, lens):
         got = gpu_attention(wl, cache, scales, desc, chunk_tokens=0, max_len=bound)
         assert np.isfinite(got).all(), bound
         assert attn_err(got, want) <= 5e-4, bound
+
+
+@pytest.mark.parametrize("mode,D", [(W.MODE_INT4, 128), (W.MODE_INT4_GROUP, 128), (W.MODE_INT8, 64), (W.MODE_FP8, 64),
+                                    (W.MODE_FP8_TENSOR, 64), (W.MODE_BF16, 64)])
+@pytest.mark.parametrize("seqs", [60, 80])
+def test_a_granule_makes_few_or_many_wavefronts(mode, D, seqs):
+    """A split-K granule of 64 tokens over 960 and over 1280 groups, below and above one wavefront for each of
+    1024 SIMDs, where other instances of the one-tile kernels run: the automatic split must agree."""
+    wl = W.custom("granule", mode, [449 + b % 64 for b in range(seqs)], 1, 8, 2, D, 16, seed=seqs)
+    errs = check(wl, chunks=(64, 0))
+    assert max(errs) <= 5e-4
