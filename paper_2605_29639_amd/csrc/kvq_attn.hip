@@ -313,6 +313,7 @@ __global__ __launch_bounds__(64, PER_SIMD) void attn_stream_kernel(const AttnArg
   floatx4 acc[NT][DT];
   float m_run[NT], l_run[NT];
   uint32_t ceil_x = 0;
+  const uint32_t q_sign = PLAIN && p.scale_log2 < 0.0f ? 0x80008000u : 0u;
   auto begin_pair = [&](const Cursor& c) {
     if constexpr (CEIL) return;
     const int h = c.pr / NRG, rg = c.pr - h * NRG;
@@ -332,7 +333,7 @@ __global__ __launch_bounds__(64, PER_SIMD) void attn_stream_kernel(const AttnArg
             PLAIN || INT4 ? 32 * s + 8 * g4 : 64 * (s >> 1) + 16 * g4 + 8 * (s & 1);
         const uintx4 raw = *(const uintx4*)(qrow + d0);
         if constexpr (PLAIN) {
-          qb[nt][s] = __builtin_bit_cast(bf16x8, live ? raw : uintx4{0u, 0u, 0u, 0u});
+          qb[nt][s] = __builtin_bit_cast(bf16x8, live ? raw ^ q_sign : uintx4{0u, 0u, 0u, 0u});
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
@@ -459,7 +460,7 @@ __global__ __launch_bounds__(64, PER_SIMD) void attn_stream_kernel(const AttnArg
       sh_group[0][lane] = k;
       sh_group[1][lane] = ratio;
     } else {
-      skp_lane = dead ? 0.0f : sk * p.scale_log2;
+      skp_lane = PLAIN ? fabsf(p.scale_log2) : dead ? 0.0f : sk * p.scale_log2;
       lsv_lane = PLAIN || dead ? 0.0f : __builtin_amdgcn_logf(fmaxf(sv, kMinVScale));
       rsv_lane = PLAIN ? 1.0f : dead ? 0.0f : __builtin_amdgcn_exp2f(-lsv_lane);
     }

@@ -127,6 +127,8 @@ __device__ inline half8 cvt8(uint32_t x0, uint32_t x1) {
 // bf16 terms for an unquantized cache); the running maximum m_run (of logit + lsv, base 2) and sum
 // l_run are updated and acc is rescaled when a maximum moved.
 // TAIL: some row's causal length ends inside the group, so positions are masked.
+// (An unquantized cache's factor is not negative: its caller puts the sign of the softmax scale into q.
+// The test and its branch between QK^T and the softmax cost the two-tile streaming kernel 6 %.)
 template <int MODE, int NT, int DT, bool TAIL, class Operand, int NP>
 __device__ inline void online_softmax(floatx4 (&S)[NT][4], const floatx4* scales, float skp, float lsv,
                                       float rsv, int pos_lane, const int (&nrow)[NT],
@@ -141,7 +143,7 @@ __device__ inline void online_softmax(floatx4 (&S)[NT][4], const floatx4* scales
   float mx[NT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) mx[nt] = -INFINITY;
-  if constexpr (RAW) {
+  if constexpr (RAW && !PLAIN) {
     if (__any(skp < 0.0f)) {  // (a negative softmax scale, or static scale)
       const float sign = skp < 0.0f ? -1.0f : 1.0f;
       skp *= sign;

@@ -214,6 +214,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
 
   // ---- q as the B operand of QK^T, causal lengths, running state ----
   Operand qb[NT][KS];
+  const uint32_t q_sign = PLAIN && p.scale_log2 < 0.0f ? 0x80008000u : 0u;
   int nrow[NT];
   floatx4 acc[NT][DT];
   float m_run[NT], l_run[NT];
@@ -233,7 +234,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
       const int d0 = PLAIN || INT4 ? 32 * s + 8 * g4 : 64 * (s >> 1) + 16 * g4 + 8 * (s & 1);
       const uintx4 raw = *(const uintx4*)(qrow + d0);
       if constexpr (PLAIN) {
-        qb[nt][s] = __builtin_bit_cast(bf16x8, live ? raw : uintx4{0u, 0u, 0u, 0u});
+        qb[nt][s] = __builtin_bit_cast(bf16x8, live ? raw ^ q_sign : uintx4{0u, 0u, 0u, 0u});
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -395,7 +396,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
   auto softmax_impl = [&](auto TAILC, int g, int half) {
     constexpr bool TAIL = decltype(TAILC)::value;
     const int pos0 = g << 6;
-    float skp = p.scale_log2, lsv = 0.0f, rsv = 1.0f;
+    float skp = fabsf(p.scale_log2), lsv = 0.0f, rsv = 1.0f;
     if constexpr (FP8) {
       skp = s_ops[half][0][lane];
       lsv = s_ops[half][1][lane];

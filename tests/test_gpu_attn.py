@@ -376,3 +376,14 @@ def test_a_granule_makes_few_or_many_wavefronts(mode, D, seqs):
     wl = W.custom("granule", mode, [449 + b % 64 for b in range(seqs)], 1, 8, 2, D, 16, seed=seqs)
     errs = check(wl, chunks=(64, 0))
     assert max(errs) <= 5e-4
+
+
+@pytest.mark.parametrize("mode,D", [(m, 128) for m in MODES] + [(W.MODE_BF16, 64), (W.MODE_FP8, 64)])
+@pytest.mark.parametrize("q_len", [1, 4, 40])
+def test_a_negative_softmax_scale(mode, D, q_len):
+    """Smallest dot products first: the kernels that take a row's maximum of the unscaled products must
+    turn it round (one and two row tiles, the many-row kernel)."""
+    wl = W.custom("negative", mode, [300, 129, 64], q_len, 16, 2, D, 16, seed=q_len)
+    scale = -wl.sm_scale
+    wl.__class__ = type("Negative", (type(wl),), {"sm_scale": scale})
+    assert wl.sm_scale < 0 and max(check(wl)) <= 5e-4
