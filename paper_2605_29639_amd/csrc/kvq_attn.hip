@@ -68,10 +68,12 @@ __device__ inline int range_begin(const Split& s, int w) {
   return w * s.q + (int)(((uint32_t)w * (uint32_t)s.r) / (uint32_t)s.num_waves);
 }
 // The wavefront whose range holds flat group f (0 <= f < flat): the w with
-// range_begin(w) <= f < range_begin(w + 1), found from an estimate and at most a few steps.
+// range_begin(w) <= f < range_begin(w + 1), which is floor(((f + 1) num_waves - 1) / flat), found from
+// an estimate and at most a step or two.  (In a list much shorter than the grid the first wavefront
+// with f behind it is num_waves / flat wavefronts earlier, and as many steps away.)
 __device__ inline int range_of(const Split& s, int f) {
   if (s.requested > 0) return f / s.requested;
-  int w = (int)(((float)f + 0.5f) * ((float)s.num_waves / (float)s.flat));
+  int w = (int)(((float)f + 1.0f) * ((float)s.num_waves / (float)s.flat));
   w = min(max(w, 0), s.num_waves - 1);
   while (range_begin(s, w) > f) --w;
   while (w + 1 < s.num_waves && range_begin(s, w + 1) <= f) ++w;
