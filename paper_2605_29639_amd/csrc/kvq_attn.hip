@@ -443,8 +443,15 @@ __global__ __launch_bounds__(64, PER_SIMD) void attn_stream_kernel(const AttnArg
   // through LDS (the wavefront's own, in order: no barrier), from where the softmax reads four
   // tokens' at a time; called ahead of QK^T, whose time covers the way there and back. ----
   __shared__ __align__(16) float sh_scales[TOKEN_SCALE ? 3 : 1][64];  // skp, log2 and 1 / of the V scale
-  __shared__ floatx4 sh_group[GROUPED ? 2 : 1][GROUPED ? 64 : 1];     // K scales; V scales relative to the token's largest
+  constexpr bool GROUP_LDS = GROUPED && PER_SIMD == 2;
+  __shared__ floatx4 sh_group[GROUP_LDS ? 2 : 1][GROUP_LDS ? 64 : 1];     // K scales; V scales relative to the token's largest
   float skp_lane = 0.0f, lsv_lane = 0.0f, rsv_lane = 0.0f;
+  // (Group-scaled int4 at one wavefront per SIMD has nothing to cover 32 reads of LDS per group with: its K
+  // scales and relative V scales stay in the lane of their token, and ride on the arithmetic as row
+  // broadcasts, four instructions more per logit.  32 query rows, 64 sequences of 2000 tokens: 82 us
+  // from LDS, 75.5 as broadcasts; all 36 reads requested ahead of QK^T: 93.)
+  constexpr bool GROUP_ROWS = GROUPED && PER_SIMD == 1;
+  [[maybe_unused]] floatx4 group_k, group_v;
   auto stage_scales = [&](ScaleT sk, ScaleT sv, const Cursor& c) {
     if constexpr (CEIL) return;
     // a slot that was never written: its scales are not data
@@ -459,8 +466,13 @@ __global__ __launch_bounds__(64, PER_SIMD) void attn_stream_kernel(const AttnArg
         k[g] = dead ? 0.0f : sk[g] * p.scale_log2;
         ratio[g] = dead ? 0.0f : sv[g] * rsv_lane;
       }
-      sh_group[0][lane] = k;
-      sh_group[1][lane] = ratio;
+      if constexpr (GROUP_ROWS) {
+        group_k = k;
+        group_v = ratio;
+      } else {
+        sh_group[0][lane] = k;
+        sh_group[1][lane] = ratio;
+      }
     } else {
       skp_lane = PLAIN ? fabsf(p.scale_log2) : dead ? 0.0f : sk * p.scale_log2;
       lsv_lane = PLAIN || dead ? 0.0f : __builtin_amdgcn_logf(fmaxf(sv, kMinVScale));
@@ -482,7 +494,16 @@ __global__ __launch_bounds__(64, PER_SIMD) void attn_stream_kernel(const AttnArg
   auto softmax_impl = [&](auto TAILC, floatx4 (&S)[NT][4], const Cursor& c, Operand (&pb)[NT][2 * EB]) {
     constexpr bool TAIL = decltype(TAILC)::value;
     const floatx4* scales = (const floatx4*)&sh_scales[0][TOKEN_SCALE ? 16 * g4 : 0];
-    if constexpr (GROUPED) {
+    if constexpr (GROUP_ROWS) {
+#pragma clang fp contract(off)  // (a broadcast rides on a multiply or an add, not on both at once)
+      static_for<16>([&](auto I) {
+        constexpr int t = decltype(I)::value, u = t >> 2, i = t & 3;
+        float z = S[0][u][i] * row_bcast<t>(group_k[0]);
+#pragma unroll
+        for (int g = 1; g < 4; ++g) z = z + SG[g - 1][u][i] * row_bcast<t>(group_k[g]);
+        S[0][u][i] = z + row_bcast<t>(lsv_lane);
+      });
+    } else if constexpr (GROUPED) {
       // the logit (plus log2 of the V scale): the four groups' contractions weighted by the token's
       // four K scales
 #pragma unroll
@@ -500,7 +521,13 @@ __global__ __launch_bounds__(64, PER_SIMD) void attn_stream_kernel(const AttnArg
     }
     online_softmax<MODE, NT, DT, TAIL>(S, scales, skp_lane, lsv_lane, rsv_lane, (c.g << 6) + 16 * g4, nrow,
                                        m_run, l_run, acc, pb);
-    if constexpr (GROUPED) {
+    if constexpr (GROUP_ROWS) {
+      static_for<16>([&](auto I) {
+        constexpr int t = decltype(I)::value;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) pbg[g][t >> 3][t & 7] = (_Float16)(S[0][t >> 2][t & 3] * row_bcast<t>(group_v[g]));
+      });
+    } else if constexpr (GROUPED) {
       // S now holds the probabilities times the largest V scale: one B operand per group
 #pragma unroll
       for (int t = 0; t < 16; ++t) {

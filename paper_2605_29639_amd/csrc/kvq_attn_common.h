@@ -2,6 +2,8 @@
 // types, stored codes -> f16, the cross-lane pieces of the softmax.
 #pragma once
 
+#include <utility>
+
 #include "kvq_internal.h"
 
 namespace kvq {
@@ -44,6 +46,21 @@ __device__ inline int lane_value(int v, int lane_index) {  // lane_index wave-un
 __device__ inline int wave_sum(int v) { return lane_value(wave_incl_scan(v), 63); }
 __device__ inline int wave_min(int v) {
   return lane_value(dpp_scan_bits(v, 0x7FFFFFFF, [](int a, int b) { return a < b ? a : b; }), 63);
+}
+
+template <class F, int... Is>
+__device__ inline void static_for_impl(F&& f, std::integer_sequence<int, Is...>) {
+  (f(std::integral_constant<int, Is>{}), ...);
+}
+template <int N, class F>
+__device__ inline void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+// value of lane I of the caller's 16-lane row
+template <int I>
+__device__ inline float row_bcast(float x) {
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x150 + I, 0xF, 0xF, true));
 }
 
 // Over the four lanes that share lane % 16: v_permlane32_swap_b32 and v_permlane16_swap_b32 of a value with

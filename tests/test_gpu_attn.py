@@ -387,3 +387,16 @@ def test_a_negative_softmax_scale(mode, D, q_len):
     scale = -wl.sm_scale
     wl.__class__ = type("Negative", (type(wl),), {"sm_scale": scale})
     assert wl.sm_scale < 0 and max(check(wl)) <= 5e-4
+
+
+@pytest.mark.parametrize("hq", [8, 16])
+@pytest.mark.parametrize("bound", [1100, 60000])
+def test_group_scaled_int4_with_one_and_two_wavefronts_per_simd(hq, bound):
+    """Up to eight query rows and a long enough list (here by its declared bound) run twice the wavefronts with
+    half the rows in a partial's slot; a short list runs the other instance of the kernel."""
+    wl = W.custom("per_simd", W.MODE_INT4_GROUP, [1100, 30, 64, 700, 415], 1, hq, 2, 128, 16, seed=hq)
+    oc, osc = oracle_fill(wl)
+    want = oracle_out(wl, oc, osc)
+    cache, scales, desc = upload_oracle_cache(wl, oc, osc)
+    got = gpu_attention(wl, cache, scales, desc, chunk_tokens=0, max_len=bound)
+    assert np.isfinite(got).all() and attn_err(got, want) <= 5e-4
