@@ -9,11 +9,12 @@
 //   write_window_kernel  prompts: a wavefront per (window of 16 tokens, kv head) does every run that
 //                        starts in its window, K and V
 //   write_run_kernel     decode steps, small chunks: a wavefront per (token, kv head, K|V); the one
-//                        that has a run's first token does the run
+//                        that has a run's first token does the run (unquantized: each its own token)
 //   write_fp8_block_kernel  prompts under block-scaled fp8 with blocks above 16 tokens: a workgroup
 //                        per (block_size tokens, kv head), a wavefront per sub-block
-// A run of one token is done two channels a lane; longer ones by sub-block: 16-byte loads, the 16
-// rows spread over the lanes so that the codes leave in 8- and 16-byte stores (see load_subblock).
+// A run of one token is done two channels a lane (in the window kernel int4 and unquantized ones only);
+// longer ones by sub-block: 16-byte loads, the 16 rows spread over the lanes so that the codes leave
+// in 8- and 16-byte stores (see load_subblock).
 // The decisions that fix an integer (the rounding of x/scale) equal fp64's: for a bf16 x and an
 // fp32 scale the fp64 quotient is either exactly a rounding tie or at least 2^-25 (relative 2^-29
 // for the fp8 midpoints) away from one, so rounding it equals rounding the exact quotient.  The
@@ -150,9 +151,9 @@ __device__ inline void store_v_codes(uint8_t* __restrict__ tile, uint32_t (&word
 // The fast rounding below marks what it cannot decide; those rows are done again by the single-token
 // routines, behind a wait for the stores they overwrite: a loop of little code and few registers, so
 // that it costs the common path nothing.  marks[i]: this lane's row of load i is to be done again (for
-// K row 4 i + g, for V row 4 g + i).
+// K row 4 i + g, for V row 4 g + i); `live`: bit mask of the rows there are.
 template <class Redo>
-__device__ inline void redo_rows(const bool (&marks)[4], int kv, int r_lo, int r_hi, Redo redo) {
+__device__ inline void redo_rows(const bool (&marks)[4], int kv, uint32_t live, Redo redo) {
   if (__builtin_expect(!__any(marks[0] || marks[1] || marks[2] || marks[3]), 1)) return;
   uint32_t rows = 0;
 #pragma unroll
@@ -162,7 +163,7 @@ __device__ inline void redo_rows(const bool (&marks)[4], int kv, int r_lo, int r
     for (int g = 0; g < 4; ++g)
       if ((m >> (16 * g)) & 0xFFFFu) rows |= 1u << (kv ? 4 * g + i : 4 * i + g);
   }
-  rows &= (1u << r_hi) - (1u << r_lo);
+  rows &= live;
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0);
   while (rows) {
@@ -320,7 +321,7 @@ __device__ inline void int8_subblock(const Piece<D> (&raw)[4], const uint16_t* _
     if (r >= r_lo && r < r_hi) srow[r] = c == 0 ? s[0] : c == 1 ? s[1] : c == 2 ? s[2] : s[3];
   }
   if (kv == 1) store_v_codes<D>(tile, v_words, off0, bs, lane, r_lo, r_hi);
-  redo_rows(marks, kv, r_lo, r_hi, [&](int r) {
+  redo_rows(marks, kv, (1u << r_hi) - (1u << r_lo), [&](int r) {
     uint32_t bits[D / 64];
     load_token<D>(src + (size_t)(r - r_lo) * tstride, lane, bits);
     int8_token<D>(bits, tile, srow + r, kv, off0 + r, bs, lane);
@@ -440,7 +441,7 @@ __device__ inline void int4_subblock(const Piece<128> (&raw)[4], const uint16_t*
       store_v_nibbles((uint32_t*)(tile + int4_v_word(off0, d)), w[e], w[e + 2], mask_lo, mask_hi);
     }
   }
-  redo_rows(marks, kv, r_lo, r_hi, [&](int r) {
+  redo_rows(marks, kv, (1u << r_hi) - (1u << r_lo), [&](int r) {
     uint32_t bits[2];
     load_token<128>(src + (size_t)(r - r_lo) * tstride, lane, bits);
     int4_token<GROUPED>(bits, tile, srow + r * NG, kv, off0 + r, lane);
@@ -556,7 +557,7 @@ __device__ inline void fp8_subblock(const Piece<D> (&raw)[4], const uint16_t* __
   } else {
     store_v_codes<D>(tile, word, base, bs, lane, r_lo, r_hi);
   }
-  redo_rows(marks, kv, r_lo, r_hi, [&](int r) {
+  redo_rows(marks, kv, (1u << r_hi) - (1u << r_lo), [&](int r) {
     uint32_t bits[D / 64];
     load_token<D>(src + (size_t)(r - r_lo) * tstride, lane, bits);
     fp8_token<D>(bits, tile, s, kv, base + r, bs, lane);
@@ -725,6 +726,44 @@ __device__ inline void plain_subblock(const Piece<D> (&raw)[4], uint16_t* __rest
   }
 }
 
+// ---- unquantized rows of many runs ---------------------------------------------------------
+// A window of many short runs (a decode step of more than a thousand sequences): run after run, each a
+// masked sub-block, is a chain of round trips.  Here the window's rows are requested eight at a time, two
+// channels a lane, and every row goes to its own slot.  Lane r + 1 holds row r's slot; `rows`: bit mask
+// of the rows to store; `src`: row 0's token, of n.  Single tokens of 8 heads x 128: 1024 33 us run
+// after run, 14 like this (9 with a wavefront for each token, head and K|V, which takes prompts 2.7
+// times as long), 4096 45 and 28 (25).  (All 16 rows at once 12 us, but then the compiler orders the
+// common path differently: a prompt of 30000 tokens 46 us instead of 44.7.)
+template <int D>
+__device__ inline void scatter_plain(const uint16_t* __restrict__ src, size_t tstride, int n,
+                                     uint16_t* __restrict__ cache, int64_t slot, uint32_t rows, int kv,
+                                     int h, int H, int bs, int lane) {
+  constexpr int E = D / 64;
+#pragma unroll 1
+  for (int r0 = 0; r0 < 16; r0 += 8) {
+    uint32_t bits[8][E];
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      load_token<D>(src + (size_t)min(r0 + r, n - 1) * tstride, lane, bits[r]);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      if (!((rows >> (r0 + r)) & 1u)) continue;
+      const int64_t to = lane_i64(slot, r0 + r + 1);
+      const int off = (int)(to & (bs - 1));
+      uint16_t* elems = cache + tile_offset(to >> __builtin_ctz(bs), kv, h, H, bs, D);
+      if constexpr (E == 2) {
+        if (kv == 0) {
+          *(uint32_t*)(elems + k_elem16(off, lane * 2, D)) = bits[r][0] | bits[r][1] << 16;
+          continue;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        elems[kv ? v_elem16(off, lane * E + e, D) : k_elem16(off, lane * E + e, D)] = (uint16_t)bits[r][e];
+    }
+  }
+}
+
 // ---- the kernels ----------------------------------------------------------------------------
 
 // Where a mode's (block, K|V, head) tile starts, and its scales of block offset `off` on.
@@ -793,6 +832,18 @@ __global__ __launch_bounds__(kWaves * 64) void write_window_kernel(
   const uint32_t conts = (uint32_t)(__ballot(cont) >> 1);
   uint32_t starts = (uint32_t)(__ballot(slot >= 0 && !cont) >> 1) & 0xFFFFu;
   const size_t tstride = (size_t)H * D;
+  if constexpr (MODE == KVQ_BF16_PLAIN) {
+    if (__builtin_expect(__builtin_popcount(starts) > 2, 0)) {
+      // all runs but the last, which may go on behind the window
+      const uint32_t last = 1u << (31 - __builtin_clz(starts)), first = starts & -starts;
+      const uint32_t rows = (uint32_t)(__ballot(slot >= 0) >> 1) & (last - first);
+      const size_t row0 = ((size_t)w0 * H + h) * D;
+      const int n = min(16, num_tokens - w0);
+      scatter_plain<D>(k + row0, tstride, n, (uint16_t*)cache, slot, rows, 0, h, H, bs, lane);
+      scatter_plain<D>(v + row0, tstride, n, (uint16_t*)cache, slot, rows, 1, h, H, bs, lane);
+      starts = last;
+    }
+  }
   while (starts) {
     const int j = __builtin_ctz(starts);
     starts &= starts - 1;
@@ -801,6 +852,19 @@ __global__ __launch_bounds__(kWaves * 64) void write_window_kernel(
     const int64_t blk = slot0 >> __builtin_ctz(bs);  // block sizes are powers of two
     const int so = (int)(slot0 & 15), off0 = (int)(slot0 & (bs - 1)) - so;
     const size_t row0 = ((size_t)(w0 + j) * H + h) * D;
+    if constexpr (MODE == KVQ_INT4_TOKEN_HEAD || MODE == KVQ_INT4_GROUP32) {
+      if (run == 1) {  // (1024 single tokens of 8 heads: 26.6 us, each as a masked sub-block 45)
+        uint32_t k_bits[2], v_bits[2];
+        load_token<D>(k + row0, lane, k_bits);
+        load_token<D>(v + row0, lane, v_bits);
+#pragma unroll
+        for (int kv = 0; kv < 2; ++kv)
+          int4_token<MODE == KVQ_INT4_GROUP32>(kv ? v_bits : k_bits, tile_of<MODE, D>(cache, blk, kv, h, H, bs),
+                                               scales_of<MODE>(scales, blk, kv, h, H, bs, off0 + so), kv,
+                                               off0 + so, lane);
+        continue;
+      }
+    }
     Piece<D> k_rows[4], v_rows[4];
     load_subblock<D>(k + row0, tstride, 0, lane, so, so + run, k_rows);
     load_subblock<D>(v + row0, tstride, 1, lane, so, so + run, v_rows);
@@ -864,6 +928,16 @@ __global__ __launch_bounds__(kWaves * 64) void write_run_kernel(
   const int64_t slot = t >= 0 && t < num_tokens ? slot_mapping[t] : -1;
   const int64_t slot0 = lane_i64(slot, 1);
   if (slot0 < 0) return;
+  if constexpr (MODE == KVQ_BF16_PLAIN) {
+    // (nothing ties the tokens of a run together: all of them in parallel, 512 tokens 4.5 us, 6.6 by runs)
+    const int64_t to = slot0 >> __builtin_ctz(bs);
+    const int at = (int)(slot0 & (bs - 1));
+    uint16_t* elems = (uint16_t*)tile_of<MODE, D>(cache, to, kv, h, H, bs);
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      elems[kv ? v_elem16(at, lane * E + e, D) : k_elem16(at, lane * E + e, D)] = (uint16_t)bits[e];
+    return;
+  }
   const int span = FP8_BLOCK ? bs : 16;  // a run ends with its block / sub-block
   const int at = (int)(slot0 & (span - 1));
   if (at > 0 && lane_i64(slot, 0) == slot0 - 1) return;  // not a run's first token
@@ -928,12 +1002,7 @@ __global__ __launch_bounds__(kWaves * 64) void write_run_kernel(
       int8_token<D>(bits, tile, sp, kv, off, bs, lane);
     } else if constexpr (MODE == KVQ_INT4_TOKEN_HEAD || MODE == KVQ_INT4_GROUP32) {
       int4_token<MODE == KVQ_INT4_GROUP32>(bits, tile, sp, kv, off, lane);
-    } else if constexpr (MODE == KVQ_BF16_PLAIN) {
-      uint16_t* elems = (uint16_t*)tile;
-#pragma unroll
-      for (int e = 0; e < E; ++e)
-        elems[kv ? v_elem16(off, lane * E + e, D) : k_elem16(off, lane * E + e, D)] = (uint16_t)bits[e];
-    } else {  // static scales
+    } else if constexpr (MODE == KVQ_FP8E4M3_TENSOR) {
       fp8_token<D>(bits, tile, *sp, kv, off, bs, lane);
     }
   }
