@@ -212,10 +212,12 @@ int paged_decode_attn(const void* q, const void* cache, const float* scales,
  * KVQ_DEBUG=1 it is checked and KVQ_E_BAD_INDEX returned.
  *
  * The prefix is used when every sequence has at least that many tokens (decided on the device
- * from seq_lens), for every format but KVQ_INT4_GROUP32, with batch >= 2 and fewer than 128
- * query rows per kv head; otherwise, and with shared_prefix_tokens < 64, the call is
- * paged_decode_attn (which, where the device finds a sequence too short, stays on the streaming
- * kernel).  shared_prefix_tokens < 0 is KVQ_E_BAD_SHAPE.
+ * from seq_lens), for every format but KVQ_INT4_GROUP32, with batch >= 2 and up to 32 query rows
+ * per kv head; with 33 to 127 only where paged_decode_attn would not run its many-row kernel or,
+ * up to 64, the prefix is at least half of max_seq_len (that kernel is faster without it).
+ * Otherwise, and with shared_prefix_tokens < 64, the call is paged_decode_attn.  (Where the
+ * device finds a sequence too short, the call has the same results up to the order of the merges.)
+ * shared_prefix_tokens < 0 is KVQ_E_BAD_SHAPE.
  *
  * workspace_bytes must be at least paged_decode_attn_prefix_workspace_bytes() for the same
  * arguments (more than paged_decode_attn needs: room for the first kernel's partials). */

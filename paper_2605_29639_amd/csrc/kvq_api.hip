@@ -138,11 +138,10 @@ void cut_contexts(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_
 // tokens, 48 rows, 91 -> 49; 128 of up to 2000, 48 rows, 177 -> 138; but 60 of up to 6000, 56 rows,
 // 190 -> 204.  (The group-scaled int4 format has no many-row kernel.)
 bool many_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t max_seq_len,
-               int64_t chunk_tokens, bool shared_prefix) {
+               int64_t chunk_tokens) {
   if (d->mode == KVQ_INT4_GROUP32) return false;
   if (rows >= kvq::kRowsPerWorkgroup) return true;
-  // (a caller's split-K granule is the streaming kernel's, and so is what follows a shared prefix)
-  if (chunk_tokens > 0 || shared_prefix) return false;
+  if (chunk_tokens > 0) return false;  // (a caller's split-K granule is the streaming kernel's)
   // (the merge's launch has 32 threads for every output row, and fewer than 2^32)
   if (batch * d->num_kv_heads > 1 << 19) return false;
   const int64_t passes = (rows + 31) / 32 + (d->mode == KVQ_BF16_PLAIN ? 1 : 0);
@@ -241,7 +240,17 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
   plan->extra_pieces = 0;
   plan->piece_min = 1;
   plan->piece_share = 0.0f;
-  plan->many_rows = batch > 0 && many_rows(d, batch, rows, max_seq_len, chunk_tokens, plan->shared_groups > 0);
+  plan->many_rows = batch > 0 && many_rows(d, batch, rows, max_seq_len, chunk_tokens);
+  // What follows a shared prefix is the streaming kernel's, so such a call does without the prefix where
+  // that costs more than the stacked rows save: with more than 64 rows they are little denser than the
+  // many-row kernel's own; up to 64 a prefix of half the context is worth it.  (The workspace keeps
+  // its size.)  32 sequences of 8192 tokens, 64 / 8 heads, hints of 64, 4096 and 6144 tokens, us with the
+  // prefix kernel and without: 96 rows int8 300, 262, 234 and 184, 166, 164; bf16 520, 385, 309 and 214,
+  // 192, 184; 40 rows bf16 342, 240, 177 and 203, 188 (at 2048), 203.
+  plan->promised_groups = plan->shared_groups;
+  if (plan->many_rows && (rows > 64 || 2 * (int64_t)plan->shared_groups < ((int64_t)max_seq_len + 63) / 64))
+    plan->shared_groups = 0;
+  if (plan->shared_groups > 0) plan->many_rows = 0;
   if (plan->many_rows)
     cut_contexts(d, batch, rows, (int64_t)q_len * num_q_heads, ((int64_t)max_seq_len + 63) / 64,
                  (int64_t)slot_rows, plan);
@@ -463,8 +472,8 @@ int attn_call(const void* q, const void* cache, const float* scales,
                            0, (hipStream_t)stream, block_tables, seq_lens, batch,
                            max_blocks_per_seq, desc->num_blocks, desc->block_size, q_len,
                            max_seq_len,
-                           (plan.shared_groups * 64 + desc->block_size - 1) / desc->block_size,
-                           plan.shared_groups * 64, word);
+                           (plan.promised_groups * 64 + desc->block_size - 1) / desc->block_size,
+                           plan.promised_groups * 64, word);
       });
       if (rc != KVQ_OK) return rc;
     }

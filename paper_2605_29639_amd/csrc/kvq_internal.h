@@ -121,6 +121,7 @@ struct AttnPlan {
   size_t ml_floats;        // workspace: (max, sum) pairs
   size_t prefix_ints;      // workspace: groups before each sequence and the prefix length (batch + 2, padded to 4)
   int32_t shared_groups;   // shared prefix in 64-token groups, 0 where the prefix kernel is not used
+  int32_t promised_groups; // the same also where the call does better without that kernel
   int32_t prefix_chunks;   // pieces the prefix kernel cuts it into (>= 1)
   int32_t many_rows;       // the call goes to the many-row kernel
   // many-row kernel: pieces beyond each sequence's first that the contexts may be cut into (0: no cut),

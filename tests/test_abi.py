@@ -118,6 +118,22 @@ def test_many_row_calls_may_always_cut_a_long_context(mode, D):
                 assert p["extra_pieces"] * q_len * 64 * D * 4 < held
 
 
+@pytest.mark.parametrize("mode,D,q_len,prefix,used", [
+    (0, 128, 4, 64, True), (0, 128, 5, 64, True),                                  # streaming calls: always
+    (0, 128, 12, 64, False), (1, 128, 12, 6144, False), (2, 64, 15, 8192, False),   # above 64 rows: never
+    (2, 128, 5, 64, False), (2, 128, 8, 4032, False), (2, 128, 8, 4096, True),      # up to 64: from half on
+    (0, 64, 12, 64, True), (0, 64, 13, 64, False)])
+def test_a_shared_prefix_does_not_keep_a_call_from_the_many_row_kernel(mode, D, q_len, prefix, used):
+    """A hint is never slower than none by more than the prefix is worth, and asks for the same workspace
+    whether the prefix is used or not."""
+    desc = d(mode=mode, H=8, D=D, nblk=64)
+    p = plan(desc, 32, q_len, 64, 8192, prefix=prefix)
+    assert p["shared_groups"] == (prefix // 64 if used else 0)
+    assert bool(p["many_rows"]) == (bool(plan(desc, 32, q_len, 64, 8192)["many_rows"]) and not used)
+    plain = kvq.workspace_bytes(desc, 32, q_len, 64, 8192, 0)
+    assert kvq.workspace_bytes(desc, 32, q_len, 64, 8192, 0, prefix) > plain
+
+
 FAKE = C.c_void_p(0x1000)  # never dereferenced: every call below fails validation first
 
 
