@@ -134,6 +134,19 @@ def test_a_shared_prefix_does_not_keep_a_call_from_the_many_row_kernel(mode, D, 
     assert kvq.workspace_bytes(desc, 32, q_len, 64, 8192, 0, prefix) > plain
 
 
+@pytest.mark.parametrize("mode,D,rows,batch,max_len,many", [
+    (0, 128, 32, 300, 512, False), (0, 128, 33, 300, 512, True), (0, 128, 64, 300, 2048, True),
+    (0, 128, 64, 300, 2049, False), (0, 128, 64, 255, 2048, False), (0, 128, 64, 256, 2048, True),
+    (0, 128, 65, 1, 40000, True), (4, 128, 40, 300, 900, True), (5, 128, 300, 300, 900, False),
+    (2, 128, 33, 1, 40000, True), (2, 128, 32, 300, 900, False), (0, 64, 96, 300, 900, False), (0, 64, 97, 1, 900, True),
+    (2, 64, 64, 300, 900, False), (2, 64, 65, 1, 900, True), (1, 64, 128, 1, 100, True)])
+def test_which_calls_go_to_the_many_row_kernel(mode, D, rows, batch, max_len, many):
+    p = plan(d(mode=mode, H=2, D=D, nblk=64), batch, 1, 2 * rows, max_len)
+    assert bool(p["many_rows"]) == many
+    # a caller's granule is the streaming kernel's below 128 rows
+    assert bool(plan(d(mode=mode, H=2, D=D, nblk=64), batch, 1, 2 * rows, max_len, 256)["many_rows"]) == (many and rows >= 128)
+
+
 FAKE = C.c_void_p(0x1000)  # never dereferenced: every call below fails validation first
 
 

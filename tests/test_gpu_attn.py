@@ -308,16 +308,27 @@ def test_shared_prefix_is_read_through_stacked_rows(mode, q_len, lens):
 @pytest.mark.parametrize("mode,D", [(m, 128) for m in MODES if m != W.MODE_INT4_GROUP] +
                          [(W.MODE_INT8, 64), (W.MODE_FP8, 64)])
 @pytest.mark.parametrize("lens,q_len", [([2000, 41, 700], 40), ([64, 65, 128, 1], 33), ([5000], 130),
-                                        ([8191, 300], 64)])
+                                        ([8191, 300], 64), ([64, 65, 128, 33, 2048, 129], 33)])
 def test_many_query_rows_over_a_split_context(mode, D, lens, q_len):
     """Calls of the many-row kernel with too few row blocks to fill the chip walk the context in
-    pieces that a second launch merges: contexts shorter than their number of pieces (empty
-    pieces), pieces a row sees nothing of, lengths around a group's edge, row blocks that are not
-    full.  The bound is the checker's; f16 probabilities give 1e-4 or less."""
+    pieces that a second launch merges: beside contexts too short to cut, of lengths around a
+    group's edge; pieces a row, or all of a row block, sees nothing of; row blocks that are not
+    full.  (The list without a long context is not cut.)  The bound is the checker's; f16 probabilities give 1e-4 or less."""
     lens = [max(l, q_len) for l in lens]
     wl = W.custom("split", mode, lens, q_len, 8, 2, D, 16, seed=len(lens) + mode)
     errs = check(wl)
     assert max(errs) <= 5e-4
+
+
+@pytest.mark.parametrize("mode,G,q_len", [(W.MODE_INT8, 8, 5), (W.MODE_INT8, 8, 8), (W.MODE_FP8, 4, 9), (W.MODE_INT4, 11, 3),
+                                          (W.MODE_FP8_TENSOR, 6, 10)])
+@pytest.mark.parametrize("longest", [2048, 2049])
+def test_two_row_tiles_of_a_crowd_of_short_sequences(mode, G, q_len, longest):
+    """33 to 64 query rows of a quantized cache: the many-row kernel with a workgroup for every slot of the
+    chip and contexts of at most 2048 tokens, the streaming kernel one token further."""
+    lens = [longest] + [40 + 29 * (i % 30) for i in range(299)]
+    wl = W.custom("tiles", mode, lens, q_len, 2 * G, 2, 128, 16, seed=G + q_len)
+    assert max(check(wl)) <= 5e-4
 
 
 @pytest.mark.parametrize("mode,D,G,q_len", [(W.MODE_INT8, 128, 8, 9), (W.MODE_INT4, 128, 6, 11), (W.MODE_FP8, 128, 8, 15),
