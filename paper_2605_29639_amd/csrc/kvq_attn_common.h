@@ -16,6 +16,8 @@ typedef short short2v __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
 
 constexpr float kPOffset = 10.0f;   // probabilities are scaled by 2^10 (cancels in acc / l)
 constexpr float kMinVScale = 7.888609052210118e-31f;  // 2^-100
@@ -212,7 +214,8 @@ __device__ inline void online_softmax(floatx4 (&S)[NT][4], const floatx4* scales
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     float lsum = 0.0f;
-    [[maybe_unused]] uint32_t hi_bits[16], lo_bits[16];
+    [[maybe_unused]] uint32_t hi_bits[16];
+    [[maybe_unused]] float rest[16];
     [[maybe_unused]] floatx4 r4[2];
     if constexpr (TOKEN_SCALE) r4[0] = scales[2 * pitch];
 #pragma unroll
@@ -229,10 +232,12 @@ __device__ inline void online_softmax(floatx4 (&S)[NT][4], const floatx4* scales
         if constexpr (TOKEN_SCALE) lsum = __builtin_fmaf(pr, r4[u & 1][i], lsum);
         else lsum += pr;
         if constexpr (PLAIN) {
-          // bf16 keeps 8 bits of a probability: it goes in as two terms, the value cut to
-          // bf16 and the (exactly representable) rest cut to bf16, 16 bits in all
+          // bf16 keeps 8 bits of a probability: it goes in as two terms, the value cut to bf16 and
+          // the (exactly representable) rest rounded to bf16, 16 bits in all.  (Rounded, not cut: a
+          // row's largest probability comes out a last place below or above 2^10, and cut it would
+          // lose up to 2^-16 of itself, which is a peaked row's whole error.)
           hi_bits[tix] = __float_as_uint(pr) & 0xFFFF0000u;
-          lo_bits[tix] = __float_as_uint(pr - __uint_as_float(hi_bits[tix]));
+          rest[tix] = pr - __uint_as_float(hi_bits[tix]);
         } else if constexpr (GROUPED) {
           S[nt][u][i] = pr;
         } else {
@@ -246,10 +251,10 @@ __device__ inline void online_softmax(floatx4 (&S)[NT][4], const floatx4* scales
       for (int hf = 0; hf < 2; ++hf) {
         uintx4 ph, pl;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {  // the upper halves of two tokens' words, packed
+        for (int e = 0; e < 4; ++e) {  // two tokens' bf16 terms to a word
           const int t = 8 * hf + 2 * e;
           ph[e] = __builtin_amdgcn_perm(hi_bits[t + 1], hi_bits[t], 0x07060302u);
-          pl[e] = __builtin_amdgcn_perm(lo_bits[t + 1], lo_bits[t], 0x07060302u);
+          pl[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{rest[t], rest[t + 1]}), bf16x2));
         }
         pb[nt][hf] = __builtin_bit_cast(bf16x8, ph);
         pb[nt][2 + hf] = __builtin_bit_cast(bf16x8, pl);

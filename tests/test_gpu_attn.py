@@ -411,3 +411,33 @@ def test_group_scaled_int4_with_one_and_two_wavefronts_per_simd(hq, bound):
     cache, scales, desc = upload_oracle_cache(wl, oc, osc)
     got = gpu_attention(wl, cache, scales, desc, chunk_tokens=0, max_len=bound)
     assert np.isfinite(got).all() and attn_err(got, want) <= 5e-4
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("q_len", [1, 4, 6, 20])
+def test_a_peaked_row_of_an_unquantized_cache(D, q_len):
+    """A row that attends to one token alone returns that token's V: its probability is 1 to within the
+    rounding of the exponent (about 130 here, so 2^-17), numerator and denominator alike, and goes into
+    P.V as two bf16 terms whose second is rounded, 2^-17 of it at most and nothing of a value beside a
+    power of two.  Cut instead of rounded it would lose 2^-16."""
+    import torch
+    from paper_2605_29639_amd import kvq
+    H, G, L, bs = 2, 8, 700, 16
+    desc = kvq.make_desc(W.MODE_BF16, L // bs + 1, bs, H, D)
+    cache, scales = kvq.alloc_cache(desc)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(D + q_len)
+    k, v = torch.randn((2, L, H, D), generator=g, device="cuda").to(torch.bfloat16)
+    kvq.kv_quant_write(k, v, torch.arange(L, device="cuda"), cache, scales, desc)
+    t = torch.randint(0, L - 128, (q_len, H, G), generator=g, device="cuda")
+    rows = k.float().permute(1, 0, 2)[torch.arange(H, device="cuda")[None, :, None], t]     # [q_len, H, G, D]
+    q = (rows * (1024.0 / D)).to(torch.bfloat16).view(q_len, H * G, D)
+    want = v.float().permute(1, 0, 2)[torch.arange(H, device="cuda")[None, :, None], t].view(q_len, H * G, D)
+    tables = torch.arange(L // bs + 1, dtype=torch.int32, device="cuda")[None].contiguous()
+    lens = torch.tensor([L], dtype=torch.int32, device="cuda")
+    out = torch.empty((q_len, H * G, D), device="cuda")
+    for chunk in (0, 64, 1024):
+        ws = kvq.alloc_workspace(desc, 1, q_len, H * G, L, chunk)
+        kvq.paged_decode_attn(q, cache, scales, desc, tables, lens, q_len, L, 1.0 / D ** 0.5, out, ws, chunk_tokens=chunk)
+        torch.cuda.synchronize()
+        assert float(((out - want).abs() / want.abs().clamp(min=1e-3)).max()) <= 2.0 ** -17, chunk
