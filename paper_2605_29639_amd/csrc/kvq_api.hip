@@ -81,8 +81,7 @@ int ilog2(int x) {
 // consumed; splitting adds the second launch and writes and reads 64 KB per workgroup.  One
 // sequence's 512 tokens over 16384 cached ones (fp8, 32 / 8 heads): 427 us in one piece, 178 in
 // four with the merge; eight such chunks over 4096 (1024 workgroups, two full rounds) stay whole.
-int64_t equal_pieces(int64_t walks, int64_t groups, int64_t room) {
-  const int64_t slots = auto_waves() / 4;
+int64_t equal_pieces(int64_t slots, int64_t walks, int64_t groups, int64_t room) {
   if (walks >= 4 * slots) return 1;
   int64_t best = 1;
   double best_us = 0.0;
@@ -112,11 +111,11 @@ int64_t equal_pieces(int64_t walks, int64_t groups, int64_t room) {
 // on its own under a bound of 32768: 21 us without leave to cut, 28 cut by the bound, 23 now (the
 // second launch finds nothing to do); over 4096 tokens, same bound: 117, 63 and 63.
 void cut_contexts(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t seq_rows,
-                  int64_t groups, int64_t slot_rows, kvq::AttnPlan* plan) {
-  const int64_t slots = auto_waves() / 4, room = slot_rows / seq_rows;
+                  int64_t groups, int64_t slot_rows, int64_t slots, kvq::AttnPlan* plan) {
+  const int64_t room = slot_rows / seq_rows;
   const int64_t per_seq = d->num_kv_heads * ((rows + kvq::kRowsPerWorkgroup - 1) / kvq::kRowsPerWorkgroup);
   plan->piece_min = (int32_t)(per_seq < 32 ? 2 : per_seq / 16);
-  const int64_t c = equal_pieces(batch * per_seq, groups, room / batch + 1);
+  const int64_t c = equal_pieces(slots, batch * per_seq, groups, room / batch + 1);
   if (c > 1) {
     plan->extra_pieces = (int32_t)(batch * (c - 1));
   } else if (rows < kvq::kRowsPerWorkgroup && groups > 2 * plan->piece_min) {
@@ -138,7 +137,7 @@ void cut_contexts(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_
 // tokens, 48 rows, 91 -> 49; 128 of up to 2000, 48 rows, 177 -> 138; but 60 of up to 6000, 56 rows,
 // 190 -> 204.  (The group-scaled int4 format has no many-row kernel.)
 bool many_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t max_seq_len,
-               int64_t chunk_tokens) {
+               int64_t chunk_tokens, int64_t slots) {
   if (d->mode == KVQ_INT4_GROUP32) return false;
   if (rows >= kvq::kRowsPerWorkgroup) return true;
   if (chunk_tokens > 0) return false;  // (a caller's split-K granule is the streaming kernel's)
@@ -147,7 +146,7 @@ bool many_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t m
   const int64_t passes = (rows + 31) / 32 + (d->mode == KVQ_BF16_PLAIN ? 1 : 0);
   if (passes >= (d->head_dim == 128 ? 3 : 4)) return rows > 32;
   return rows > 32 && d->head_dim == 128 && max_seq_len <= 2048 &&
-         batch * d->num_kv_heads >= auto_waves() / 4;
+         batch * d->num_kv_heads >= slots;
 }
 
 // Everything the launch needs that depends only on host-side arguments.
@@ -177,6 +176,7 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
     return false;
   }
   const int64_t flat_max = (int64_t)flat_wide;
+  const int64_t waves = auto_waves(), slots_128 = waves / 4;  // (workgroups of the many-row kernel)
   plan->rows = (int32_t)rows;
   plan->row_tiles = (int32_t)row_tiles;
   plan->num_row_groups = (int32_t)row_groups;
@@ -188,7 +188,6 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
     // (an unquantized cache needs twice the registers per group: one wavefront per SIMD; so
     // does the group-scaled int4 cache, for its four accumulators per logit, in the workspace; see
     // below for its launch)
-    const int64_t waves = auto_waves();
     const bool two_per_simd = (plan->row_tiles == 1 || d->head_dim == 64) &&
                               d->mode != KVQ_BF16_PLAIN && d->mode != KVQ_INT4_GROUP32;
     const int64_t resident = two_per_simd ? waves : waves / 2;
@@ -210,7 +209,7 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
       rows < 128 && d->mode != KVQ_INT4_GROUP32 && stacked <= (1 << 30)) {
     plan->shared_groups = shared_prefix_tokens / 64;
     const int64_t walks = d->num_kv_heads * ((stacked + 127) / 128);
-    int64_t chunks = (auto_waves() / 4 + walks - 1) / walks;
+    int64_t chunks = (slots_128 + walks - 1) / walks;
     if (chunks > kvq::kMaxPrefixChunks) chunks = kvq::kMaxPrefixChunks;
     if (chunks > plan->shared_groups) chunks = plan->shared_groups;
     plan->prefix_chunks = (int32_t)chunks;
@@ -230,17 +229,17 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
   // more the call keeps to one.  So do lists of less than four groups for each of the 2048, where a
   // wavefront has little to stream and leaves as many partials (one against two wavefronts per SIMD, 8
   // rows of 8 kv heads, 1600 tokens: 21 sequences 20.2 and 22.9 us, 40 27.4 and 27.3, 100 54.5 and 47.9).
-  if (d->mode == KVQ_INT4_GROUP32 && chunk_tokens == 0 && rows <= 8 && flat_max >= 4 * auto_waves()) {
+  if (d->mode == KVQ_INT4_GROUP32 && chunk_tokens == 0 && rows <= 8 && flat_max >= 4 * waves) {
     plan->slot_rows = 8;
-    plan->num_waves = (int32_t)auto_waves();
+    plan->num_waves = (int32_t)waves;
   }
-  plan->few_waves = plan->num_waves <= auto_waves() / 2;
+  plan->few_waves = plan->num_waves <= waves / 2;
   // A many-row call has the same workspace as if it went through the streaming kernel; the pieces
   // of a cut context beyond the first (whose rows go to `out`) use it, a sequence's rows each.
   plan->extra_pieces = 0;
   plan->piece_min = 1;
   plan->piece_share = 0.0f;
-  plan->many_rows = batch > 0 && many_rows(d, batch, rows, max_seq_len, chunk_tokens);
+  plan->many_rows = batch > 0 && many_rows(d, batch, rows, max_seq_len, chunk_tokens, slots_128);
   // What follows a shared prefix is the streaming kernel's, so such a call does without the prefix where
   // that costs more than the stacked rows save: with more than 64 rows they are little denser than the
   // many-row kernel's own; up to 64 a prefix of half the context is worth it.  (The workspace keeps
@@ -253,7 +252,7 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
   if (plan->shared_groups > 0) plan->many_rows = 0;
   if (plan->many_rows)
     cut_contexts(d, batch, rows, (int64_t)q_len * num_q_heads, ((int64_t)max_seq_len + 63) / 64,
-                 (int64_t)slot_rows, plan);
+                 (int64_t)slot_rows, slots_128, plan);
   return true;
 }
 
