@@ -33,9 +33,9 @@ void kvq_profile_read_ceiling(int on);
  * is a run of back-to-back streaming kernels that two events can bracket.  Off initially. */
 void kvq_profile_skip_reduce(int on);
 
-/* 0 makes paged_decode_attn use its streaming kernels also for 128
- * and more query rows per kv head, where it otherwise takes the kernel that shares the
- * dequantization among 128 rows.  On initially.  Process-global. */
+/* 0 makes paged_decode_attn use its streaming kernels also where it otherwise takes the kernel
+ * that shares the dequantization among 128 rows: from 128 query rows per kv head on, and from 33
+ * on where that is faster.  On initially.  Process-global. */
 void kvq_profile_prefill_kernel(int on);
 
 /* What paged_decode_attn (or, with shared_prefix_tokens, paged_decode_attn_prefix) would launch for

@@ -138,8 +138,8 @@ __device__ inline half8 cvt8(uint32_t x0, uint32_t x1) {
 // `scales` points at the lane's 16 tokens' skp, then lsv, then rsv, each array 64 floats long.  The 16
 // lanes of a row read the same address, a broadcast, so a logit costs one multiply-add (as row
 // broadcasts riding on a multiply and an add they cost two instructions of the slower DPP form: the
-// many-row kernel 406 -> 396 us int8, 351 -> 341 int4; the two-tile streaming kernel 152 -> 149).  The other formats have one skp, lsv, rsv per lane: the maximum is
-// taken of the raw contractions and the exponent is one multiply-add.  Group-scaled int4: S already
+// many-row kernel 406 -> 396 us int8, 351 -> 341 int4; the two-tile streaming kernel 152 -> 149).  The
+// other formats have one skp, lsv, rsv per lane: the maximum is taken of the raw contractions and the exponent is one multiply-add.  Group-scaled int4: S already
 // holds the logits (plus lsv), and is left holding the probabilities in fp32 for its caller to scale
 // once more.
 // Out: pb, the probabilities times the V scale as the B operand of P.V (f16 scaled by 2^10, or two

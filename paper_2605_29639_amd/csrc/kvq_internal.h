@@ -90,7 +90,7 @@ struct ReduceLaunch {
 };
 // A unit of head_dim / 4 lanes for each row, or for every eight of a row's partials where it has more
 // than that on average (a shared prefix does not count: a prefix that is dropped on the device
-// leaves the call as it is without one, bit for bit); as many rows to a workgroup as its threads
+// leaves the call as it is on the streaming kernel without one, bit for bit); as many rows to a workgroup as its threads
 // hold.  A launch has fewer than 2^32 threads in x, so very many pairs get smaller workgroups.
 inline ReduceLaunch reduce_launch(int64_t batch, int64_t pairs_per_seq, int64_t num_waves, int rows,
                                   int row_tiles, int head_dim) {

@@ -1015,8 +1015,8 @@ __global__ __launch_bounds__(kWaves * 64) void write_run_kernel(
 // encodes its own sub-block under the block's scale.  A run whose scale would grow over older codes of
 // the block goes to the general routine (wavefront 0).  The slots are read once: wavefront j takes 32
 // of the 2 bs tokens a run can reach and leaves their slots and two bit masks (token starts a run,
-// token continues one) in LDS.  64-token blocks, 30 k tokens: 54 -> 44 us, 4.2 TB/s.  Every wavefront takes every barrier: the list of runs comes from LDS
-// and the loops over it are uniform.
+// token continues one) in LDS.  64-token blocks, 30 k tokens: 54 -> 44 us, 4.2 TB/s.  Every wavefront
+// takes every barrier: the list of runs comes from LDS and the loops over it are uniform.
 template <int D>
 __global__ __launch_bounds__(1024) void write_fp8_block_kernel(
     const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,

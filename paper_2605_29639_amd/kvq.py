@@ -134,7 +134,7 @@ def strerror(code):
 
 # A decode step makes two calls of a few microseconds of GPU work each, so what the marshalling below
 # costs counts: one token of one sequence took 26 us a step with a stream object looked up and an
-# argument object made for every tensor, now 18, of which 11.6 are the library's own calls and kernels.
+# argument object made for every tensor, now 18 to 20, of which 11.6 are the library's own calls and kernels.
 _torch_module = None
 
 
