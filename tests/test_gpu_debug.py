@@ -114,6 +114,30 @@ def test_a_broken_shared_prefix_promise_is_reported(debug_on):
     assert np.isfinite(out.cpu().numpy()).all()
 
 
+@pytest.mark.parametrize("q_len", [20])
+def test_a_broken_promise_is_reported_where_the_prefix_is_not_used(debug_on, q_len):
+    """80 query rows per kv head: the call does better without the prefix kernel and drops the hint, but the
+    promise is checked all the same."""
+    import torch
+    from paper_2605_29639_amd import kvq
+    from helpers import gpu_attention, upload_oracle_cache
+    wl = W.custom("debug_dropped", W.MODE_INT8, [300, 276, 400], q_len, 8, 2, 128, 16, seed=6, shared_prefix=256)
+    oc, osc = oracle_fill(wl)
+    want = oracle.paged_decode_attn(wl.q, oc, osc, wl.mode, wl.block_tables, wl.seq_lens, q_len, wl.sm_scale)
+    cache, scales, desc = upload_oracle_cache(wl, oc, osc)
+    assert attn_err(gpu_attention(wl, cache, scales, desc, shared_prefix_tokens=256), want) <= 2e-3
+    broken = _with(wl.block_tables, (2, 3), int(wl.block_tables[2, 17]))
+    out = torch.full((3 * q_len, 8, 128), 7.0, dtype=torch.float32, device="cuda")
+    ws = kvq.alloc_workspace(desc, 3, q_len, 8, wl.max_seq_len, shared_prefix_tokens=256)
+    with pytest.raises(kvq.KvqError) as e:
+        kvq.paged_decode_attn(bits_to_bf16_tensor(wl.q), cache, scales, desc, torch.from_numpy(broken).cuda(),
+                              torch.from_numpy(wl.seq_lens).cuda(), q_len, wl.max_seq_len, wl.sm_scale,
+                              out, ws, shared_prefix_tokens=256)
+    assert e.value.code == kvq.E_BAD_INDEX
+    torch.cuda.synchronize()
+    assert bool((out == 7.0).all())
+
+
 def _with(a, at, value):
     a = a.copy()
     a[at] = value
