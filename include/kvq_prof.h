@@ -40,7 +40,7 @@ void kvq_profile_prefill_kernel(int on);
 
 /* What paged_decode_attn (or, with shared_prefix_tokens, paged_decode_attn_prefix) would launch for
  * these host-side arguments; batch >= 1.  Host only.  plan_out: [0] 1 if the call goes to the
- * many-row kernel, [1] cuts that kernel may make in the contexts of the batch, [2] wavefronts of the streaming
+ * many-row kernel (2 where long contexts go to the one of 256 rows a workgroup), [1] cuts that kernel may make in the contexts of the batch, [2] wavefronts of the streaming
  * kernel, [3] 64-token groups of the shared prefix that the prefix kernel takes, [4] rows of a row
  * group, and the reduce's [5] grid in x, [6] grid in y and [7] threads per workgroup. */
 int kvq_profile_plan(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,

@@ -81,21 +81,26 @@ int ilog2(int x) {
 // consumed; splitting adds the second launch and writes and reads 64 KB per workgroup.  One
 // sequence's 512 tokens over 16384 cached ones (fp8, 32 / 8 heads): 427 us in one piece, 178 in
 // four with the merge; eight such chunks over 4096 (1024 workgroups, two full rounds) stay whole.
-int64_t equal_pieces(int64_t slots, int64_t walks, int64_t groups, int64_t room) {
-  if (walks >= 4 * slots) return 1;
+// (wide: the kernel for kWideRows, one workgroup of 256 rows on a compute unit where the other kernel has two
+// of 128: 2.3 us per group, the same for the last round, 5 until a first group is consumed and 9 from one
+// workgroup of a compute unit to the next, which nothing overlaps.)
+int64_t equal_pieces(int64_t slots, int64_t walks, int64_t groups, int64_t room, bool wide, double* least_us) {
   int64_t best = 1;
   double best_us = 0.0;
   for (int64_t c = 1; c <= room && c <= kvq::kMaxContextSplits && (c == 1 || c * 2 <= groups); ++c) {
     const int64_t n = walks * c, rest = n % slots;
-    if (c > 1 && n > 4 * slots) break;
-    const double rounds = (double)(n / slots) + (rest == 0 ? 0.0 : 2 * rest <= slots ? 0.6 : 1.0);
-    const double us = rounds * (3.0 + 2.6 * (double)((groups + c - 1) / c)) +
-                      (c > 1 ? 6.0 + 0.025 * (double)n : 0.0);
+    if (c > 1 && (n > 4 * slots || walks >= 4 * slots)) break;
+    const double rounds = (double)(n / slots) + (rest == 0 ? 0.0 : 2 * rest <= slots && !wide ? 0.6 : 1.0);
+    const double piece = (double)((groups + c - 1) / c);
+    const double us = (wide ? rounds * 2.3 * piece + 5.0 + 9.0 * (rounds > 1.0 ? rounds - 1.0 : 0.0)
+                            : rounds * (3.0 + 2.6 * piece)) +
+                      (c > 1 ? 6.0 + (wide ? 0.05 : 0.025) * (double)n : 0.0);
     if (c == 1 || us < best_us) {
       best = c;
       best_us = us;
     }
   }
+  *least_us = best_us;
   return best;
 }
 
@@ -110,12 +115,26 @@ int64_t equal_pieces(int64_t slots, int64_t walks, int64_t groups, int64_t room)
 // 2000 tokens: 414, 162 and 175 (the pieces are worked out, and none is needed).  A 512-token chunk
 // on its own under a bound of 32768: 21 us without leave to cut, 28 cut by the bound, 23 now (the
 // second launch finds nothing to do); over 4096 tokens, same bound: 117, 63 and 63.
+// Where the kernel for kWideRows should be faster for contexts of max_seq_len, both are launched, and the
+// lengths decide on the device which of them does the call: contexts much shorter than the bound are the
+// other's (an empty launch of about a microsecond is left).  Measured, kernel for 128 rows -> both: 8 x 512
+// tokens over 4608 int8 373 -> 345 us, fp8 305 -> 290, bf16 390 -> 375; 1 x 512 over 16896 183 -> 165,
+// 158 -> 145, 194 -> 183; 8 x 512 over 520 under a bound of 32768 53 -> 54, where the wide kernel takes 59.
 void cut_contexts(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t seq_rows,
                   int64_t groups, int64_t slot_rows, int64_t slots, kvq::AttnPlan* plan) {
   const int64_t room = slot_rows / seq_rows;
   const int64_t per_seq = d->num_kv_heads * ((rows + kvq::kRowsPerWorkgroup - 1) / kvq::kRowsPerWorkgroup);
+  double us, wide_us;
+  int64_t c = equal_pieces(slots, batch * per_seq, groups, room / batch + 1, false, &us);
+  if (d->head_dim == 128 && rows > kvq::kRowsPerWorkgroup && groups * 64 <= (int64_t)kvq::kWideTable * d->block_size) {
+    const int64_t wide_per_seq = d->num_kv_heads * ((rows + kvq::kWideRows - 1) / kvq::kWideRows);
+    const int64_t wide_c = equal_pieces(slots / 2, batch * wide_per_seq, groups, room / batch + 1, true, &wide_us);
+    if (wide_us < 0.93 * us) {
+      plan->wide_groups = (int32_t)(batch * groups * 5 / 8);
+      c = wide_c;
+    }
+  }
   plan->piece_min = (int32_t)(per_seq < 32 ? 2 : per_seq / 16);
-  const int64_t c = equal_pieces(slots, batch * per_seq, groups, room / batch + 1);
   if (c > 1) {
     plan->extra_pieces = (int32_t)(batch * (c - 1));
   } else if (rows < kvq::kRowsPerWorkgroup && groups > 2 * plan->piece_min) {
@@ -250,6 +269,7 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
   if (plan->many_rows && (rows > 64 || 2 * (int64_t)plan->shared_groups < ((int64_t)max_seq_len + 63) / 64))
     plan->shared_groups = 0;
   if (plan->shared_groups > 0) plan->many_rows = 0;
+  plan->wide_groups = 0;
   if (plan->many_rows)
     cut_contexts(d, batch, rows, (int64_t)q_len * num_q_heads, ((int64_t)max_seq_len + 63) / 64,
                  (int64_t)slot_rows, slots_128, plan);
@@ -511,6 +531,7 @@ int attn_call(const void* q, const void* cache, const float* scales,
   a.shared_groups = plan.shared_groups;
   a.prefix_chunks = plan.prefix_chunks;
   a.many_rows = plan.many_rows;
+  a.wide_groups = plan.wide_groups;
   a.extra_pieces = plan.extra_pieces;
   a.piece_min = plan.piece_min;
   a.piece_share = plan.piece_share;
@@ -622,7 +643,7 @@ int kvq_profile_plan(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len,
   if (batch == 0) return KVQ_E_BAD_SHAPE;
   const kvq::ReduceLaunch r =
       kvq::reduce_launch(batch, p.pairs_per_seq, p.num_waves, p.rows, p.row_tiles, desc->head_dim);
-  const int64_t values[8] = {p.many_rows, p.extra_pieces, p.num_waves, p.shared_groups,
+  const int64_t values[8] = {p.many_rows + (p.wide_groups > 0), p.extra_pieces, p.num_waves, p.shared_groups,
                              16 * p.row_tiles, r.pairs, r.parts, r.threads};
   for (int i = 0; i < 8; ++i) plan_out[i] = values[i];
   return KVQ_OK;

@@ -148,105 +148,98 @@ __device__ inline half8 cvt8(uint32_t x0, uint32_t x1) {
 // TAIL: some row's causal length ends inside the group, so positions are masked.
 // (An unquantized cache's factor is not negative: its caller puts the sign of the softmax scale into q.
 // The test and its branch between QK^T and the softmax cost the two-tile streaming kernel 6 %.)
-template <int MODE, int NT, int DT, bool TAIL, class Operand, int NP>
-__device__ inline void online_softmax(floatx4 (&S)[NT][4], const floatx4* scales, float skp, float lsv,
-                                      float rsv, int pos_lane, const int (&nrow)[NT],
-                                      float (&m_run)[NT], float (&l_run)[NT],
-                                      floatx4 (&acc)[NT][DT], Operand (&pb)[NT][NP]) {
-  constexpr int pitch = 16;  // floatx4s per array of scales
-  constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN;
-  constexpr bool FP8 = MODE == KVQ_FP8E4M3_BLOCK_HEAD || MODE == KVQ_FP8E4M3_TENSOR;
-  constexpr bool GROUPED = MODE == KVQ_INT4_GROUP32;
-  constexpr bool TOKEN_SCALE = MODE == KVQ_INT8_TOKEN_HEAD || MODE == KVQ_INT4_TOKEN_HEAD || GROUPED;
-  constexpr bool RAW = !TOKEN_SCALE && !TAIL;  // S stays the raw contraction, its factor >= 0
-  float mx[NT];
+// The kernel for 256 rows takes its three parts apart: the first runs under its matrix instructions.
+template <int MODE, bool TAIL>
+struct SoftmaxForm {
+  static constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN;
+  static constexpr bool FP8 = MODE == KVQ_FP8E4M3_BLOCK_HEAD || MODE == KVQ_FP8E4M3_TENSOR;
+  static constexpr bool GROUPED = MODE == KVQ_INT4_GROUP32;
+  static constexpr bool TOKEN_SCALE = MODE == KVQ_INT8_TOKEN_HEAD || MODE == KVQ_INT4_TOKEN_HEAD || GROUPED;
+  static constexpr bool RAW = !TOKEN_SCALE && !TAIL;  // S stays the raw contraction, its factor >= 0
+  static constexpr bool kLogits = TOKEN_SCALE && !GROUPED;  // from S by softmax_logits
+};
+constexpr int kScalePitch = 16;  // floatx4s per array of scales
+
+// Part 1: quad u of the lane's tokens (its K scales k4, logarithms of the V scales l4): S becomes the
+// logits where the format needs it, mx their maximum so far.
+template <int MODE, int NT, bool TAIL>
+__device__ inline void softmax_logits(floatx4 (&S)[NT][4], int u, const floatx4& k4, const floatx4& l4,
+                                      float skp, float lsv, int pos_lane, const int (&nrow)[NT],
+                                      float (&mx)[NT]) {
+  using F = SoftmaxForm<MODE, TAIL>;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) mx[nt] = -INFINITY;
-  if constexpr (RAW && !PLAIN) {
-    if (__any(skp < 0.0f)) {  // (a negative softmax scale, or static scale)
-      const float sign = skp < 0.0f ? -1.0f : 1.0f;
-      skp *= sign;
+  for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) S[nt][u] *= sign;
+    for (int i = 0; i < 4; ++i) {
+      float z = S[nt][u][i];
+      if constexpr (F::kLogits) z = __builtin_fmaf(z, k4[i], l4[i]);
+      else if constexpr (TAIL && !F::GROUPED) z = __builtin_fmaf(z, skp, lsv);
+      if constexpr (TAIL) z = (pos_lane + 4 * u + i < nrow[nt]) ? z : -INFINITY;
+      if constexpr (!F::RAW) S[nt][u][i] = z;
+      mx[nt] = fmaxf(mx[nt], z);
     }
-  }
-  // (the next four tokens' scales are requested while these are used, and no earlier: registers)
-  [[maybe_unused]] floatx4 k4[2], l4[2];
-  constexpr bool kLogits = TOKEN_SCALE && !GROUPED;  // from S by this loop
-  if constexpr (kLogits) {
-    k4[0] = scales[0];
-    l4[0] = scales[pitch];
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    if constexpr (kLogits) {
-      if (u < 3) {
-        k4[(u + 1) & 1] = scales[u + 1];
-        l4[(u + 1) & 1] = scales[pitch + u + 1];
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float z = S[nt][u][i];
-        if constexpr (kLogits) z = __builtin_fmaf(z, k4[u & 1][i], l4[u & 1][i]);
-        else if constexpr (TAIL && !GROUPED) z = __builtin_fmaf(z, skp, lsv);
-        if constexpr (TAIL) z = (pos_lane + 4 * u + i < nrow[nt]) ? z : -INFINITY;
-        if constexpr (!RAW) S[nt][u][i] = z;
-        mx[nt] = fmaxf(mx[nt], z);
-      }
-    if constexpr (kLogits) __builtin_amdgcn_sched_barrier(0);
-  }
-  float alpha[NT], msub[NT];
+}
+
+// Part 2: the running maxima, the factors alpha the accumulators shrink by, and what part 3 subtracts.
+template <int MODE, int NT, bool TAIL>
+__device__ inline void softmax_maxima(const float (&mx)[NT], float skp, float lsv, float (&m_run)[NT],
+                                      float (&alpha)[NT], float (&msub)[NT]) {
+  using F = SoftmaxForm<MODE, TAIL>;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
-    const float m_here = RAW ? __builtin_fmaf(mx[nt], skp, lsv) : mx[nt];
+    const float m_here = F::RAW ? __builtin_fmaf(mx[nt], skp, lsv) : mx[nt];
     const float m_new = fmaxf(m_run[nt], xor16_max(m_here));
     const float m_safe = (m_new == -INFINITY) ? 0.0f : m_new;
     alpha[nt] = __builtin_amdgcn_exp2f(m_run[nt] - m_safe);
     m_run[nt] = m_new;
-    msub[nt] = RAW ? lsv - (m_safe - kPOffset) : m_safe - kPOffset;
+    msub[nt] = F::RAW ? lsv - (m_safe - kPOffset) : m_safe - kPOffset;
   }
+}
+
+// Part 3: probabilities and sums.  AHEAD: r_all holds the lane's 16 reciprocals of the V scales, else
+// they are read from `scales` as they are needed.
+template <int MODE, int NT, bool TAIL, bool AHEAD, class Operand, int NP>
+__device__ inline void softmax_probabilities(floatx4 (&S)[NT][4], const floatx4* scales, const floatx4 (&r_all)[4],
+                                             float skp, float rsv, const float (&alpha)[NT],
+                                             const float (&msub)[NT], float (&l_run)[NT], Operand (&pb)[NT][NP]) {
+  using F = SoftmaxForm<MODE, TAIL>;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     float lsum = 0.0f;
     [[maybe_unused]] uint32_t hi_bits[16];
     [[maybe_unused]] float rest[16];
     [[maybe_unused]] floatx4 r4[2];
-    if constexpr (TOKEN_SCALE) r4[0] = scales[2 * pitch];
+    constexpr bool READ = F::TOKEN_SCALE && !AHEAD;
+    if constexpr (READ) r4[0] = scales[2 * kScalePitch];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      if constexpr (TOKEN_SCALE) {
-        if (u < 3) r4[(u + 1) & 1] = scales[2 * pitch + u + 1];
+      if constexpr (READ) {
+        if (u < 3) r4[(u + 1) & 1] = scales[2 * kScalePitch + u + 1];
         __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int tix = 4 * u + i;
-        const float pr = __builtin_amdgcn_exp2f(RAW ? __builtin_fmaf(S[nt][u][i], skp, msub[nt])
-                                                    : S[nt][u][i] - msub[nt]);
-        if constexpr (TOKEN_SCALE) lsum = __builtin_fmaf(pr, r4[u & 1][i], lsum);
+        const float pr = __builtin_amdgcn_exp2f(F::RAW ? __builtin_fmaf(S[nt][u][i], skp, msub[nt])
+                                                       : S[nt][u][i] - msub[nt]);
+        if constexpr (F::TOKEN_SCALE) lsum = __builtin_fmaf(pr, AHEAD ? r_all[u][i] : r4[u & 1][i], lsum);
         else lsum += pr;
-        if constexpr (PLAIN) {
+        if constexpr (F::PLAIN) {
           // bf16 keeps 8 bits of a probability: it goes in as two terms, the value cut to bf16 and
           // the (exactly representable) rest rounded to bf16, 16 bits in all.  (Rounded, not cut: a
           // row's largest probability comes out a last place below or above 2^10, and cut it would
           // lose up to 2^-16 of itself, which is a peaked row's whole error.)
           hi_bits[tix] = __float_as_uint(pr) & 0xFFFF0000u;
           rest[tix] = pr - __uint_as_float(hi_bits[tix]);
-        } else if constexpr (GROUPED) {
+        } else if constexpr (F::GROUPED) {
           S[nt][u][i] = pr;
         } else {
           pb[nt][tix >> 3][tix & 7] = (_Float16)pr;
         }
       }
-      if constexpr (TOKEN_SCALE) __builtin_amdgcn_sched_barrier(0);
+      if constexpr (READ) __builtin_amdgcn_sched_barrier(0);
     }
-    if constexpr (PLAIN) {
+    if constexpr (F::PLAIN) {
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf) {
         uintx4 ph, pl;
@@ -260,10 +253,14 @@ __device__ inline void online_softmax(floatx4 (&S)[NT][4], const floatx4* scales
         pb[nt][2 + hf] = __builtin_bit_cast(bf16x8, pl);
       }
     }
-    if constexpr (FP8) lsum *= rsv;  // one scale per lane
+    if constexpr (F::FP8) lsum *= rsv;  // one scale per lane
     l_run[nt] = __builtin_fmaf(l_run[nt], alpha[nt], lsum);
   }
-  // (per 16-row tile: a tile none of whose rows' maxima moved keeps its accumulators as they are)
+}
+
+// (per 16-row tile: a tile none of whose rows' maxima moved keeps its accumulators as they are)
+template <int NT, int DT>
+__device__ inline void softmax_rescale(const float (&alpha)[NT], floatx4 (&acc)[NT][DT]) {
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     if (__any(alpha[nt] != 1.0f)) {
@@ -271,6 +268,49 @@ __device__ inline void online_softmax(floatx4 (&S)[NT][4], const floatx4* scales
       for (int tt = 0; tt < DT; ++tt) acc[nt][tt] *= alpha[nt];
     }
   }
+}
+
+template <int MODE, int NT, int DT, bool TAIL, class Operand, int NP>
+__device__ inline void online_softmax(floatx4 (&S)[NT][4], const floatx4* scales, float skp, float lsv,
+                                      float rsv, int pos_lane, const int (&nrow)[NT],
+                                      float (&m_run)[NT], float (&l_run)[NT],
+                                      floatx4 (&acc)[NT][DT], Operand (&pb)[NT][NP]) {
+  using F = SoftmaxForm<MODE, TAIL>;
+  float mx[NT], alpha[NT], msub[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) mx[nt] = -INFINITY;
+  if constexpr (F::RAW && !F::PLAIN) {
+    if (__any(skp < 0.0f)) {  // (a negative softmax scale, or static scale)
+      const float sign = skp < 0.0f ? -1.0f : 1.0f;
+      skp *= sign;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) S[nt][u] *= sign;
+    }
+  }
+  // (the next four tokens' scales are requested while these are used, and no earlier: registers)
+  [[maybe_unused]] floatx4 k4[2], l4[2];
+  if constexpr (F::kLogits) {
+    k4[0] = scales[0];
+    l4[0] = scales[kScalePitch];
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if constexpr (F::kLogits) {
+      if (u < 3) {
+        k4[(u + 1) & 1] = scales[u + 1];
+        l4[(u + 1) & 1] = scales[kScalePitch + u + 1];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    softmax_logits<MODE, NT, TAIL>(S, u, k4[u & 1], l4[u & 1], skp, lsv, pos_lane, nrow, mx);
+    if constexpr (F::kLogits) __builtin_amdgcn_sched_barrier(0);
+  }
+  softmax_maxima<MODE, NT, TAIL>(mx, skp, lsv, m_run, alpha, msub);
+  const floatx4 none[4] = {};
+  softmax_probabilities<MODE, NT, TAIL, false>(S, scales, none, skp, rsv, alpha, msub, l_run, pb);
+  softmax_rescale<NT, DT>(alpha, acc);
 }
 
 }  // namespace

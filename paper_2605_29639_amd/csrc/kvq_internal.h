@@ -78,6 +78,8 @@ __host__ __device__ inline uint8_t stored_byte(uint8_t code, int mode) {
 
 constexpr int kMaxPrefixChunks = 8;  // pieces a shared prefix is cut into at most
 constexpr int kRowsPerWorkgroup = 128;    // query rows a workgroup of the many-row kernel owns
+constexpr int kWideRows = 256;            // the same for the kernel of calls with more rows
+constexpr int kWideTable = 16384;         // block-table entries a walk of that kernel may span
 constexpr int kMaxContextSplits = 64;     // pieces that kernel cuts contexts of one length into at most
 
 constexpr int kReduceBatch = 8;      // partials a unit of the reduce requests at once
@@ -123,7 +125,9 @@ struct AttnPlan {
   int32_t shared_groups;   // shared prefix in 64-token groups, 0 where the prefix kernel is not used
   int32_t promised_groups; // the same also where the call does better without that kernel
   int32_t prefix_chunks;   // pieces the prefix kernel cuts it into (>= 1)
-  int32_t many_rows;       // the call goes to the many-row kernel
+  int32_t many_rows;       // the call goes to a many-row kernel
+  int32_t wide_groups;     // to the one with workgroups of kWideRows where all contexts together have so many
+                           // groups (0: never)
   // many-row kernel: pieces beyond each sequence's first that the contexts may be cut into (0: no cut),
   // groups a piece holds at least, and the share of all groups that it holds at least
   int32_t extra_pieces, piece_min;
@@ -150,7 +154,8 @@ struct AttnArgs {
   int32_t shared_groups;  // leading 64-token groups that all sequences' tables map to the same
                           // blocks (0: none, or a call the prefix kernel does not serve)
   int32_t prefix_chunks;  // pieces the prefix kernel cuts those groups into: one partial each
-  int32_t many_rows;      // the call goes to the many-row kernel (kvq_prefill.hip)
+  int32_t many_rows;      // the call goes to a many-row kernel (kvq_prefill.hip)
+  int32_t wide_groups;    // groups that give it to the one with workgroups of kWideRows, as in AttnPlan
   int32_t extra_pieces, piece_min;  // how the many-row kernel may cut the contexts, as in AttnPlan
   float piece_share;
   unsigned long long* wave_clock;  // measurement build: 8 clock readings per wavefront; else null

@@ -3,16 +3,24 @@
 //
 // With many query rows per kv head (128 and more; from 33 on where the plan finds it faster)
 // the work is arithmetic, not memory traffic, and what has to be shared is the dequantization:
-// the streaming kernel converts a group's codes once per 32 rows, this kernel once per 128.  A
-// workgroup of four wavefronts owns 128 query rows of one (sequence, kv head) and walks the context
-// from position 0 to the last position any of its rows may see, or a piece of it where the call has too
-// few such workgroups to fill the chip or some contexts are far longer than others (see
-// context_piece and merge_kernel below).  Per 64-token group each wavefront loads a quarter of the K and V codes, converts them to f16 and puts them in
-// LDS in the order the matrix instruction wants its A operand (one 16-byte read per lane and
-// instruction, no bank conflicts); after a barrier every wavefront runs QK^T, the online
-// softmax and P.V for its own 32 rows against the shared operands.  LDS holds two groups, so
-// one barrier per group suffices: while a group is consumed, the next one's codes are in
+// the streaming kernel converts a group's codes once per 32 rows, these kernels once per 128 or 256.  A
+// workgroup of four wavefronts (attn_rows_kernel) owns 128 query rows of one (sequence, kv head) and walks
+// the context from position 0 to the last position any of its rows may see, or a piece of it where the call
+// has too few such workgroups to fill the chip or some contexts are far longer than others (see
+// context_piece and merge_kernel below).  Per 64-token group each wavefront loads a quarter of the K and V
+// codes, converts them to f16 and puts them in LDS in the order the matrix instruction wants its A operand
+// (one 16-byte read per lane and instruction, no bank conflicts); after a barrier every wavefront runs
+// QK^T, the online softmax and P.V for its own 32 rows against the shared operands.  LDS holds two groups,
+// so one barrier per group suffices: while a group is consumed, the next one's codes are in
 // flight and are converted into the other half.
+//
+// A wavefront issues one vector instruction in 4.4 cycles, whatever its neighbour does, and a matrix
+// instruction keeps the matrix unit busy for 16: what a wavefront can do under its own matrix instructions
+// is free.  So the conversions of the next group's codes are dealt out under P.V and the logits of the first
+// tokens under the contraction of the last ones (sched_group_barrier; the conversions are pinned by an
+// empty asm, and the loop has no branch around a matrix phase: code that two branches share is moved ahead
+// of both, and the wait for its loads with it).  8 x 512 tokens over 4608, 32 / 8 heads: int8 381 -> 373 us,
+// bf16 411 -> 390; 16 x 33 tokens over 2000: int8 61.8 -> 57.6, bf16 69 -> 62.5.
 //
 // The arithmetic (logits in base 2 with the K scale applied after the contraction, V scale
 // folded into the probability, f16 probabilities scaled by 2^10, masks) is the streaming
@@ -23,8 +31,9 @@
 namespace kvq {
 namespace {
 
-constexpr int kWavesPerGroup = 4;
+constexpr int kWavesPerGroup = 4;  // (the kernels for 128 rows)
 static_assert(kRowsPerWorkgroup == kWavesPerGroup * 32, "a wavefront owns two 16-row tiles");
+static_assert(kWideRows == 2 * kRowsPerWorkgroup, "twice the wavefronts");
 
 // minimum over the wavefront (by shuffles: with a result the compiler knows to be uniform it makes two
 // copies of the PREFIX kernel's loop and spills)
@@ -110,50 +119,39 @@ __device__ inline bool context_piece(const AttnArgs& p, int f, bool leave, Piece
   return found;
 }
 
-// PREFIX = true is the kernel for a prefix that every sequence of a decode or verification
-// batch shares (the same physical blocks at the head of every block table; Section 1 and
-// Section 5.2.3: prompt prefixes served from the prefix cache).  The query rows of all
-// sequences are stacked, 128 to a workgroup, so a group of the prefix is read and converted
-// once per 128 rows (four sequences of a 4-token verification step with 8 query heads per kv
-// head) instead of once per sequence.  The prefix is cut into p.prefix_chunks pieces to get
-// enough workgroups; a workgroup walks one piece and leaves, per row, an unnormalised partial
-// (max, sum, accumulator) in the workspace, in the slots behind the streaming kernel's, which
-// the reduce merges with the streaming kernel's partials over the rest of each sequence.
-template <int MODE, int D, bool PREFIX>
-__global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(const AttnArgs p) {
-  constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN;  // unquantized cache: the operands are its bytes
-  constexpr bool FP8 = MODE == KVQ_FP8E4M3_BLOCK_HEAD || MODE == KVQ_FP8E4M3_TENSOR;
-  constexpr bool INT4 = MODE == KVQ_INT4_TOKEN_HEAD;  // two codes per byte (head_dim 128)
-  constexpr bool TOKEN_SCALE = MODE == KVQ_INT8_TOKEN_HEAD || INT4;
-  static_assert(!INT4 || D == 128, "int4 codes come with head_dim 128 only");
-  constexpr int NT = 2;
-  constexpr int EB = PLAIN ? 2 : 1;  // bytes per cache element
-  constexpr int RB = INT4 ? D / 2 : D * EB;  // bytes per token row in a tile
-  constexpr int DT = D / 16;       // 16-channel tiles of V / of the output
-  constexpr int KJ = RB / 64;      // 16-byte K pieces per lane and quad
-  constexpr int KS = D / 32;       // matrix-instruction steps over the channels
-  constexpr int VT = DT / kWavesPerGroup;  // V tiles a wavefront converts
-  constexpr int VP = INT4 ? VT / 2 : VT * EB;  // 16-byte V pieces per lane (int4: one piece = two tiles)
-  // matrix-instruction operand of 8 values: f16 (from codes) or the cache's own bf16
-  using Operand = std::conditional_t<PLAIN, bf16x8, half8>;
-  __shared__ half8 k_ops[2][4][KS][64];    // [half][quad of the sub-block][step][lane]
-  __shared__ half8 v_ops[2][DT][2][64];    // [half][channel tile][tokens 0-7 | 8-15][lane]
-  // [half]: K scale * log2e / sqrt(D), log2 and reciprocal of the V scale of the 64 tokens
-  __shared__ __align__(16) float s_ops[2][3][64];
-
-  const int lane = threadIdx.x & 63;
-  const int wv = threadIdx.x >> 6;
-  const int m16 = lane & 15, g4 = lane >> 4;
-  const int H = p.num_kv_heads, G = p.group, bs = p.block_size, bs_shift = p.bs_shift;
+// What a wavefront of either many-row kernel works on: 32 query rows from r0 on of `all_rows` that kv head
+// h has here (one sequence's, or under PREFIX all sequences' stacked), over groups [g0, ng) of sequence
+// b's context.
+struct Place {
+  int all_rows, h, r0, b, L, g0, ng, n_min, chunk;  // n_min: the shortest causal length of the rows
+  bool wave_live;
+  Piece piece;
+};
+// Where the plan launches both kernels, which of them the lengths give the call to: the wide one where all
+// contexts together have p.wide_groups groups.
+__device__ inline bool whole_wide(const AttnArgs& p, int lane) {
+  int total = 0;
+  for (int i = lane; i < p.batch; i += 64) total += (p.seq_lens[i] + 63) >> 6;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) total += __shfl_xor(total, d, 64);  // (shuffles: as in wave_min_int)
+  return total >= p.wide_groups;
+}
+// Returns false for a workgroup that has nothing to do (the same in all its wavefronts).
+// CHOICE: the plan launches both kernels.
+template <bool PREFIX, int ROWS, bool CHOICE>
+__device__ inline bool place_rows(const AttnArgs& p, int lane, int wv, Place& o) {
+  const int H = p.num_kv_heads, G = p.group;
   // rows a (kv head) has in this kernel: one sequence's, or all sequences' stacked
-  const int all_rows = PREFIX ? p.batch * p.rows : p.rows;
-  const int row_blocks = (all_rows + kRowsPerWorkgroup - 1) / kRowsPerWorkgroup;
+  o.all_rows = PREFIX ? p.batch * p.rows : p.rows;
+  const int row_blocks = (o.all_rows + ROWS - 1) / ROWS;
   int P = 0;  // PREFIX: the shared groups, if every sequence has that many full ones
   if constexpr (PREFIX) {
     int min_full = 0x7FFFFFFF;
     for (int i = lane; i < p.batch; i += 64) min_full = min(min_full, p.seq_lens[i] >> 6);
-    if (p.shared_groups > wave_min_int(min_full)) return;  // the streaming kernel does it all
+    if (p.shared_groups > wave_min_int(min_full)) return false;  // the streaming kernel does it all
     P = p.shared_groups;
+  } else if constexpr (CHOICE) {
+    if (whole_wide(p, lane) != (ROWS == kWideRows)) return false;  // the other kernel's
   }
   // Workgroup -> (sequence, kv head, row block).  The hardware hands consecutive workgroups to
   // the eight XCDs in turn, each with an L2 of its own, and the row blocks of one (sequence,
@@ -172,63 +170,55 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
     }
     rb = row_blocks - 1 - rb;  // the later a chunk's rows, the longer their walk: the longest start first
   }
-  const int h = pair % H;
+  o.h = pair % H;
   // this wavefront's rows, and the groups [g0, ng) the workgroup has to walk
-  const int r0 = rb * kRowsPerWorkgroup + wv * 32;
-  const bool wave_live = r0 < all_rows;
-  int b, L, g0, ng, n_min, chunk = 0;
-  Piece piece{0, 0, 1, 0};
+  o.r0 = rb * ROWS + wv * 32;
+  o.wave_live = o.r0 < o.all_rows;
+  o.chunk = 0;
+  o.piece = Piece{0, 0, 1, 0};
   if constexpr (PREFIX) {
-    chunk = pair / H;
-    b = rb * kRowsPerWorkgroup / p.rows;  // whose block table: the first row's sequence (all agree)
-    L = P << 6;                           // every position below it exists in every sequence
-    g0 = (int)((long long)chunk * P / p.prefix_chunks);
-    ng = (int)((long long)(chunk + 1) * P / p.prefix_chunks);
-    n_min = 0;  // (set below, from the rows' own causal lengths)
+    o.chunk = pair / H;
+    o.b = rb * ROWS / p.rows;  // whose block table: the first row's sequence (all agree)
+    o.L = P << 6;                           // every position below it exists in every sequence
+    o.g0 = (int)((long long)o.chunk * P / p.prefix_chunks);
+    o.ng = (int)((long long)(o.chunk + 1) * P / p.prefix_chunks);
+    o.n_min = 0;  // (set below, from the rows' own causal lengths)
   } else {
-    piece.b = pair / H;
+    o.piece.b = pair / H;
     if (p.extra_pieces > 0 &&
-        !context_piece(p, piece.b, __builtin_amdgcn_readfirstlane((int)(blockIdx.x == 0 && wv == 0)), piece))
-      return;
-    b = piece.b;
-    L = p.seq_lens[b];
-    const int r_last = min(p.rows, (rb + 1) * kRowsPerWorkgroup) - 1;
-    const int n_max = L - p.q_len + r_last / G + 1;
+        !context_piece(p, o.piece.b, __builtin_amdgcn_readfirstlane((int)(blockIdx.x == 0 && wv == 0)), o.piece))
+      return false;
+    o.b = o.piece.b;
+    o.L = p.seq_lens[o.b];
+    const int r_last = min(p.rows, (rb + 1) * ROWS) - 1;
+    const int n_max = o.L - p.q_len + r_last / G + 1;
     const int all = (n_max + 63) >> 6;
-    g0 = (int)((long long)piece.chunk * all / piece.pieces);
-    ng = (int)((long long)(piece.chunk + 1) * all / piece.pieces);
-    n_min = wave_live ? L - p.q_len + r0 / G + 1 : L;  // shortest causal length here
+    o.g0 = (int)((long long)o.piece.chunk * all / o.piece.pieces);
+    o.ng = (int)((long long)(o.piece.chunk + 1) * all / o.piece.pieces);
+    o.n_min = o.wave_live ? o.L - p.q_len + o.r0 / G + 1 : o.L;  // shortest causal length here
   }
+  return true;
+}
 
-  const uint8_t* __restrict__ cache = p.cache;
-  const float* __restrict__ scales = p.scales;
-  const int32_t* __restrict__ table = p.block_tables + (size_t)b * p.max_blocks_per_seq;
-  const uint32_t tile_bytes = (uint32_t)bs * RB;
-  const uint32_t block_stride = 2u * (uint32_t)H * tile_bytes;
-  const int sbk = m16 >> 2;  // sub-block this lane reads K from
-  const uint32_t k_lane = 64u * g4 + 16u * (m16 & 3) + (uint32_t)wv * (4 * RB);  // quad wv
-  const uint32_t v_lane = (uint32_t)H * tile_bytes + 16u * m16 + 256u * (wv * (INT4 ? VP : VT));
-  const uint32_t s_block_stride = TOKEN_SCALE ? 2u * H * bs : (MODE == KVQ_FP8E4M3_TENSOR ? 0u : 2u * H);
-  const uint32_t s_kv = TOKEN_SCALE ? (uint32_t)H * bs : (MODE == KVQ_FP8E4M3_TENSOR ? 1u : (uint32_t)H);
-  const int last_sb = ((L - 1) >> 4) << 4;
-
-  // ---- q as the B operand of QK^T, causal lengths, running state ----
-  Operand qb[NT][KS];
+// q of a wavefront's rows as the B operand of QK^T, the rows' causal lengths, an empty running state.
+template <int MODE, int D, bool PREFIX, class Operand>
+__device__ inline void load_queries(const AttnArgs& p, int lane, Place& o, Operand (&qb)[2][D / 32], int (&nrow)[2],
+                                    floatx4 (&acc)[2][D / 16], float (&m_run)[2], float (&l_run)[2]) {
+  constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN, INT4 = MODE == KVQ_INT4_TOKEN_HEAD;
+  constexpr int NT = 2, KS = D / 32, DT = D / 16;
+  const int m16 = lane & 15, g4 = lane >> 4, G = p.group;
   const uint32_t q_sign = PLAIN && p.scale_log2 < 0.0f ? 0x80008000u : 0u;
-  int nrow[NT];
-  floatx4 acc[NT][DT];
-  float m_run[NT], l_run[NT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
-    const int rs = r0 + nt * 16 + m16;  // PREFIX: stacked row = sequence * rows + row
-    const bool live = rs < all_rows;
-    const int br = PREFIX ? (live ? rs / p.rows : 0) : b;
+    const int rs = o.r0 + nt * 16 + m16;  // PREFIX: stacked row = sequence * rows + row
+    const bool live = rs < o.all_rows;
+    const int br = PREFIX ? (live ? rs / p.rows : 0) : o.b;
     const int r = PREFIX ? rs - br * p.rows : rs;
     const int j = live ? r / G : 0;
     const int gi = live ? r - j * G : 0;
-    nrow[nt] = live ? (PREFIX ? p.seq_lens[br] : L) - p.q_len + j + 1 : L;
+    nrow[nt] = live ? (PREFIX ? p.seq_lens[br] : o.L) - p.q_len + j + 1 : o.L;
     const uint16_t* qrow =
-        p.q + (((size_t)br * p.q_len + j) * p.num_q_heads + (size_t)h * G + gi) * D;
+        p.q + (((size_t)br * p.q_len + j) * p.num_q_heads + (size_t)o.h * G + gi) * D;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int d0 = PLAIN || INT4 ? 32 * s + 8 * g4 : 64 * (s >> 1) + 16 * g4 + 8 * (s & 1);
@@ -250,8 +240,498 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
 #pragma unroll
     for (int tt = 0; tt < DT; ++tt) acc[nt][tt] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
+  if constexpr (PREFIX) o.n_min = wave_min_int(min(nrow[0], nrow[1]));
+}
 
-  if constexpr (PREFIX) n_min = wave_min_int(min(nrow[0], nrow[1]));
+// Where a wavefront's rows go at the end.
+template <int D, bool PREFIX>
+__device__ inline void store_rows(const AttnArgs& p, int lane, const Place& o, const floatx4 (&acc)[2][D / 16],
+                                  const float (&m_run)[2], const float (&l_run)[2]) {
+  constexpr int NT = 2, DT = D / 16;
+  const int m16 = lane & 15, g4 = lane >> 4, G = p.group;
+  if constexpr (PREFIX) {
+    // ---- partials: slot = wavefronts + (1 + piece) * pairs + the row's pair, as the reduce
+    // expects them ----
+    const int rt = 16 * p.row_tiles;
+    const size_t slot0 = (size_t)p.num_waves + (size_t)(o.chunk + 1) * p.batch * p.pairs_per_seq;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const float l = xor16_sum(l_run[nt]);
+      const int rs = o.r0 + nt * 16 + m16;
+      if (rs >= o.all_rows) continue;
+      const int br = rs / p.rows, r = rs - br * p.rows;
+      const int rg = r / rt, rl = r - rg * rt;
+      const size_t row =
+          (slot0 + (size_t)br * p.pairs_per_seq + o.h * p.num_row_groups + rg) * rt + rl;
+      float* arow = p.ws_acc + row * D;
+#pragma unroll
+      for (int tt = 0; tt < DT; ++tt) *(floatx4*)(arow + 16 * tt + 4 * g4) = acc[nt][tt];
+      if (g4 == 0) {
+        p.ws_ml[row * 2] = m_run[nt];
+        p.ws_ml[row * 2 + 1] = l;
+      }
+    }
+    return;
+  }
+  // ---- normalised rows: those of a sequence's first piece (mostly the only one) go to `out`, the
+  // others' to the workspace, a piece's rows in the order its sequence's have in `out`; the logarithms
+  // of the denominators likewise, those of first pieces ahead ----
+  const size_t seq_rows = (size_t)p.q_len * p.num_q_heads;
+  const size_t to = (size_t)(o.piece.chunk == 0 ? o.b : o.piece.extra) * seq_rows;
+  float* dst = (o.piece.chunk == 0 ? p.out : p.ws_acc) + to * D;
+  float* lse = p.ws_ml + ((o.piece.chunk == 0 ? 0 : (size_t)p.batch * seq_rows) + to);
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    const float l = xor16_sum(l_run[nt]);
+    const int r = o.r0 + nt * 16 + m16;
+    if (r >= p.rows) continue;
+    const int j = r / G, gi = r - j * G;
+    const size_t row = (size_t)j * p.num_q_heads + (size_t)o.h * G + gi;
+    float* orow = dst + row * D;
+    float inv = 1.0f / l;
+    if (o.piece.pieces > 1) {  // a row may see nothing of a piece
+      inv = l > 0.0f ? inv : 0.0f;
+      if (g4 == 0) lse[row] = l > 0.0f ? m_run[nt] + __builtin_amdgcn_logf(l) : -INFINITY;
+    }
+#pragma unroll
+    for (int tt = 0; tt < DT; ++tt) *(floatx4*)(orow + 16 * tt + 4 * g4) = acc[nt][tt] * inv;
+  }
+}
+
+// PREFIX = true is the kernel for a prefix that every sequence of a decode or verification
+// batch shares (the same physical blocks at the head of every block table; Section 1 and
+// Section 5.2.3: prompt prefixes served from the prefix cache).  The query rows of all
+// sequences are stacked, 128 to a workgroup, so a group of the prefix is read and converted
+// once per 128 rows (four sequences of a 4-token verification step with 8 query heads per kv
+// head) instead of once per sequence.  The prefix is cut into p.prefix_chunks pieces to get
+// enough workgroups; a workgroup walks one piece and leaves, per row, an unnormalised partial
+// (max, sum, accumulator) in the workspace, in the slots behind the streaming kernel's, which
+// the reduce merges with the streaming kernel's partials over the rest of each sequence.
+template <int MODE, int D, bool PREFIX, bool CHOICE>
+__global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_kernel(const AttnArgs p) {
+  constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN;  // unquantized cache: the operands are its bytes
+  constexpr bool FP8 = MODE == KVQ_FP8E4M3_BLOCK_HEAD || MODE == KVQ_FP8E4M3_TENSOR;
+  constexpr bool INT4 = MODE == KVQ_INT4_TOKEN_HEAD;  // two codes per byte (head_dim 128)
+  constexpr bool TOKEN_SCALE = MODE == KVQ_INT8_TOKEN_HEAD || INT4;
+  static_assert(!INT4 || D == 128, "int4 codes come with head_dim 128 only");
+  constexpr int NT = 2;
+  constexpr int EB = PLAIN ? 2 : 1;  // bytes per cache element
+  constexpr int RB = INT4 ? D / 2 : D * EB;  // bytes per token row in a tile
+  constexpr int DT = D / 16;       // 16-channel tiles of V / of the output
+  constexpr int KJ = RB / 64;      // 16-byte K pieces per lane and quad
+  constexpr int KS = D / 32;       // matrix-instruction steps over the channels
+  constexpr int NP = RB / 16;      // 16-byte pieces per lane that K (and V) of a group consist of
+  constexpr int WP = NP / kWavesPerGroup;  // and those that a wavefront converts
+  constexpr int kPace = INT4 ? 5 : 2;  // vector instructions behind a matrix instruction
+  // matrix-instruction operand of 8 values: f16 (from codes) or the cache's own bf16
+  using Operand = std::conditional_t<PLAIN, bf16x8, half8>;
+  __shared__ half8 k_ops[2][4][KS][64];    // [half][quad of the sub-block][step][lane]
+  __shared__ half8 v_ops[2][DT][2][64];    // [half][channel tile][tokens 0-7 | 8-15][lane]
+  // [half]: K scale * log2e / sqrt(D), log2 and reciprocal of the V scale of the 64 tokens
+  __shared__ __align__(16) float s_ops[2][3][64];
+
+  const int lane = threadIdx.x & 63;
+  const int wv = threadIdx.x >> 6;
+  const int m16 = lane & 15, g4 = lane >> 4;
+  const int H = p.num_kv_heads, bs = p.block_size, bs_shift = p.bs_shift;
+  Place at;
+  if (!place_rows<PREFIX, kRowsPerWorkgroup, CHOICE>(p, lane, wv, at)) return;
+  const int h = at.h, b = at.b, L = at.L, g0 = at.g0, ng = at.ng;
+
+  const uint8_t* __restrict__ cache = p.cache;
+  const float* __restrict__ scales = p.scales;
+  const int32_t* __restrict__ table = p.block_tables + (size_t)b * p.max_blocks_per_seq;
+  const uint32_t tile_bytes = (uint32_t)bs * RB;
+  const uint32_t block_stride = 2u * (uint32_t)H * tile_bytes;
+  const int sbk = m16 >> 2;  // sub-block this lane reads K from
+  const uint32_t s_block_stride = TOKEN_SCALE ? 2u * H * bs : (MODE == KVQ_FP8E4M3_TENSOR ? 0u : 2u * H);
+  const uint32_t s_kv = TOKEN_SCALE ? (uint32_t)H * bs : (MODE == KVQ_FP8E4M3_TENSOR ? 1u : (uint32_t)H);
+  const int last_sb = ((L - 1) >> 4) << 4;
+
+  // ---- q as the B operand of QK^T, causal lengths, running state ----
+  Operand qb[NT][KS];
+  int nrow[NT];
+  floatx4 acc[NT][DT];
+  float m_run[NT], l_run[NT];
+  load_queries<MODE, D, PREFIX>(p, lane, at, qb, nrow, acc, m_run, l_run);
+  const int n_min = at.n_min;
+
+  // ---- producer side: this wavefront's quarter of a group's codes ----
+  const int first = wv * WP;  // its pieces of K, and of V
+  const uint32_t k_fixed = (uint32_t)h * tile_bytes + 64u * g4 + 16u * (m16 & 3);
+  const uint32_t v_fixed = (uint32_t)(H + h) * tile_bytes + 16u * m16;
+  // Table entries are requested ahead of the codes of the group before, so that waiting for them is not
+  // waiting for those.  (indices past the end repeat the last group)
+  uint32_t entry_k, entry_v;
+  auto positions = [&](int g, uint32_t& tk, uint32_t& tv) {
+    g = min(g, ng - 1);
+    tk = (uint32_t)min((g << 6) + 16 * sbk, last_sb);
+    tv = (uint32_t)min((g << 6) + 16 * g4, last_sb);
+  };
+  auto fetch_entries = [&](int g) {
+    uint32_t tk, tv;
+    positions(g, tk, tv);
+    entry_k = (uint32_t)table[tk >> bs_shift];
+    entry_v = (uint32_t)table[tv >> bs_shift];
+  };
+  uint64_t k_from = 0, v_from = 0;  // byte offsets in the cache
+  uintx4 rk[WP], rv[WP];
+  float sk_next = 0.0f, sv_next = 0.0f;
+  auto locate = [&](int g) {  // whose entries have been fetched
+    uint32_t tk, tv;
+    positions(g, tk, tv);
+    k_from = (uint64_t)entry_k * block_stride + ((tk & (uint32_t)(bs - 1)) * RB + k_fixed);
+    v_from = (uint64_t)entry_v * block_stride + ((tv & (uint32_t)(bs - 1)) * RB + v_fixed);
+    asm volatile("" : "+v"(k_from), "+v"(v_from));  // (here, not where they are used)
+  };
+  auto request_scales = [&](int g) {  // the same; lane = token
+    uint32_t tk, tv;
+    positions(g, tk, tv);
+    const float* from = scales + ((uint64_t)entry_v * s_block_stride + (TOKEN_SCALE ? (uint32_t)(h * bs + m16) + (tv & (uint32_t)(bs - 1)) : (MODE == KVQ_FP8E4M3_TENSOR ? 0u : (uint32_t)h)));
+    sk_next = from[0];
+    sv_next = from[s_kv];
+  };
+  auto request = [&]() {
+#pragma unroll
+    for (int x = 0; x < WP; ++x) {
+      const int pc = first + x;
+      rk[x] = *(const uintx4*)(cache + k_from + (pc / KJ) * (4 * RB) + 256 * (pc % KJ));
+    }
+    // (unquantized: piece 2 t + hf is channel tile t, tokens 8 hf .. 8 hf + 7)
+#pragma unroll
+    for (int x = 0; x < WP; ++x) {
+      const int pc = first + x;
+      rv[x] = *(const uintx4*)(cache + v_from + (PLAIN ? (pc & 1) * (16 * D) + 256 * (pc >> 1) : 256 * pc));
+    }
+  };
+  auto publish_k = [&](int x, int buf) {
+    asm volatile("" : "+v"(rk[x]));  // (converted here, not earlier)
+    const int pc = first + x, u = pc / KJ, at = pc % KJ;
+    if constexpr (PLAIN) {  // bf16 rows are operands as they are; the LDS arrays hold their bits
+      k_ops[buf][u][at][lane] = __builtin_bit_cast(half8, rk[x]);
+    } else if constexpr (INT4) {  // word st of the lane's piece holds the 8 channels of step st
+#pragma unroll
+      for (int st = 0; st < 4; ++st) k_ops[buf][u][st][lane] = cvt_int4(rk[x][st]);
+    } else {
+      k_ops[buf][u][2 * at][lane] = cvt8<MODE>(rk[x][0], rk[x][1]);
+      k_ops[buf][u][2 * at + 1][lane] = cvt8<MODE>(rk[x][2], rk[x][3]);
+    }
+  };
+  auto publish_v = [&](int x, int half) {
+    asm volatile("" : "+v"(rv[x]));
+    const int pc = first + x;
+    if constexpr (PLAIN) {
+      v_ops[half][pc >> 1][pc & 1][lane] = __builtin_bit_cast(half8, rv[x]);
+    } else if constexpr (INT4) {
+#pragma unroll
+      for (int w4 = 0; w4 < 4; ++w4) v_ops[half][2 * pc + (w4 >> 1)][w4 & 1][lane] = cvt_int4(rv[x][w4]);
+    } else {
+      v_ops[half][pc][0][lane] = cvt8<MODE>(rv[x][0], rv[x][1]);
+      v_ops[half][pc][1][lane] = cvt8<MODE>(rv[x][2], rv[x][3]);
+    }
+  };
+  // V bits of tokens past the last position are cleared first: a NaN times 0 is NaN
+  auto clear_missing = [&](int g) {
+    if (!(PLAIN || FP8) || (g << 6) + 64 <= L) return;
+    const int live = L - ((g << 6) + 16 * g4);  // tokens of this lane's sub-block below L
+#pragma unroll
+    for (int x = 0; x < WP; ++x)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (PLAIN) {
+          const int n = live - (8 * ((first + x) & 1) + 2 * e);
+          rv[x][e] &= n >= 2 ? ~0u : n == 1 ? 0xFFFFu : 0u;
+        } else {
+          const int n = min(max(live - 4 * e, 0), 4);
+          rv[x][e] &= n == 4 ? ~0u : (1u << (8 * n)) - 1u;
+        }
+      }
+  };
+  auto publish_scales = [&](int j, float sk, float sv) {  // of group g0 + j
+    const int g = min(g0 + j, ng - 1), buf = j & 1;
+    float skp = sk * p.scale_log2;
+    float lsv = __builtin_amdgcn_logf(fmaxf(sv, kMinVScale));
+    float rsv = __builtin_amdgcn_exp2f(-lsv);
+    if (TOKEN_SCALE && (g << 6) + lane >= L) {
+      skp = 0.0f;  // a slot that was never written: its scales are not data
+      lsv = 0.0f;
+      rsv = 0.0f;
+    }
+    s_ops[buf][0][lane] = skp;
+    s_ops[buf][1][lane] = lsv;
+    s_ops[buf][2][lane] = rsv;
+  };
+
+  // ---- consumer side ----
+  floatx4 S[NT][4];
+  Operand pb[NT][2 * EB];  // unquantized: a probability goes in as two bf16 terms (hi, lo)
+  auto load_op = [&](const half8& bits) {
+    if constexpr (PLAIN) return __builtin_bit_cast(bf16x8, bits);
+    else return bits;
+  };
+  auto mma = [&](const Operand& a, const Operand& b, const floatx4& c) {
+    if constexpr (PLAIN) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+  };
+  float mx[NT];
+  constexpr float skp = 0.0f, lsv = 0.0f;  // (the maxima of formats without token scales are those of S)
+  Operand op[2][4];  // operands of two chunks of eight matrix instructions
+  floatx4 k4[2] = {}, l4[2] = {};
+  constexpr int HS = KS / 2, QC = 2 * HS, PC = DT / 2;  // chunks of QK^T (two quads, two steps) and of P.V (two tiles)
+  auto read_k = [&](int c, int buf) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) op[c & 1][x] = load_op(k_ops[buf][2 * (c / HS) + (x & 1)][2 * (c % HS) + (x >> 1)][lane]);
+  };
+  auto read_v = [&](int c, int half) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) op[(QC + c) & 1][x] = load_op(v_ops[half][2 * c + (x & 1)][x >> 1][lane]);
+  };
+  auto read_scales = [&](int pair, int buf) {
+    const floatx4* sc = (const floatx4*)&s_ops[buf][0][16 * g4];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      k4[x] = sc[2 * pair + x];
+      l4[x] = sc[kScalePitch + 2 * pair + x];
+    }
+  };
+  auto mm_k = [&](int c) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const int u = 2 * (c / HS) + (x & 1);
+        S[nt][u] = mma(op[c & 1][x], qb[nt][2 * (c % HS) + (x >> 1)], S[nt][u]);
+      }
+  };
+  auto mm_v = [&](int c) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        floatx4& d = acc[nt][2 * c + (x & 1)];
+        d = mma(op[(QC + c) & 1][x], pb[nt][x >> 1], d);
+        if constexpr (PLAIN) d = mma(op[(QC + c) & 1][x], pb[nt][2 + (x >> 1)], d);
+      }
+  };
+  // N matrix instructions, with READS LDS reads dealt out between them and VALU vector ones behind each
+  auto pace = [&](auto N, auto READS, auto VALU) {
+    static_for<decltype(N)::value>([&](auto X) {
+      constexpr int x = decltype(X)::value, n = decltype(N)::value, r = decltype(READS)::value;
+      __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+      constexpr int now = (x + 1) * r / n - x * r / n;
+      if constexpr (now > 0) __builtin_amdgcn_sched_group_barrier(0x100, now, 0);
+      if constexpr (decltype(VALU)::value > 0) __builtin_amdgcn_sched_group_barrier(0x2, decltype(VALU)::value, 0);
+      __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  using Whole = SoftmaxForm<MODE, false>;
+  // TAIL: some row's causal length ends inside the group: positions past it are masked, and the
+  // maxima taken again.
+  auto vector_phase = [&](auto TAILC, int g, int sbuf) {
+    constexpr bool TAIL = decltype(TAILC)::value;
+    using F = SoftmaxForm<MODE, TAIL>;
+    const floatx4* sc = (const floatx4*)&s_ops[sbuf][0][16 * g4];
+    floatx4 r4[4] = {};
+    if constexpr (F::TOKEN_SCALE) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) r4[u] = sc[2 * kScalePitch + u];
+    }
+    float skp = fabsf(p.scale_log2), lsv = 0.0f, rsv = 1.0f;
+    if constexpr (FP8) {
+      skp = s_ops[sbuf][0][lane];
+      lsv = s_ops[sbuf][1][lane];
+      rsv = s_ops[sbuf][2][lane];
+    }
+    if constexpr (TAIL) {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        mx[nt] = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            float z = S[nt][u][i];
+            if constexpr (!F::kLogits) z = __builtin_fmaf(z, skp, lsv);
+            z = (g << 6) + 16 * g4 + 4 * u + i < nrow[nt] ? z : -INFINITY;
+            S[nt][u][i] = z;
+            mx[nt] = fmaxf(mx[nt], z);
+          }
+      }
+    } else if constexpr (FP8) {
+      if (__any(skp < 0.0f)) {  // (a negative softmax scale, or static scale)
+        const float sign = skp < 0.0f ? -1.0f : 1.0f;
+        skp *= sign;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          mx[nt] = -INFINITY;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            S[nt][u] *= sign;
+            softmax_logits<MODE, NT, TAIL>(S, u, k4[0], l4[0], skp, lsv, 0, nrow, mx);
+          }
+        }
+      }
+    }
+    float alpha[NT], msub[NT];
+    softmax_maxima<MODE, NT, TAIL>(mx, skp, lsv, m_run, alpha, msub);
+    softmax_probabilities<MODE, NT, TAIL, true>(S, sc, r4, skp, rsv, alpha, msub, l_run, pb);
+    softmax_rescale<NT, DT>(alpha, acc);
+  };
+
+  // The matrix instructions: QK^T of group g0 + j from half j % 2, the logits of the first tokens and their
+  // maxima (unmasked) worked out while the last ones' are contracted; and P.V, the next group's codes
+  // converted into the other half under it.
+  auto contract_k = [&](int half) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      mx[nt] = -INFINITY;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) S[nt][u] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    read_k(0, half);
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<QC>([&](auto C) {
+      constexpr int c = decltype(C)::value;
+      constexpr bool sc = Whole::kLogits && (c + 1) % HS == 0;
+      mm_k(c);
+      if constexpr (c + 1 < QC) read_k(c + 1, half);
+      if constexpr (c == HS) {
+        softmax_logits<MODE, NT, false>(S, 0, k4[0], l4[0], skp, lsv, 0, nrow, mx);
+        softmax_logits<MODE, NT, false>(S, 1, k4[1], l4[1], skp, lsv, 0, nrow, mx);
+      }
+      if constexpr (sc) read_scales(c / HS, half);
+      pace(std::integral_constant<int, 8>{}, std::integral_constant<int, (c + 1 < QC ? 4 : 0) + (sc ? 4 : 0)>{}, std::integral_constant<int, c == HS ? kPace : 0>{});
+    });
+    softmax_logits<MODE, NT, false>(S, 2, k4[0], l4[0], skp, lsv, 0, nrow, mx);
+    softmax_logits<MODE, NT, false>(S, 3, k4[1], l4[1], skp, lsv, 0, nrow, mx);
+  };
+  constexpr int PIECES = 2 * WP;
+  auto publish = [&](int x, int half) {
+    if (x < WP) publish_k(x, half);
+    else publish_v(x - WP, half);
+  };
+  auto contract_v = [&](int half) {
+    static_for<PC>([&](auto C) {
+      constexpr int c = decltype(C)::value;
+      mm_v(c);
+      if constexpr (c + 1 < PC) read_v(c + 1, half);
+#pragma unroll
+      for (int x = c * PIECES / PC; x < (c + 1) * PIECES / PC; ++x) publish(x, half ^ 1);
+      pace(std::integral_constant<int, PLAIN ? 16 : 8>{}, std::integral_constant<int, c + 1 < PC ? 4 : 0>{}, std::integral_constant<int, PLAIN ? 0 : kPace>{});
+    });
+  };
+  // ---- the walk: group g is consumed from half g % 2 while group g + 1 is converted into the
+  // other half and group g + 2 is requested ----
+  const bool live = __builtin_amdgcn_readfirstlane((int)at.wave_live) != 0;
+  const int n = ng - g0;
+  if (n > 0) {  // (a chunk's first rows see fewer groups than there may be pieces)
+    const bool scale_wave = !PLAIN && wv == 0;
+    fetch_entries(g0);
+    locate(g0);
+    request();
+    if (scale_wave) {
+      request_scales(g0);
+      publish_scales(0, sk_next, sv_next);
+    }
+    clear_missing(g0);
+#pragma unroll
+    for (int x = 0; x < PIECES; ++x) publish(x, 0);
+    fetch_entries(g0 + 1);
+    locate(g0 + 1);
+    if (scale_wave) request_scales(g0 + 1);
+    fetch_entries(g0 + 2);
+    request();
+    __syncthreads();
+    auto prepare = [&](int i) {  // scales of group i + 1 published, of i + 2 requested, its codes located
+      if (scale_wave) {
+        publish_scales(i + 1, sk_next, sv_next);
+        request_scales(g0 + i + 2);
+      }
+      locate(g0 + i + 2);
+    };
+    auto advance = [&](int i) {
+      fetch_entries(g0 + i + 3);
+      request();
+      __syncthreads();
+    };
+    if (live) {
+      for (int i = 0; i < n; ++i) {
+        const int g = g0 + i, half = i & 1;
+        contract_k(half);
+        prepare(i);
+        if ((g << 6) + 64 > n_min) vector_phase(std::true_type{}, g, half);
+        else vector_phase(std::false_type{}, g, half);
+        read_v(0, half);
+        clear_missing(min(g + 1, ng - 1));
+        contract_v(half);
+        advance(i);
+      }
+    } else {
+      for (int i = 0; i < n; ++i) {
+        prepare(i);
+        clear_missing(min(g0 + i + 1, ng - 1));
+#pragma unroll
+        for (int x = 0; x < PIECES; ++x) publish(x, ~i & 1);
+        advance(i);
+      }
+    }
+  }
+
+  store_rows<D, PREFIX>(p, lane, at, acc, m_run, l_run);
+}
+
+// The same at head_dim 64 for the int8 and the unquantized cache, a phase after the other: in 164 registers,
+// so that three wavefronts run on a SIMD, which is worth more there than logits and conversions under the
+// matrix instructions (175 and 183 registers; 3 x 1000 tokens over 3000: int8 117 us here and 122 above,
+// bf16 129 and 133; the e4m3 formats fit either way and take 104 us above, 106 here).
+template <int MODE, bool PREFIX>
+__global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows64_kernel(const AttnArgs p) {
+  constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN;  // unquantized cache: the operands are its bytes
+  static_assert(PLAIN || MODE == KVQ_INT8_TOKEN_HEAD, "the other formats take attn_rows_kernel");
+  constexpr int NT = 2, D = 64;
+  constexpr int EB = PLAIN ? 2 : 1;  // bytes per cache element
+  constexpr int RB = D * EB;         // bytes per token row in a tile
+  constexpr int DT = D / 16;       // 16-channel tiles of V / of the output
+  constexpr int KJ = RB / 64;      // 16-byte K pieces per lane and quad
+  constexpr int KS = D / 32;       // matrix-instruction steps over the channels
+  constexpr int VT = DT / kWavesPerGroup;  // V tiles a wavefront converts
+  constexpr int VP = VT * EB;      // 16-byte V pieces per lane
+  // matrix-instruction operand of 8 values: f16 (from codes) or the cache's own bf16
+  using Operand = std::conditional_t<PLAIN, bf16x8, half8>;
+  __shared__ half8 k_ops[2][4][KS][64];    // [half][quad of the sub-block][step][lane]
+  __shared__ half8 v_ops[2][DT][2][64];    // [half][channel tile][tokens 0-7 | 8-15][lane]
+  // [half]: K scale * log2e / sqrt(D), log2 and reciprocal of the V scale of the 64 tokens
+  __shared__ __align__(16) float s_ops[2][3][64];
+
+  const int lane = threadIdx.x & 63;
+  const int wv = threadIdx.x >> 6;
+  const int m16 = lane & 15, g4 = lane >> 4;
+  const int H = p.num_kv_heads, bs = p.block_size, bs_shift = p.bs_shift;
+  Place at;
+  if (!place_rows<PREFIX, kRowsPerWorkgroup, false>(p, lane, wv, at)) return;
+  const int h = at.h, b = at.b, L = at.L, g0 = at.g0, ng = at.ng;
+  const bool wave_live = at.wave_live;
+
+  const uint8_t* __restrict__ cache = p.cache;
+  const float* __restrict__ scales = p.scales;
+  const int32_t* __restrict__ table = p.block_tables + (size_t)b * p.max_blocks_per_seq;
+  const uint32_t tile_bytes = (uint32_t)bs * RB;
+  const uint32_t block_stride = 2u * (uint32_t)H * tile_bytes;
+  const int sbk = m16 >> 2;  // sub-block this lane reads K from
+  const uint32_t k_lane = 64u * g4 + 16u * (m16 & 3) + (uint32_t)wv * (4 * RB);  // quad wv
+  const uint32_t v_lane = (uint32_t)H * tile_bytes + 16u * m16 + 256u * (wv * VT);
+  const uint32_t s_block_stride = 2u * H * bs;
+  const uint32_t s_kv = (uint32_t)H * bs;
+  const int last_sb = ((L - 1) >> 4) << 4;
+
+  // ---- q as the B operand of QK^T, causal lengths, running state ----
+  Operand qb[NT][KS];
+  int nrow[NT];
+  floatx4 acc[NT][DT];
+  float m_run[NT], l_run[NT];
+  load_queries<MODE, D, PREFIX>(p, lane, at, qb, nrow, acc, m_run, l_run);
+  const int n_min = at.n_min;
 
   // ---- producer side: this wavefront's quarter of a group's codes ----
   // (a group's table entries come with the lane's offsets inside their blocks: the position that
@@ -279,7 +759,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
     for (int x = 0; x < VP; ++x)
       rv[x] = *(const uintx4*)(vbase + (PLAIN ? (x & 1) * (16 * D) + 256 * (x >> 1) : 256 * x));
     if (!PLAIN && wv == 0) {  // the scales of the group's 64 tokens, lane = token
-      const uint32_t s_lane = TOKEN_SCALE ? (uint32_t)(h * bs + m16) + e.v_at : (MODE == KVQ_FP8E4M3_TENSOR ? 0u : (uint32_t)h);
+      const uint32_t s_lane = (uint32_t)(h * bs + m16) + e.v_at;
       const float* sp = scales + ((uint64_t)e.v * s_block_stride + s_lane);
       sk_next = sp[0];
       sv_next = sp[s_kv];
@@ -304,37 +784,15 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
       }
       return;
     }
-    if constexpr (INT4) {
-      // K: word st of the lane's piece holds the 8 channels of step st; V: a piece holds two
-      // channel tiles, words 0, 1 the first tile's tokens 0-7 and 8-15, words 2, 3 the second's
 #pragma unroll
-      for (int st = 0; st < 4; ++st) k_ops[half][wv][st][lane] = cvt_int4(rk[0][st]);
+    for (int j = 0; j < KJ; ++j) {
+      k_ops[half][wv][2 * j][lane] = cvt8<MODE>(rk[j][0], rk[j][1]);
+      k_ops[half][wv][2 * j + 1][lane] = cvt8<MODE>(rk[j][2], rk[j][3]);
+    }
 #pragma unroll
-      for (int x = 0; x < VP; ++x)
-#pragma unroll
-        for (int w4 = 0; w4 < 4; ++w4)
-          v_ops[half][2 * (wv * VP + x) + (w4 >> 1)][w4 & 1][lane] = cvt_int4(rv[x][w4]);
-    } else {
-#pragma unroll
-      for (int j = 0; j < KJ; ++j) {
-        k_ops[half][wv][2 * j][lane] = cvt8<MODE>(rk[j][0], rk[j][1]);
-        k_ops[half][wv][2 * j + 1][lane] = cvt8<MODE>(rk[j][2], rk[j][3]);
-      }
-      if (FP8 && (g << 6) + 64 > L) {  // V bytes of missing tokens: an e4m3 NaN times 0 is NaN
-        const int live = L - ((g << 6) + 16 * g4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int n = min(max(live - 4 * e, 0), 4);
-          const uint32_t keep = n == 4 ? ~0u : (1u << (8 * n)) - 1u;
-#pragma unroll
-          for (int t = 0; t < VT; ++t) rv[t][e] &= keep;
-        }
-      }
-#pragma unroll
-      for (int t = 0; t < VT; ++t) {
-        v_ops[half][wv * VT + t][0][lane] = cvt8<MODE>(rv[t][0], rv[t][1]);
-        v_ops[half][wv * VT + t][1][lane] = cvt8<MODE>(rv[t][2], rv[t][3]);
-      }
+    for (int t = 0; t < VT; ++t) {
+      v_ops[half][wv * VT + t][0][lane] = cvt8<MODE>(rv[t][0], rv[t][1]);
+      v_ops[half][wv * VT + t][1][lane] = cvt8<MODE>(rv[t][2], rv[t][3]);
     }
     // The scales go the same way: held in registers from the load to the softmax two iterations
     // later, they would have to be copied at the end of the iteration that requested them, and
@@ -343,7 +801,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
       float skp = sk_next * p.scale_log2;
       float lsv = __builtin_amdgcn_logf(fmaxf(sv_next, kMinVScale));
       float rsv = __builtin_amdgcn_exp2f(-lsv);
-      if (TOKEN_SCALE && (g << 6) + lane >= L) {
+      if ((g << 6) + lane >= L) {
         skp = 0.0f;  // a slot that was never written: its scales are not data
         lsv = 0.0f;
         rsv = 0.0f;
@@ -396,13 +854,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
   auto softmax_impl = [&](auto TAILC, int g, int half) {
     constexpr bool TAIL = decltype(TAILC)::value;
     const int pos0 = g << 6;
-    float skp = fabsf(p.scale_log2), lsv = 0.0f, rsv = 1.0f;
-    if constexpr (FP8) {
-      skp = s_ops[half][0][lane];
-      lsv = s_ops[half][1][lane];
-      rsv = s_ops[half][2][lane];
-    }
-    online_softmax<MODE, NT, DT, TAIL>(S, (const floatx4*)&s_ops[half][0][16 * g4], skp, lsv, rsv,
+    online_softmax<MODE, NT, DT, TAIL>(S, (const floatx4*)&s_ops[half][0][16 * g4], fabsf(p.scale_log2), 0.0f, 1.0f,
                                        pos0 + 16 * g4, nrow, m_run, l_run, acc, pb);
   };
   auto pv = [&](int half) {
@@ -465,54 +917,497 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_prefill_kernel(co
     fetch_entries(min(g + 3, ng - 1), e_after);
     __syncthreads();
   }
+  store_rows<D, PREFIX>(p, lane, at, acc, m_run, l_run);
+}
 
-  if constexpr (PREFIX) {
-    // ---- partials: slot = wavefronts + (1 + piece) * pairs + the row's pair, as the reduce
-    // expects them ----
-    const int rt = 16 * p.row_tiles;
-    const size_t slot0 = (size_t)p.num_waves + (size_t)(chunk + 1) * p.batch * p.pairs_per_seq;
+// The kernel for more than kRowsPerWorkgroup rows at head_dim 128: eight wavefronts own 256 rows, one such
+// workgroup runs on a compute unit, two wavefronts on a SIMD.  The matrix unit and the vector unit of a SIMD
+// work side by side only for different wavefronts or for independent instructions of one, and two
+// workgroups of the kernel above on a compute unit drift into doing the same thing at the same time: its
+// two wavefronts took 4900 cycles for a group each (int8), of which the matrix unit was busy 2050.  Here
+// the two wavefronts of a SIMD belong to two teams (0-3 and 4-7), and barriers hold them half a group
+// apart, one in its matrix phase while the other is in its vector phase:
+//   matrix phase: QK^T of the next group and P.V of this one; under the matrix instructions the wavefront's
+//     share (an eighth, half of what it is above) of the codes is converted and published, and the
+//     logits of the first tokens and their maxima are worked out while the last ones' are contracted.  One
+//     code path, without a branch: the compiler moves what two branches share ahead of both, which put
+//     all conversions and the wait for their loads in front of the first matrix instruction;
+//   vector phase: maxima across lanes, probabilities, rescaling, masks, the addresses of the next loads.
+// K runs a phase ahead of V, so that a phase's first operands can be read before the barrier that opens it:
+// K is held in three buffers, V in two; 83 KB of operands and scales, 64 KB of table entries.  (V phases at
+// the higher priority: 318 -> 315 us int8, 295 -> 290 fp8; the matrix phases at the higher: 332 and 300.)
+// 8 x 512 tokens over 4608, 32 / 8 heads: int8 347 -> 315 us, fp8 312 -> 290, bf16 410 -> 367, int4 342 ->
+// 318.  What bounds it: a matrix phase takes 1700 to 2200 cycles beside a vector phase, 1024 of them matrix
+// instructions; v_exp_f32 and matrix instructions of two wavefronts barely overlap (matched streams of
+// 125 us each take 176 together, multiply-adds 133).  head_dim 64 does better on the kernel above,
+// which runs three wavefronts per SIMD there (int8 230 us against 251).
+template <int MODE>
+__global__ __launch_bounds__(512, 2) void attn_wide_kernel(const AttnArgs p) {
+  constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN;  // unquantized cache: the operands are its bytes
+  constexpr bool FP8 = MODE == KVQ_FP8E4M3_BLOCK_HEAD || MODE == KVQ_FP8E4M3_TENSOR;
+  constexpr bool INT4 = MODE == KVQ_INT4_TOKEN_HEAD;  // two codes per byte
+  constexpr bool TOKEN_SCALE = MODE == KVQ_INT8_TOKEN_HEAD || INT4;
+  constexpr int W = 8, D = 128, NT = 2;
+  constexpr int EB = PLAIN ? 2 : 1;  // bytes per cache element
+  constexpr int RB = INT4 ? D / 2 : D * EB;  // bytes per token row in a tile
+  constexpr int DT = D / 16;       // 16-channel tiles of V / of the output
+  constexpr int KJ = RB / 64;      // 16-byte K pieces per lane and quad
+  constexpr int KS = D / 32;       // matrix-instruction steps over the channels
+  // 16-byte pieces per lane that K (and V) of a group consist of, and how many of them a wavefront
+  // converts (BOTH: of K and of V; else team 0 has one of K each, team 1 one of V)
+  constexpr int NP = RB / 16;
+  constexpr bool BOTH = NP >= W;
+  constexpr int WP = BOTH ? NP / W : 1;
+  constexpr int kPace = INT4 ? 5 : 2;  // vector instructions behind a matrix instruction
+  // matrix-instruction operand of 8 values: f16 (from codes) or the cache's own bf16
+  using Operand = std::conditional_t<PLAIN, bf16x8, half8>;
+  __shared__ half8 k_ops[3][4][KS][64];  // [buffer][quad of the sub-block][step][lane]
+  __shared__ half8 v_ops[2][DT][2][64];  // [half][channel tile][tokens 0-7 | 8-15][lane]
+  // [buffer]: K scale * log2e / sqrt(D), log2 and reciprocal of the V scale of the 64 tokens
+  __shared__ __align__(16) float s_ops[3][3][64];
+  __shared__ int32_t sh_table[kWideTable];  // block-table entries of the walk
+
+  const int lane = threadIdx.x & 63;
+  const int wv = threadIdx.x >> 6;
+  const int m16 = lane & 15, g4 = lane >> 4;
+  const int H = p.num_kv_heads, bs = p.block_size, bs_shift = p.bs_shift;
+  Place at;
+  if (!place_rows<false, kWideRows, true>(p, lane, wv, at)) return;
+  const int h = at.h, b = at.b, L = at.L, g0 = at.g0, ng = at.ng;
+
+  const uint8_t* __restrict__ cache = p.cache;
+  const float* __restrict__ scales = p.scales;
+  const int32_t* __restrict__ table = p.block_tables + (size_t)b * p.max_blocks_per_seq;
+  const uint32_t tile_bytes = (uint32_t)bs * RB;
+  const uint32_t block_stride = 2u * (uint32_t)H * tile_bytes;
+  const int sbk = m16 >> 2;  // sub-block this lane reads K from
+  const uint32_t s_block_stride = TOKEN_SCALE ? 2u * H * bs : (MODE == KVQ_FP8E4M3_TENSOR ? 0u : 2u * H);
+  const uint32_t s_kv = TOKEN_SCALE ? (uint32_t)H * bs : (MODE == KVQ_FP8E4M3_TENSOR ? 1u : (uint32_t)H);
+  const int last_sb = ((L - 1) >> 4) << 4;
+
+  // ---- q as the B operand of QK^T, causal lengths, running state ----
+  Operand qb[NT][KS];
+  int nrow[NT];
+  floatx4 acc[NT][DT];
+  float m_run[NT], l_run[NT];
+  load_queries<MODE, D, false>(p, lane, at, qb, nrow, acc, m_run, l_run);
+  const int n_min = at.n_min;
+
+  // ---- producer side: this wavefront's share of a group's codes.  K runs a group ahead of V ----
+  const bool has_k = BOTH || wv < W / 2, has_v = BOTH || wv >= W / 2;
+  const int k_first = wv * WP, v_first = BOTH ? wv * WP : wv - W / 2;
+  const uint32_t k_fixed = (uint32_t)h * tile_bytes + 64u * g4 + 16u * (m16 & 3);
+  const uint32_t v_fixed = (uint32_t)(H + h) * tile_bytes + 16u * m16;
+  const int blk0 = (g0 << 6) >> bs_shift;
+  // (the table entries of the walk come from LDS: as loads they would have to be waited for, and every
+  // load in flight behind them, before the addresses they give can be worked out)
+  auto entry = [&](uint32_t pos) { return (uint64_t)(uint32_t)sh_table[min((int)(pos >> bs_shift) - blk0, kWideTable - 1)]; };
+  uintx4 rk[WP], rv[WP];
+  float sk_next = 0.0f, sv_next = 0.0f;
+  uint64_t k_from = 0, v_from = 0;  // byte offsets in the cache
+  // K of group g0 + jk, V of group g0 + jv: where this lane's pieces lie
+  // (indices past the end repeat the last group)
+  auto locate = [&](int jk, int jv) {
+    const int gk = min(g0 + jk, ng - 1), gv = min(g0 + jv, ng - 1);
+    const uint32_t tk = (uint32_t)min((gk << 6) + 16 * sbk, last_sb), tv = (uint32_t)min((gv << 6) + 16 * g4, last_sb);
+    k_from = entry(tk) * block_stride + ((tk & (uint32_t)(bs - 1)) * RB + k_fixed);
+    v_from = entry(tv) * block_stride + ((tv & (uint32_t)(bs - 1)) * RB + v_fixed);
+    asm volatile("" : "+v"(k_from), "+v"(v_from));  // (here, not where they are used)
+  };
+  auto request_scales_at = [&](uint64_t block, uint32_t t) {
+    const float* from = scales + (block * s_block_stride + (TOKEN_SCALE ? (uint32_t)(h * bs + m16) + (t & (uint32_t)(bs - 1)) : (MODE == KVQ_FP8E4M3_TENSOR ? 0u : (uint32_t)h)));
+    sk_next = from[0];  // lane = token
+    sv_next = from[s_kv];
+  };
+  auto request_scales = [&](int j) {
+    const uint32_t t = (uint32_t)min((min(g0 + j, ng - 1) << 6) + 16 * g4, last_sb);
+    request_scales_at(entry(t), t);
+  };
+  auto request_k = [&]() {
+    if (has_k) {
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const float l = xor16_sum(l_run[nt]);
-      const int rs = r0 + nt * 16 + m16;
-      if (rs >= all_rows) continue;
-      const int br = rs / p.rows, r = rs - br * p.rows;
-      const int rg = r / rt, rl = r - rg * rt;
-      const size_t row =
-          (slot0 + (size_t)br * p.pairs_per_seq + h * p.num_row_groups + rg) * rt + rl;
-      float* arow = p.ws_acc + row * D;
-#pragma unroll
-      for (int tt = 0; tt < DT; ++tt) *(floatx4*)(arow + 16 * tt + 4 * g4) = acc[nt][tt];
-      if (g4 == 0) {
-        p.ws_ml[row * 2] = m_run[nt];
-        p.ws_ml[row * 2 + 1] = l;
+      for (int x = 0; x < WP; ++x) {
+        const int pc = k_first + x;
+        rk[x] = *(const uintx4*)(cache + k_from + (pc / KJ) * (4 * RB) + 256 * (pc % KJ));
       }
     }
-    return;
-  }
-  // ---- normalised rows: those of a sequence's first piece (mostly the only one) go to `out`, the
-  // others' to the workspace, a piece's rows in the order its sequence's have in `out`; the logarithms
-  // of the denominators likewise, those of first pieces ahead ----
-  const size_t seq_rows = (size_t)p.q_len * p.num_q_heads;
-  const size_t to = (size_t)(piece.chunk == 0 ? b : piece.extra) * seq_rows;
-  float* dst = (piece.chunk == 0 ? p.out : p.ws_acc) + to * D;
-  float* lse = p.ws_ml + ((piece.chunk == 0 ? 0 : (size_t)p.batch * seq_rows) + to);
+  };
+  auto request_v = [&]() {
+    // (unquantized: piece 2 t + hf is channel tile t, tokens 8 hf .. 8 hf + 7)
+    if (has_v) {
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const float l = xor16_sum(l_run[nt]);
-    const int r = r0 + nt * 16 + m16;
-    if (r >= p.rows) continue;
-    const int j = r / G, gi = r - j * G;
-    const size_t row = (size_t)j * p.num_q_heads + (size_t)h * G + gi;
-    float* orow = dst + row * D;
-    float inv = 1.0f / l;
-    if (piece.pieces > 1) {  // a row may see nothing of a piece
-      inv = l > 0.0f ? inv : 0.0f;
-      if (g4 == 0) lse[row] = l > 0.0f ? m_run[nt] + __builtin_amdgcn_logf(l) : -INFINITY;
+      for (int x = 0; x < WP; ++x) {
+        const int pc = v_first + x;
+        rv[x] = *(const uintx4*)(cache + v_from + (PLAIN ? (pc & 1) * (16 * D) + 256 * (pc >> 1) : 256 * pc));
+      }
+    }
+  };
+  auto request = [&]() {
+    request_k();
+    request_v();
+  };
+  auto publish_k = [&](uintx4& codes, int x, int buf) {
+    if (!has_k) return;
+    asm volatile("" : "+v"(codes));  // (converted here, not earlier)
+    const int pc = k_first + x, u = pc / KJ, at = pc % KJ;
+    if constexpr (PLAIN) {  // bf16 rows are operands as they are; the LDS arrays hold their bits
+      k_ops[buf][u][at][lane] = __builtin_bit_cast(half8, codes);
+    } else if constexpr (INT4) {  // word st of the lane's piece holds the 8 channels of step st
+#pragma unroll
+      for (int st = 0; st < 4; ++st) k_ops[buf][u][st][lane] = cvt_int4(codes[st]);
+    } else {
+      k_ops[buf][u][2 * at][lane] = cvt8<MODE>(codes[0], codes[1]);
+      k_ops[buf][u][2 * at + 1][lane] = cvt8<MODE>(codes[2], codes[3]);
+    }
+  };
+  auto publish_v = [&](int x, int half) {
+    if (!has_v) return;
+    asm volatile("" : "+v"(rv[x]));
+    const int pc = v_first + x;
+    if constexpr (PLAIN) {
+      v_ops[half][pc >> 1][pc & 1][lane] = __builtin_bit_cast(half8, rv[x]);
+    } else if constexpr (INT4) {
+#pragma unroll
+      for (int w4 = 0; w4 < 4; ++w4) v_ops[half][2 * pc + (w4 >> 1)][w4 & 1][lane] = cvt_int4(rv[x][w4]);
+    } else {
+      v_ops[half][pc][0][lane] = cvt8<MODE>(rv[x][0], rv[x][1]);
+      v_ops[half][pc][1][lane] = cvt8<MODE>(rv[x][2], rv[x][3]);
+    }
+  };
+  // V bits of tokens past the last position are cleared first: a NaN times 0 is NaN
+  auto clear_missing = [&](int g) {
+    if (!(PLAIN || FP8) || (g << 6) + 64 <= L) return;
+    const int live = L - ((g << 6) + 16 * g4);  // tokens of this lane's sub-block below L
+#pragma unroll
+    for (int x = 0; x < WP; ++x)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (PLAIN) {
+          const int n = live - (8 * ((v_first + x) & 1) + 2 * e);
+          rv[x][e] &= n >= 2 ? ~0u : n == 1 ? 0xFFFFu : 0u;
+        } else {
+          const int n = min(max(live - 4 * e, 0), 4);
+          rv[x][e] &= n == 4 ? ~0u : (1u << (8 * n)) - 1u;
+        }
+      }
+  };
+  auto publish_scales = [&](int j, float sk, float sv) {  // of group g0 + j
+    const int g = min(g0 + j, ng - 1), buf = j % 3;
+    float skp = sk * p.scale_log2;
+    float lsv = __builtin_amdgcn_logf(fmaxf(sv, kMinVScale));
+    float rsv = __builtin_amdgcn_exp2f(-lsv);
+    if (TOKEN_SCALE && (g << 6) + lane >= L) {
+      skp = 0.0f;  // a slot that was never written: its scales are not data
+      lsv = 0.0f;
+      rsv = 0.0f;
+    }
+    s_ops[buf][0][lane] = skp;
+    s_ops[buf][1][lane] = lsv;
+    s_ops[buf][2][lane] = rsv;
+  };
+
+  // ---- consumer side ----
+  floatx4 S[NT][4];
+  Operand pb[NT][2 * EB];  // unquantized: a probability goes in as two bf16 terms (hi, lo)
+  auto load_op = [&](const half8& bits) {
+    if constexpr (PLAIN) return __builtin_bit_cast(bf16x8, bits);
+    else return bits;
+  };
+  auto mma = [&](const Operand& a, const Operand& b, const floatx4& c) {
+    if constexpr (PLAIN) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+  };
+  float mx[NT];
+  constexpr float skp = 0.0f, lsv = 0.0f;  // (the maxima of formats without token scales are those of S)
+  Operand op[2][4];  // operands of two chunks of eight matrix instructions
+  floatx4 k4[2] = {}, l4[2] = {};
+  constexpr int HS = KS / 2, QC = 2 * HS, PC = DT / 2;  // chunks of QK^T (two quads, two steps) and of P.V (two tiles)
+  auto read_k = [&](int c, int buf) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) op[c & 1][x] = load_op(k_ops[buf][2 * (c / HS) + (x & 1)][2 * (c % HS) + (x >> 1)][lane]);
+  };
+  auto read_v = [&](int c, int half) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) op[(QC + c) & 1][x] = load_op(v_ops[half][2 * c + (x & 1)][x >> 1][lane]);
+  };
+  auto read_scales = [&](int pair, int buf) {
+    const floatx4* sc = (const floatx4*)&s_ops[buf][0][16 * g4];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      k4[x] = sc[2 * pair + x];
+      l4[x] = sc[kScalePitch + 2 * pair + x];
+    }
+  };
+  auto mm_k = [&](int c) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const int u = 2 * (c / HS) + (x & 1);
+        S[nt][u] = mma(op[c & 1][x], qb[nt][2 * (c % HS) + (x >> 1)], S[nt][u]);
+      }
+  };
+  auto mm_v = [&](int c) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        floatx4& d = acc[nt][2 * c + (x & 1)];
+        d = mma(op[(QC + c) & 1][x], pb[nt][x >> 1], d);
+        if constexpr (PLAIN) d = mma(op[(QC + c) & 1][x], pb[nt][2 + (x >> 1)], d);
+      }
+  };
+  // N matrix instructions, with READS LDS reads dealt out between them and VALU vector ones behind each
+  auto pace = [&](auto N, auto READS, auto VALU) {
+    static_for<decltype(N)::value>([&](auto X) {
+      constexpr int x = decltype(X)::value, n = decltype(N)::value, r = decltype(READS)::value;
+      __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+      constexpr int now = (x + 1) * r / n - x * r / n;
+      if constexpr (now > 0) __builtin_amdgcn_sched_group_barrier(0x100, now, 0);
+      if constexpr (decltype(VALU)::value > 0) __builtin_amdgcn_sched_group_barrier(0x2, decltype(VALU)::value, 0);
+      __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  using Whole = SoftmaxForm<MODE, false>;
+  // The matrix phase: QK^T of group g0 + j (its first operands are already in op[0]), P.V of the group
+  // before.  Under the matrix instructions: this wavefront's share of the next K and V is converted, and
+  // the logits and their maxima are worked out (unmasked).
+  auto matrix_phase = [&](auto PVC, int j, int kbuf, int next_kbuf) {
+    constexpr bool PV = decltype(PVC)::value;
+    const int vhalf = (j + 1) & 1;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      mx[nt] = -INFINITY;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) S[nt][u] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<QC>([&](auto C) {
+      constexpr int c = decltype(C)::value;
+      constexpr bool sc = Whole::kLogits && (c + 1) % HS == 0;
+      mm_k(c);
+      if constexpr (c + 1 < QC) read_k(c + 1, kbuf);
+      else if constexpr (PV) read_v(0, vhalf);
+      if constexpr (c == HS) {
+        softmax_logits<MODE, NT, false>(S, 0, k4[0], l4[0], skp, lsv, 0, nrow, mx);
+        softmax_logits<MODE, NT, false>(S, 1, k4[1], l4[1], skp, lsv, 0, nrow, mx);
+      }
+      if constexpr (sc) read_scales(c / HS, kbuf);
+      if constexpr (c == 0) {
+#pragma unroll
+        for (int x = 0; x < WP; ++x) publish_k(rk[x], x, next_kbuf);
+      }
+      if constexpr (c == (QC > 2 ? 1 : 0)) {
+#pragma unroll
+        for (int x = 0; x < WP; ++x) publish_v(x, j & 1);
+      }
+      pace(std::integral_constant<int, 8>{}, std::integral_constant<int, (c + 1 < QC || PV ? 4 : 0) + (sc ? 4 : 0)>{}, std::integral_constant<int, kPace>{});
+      if constexpr (c == QC - 1) {
+        request();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    });
+    if constexpr (PV) {
+      static_for<PC>([&](auto C) {
+        constexpr int c = decltype(C)::value;
+        mm_v(c);
+        if constexpr (c + 1 < PC) read_v(c + 1, vhalf);
+        if constexpr (c == 0) {
+          softmax_logits<MODE, NT, false>(S, 2, k4[0], l4[0], skp, lsv, 0, nrow, mx);
+          softmax_logits<MODE, NT, false>(S, 3, k4[1], l4[1], skp, lsv, 0, nrow, mx);
+        }
+        pace(std::integral_constant<int, PLAIN ? 16 : 8>{}, std::integral_constant<int, c + 1 < PC ? 4 : 0>{}, std::integral_constant<int, c == 0 ? kPace : 0>{});
+      });
+    } else {
+      softmax_logits<MODE, NT, false>(S, 2, k4[0], l4[0], skp, lsv, 0, nrow, mx);
+      softmax_logits<MODE, NT, false>(S, 3, k4[1], l4[1], skp, lsv, 0, nrow, mx);
+    }
+  };
+  // TAIL: some row's causal length ends inside the group: positions past it are masked, and the
+  // maxima taken again.
+  auto vector_phase = [&](auto TAILC, int g, int sbuf) {
+    constexpr bool TAIL = decltype(TAILC)::value;
+    using F = SoftmaxForm<MODE, TAIL>;
+    const floatx4* sc = (const floatx4*)&s_ops[sbuf][0][16 * g4];
+    floatx4 r4[4] = {};
+    if constexpr (F::TOKEN_SCALE) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) r4[u] = sc[2 * kScalePitch + u];
+    }
+    float skp = fabsf(p.scale_log2), lsv = 0.0f, rsv = 1.0f;
+    if constexpr (FP8) {
+      skp = s_ops[sbuf][0][lane];
+      lsv = s_ops[sbuf][1][lane];
+      rsv = s_ops[sbuf][2][lane];
+    }
+    if constexpr (TAIL) {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        mx[nt] = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            float z = S[nt][u][i];
+            if constexpr (!F::kLogits) z = __builtin_fmaf(z, skp, lsv);
+            z = (g << 6) + 16 * g4 + 4 * u + i < nrow[nt] ? z : -INFINITY;
+            S[nt][u][i] = z;
+            mx[nt] = fmaxf(mx[nt], z);
+          }
+      }
+    } else if constexpr (FP8) {
+      if (__any(skp < 0.0f)) {  // (a negative softmax scale, or static scale)
+        const float sign = skp < 0.0f ? -1.0f : 1.0f;
+        skp *= sign;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          mx[nt] = -INFINITY;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            S[nt][u] *= sign;
+            softmax_logits<MODE, NT, TAIL>(S, u, k4[0], l4[0], skp, lsv, 0, nrow, mx);
+          }
+        }
+      }
+    }
+    float alpha[NT], msub[NT];
+    softmax_maxima<MODE, NT, TAIL>(mx, skp, lsv, m_run, alpha, msub);
+    softmax_probabilities<MODE, NT, TAIL, true>(S, sc, r4, skp, rsv, alpha, msub, l_run, pb);
+    softmax_rescale<NT, DT>(alpha, acc);
+  };
+
+  // ---- the walk ----
+  const int team = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
+  const bool live = __builtin_amdgcn_readfirstlane((int)at.wave_live) != 0;
+  const int n = ng - g0;
+  if (n > 0) {  // (a chunk's first rows see fewer groups than there may be pieces)
+    auto fence = [&]() {
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto phase_end = [&]() {  // this wavefront's writes to LDS are done
+      fence();
+      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+      __builtin_amdgcn_s_barrier();
+      fence();
+    };
+    auto phase_end_reads = [&]() {  // nothing was written
+      fence();
+      __builtin_amdgcn_s_barrier();
+      fence();
+    };
+    // (start: entries, then codes, then LDS, a round trip each and nothing twice; the entries of the first
+    // groups do not go through LDS)
+    const int blocks = min((min(last_sb, (ng << 6) - 1) >> bs_shift) - blk0 + 1, kWideTable);
+    uintx4 first_k[2][WP];  // K of groups 0 and (team 1) 1
+    {
+      uint32_t e[3], ev, es;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) e[j] = table[min((min(g0 + j, ng - 1) << 6) + 16 * sbk, last_sb) >> bs_shift];
+      const uint32_t tv = (uint32_t)min((g0 << 6) + 16 * g4, last_sb), ts = (uint32_t)min((min(g0 + 1, ng - 1) << 6) + 16 * g4, last_sb);
+      ev = table[tv >> bs_shift];
+      es = table[ts >> bs_shift];
+      const int mine = (int)threadIdx.x < blocks ? table[blk0 + (int)threadIdx.x] : 0;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        if (j > team + 1) continue;
+        const uint32_t tk = (uint32_t)min((min(g0 + j, ng - 1) << 6) + 16 * sbk, last_sb);
+        k_from = (uint64_t)e[j] * block_stride + ((tk & (uint32_t)(bs - 1)) * RB + k_fixed);
+        request_k();
+        if (j <= team) {
+#pragma unroll
+          for (int x = 0; x < WP; ++x) first_k[j & 1][x] = rk[x];
+        }
+      }
+      v_from = (uint64_t)ev * block_stride + ((tv & (uint32_t)(bs - 1)) * RB + v_fixed);
+      request_v();
+      if (!PLAIN && wv == 0) {
+        request_scales_at(ev, tv);
+        const float sk = sk_next, sv = sv_next;
+        request_scales_at(es, ts);
+        publish_scales(0, sk, sv);
+      }
+      if ((int)threadIdx.x < blocks) sh_table[threadIdx.x] = mine;
+      for (int i = (int)threadIdx.x + 64 * W; i < blocks; i += 64 * W) sh_table[i] = table[blk0 + i];
     }
 #pragma unroll
-    for (int tt = 0; tt < DT; ++tt) *(floatx4*)(orow + 16 * tt + 4 * g4) = acc[nt][tt] * inv;
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int x = 0; x < WP; ++x)
+        if (j <= team) publish_k(first_k[j][x], x, j);
+    phase_end();
+    locate(2 + team, 1);
+    if (team == 1) phase_end_reads();
+    int kbuf = 0, kb1 = 1, kb2 = 2;  // buffers of K of groups i, i + 1, i + 2
+    auto rotate = [&]() {
+      const int t = kbuf;
+      kbuf = kb1;
+      kb1 = kb2;
+      kb2 = t;
+    };
+    auto vector_part = [&](int i) {
+      if (((g0 + i) << 6) + 64 > n_min) vector_phase(std::true_type{}, g0 + i, kbuf);
+      else vector_phase(std::false_type{}, g0 + i, kbuf);
+    };
+    auto scales_part = [&](int i) {
+      if (!PLAIN && wv == 0) {
+        publish_scales(i + 1, sk_next, sv_next);
+        request_scales(i + 2);
+      }
+    };
+    if (live) {
+      read_k(0, 0);
+      clear_missing(g0);
+      matrix_phase(std::false_type{}, 0, 0, team ? 2 : 1);
+      phase_end();
+      for (int i = 0; i + 1 < n; ++i) {
+        scales_part(i);
+        locate(i + 3 + team, i + 2);
+        vector_part(i);
+        // (in the registers or on their way: K of group i + 2 + team, V of group i + 1)
+        rotate();
+        read_k(0, kbuf);
+        phase_end();
+        clear_missing(g0 + i + 1);
+        __builtin_amdgcn_s_setprio(0);
+        matrix_phase(std::true_type{}, i + 1, kbuf, team ? kb2 : kb1);
+        __builtin_amdgcn_s_setprio(1);
+        phase_end();
+      }
+      vector_part(n - 1);
+      phase_end_reads();
+      read_v(0, (n - 1) & 1);
+#pragma unroll
+      for (int c = 0; c < PC; ++c) {
+        if (c + 1 < PC) read_v(c + 1, (n - 1) & 1);
+        mm_v(c);
+      }
+    } else {
+      auto publish_all = [&](int j) {
+        clear_missing(min(g0 + j, ng - 1));
+#pragma unroll
+        for (int x = 0; x < WP; ++x) {
+          publish_k(rk[x], x, team ? kb2 : kb1);
+          publish_v(x, j & 1);
+        }
+        request();
+      };
+      publish_all(0);
+      phase_end();
+      for (int i = 0; i + 1 < n; ++i) {
+        scales_part(i);
+        locate(i + 3 + team, i + 2);
+        rotate();
+        phase_end();
+        publish_all(i + 1);
+        phase_end();
+      }
+      phase_end_reads();
+    }
+    if (team == 0) phase_end_reads();
   }
+  store_rows<D, false>(p, lane, at, acc, m_run, l_run);
 }
 
 // ---- the pieces of cut contexts put together: out = sum_c w_c out_c / sum_c w_c with
@@ -566,29 +1461,48 @@ hipError_t launch_many_rows(const AttnArgs& a, int all_rows, int walks, hipStrea
   const int row_blocks = (all_rows + kRowsPerWorkgroup - 1) / kRowsPerWorkgroup;
   const dim3 grid((unsigned)((size_t)walks * a.num_kv_heads * row_blocks));
   const dim3 block(64 * kWavesPerGroup);
-#define KVQ_LAUNCH_PREFILL(MODE)                                                                \
-  if (a.head_dim == 128)                                                                        \
-    hipLaunchKernelGGL((attn_prefill_kernel<MODE, 128, PREFIX>), grid, block, 0, stream, a);    \
-  else                                                                                          \
-    hipLaunchKernelGGL((attn_prefill_kernel<MODE, 64, PREFIX>), grid, block, 0, stream, a)
+#define KVQ_LAUNCH_PREFILL(MODE, KERNEL_64)                                                   \
+  if (!PREFIX && a.wide_groups > 0)                                                           \
+    hipLaunchKernelGGL((attn_rows_kernel<MODE, 128, false, true>), grid, block, 0, stream, a); \
+  else if (a.head_dim == 128)                                                                 \
+    hipLaunchKernelGGL((attn_rows_kernel<MODE, 128, PREFIX, false>), grid, block, 0, stream, a); \
+  else                                                                                        \
+    hipLaunchKernelGGL(KERNEL_64, grid, block, 0, stream, a)
   if (a.mode == KVQ_INT8_TOKEN_HEAD) {
-    KVQ_LAUNCH_PREFILL(KVQ_INT8_TOKEN_HEAD);
+    KVQ_LAUNCH_PREFILL(KVQ_INT8_TOKEN_HEAD, (attn_rows64_kernel<KVQ_INT8_TOKEN_HEAD, PREFIX>));
   } else if (a.mode == KVQ_FP8E4M3_BLOCK_HEAD) {
-    KVQ_LAUNCH_PREFILL(KVQ_FP8E4M3_BLOCK_HEAD);
+    KVQ_LAUNCH_PREFILL(KVQ_FP8E4M3_BLOCK_HEAD, (attn_rows_kernel<KVQ_FP8E4M3_BLOCK_HEAD, 64, PREFIX, false>));
   } else if (a.mode == KVQ_BF16_PLAIN) {
-    KVQ_LAUNCH_PREFILL(KVQ_BF16_PLAIN);
+    KVQ_LAUNCH_PREFILL(KVQ_BF16_PLAIN, (attn_rows64_kernel<KVQ_BF16_PLAIN, PREFIX>));
   } else if (a.mode == KVQ_INT4_TOKEN_HEAD) {  // (head_dim 128 only)
-    hipLaunchKernelGGL((attn_prefill_kernel<KVQ_INT4_TOKEN_HEAD, 128, PREFIX>), grid, block, 0,
-                       stream, a);
+    if (!PREFIX && a.wide_groups > 0)
+      hipLaunchKernelGGL((attn_rows_kernel<KVQ_INT4_TOKEN_HEAD, 128, false, true>), grid, block, 0, stream, a);
+    else
+      hipLaunchKernelGGL((attn_rows_kernel<KVQ_INT4_TOKEN_HEAD, 128, PREFIX, false>), grid, block, 0, stream, a);
   } else {
-    KVQ_LAUNCH_PREFILL(KVQ_FP8E4M3_TENSOR);
+    KVQ_LAUNCH_PREFILL(KVQ_FP8E4M3_TENSOR, (attn_rows_kernel<KVQ_FP8E4M3_TENSOR, 64, PREFIX, false>));
   }
 #undef KVQ_LAUNCH_PREFILL
   return hipGetLastError();
 }
 
+hipError_t launch_wide(const AttnArgs& a, hipStream_t stream) {
+  const int row_blocks = (a.rows + kWideRows - 1) / kWideRows;
+  const dim3 grid((unsigned)((size_t)(a.batch + a.extra_pieces) * a.num_kv_heads * row_blocks)), block(512);
+  switch (a.mode) {
+    case KVQ_INT8_TOKEN_HEAD: hipLaunchKernelGGL((attn_wide_kernel<KVQ_INT8_TOKEN_HEAD>), grid, block, 0, stream, a); break;
+    case KVQ_FP8E4M3_BLOCK_HEAD: hipLaunchKernelGGL((attn_wide_kernel<KVQ_FP8E4M3_BLOCK_HEAD>), grid, block, 0, stream, a); break;
+    case KVQ_BF16_PLAIN: hipLaunchKernelGGL((attn_wide_kernel<KVQ_BF16_PLAIN>), grid, block, 0, stream, a); break;
+    case KVQ_INT4_TOKEN_HEAD: hipLaunchKernelGGL((attn_wide_kernel<KVQ_INT4_TOKEN_HEAD>), grid, block, 0, stream, a); break;
+    default: hipLaunchKernelGGL((attn_wide_kernel<KVQ_FP8E4M3_TENSOR>), grid, block, 0, stream, a);
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_prefill(const AttnArgs& a, hipStream_t stream) {
-  const hipError_t e = launch_many_rows<false>(a, a.rows, a.batch + a.extra_pieces, stream);
+  hipError_t e = hipSuccess;
+  if (a.wide_groups > 0) e = launch_wide(a, stream);  // (one of the two ends at once)
+  if (e == hipSuccess) e = launch_many_rows<false>(a, a.rows, a.batch + a.extra_pieces, stream);
   if (e != hipSuccess || a.extra_pieces == 0) return e;
   const int quads_shift = a.head_dim == 128 ? 5 : 4;
   const int64_t parts = ((((int64_t)a.q_len * a.num_q_heads) << quads_shift) + 255) / 256;

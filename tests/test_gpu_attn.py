@@ -378,6 +378,46 @@ def test_contexts_are_cut_by_their_lengths(mode, D, G, q_len, lens):
         assert attn_err(got, want) <= 5e-4, bound
 
 
+WIDE = {  # lengths, query tokens, query heads, kv heads, declared bound, whether the lengths are long for it
+    "dead wavefronts": ([1500, 1337, 1100, 1499], 130, 64, 64, 1500, True),
+    "a row block of one row": ([2200, 2113, 2049, 2200], 257, 32, 32, 2200, True),
+    "cut": ([9000], 512, 32, 8, 9000, True),
+    "cut, no group for some rows": ([5700], 512, 32, 8, 9000, True),
+    "just too short": ([1300, 512, 1090, 768], 130, 64, 64, 1500, False),
+    "just long enough": ([1300, 512, 1090, 769], 130, 64, 64, 1500, True),
+    "short": ([130, 191, 257, 200], 130, 64, 64, 1500, False),
+}
+
+
+@pytest.mark.parametrize("mode", [m for m in MODES if m != W.MODE_INT4_GROUP])
+@pytest.mark.parametrize("case", sorted(WIDE))
+def test_workgroups_of_256_rows_against_the_streaming_kernels(mode, case):
+    """Where contexts of max_seq_len would fill the chip with workgroups of 256 rows, the lengths decide on the
+    device between that kernel and the one of 128 rows.  Either must agree with the streaming kernels,
+    also under a negative softmax scale.  Both sides are within the checker's bound elsewhere; f16
+    probabilities differ by 2^-12 of a row's largest term at most (measured 1e-4)."""
+    import ctypes as C
+    from paper_2605_29639_amd import kvq
+    lens, q_len, hq, hkv, bound, long = WIDE[case]
+    groups = [-(-l // 64) for l in lens]
+    assert (sum(groups) >= len(lens) * -(-bound // 64) * 5 // 8) == long
+    wl = W.custom("wide", mode, lens, q_len, hq, hkv, 128, 16, seed=len(case))
+    cache, scales, desc = gpu_fill(wl)
+    prof, out = kvq.prof_lib(), (C.c_int64 * 8)()
+    assert prof.kvq_profile_plan(C.byref(desc), len(lens), q_len, hq, bound, 0, 0, out) == kvq.OK and out[0] == 2
+    for sign in (1.0, -1.0):
+        signed = type("Signed", (type(wl),), {"sm_scale": sign * abs(wl.sm_scale)})
+        wl.__class__ = signed
+        got = gpu_attention(wl, cache, scales, desc, chunk_tokens=0, max_len=bound)
+        prof.kvq_profile_prefill_kernel(0)
+        try:
+            want = gpu_attention(wl, cache, scales, desc, chunk_tokens=0, max_len=bound, L=prof)
+        finally:
+            prof.kvq_profile_prefill_kernel(1)
+        assert np.isfinite(got).all()
+        assert attn_err(got, want.astype(np.float64)) <= 5e-4
+
+
 @pytest.mark.parametrize("mode,D", [(W.MODE_INT4, 128), (W.MODE_INT4_GROUP, 128), (W.MODE_INT8, 64), (W.MODE_FP8, 64),
                                     (W.MODE_FP8_TENSOR, 64), (W.MODE_BF16, 64)])
 @pytest.mark.parametrize("seqs", [60, 80])
