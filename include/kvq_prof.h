@@ -35,17 +35,24 @@ void kvq_profile_skip_reduce(int on);
 
 /* 0 makes paged_decode_attn use its streaming kernels also where it otherwise takes the kernel
  * that shares the dequantization among 128 rows: from 128 query rows per kv head on, and from 33
- * on where that is faster.  On initially.  Process-global. */
+ * on where that is faster; and its flat list of groups also where each (sequence, kv head) otherwise gets a
+ * workgroup of its own.  On initially.  Process-global. */
 void kvq_profile_prefill_kernel(int on);
 
 /* What paged_decode_attn (or, with shared_prefix_tokens, paged_decode_attn_prefix) would launch for
  * these host-side arguments; batch >= 1.  Host only.  plan_out: [0] 1 if the call goes to the
  * many-row kernel (2 where long contexts go to the one of 256 rows a workgroup), [1] cuts that kernel may make in the contexts of the batch, [2] wavefronts of the streaming
  * kernel, [3] 64-token groups of the shared prefix that the prefix kernel takes, [4] rows of a row
- * group, and the reduce's [5] grid in x, [6] grid in y and [7] threads per workgroup. */
+ * group, and the reduce's [5] grid in x, [6] grid in y and [7] threads per workgroup ([2] and [5] to [7]
+ * where the flat list is used). */
 int kvq_profile_plan(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,
                      int32_t max_seq_len, int32_t chunk_tokens, int32_t shared_prefix_tokens,
                      int64_t plan_out[8]);
+
+/* Wavefronts of the workgroup that each (sequence, kv head, row group) would get, 0 where the call goes over
+ * the flat list of groups (or to a many-row kernel).  Host only. */
+int kvq_profile_pair_waves(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,
+                           int32_t max_seq_len, int32_t chunk_tokens);
 
 /* While `buf` (device, 16 x uint64 per launched
  * wavefront, i.e. 16 * 8 * (number of wavefronts) bytes) is registered, every wavefront of the

@@ -168,6 +168,36 @@ bool many_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t m
          batch * d->num_kv_heads >= slots;
 }
 
+// Wavefronts of the workgroup that each (sequence, kv head, row group) pair gets in a call that does without the
+// flat list and the reduce, or 0.  The wavefronts of a pair take equal slices of its context and put their
+// sums together in LDS, so a second launch and a round trip of partials through memory fall away; what it
+// costs is that a compute unit's share is whole pairs, however few there are and however long.  All in
+// units of microseconds and 64-token groups, fitted to measurements with 1 to 60 sequences of 40 to
+// 8000 tokens, 8 kv heads: a group takes a wavefront `alone` where few compute units have one and
+// `crowded` where all have (memory, or for int4 and two row tiles arithmetic); beside that a workgroup per
+// pair takes 3.7 and the flat list with its reduce 8.3.  Bounds looser than the contexts make this path
+// rarer, never slower.  At most 8 groups to a wavefront: beyond (group-scaled int4: 6), uneven lengths cost more than the
+// reduce.  us a call, flat list -> workgroup per pair: 4 query heads per kv head, int8, 1 x 600 tokens 8.4 -> 7.7,
+// 12 x 1500 17.1 -> 12.9, 32 x 600 16.0 -> 10.7, 32 of 300 to 2500 23.5 -> 20.9; 32 query rows, 31 x 600
+// 26.5 -> 13.3; not taken: 12 x 4000 24.2 -> 27.4, 1 x 2500 9.9 -> 13.6.  With more pairs than compute
+// units a workgroup has half of the wavefronts, and two share one.
+int32_t pair_waves(const kvq_cache_desc_t* d, int64_t pairs, int64_t groups, int row_tiles, int64_t waves) {
+  const int per_simd = kvq::waves_per_simd(d->mode, d->head_dim, row_tiles);
+  const int64_t cus = waves / 8;
+  if (pairs < 1 || pairs > 2 * cus || groups < 1) return 0;
+  const int64_t team = pairs <= cus ? 4 * per_simd : 2 * per_simd, slots = pairs <= cus ? cus : 2 * cus;
+  const int64_t rounds = (groups + team - 1) / team;
+  if (rounds > (d->mode == KVQ_INT4_GROUP32 ? 6 : 8)) return 0;
+  const bool small = d->head_dim == 64, bf16 = d->mode == KVQ_BF16_PLAIN;
+  double alone = small ? 1.4 : 2.1, crowded = small ? 2.65 : bf16 ? 4.6 : 5.0;
+  if (d->mode == KVQ_INT4_TOKEN_HEAD) crowded = 2.9;
+  if (d->mode == KVQ_INT4_GROUP32) alone = 2.9, crowded = 3.2;
+  if (row_tiles == 2 && !bf16) alone = small ? 1.9 : 2.1, crowded = 2.65;
+  const double here = 3.7 + (double)rounds * (alone + (crowded - alone) * (double)pairs / (double)slots);
+  const double flat = 8.3 + crowded * (double)(pairs * groups) / (double)(4 * cus * per_simd);
+  return here <= flat ? (int32_t)team : 0;
+}
+
 // Everything the launch needs that depends only on host-side arguments.
 bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t num_q_heads,
                int32_t max_seq_len, int32_t chunk_tokens, int32_t shared_prefix_tokens,
@@ -207,8 +237,8 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
     // (an unquantized cache needs twice the registers per group: one wavefront per SIMD; so
     // does the group-scaled int4 cache, for its four accumulators per logit, in the workspace; see
     // below for its launch)
-    const bool two_per_simd = (plan->row_tiles == 1 || d->head_dim == 64) &&
-                              d->mode != KVQ_BF16_PLAIN && d->mode != KVQ_INT4_GROUP32;
+    const bool two_per_simd = kvq::waves_per_simd(d->mode, d->head_dim, plan->row_tiles) == 2 &&
+                              d->mode != KVQ_INT4_GROUP32;
     const int64_t resident = two_per_simd ? waves : waves / 2;
     plan->range_groups = 0;
     plan->num_waves = (int32_t)(flat_max < resident ? flat_max : resident);
@@ -269,6 +299,11 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
   if (plan->many_rows && (rows > 64 || 2 * (int64_t)plan->shared_groups < ((int64_t)max_seq_len + 63) / 64))
     plan->shared_groups = 0;
   if (plan->shared_groups > 0) plan->many_rows = 0;
+  // (A call whose pairs get a workgroup each needs no prefix kernel either, and the same whether it has a
+  // hint or not.)
+  plan->pair_waves = plan->many_rows || chunk_tokens > 0
+                         ? 0 : pair_waves(d, batch * pairs, ((int64_t)max_seq_len + 63) / 64, plan->row_tiles, waves);
+  if (plan->pair_waves > 0) plan->shared_groups = 0;
   plan->wide_groups = 0;
   if (plan->many_rows)
     cut_contexts(d, batch, rows, (int64_t)q_len * num_q_heads, ((int64_t)max_seq_len + 63) / 64,
@@ -530,6 +565,7 @@ int attn_call(const void* q, const void* cache, const float* scales,
   a.wave_clock = nullptr;
   a.shared_groups = plan.shared_groups;
   a.prefix_chunks = plan.prefix_chunks;
+  a.pair_waves = plan.pair_waves;
   a.many_rows = plan.many_rows;
   a.wide_groups = plan.wide_groups;
   a.extra_pieces = plan.extra_pieces;
@@ -647,6 +683,14 @@ int kvq_profile_plan(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len,
                              16 * p.row_tiles, r.pairs, r.parts, r.threads};
   for (int i = 0; i < 8; ++i) plan_out[i] = values[i];
   return KVQ_OK;
+}
+
+int kvq_profile_pair_waves(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,
+                           int32_t max_seq_len, int32_t chunk_tokens) {
+  kvq::AttnPlan p;
+  int err;
+  if (!make_plan(desc, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, 0, &p, &err)) return err;
+  return p.pair_waves;
 }
 
 void kvq_profile_split_events(void* before, void* after) {

@@ -93,8 +93,10 @@ __device__ inline int range_of(const Split& s, int f) {
 // values in AGPRs and copying them back, 1-2 % faster.  At head_dim 64 the two-tile kernels,
 // double buffers included, fit 256 registers as well and run two per SIMD too.)
 // EVEN: the launch has no more wavefronts than are resident at PER_SIMD of them.
-template <int MODE, int D, int NT, bool CEIL, int DEPTH, bool CLOCK, int PER_SIMD, bool EVEN>
-__global__ __launch_bounds__(64, PER_SIMD) void attn_stream_kernel(const AttnArgs p) {
+// TEAM > 0: not a range of the flat list but a workgroup of TEAM wavefronts for one pair, each a slice of its
+// groups, put together in LDS: one launch instead of two (see pair_waves in kvq_api.hip).
+template <int MODE, int D, int NT, bool CEIL, int DEPTH, bool CLOCK, int PER_SIMD, bool EVEN, int TEAM = 0>
+__global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stream_kernel(const AttnArgs p) {
   constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN;  // unquantized cache: 2-byte elements
   // e4m3 codes, one scale per lane and group: the block's, or the whole layer's
   constexpr bool FP8 = MODE == KVQ_FP8E4M3_BLOCK_HEAD || MODE == KVQ_FP8E4M3_TENSOR;
@@ -117,7 +119,8 @@ __global__ __launch_bounds__(64, PER_SIMD) void attn_stream_kernel(const AttnArg
   constexpr int KS = D / 32;       // MFMA steps over the channels
   // matrix-instruction operand of 8 values: f16 (from codes) or the cache's own bf16
   using Operand = std::conditional_t<PLAIN, bf16x8, half8>;
-  const int lane = threadIdx.x;
+  const int lane = TEAM > 0 ? threadIdx.x & 63 : threadIdx.x;
+  const int wv = TEAM > 0 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) : 0;
   const int m16 = lane & 15, g4 = lane >> 4;
   const int w = blockIdx.x;
   const int B = p.batch, Hp = p.pairs_per_seq;
@@ -169,7 +172,14 @@ __global__ __launch_bounds__(64, PER_SIMD) void attn_stream_kernel(const AttnArg
     cur.g = P + (local - cur.pr * len);
     return true;
   };
-  if (B <= 64) {
+  if constexpr (TEAM > 0) {
+    cur.b = w / Hp;
+    cur.pr = w - cur.b * Hp;
+    cur.L = seq_lens[cur.b];
+    cur.ng = (cur.L + 63) >> 6;
+    f0 = cur.g = cur.ng * wv / TEAM;
+    f1 = cur.ng * (wv + 1) / TEAM;
+  } else if (B <= 64) {
     // lane i holds sequence i: one load and one scan give the list's length, the prefix sums
     // the reduce wants and, by a ballot, the sequence this wave's range starts in
     const int Li = lane < B ? seq_lens[lane] : 0;
@@ -442,9 +452,12 @@ __global__ __launch_bounds__(64, PER_SIMD) void attn_stream_kernel(const AttnArg
   // ---- the scales of a group, lane = token: what the softmax multiplies and shifts by.  Token scales go
   // through LDS (the wavefront's own, in order: no barrier), from where the softmax reads four
   // tokens' at a time; called ahead of QK^T, whose time covers the way there and back. ----
-  __shared__ __align__(16) float sh_scales[TOKEN_SCALE ? 3 : 1][64];  // skp, log2 and 1 / of the V scale
+  constexpr int kWaves = TEAM > 0 ? TEAM : 1;
+  __shared__ __align__(16) float sh_scales_all[kWaves][TOKEN_SCALE ? 3 : 1][64];  // skp, log2 and 1 / of the V scale
+  auto& sh_scales = sh_scales_all[wv];
   constexpr bool GROUP_LDS = GROUPED && PER_SIMD == 2;
-  __shared__ floatx4 sh_group[GROUP_LDS ? 2 : 1][GROUP_LDS ? 64 : 1];     // K scales; V scales relative to the token's largest
+  __shared__ floatx4 sh_group_all[kWaves][GROUP_LDS ? 2 : 1][GROUP_LDS ? 64 : 1];  // K scales; V scales relative to the token's largest
+  auto& sh_group = sh_group_all[wv];
   float skp_lane = 0.0f, lsv_lane = 0.0f, rsv_lane = 0.0f;
   // (Group-scaled int4 at one wavefront per SIMD has nothing to cover 32 reads of LDS per group with: its K
   // scales and relative V scales stay in the lane of their token, and ride on the arithmetic as row
@@ -648,7 +661,15 @@ __global__ __launch_bounds__(64, PER_SIMD) void attn_stream_kernel(const AttnArg
   if (count > 1) advance(nxt);
   Cursor nn = nxt;
   bool from_start = cur.g == P;  // did this wave see the current pair from its first listed group
-  if constexpr (DEPTH == 1) {
+  if (TEAM > 0 && count == 0) {  // (a context of fewer groups than wavefronts)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      m_run[nt] = -INFINITY;
+      l_run[nt] = 0.0f;
+#pragma unroll
+      for (int tt = 0; tt < DT; ++tt) acc[nt][tt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+  } else if constexpr (DEPTH == 1) {
     uintx4 kt[4][KJ], vt[VW];
     ScaleT sk, sv;
     const uint8_t* vbase;
@@ -768,6 +789,50 @@ __global__ __launch_bounds__(64, PER_SIMD) void attn_stream_kernel(const AttnArg
       softmax(S, ska, sva, cur, pb);
       pv(vta, pb, cur);
     }
+  }
+  if constexpr (TEAM > 0) {
+    // ---- the pair's wavefronts put together: every wavefront scales its sums to the common maximum, LDS
+    // holds them (rows padded by four floats: 16 rows at a time without bank conflicts), and each
+    // thread adds up four channels of a row ----
+    constexpr int RT = 16 * NT, PITCH = D / 4 + 1;
+    __shared__ float sh_m[TEAM][RT], sh_l[TEAM][RT];
+    __shared__ floatx4 sh_sum[TEAM][RT][PITCH];
+    const int h = cur.pr / NRG, rg = cur.pr - h * NRG, live = min(RT, p.rows - rg * RT);
+    float l_all[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      l_all[nt] = xor16_sum(l_run[nt]);
+      if (g4 == 0) sh_m[wv][16 * nt + m16] = m_run[nt];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const int rl = 16 * nt + m16;
+      float top = sh_m[0][rl];
+#pragma unroll
+      for (int k = 1; k < TEAM; ++k) top = fmaxf(top, sh_m[k][rl]);
+      const float scale = __builtin_amdgcn_exp2f(m_run[nt] - (top == -INFINITY ? 0.0f : top));
+      if (g4 == 0) sh_l[wv][rl] = l_all[nt] * scale;
+      if (rl < live) {
+#pragma unroll
+        for (int tt = 0; tt < DT; ++tt) sh_sum[wv][rl][4 * tt + g4] = acc[nt][tt] * scale;
+      }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < live * (D / 4); i += 64 * TEAM) {
+      const int rl = i / (D / 4), c = i % (D / 4), r = rg * RT + rl;
+      float den = sh_l[0][rl];
+      floatx4 num = sh_sum[0][rl][c];
+#pragma unroll
+      for (int k = 1; k < TEAM; ++k) {
+        den += sh_l[k][rl];
+        num += sh_sum[k][rl][c];
+      }
+      const int j = r / p.group, gi = r - j * p.group;
+      float* orow = p.out + (((size_t)cur.b * p.q_len + j) * p.num_q_heads + (size_t)h * p.group + gi) * D;
+      ((floatx4*)orow)[c] = num * (1.0f / den);
+    }
+    return;
   }
   end_pair(cur, from_start && cur.g == cur.ng - 1);
   stamp(5);
@@ -902,7 +967,7 @@ unsigned long long* g_wave_clock = nullptr;
 template <int MODE, int D, bool CEIL, bool CLOCK>
 void launch_variant(const AttnArgs& a, hipStream_t stream) {
   constexpr int kDepth = MODE == KVQ_BF16_PLAIN ? 1 : 2;
-  constexpr int kOneTile = MODE == KVQ_BF16_PLAIN ? 1 : 2, kTwoTiles = D == 64 ? kOneTile : 1;  // per SIMD
+  constexpr int kOneTile = waves_per_simd(MODE, D, 1), kTwoTiles = waves_per_simd(MODE, D, 2);
   const dim3 grid(a.num_waves), block(64);
   // A caller's granule (range_groups > 0) can make any number of wavefronts.  Few of them, at most one
   // for every SIMD, are kept apart under int4, whose kernels would share SIMDs and leave others idle: int4,
@@ -930,11 +995,39 @@ void launch_variant(const AttnArgs& a, hipStream_t stream) {
   }
 }
 
+// A workgroup for each pair, one launch for the call: as many wavefronts as a compute unit holds
+// (per_simd on each SIMD), or half of them.
+template <int MODE, int D, int NT, int DEPTH, int PER_SIMD>
+void launch_team(const AttnArgs& a, hipStream_t stream) {
+  constexpr int kWhole = 4 * PER_SIMD, kHalf = kWhole / 2;
+  const dim3 grid((unsigned)(a.batch * a.pairs_per_seq));
+  if (a.pair_waves == kWhole)
+    hipLaunchKernelGGL((attn_stream_kernel<MODE, D, NT, false, DEPTH, false, PER_SIMD, false, kWhole>), grid,
+                       dim3(64 * kWhole), 0, stream, a);
+  else
+    hipLaunchKernelGGL((attn_stream_kernel<MODE, D, NT, false, DEPTH, false, PER_SIMD, false, kHalf>), grid,
+                       dim3(64 * kHalf), 0, stream, a);
+}
+template <int MODE, int D>
+hipError_t launch_pairs(const AttnArgs& a, hipStream_t stream) {
+  constexpr int kDepth = MODE == KVQ_BF16_PLAIN ? 1 : 2;
+  constexpr int kOneTile = waves_per_simd(MODE, D, 1), kTwoTiles = waves_per_simd(MODE, D, 2);
+  if constexpr (MODE != KVQ_INT4_GROUP32) {  // (one row tile always)
+    if (a.row_tiles == 2) {
+      launch_team<MODE, D, 2, kDepth, kTwoTiles>(a, stream);
+      return hipGetLastError();
+    }
+  }
+  launch_team<MODE, D, 1, 1, kOneTile>(a, stream);
+  return hipGetLastError();
+}
+
 template <int MODE, int D>
 hipError_t launch_stream(const AttnArgs& a0, hipStream_t stream) {
 #ifdef KVQ_PROFILE
   AttnArgs a = a0;
   a.wave_clock = g_wave_clock;
+  if (a.pair_waves > 0) return launch_pairs<MODE, D>(a, stream);
   // (with a shared prefix the first event lies before the prefix kernel)
   if (g_ev_before && (a.shared_groups == 0 || g_read_ceiling || g_skip_reduce))
     (void)hipEventRecord(g_ev_before, stream);
@@ -948,6 +1041,7 @@ hipError_t launch_stream(const AttnArgs& a0, hipStream_t stream) {
   if (g_ev_after) (void)hipEventRecord(g_ev_after, stream);
   return e;
 #else
+  if (a0.pair_waves > 0) return launch_pairs<MODE, D>(a0, stream);
   launch_variant<MODE, D, false, false>(a0, stream);
   return hipGetLastError();
 #endif
@@ -966,11 +1060,15 @@ void set_prefill_kernel(bool on) { g_prefill_kernel = on; }
 void set_wave_clock(unsigned long long* buf) { g_wave_clock = buf; }
 #endif
 
-hipError_t launch_attn(const AttnArgs& a, hipStream_t stream) {
 #ifdef KVQ_PROFILE
+hipError_t launch_attn(const AttnArgs& args, hipStream_t stream) {
+  // (what the switches measure is the streaming kernel over the flat list)
+  AttnArgs a = args;
+  if (g_ev_before || g_ev_after || g_read_ceiling || g_skip_reduce || g_wave_clock || !g_prefill_kernel) a.pair_waves = 0;
   const bool stream_only = g_read_ceiling || g_skip_reduce;
   const bool many_rows_kernel = g_prefill_kernel && !g_read_ceiling;
 #else
+hipError_t launch_attn(const AttnArgs& a, hipStream_t stream) {
   constexpr bool stream_only = false, many_rows_kernel = true;
 #endif
   if (many_rows_kernel && a.many_rows) return launch_prefill(a, stream);
@@ -998,7 +1096,7 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t stream) {
   else
     e = a.head_dim == 128 ? launch_stream<KVQ_BF16_PLAIN, 128>(a, stream)
                           : launch_stream<KVQ_BF16_PLAIN, 64>(a, stream);
-  if (e != hipSuccess || stream_only) return e;
+  if (e != hipSuccess || stream_only || a.pair_waves > 0) return e;
   const ReduceLaunch r = reduce_launch(a.batch, a.pairs_per_seq, a.num_waves, a.rows, a.row_tiles, a.head_dim);
   const dim3 rgrid((unsigned)r.pairs, (unsigned)r.parts), threads((unsigned)r.threads);
   if (a.head_dim == 128)

@@ -76,6 +76,11 @@ __host__ __device__ inline uint8_t stored_byte(uint8_t code, int mode) {
   return mode == KVQ_INT8_TOKEN_HEAD ? (uint8_t)(code ^ 0x80) : code;
 }
 
+// Wavefronts of the streaming kernel that a SIMD holds, by format and 16-row tiles.
+constexpr int waves_per_simd(int mode, int head_dim, int row_tiles) {
+  return mode == KVQ_BF16_PLAIN || (row_tiles == 2 && head_dim == 128) ? 1 : 2;
+}
+
 constexpr int kMaxPrefixChunks = 8;  // pieces a shared prefix is cut into at most
 constexpr int kRowsPerWorkgroup = 128;    // query rows a workgroup of the many-row kernel owns
 constexpr int kWideRows = 256;            // the same for the kernel of calls with more rows
@@ -125,6 +130,7 @@ struct AttnPlan {
   int32_t shared_groups;   // shared prefix in 64-token groups, 0 where the prefix kernel is not used
   int32_t promised_groups; // the same also where the call does better without that kernel
   int32_t prefix_chunks;   // pieces the prefix kernel cuts it into (>= 1)
+  int32_t pair_waves;      // > 0: a workgroup of so many wavefronts for each pair, and no reduce
   int32_t many_rows;       // the call goes to a many-row kernel
   int32_t wide_groups;     // to the one with workgroups of kWideRows where all contexts together have so many
                            // groups (0: never)
@@ -154,6 +160,7 @@ struct AttnArgs {
   int32_t shared_groups;  // leading 64-token groups that all sequences' tables map to the same
                           // blocks (0: none, or a call the prefix kernel does not serve)
   int32_t prefix_chunks;  // pieces the prefix kernel cuts those groups into: one partial each
+  int32_t pair_waves;     // > 0: a workgroup of so many wavefronts for each pair, and no reduce
   int32_t many_rows;      // the call goes to a many-row kernel (kvq_prefill.hip)
   int32_t wide_groups;    // groups that give it to the one with workgroups of kWideRows, as in AttnPlan
   int32_t extra_pieces, piece_min;  // how the many-row kernel may cut the contexts, as in AttnPlan

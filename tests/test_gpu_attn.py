@@ -89,6 +89,58 @@ def test_shapes_and_splits(mode, case):
     check(wl, chunks=(0, 64, 256))
 
 
+def over_the_flat_list(wl, cache, scales, desc, **kw):
+    """The call through the measurement build, kept on the flat list of groups and the reduce."""
+    from paper_2605_29639_amd import kvq
+    prof = kvq.prof_lib()
+    prof.kvq_profile_prefill_kernel(0)
+    try:
+        return gpu_attention(wl, cache, scales, desc, chunk_tokens=0, L=prof, **kw)
+    finally:
+        prof.kvq_profile_prefill_kernel(1)
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_small_shapes_over_the_flat_list(mode, case):
+    """Calls this small mostly give each (sequence, kv head) a workgroup; the flat list and its reduce must
+    give the same (the checker's bound; the two differ by the order of sums and by where f16 is exact)."""
+    name, lens, q_len, Hq, Hkv, D, bs = case
+    skip_unsupported(mode, D)
+    lens = [max(l, q_len) for l in lens]
+    wl = W.custom(name, mode, lens, q_len, Hq, Hkv, D, bs, seed=zlib.crc32(name.encode()) % 1000 + mode)
+    oc, osc = oracle_fill(wl)
+    got = over_the_flat_list(wl, *upload_oracle_cache(wl, oc, osc))
+    assert np.isfinite(got).all() and attn_err(got, oracle_out(wl, oc, osc)) <= TOL
+
+
+@pytest.mark.parametrize("mode,D,G,q_len", [(m, 128, 4, 1) for m in MODES] + [(W.MODE_INT8, 64, 2, 3), (W.MODE_FP8, 64, 8, 4),
+                                            (W.MODE_BF16, 64, 1, 1), (W.MODE_INT8, 128, 8, 4), (W.MODE_INT4, 128, 7, 3),
+                                            (W.MODE_BF16, 128, 8, 3), (W.MODE_INT4_GROUP, 128, 8, 3), (W.MODE_FP8, 128, 5, 7)])
+@pytest.mark.parametrize("seqs", [1, 40, 130])
+def test_a_workgroup_for_each_pair(mode, D, G, q_len, seqs):
+    """Contexts from one token to a few groups more than the workgroup has wavefronts, on and around the edges
+    of groups (wavefronts without a group, with one, with one more than others); one and two row tiles, rows
+    that fill neither, several row groups; up to one pair for each compute unit (whole workgroups)
+    and up to two (half ones); against the checker and the flat list."""
+    import ctypes as C
+    from paper_2605_29639_amd import kvq
+    one_tile = G * q_len <= 16 or mode == W.MODE_INT4_GROUP
+    pairs = 2 * seqs * -(-G * q_len // (16 if one_tile else 32))
+    whole = 4 if mode == W.MODE_BF16 or (not one_tile and D == 128) else 8
+    team = whole if pairs <= 256 else whole // 2
+    span = team + (0 if mode == W.MODE_INT4_GROUP and pairs <= 256 else 2)   # (two groups in a row do not pay there)
+    lens = [max(q_len, 64 * (i % span) + (0, 1, 63, 17)[i % 4], 1) for i in range(span - 1, span - 1 + seqs)]
+    wl = W.custom("pairs", mode, lens, q_len, 2 * G, 2, D, 16, seed=seqs + G)
+    oc, osc = oracle_fill(wl)
+    cache, scales, desc = upload_oracle_cache(wl, oc, osc)
+    waves = kvq.prof_lib().kvq_profile_pair_waves(C.byref(desc), seqs, q_len, 2 * G, max(lens), 0)
+    assert waves == (team if pairs <= 512 else 0), (pairs, waves)
+    got, want = gpu_attention(wl, cache, scales, desc, chunk_tokens=0), oracle_out(wl, oc, osc)
+    assert np.isfinite(got).all() and attn_err(got, want) <= 5e-4
+    assert attn_err(got, over_the_flat_list(wl, cache, scales, desc).astype(np.float64)) <= 5e-4
+
+
 @pytest.mark.parametrize("mode", MODES)
 def test_gpu_written_cache_gives_the_same_attention(mode):
     """End to end through both entry points: the library's own cache (bit-identical to the
