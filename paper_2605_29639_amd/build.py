@@ -4,6 +4,7 @@
 """
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -12,6 +13,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libkvq.so")
 OBJ_PROF = os.path.join(HERE, "_build", "prof")
 LIB_PROF = os.path.join(HERE, "libkvq_prof.so")
+LIB_FAST = os.path.join(HERE, "_kvq_fast.so")
 SOURCES = ["kvq_api.hip", "kvq_write.hip", "kvq_attn.hip", "kvq_prefill.hip", "kvq_repack.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -36,15 +38,32 @@ def _link(objs, lib):
     os.replace(tmp, lib)
 
 
+def _fast():
+    """The native half of the Python binding, on torch's headers and libraries."""
+    import torch
+    from torch.utils import cpp_extension
+    tmp = LIB_FAST + ".tmp%d" % os.getpid()
+    include = [x for p in cpp_extension.include_paths() for x in ("-isystem", p)]
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+                           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+                           "-I", sysconfig.get_paths()["include"], *include, os.path.join(CSRC, "kvq_fast.cpp"),
+                           "-o", tmp, "-L", os.path.join(os.path.dirname(torch.__file__), "lib"),
+                           "-ltorch_python", "-ltorch_cpu", "-lc10"])
+    os.replace(tmp, LIB_FAST)
+
+
 def build(verbose: bool = False) -> str:
-    """libkvq.so (the library) and libkvq_prof.so (the same sources with -DKVQ_PROFILE: the
-    measurement switches of include/kvq_prof.h on top)."""
+    """libkvq.so (the library), libkvq_prof.so (the same sources with -DKVQ_PROFILE: the
+    measurement switches of include/kvq_prof.h on top) and _kvq_fast.so (the native half of the
+    Python binding)."""
     jobs = []
     for objdir, defines in ((OBJ, []), (OBJ_PROF, ["-DKVQ_PROFILE"])):
         os.makedirs(objdir, exist_ok=True)
         jobs += [(src, objdir, defines) for src in SOURCES]
     with ThreadPoolExecutor(max_workers=8) as ex:
+        fast = ex.submit(_fast)
         objs = list(ex.map(_compile, jobs))
+        fast.result()
     _link(objs[:len(SOURCES)], LIB)
     _link(objs[len(SOURCES):], LIB_PROF)
     if verbose:

@@ -18,6 +18,8 @@ OK, E_NULLPTR, E_BAD_MODE, E_BAD_SHAPE, E_WORKSPACE, E_HIP, E_BAD_INDEX = 0, -1,
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libkvq.so")
 
+FAST_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_kvq_fast.so")
+
 EXPORTS = ("kvq_cache_bytes", "kvq_scales_bytes", "kv_quant_write",
            "paged_decode_attn_workspace_bytes", "paged_decode_attn_prefix_workspace_bytes",
            "paged_decode_attn", "paged_decode_attn_prefix", "paged_decode_attn_static",
@@ -135,9 +137,33 @@ def strerror(code):
     return lib().kvq_strerror(int(code)).decode()
 
 
-# A decode step makes two calls of a few microseconds of GPU work each, so what the marshalling below
-# costs counts: one token of one sequence took 26 us a step with a stream object looked up and an
-# argument object made for every tensor, now 18 to 20, of which 11.6 are the library's own calls and kernels.
+# A decode step makes two calls of a few microseconds of GPU work each, so what the marshalling costs
+# counts.  kv_quant_write, paged_decode_attn and the block moves first offer their arguments to the native module, which
+# takes plain tensors and ints straight to the library; everything else (and every error) goes the
+# way written out below.  One token of one sequence: 16.3 us of host time a step through ctypes, now 6.6.
+_fast_module = None
+
+
+def _fast():
+    """The native module, bound to the library's functions by the first call that needs it."""
+    global _fast_module
+    if _fast_module is None:
+        c, L = _torch()._C, lib()
+        if not hasattr(c, "_cuda_getCurrentRawStream"):   # (as in _stream: all calls take the long way)
+            from types import SimpleNamespace
+            _fast_module = SimpleNamespace(write=lambda *a: None, attn=lambda *a: None, move=lambda *a: None)
+            return _fast_module
+        if not os.path.exists(FAST_PATH):
+            raise RuntimeError("%s is not built: run `python -m paper_2605_29639_amd.build`" % FAST_PATH)
+        from . import _kvq_fast as module
+        address = [C.cast(f, C.c_void_p).value for f in (
+            L.kvq_cache_bytes, L.kvq_scales_bytes, L.paged_decode_attn, L.paged_decode_attn_prefix,
+            L.kv_quant_write, L.kvq_blocks_export, L.kvq_blocks_import)]
+        module.bind(*address, c._cuda_getDevice, c._cuda_getCurrentRawStream)
+        _fast_module = module
+    return _fast_module
+
+
 _torch_module = None
 
 
@@ -212,6 +238,12 @@ def _check_pool(cache, scales, desc):
 
 
 def kv_quant_write(k, v, slot_mapping, cache, scales, desc, stream=None, L=None):
+    if L is None:
+        rc = (_fast_module or _fast()).write(k, v, slot_mapping, cache, scales, desc, stream)
+        if rc == OK:
+            return
+        if rc == E_HIP or rc == E_BAD_INDEX:
+            raise KvqError(rc, "kv_quant_write")
     torch = _torch()
     num_tokens = k.shape[0]
     rows = (num_tokens, desc.num_kv_heads, desc.head_dim)
@@ -270,6 +302,13 @@ def paged_decode_attn(q, cache, scales, desc, block_tables, seq_lens, q_len, max
                       sm_scale, out, workspace, chunk_tokens=0, stream=None, L=None,
                       shared_prefix_tokens=0):
     """paged_decode_attn, or paged_decode_attn_prefix when shared_prefix_tokens is given."""
+    if L is None:
+        rc = (_fast_module or _fast()).attn(q, cache, scales, desc, block_tables, seq_lens, q_len, max_seq_len,
+                                            sm_scale, out, workspace, chunk_tokens, stream, shared_prefix_tokens)
+        if rc == OK:
+            return
+        if rc == E_HIP or rc == E_BAD_INDEX:
+            raise KvqError(rc, "paged_decode_attn_prefix" if shared_prefix_tokens else "paged_decode_attn")
     torch = _torch()
     batch = _check_attn_shapes(q, cache, scales, desc, block_tables, seq_lens, q_len, out)
     num_q_heads, held = q.shape[1], workspace.numel() * workspace.element_size()
@@ -332,6 +371,9 @@ def packed_sizes(desc, num):
 
 
 def blocks_export(cache, scales, desc, block_ids, packed_cache, packed_scales, stream=None):
+    rc = (_fast_module or _fast()).move(True, cache, scales, desc, block_ids, packed_cache, packed_scales, stream)
+    if rc == OK:
+        return
     import torch
     rc = lib().kvq_blocks_export(_dev(cache, torch.uint8, "cache"), _dev(scales, torch.float32, "scales"),
                                  C.byref(desc), _dev(block_ids, torch.int32, "block_ids"),
@@ -342,6 +384,9 @@ def blocks_export(cache, scales, desc, block_ids, packed_cache, packed_scales, s
 
 
 def blocks_import(packed_cache, packed_scales, desc, block_ids, cache, scales, stream=None):
+    rc = (_fast_module or _fast()).move(False, cache, scales, desc, block_ids, packed_cache, packed_scales, stream)
+    if rc == OK:
+        return
     import torch
     rc = lib().kvq_blocks_import(_any(packed_cache, torch.uint8, "packed_cache"),
                                  _any(packed_scales, torch.float32, "packed_scales"), C.byref(desc),
