@@ -176,7 +176,7 @@ bool many_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t m
 // 8000 tokens, 8 kv heads: a group takes a wavefront `alone` where few compute units have one and
 // `crowded` where all have (memory, or for int4 and two row tiles arithmetic); beside that a workgroup per
 // pair takes 3.7 and the flat list with its reduce 8.3.  Bounds looser than the contexts make this path
-// rarer, never slower.  At most 8 groups to a wavefront: beyond (group-scaled int4: 6), uneven lengths cost more than the
+// rarer, never slower.  At most 8 groups to a wavefront: beyond, uneven lengths cost more than the
 // reduce.  us a call, flat list -> workgroup per pair: 4 query heads per kv head, int8, 1 x 600 tokens 8.4 -> 7.7,
 // 12 x 1500 17.1 -> 12.9, 32 x 600 16.0 -> 10.7, 32 of 300 to 2500 23.5 -> 20.9; 32 query rows, 31 x 600
 // 26.5 -> 13.3; not taken: 12 x 4000 24.2 -> 27.4, 1 x 2500 9.9 -> 13.6.  With more pairs than compute
@@ -187,7 +187,7 @@ int32_t pair_waves(const kvq_cache_desc_t* d, int64_t pairs, int64_t groups, int
   if (pairs < 1 || pairs > 2 * cus || groups < 1) return 0;
   const int64_t team = pairs <= cus ? 4 * per_simd : 2 * per_simd, slots = pairs <= cus ? cus : 2 * cus;
   const int64_t rounds = (groups + team - 1) / team;
-  if (rounds > (d->mode == KVQ_INT4_GROUP32 ? 6 : 8)) return 0;
+  if (rounds > 8) return 0;
   const bool small = d->head_dim == 64, bf16 = d->mode == KVQ_BF16_PLAIN;
   double alone = small ? 1.4 : 2.1, crowded = small ? 2.65 : bf16 ? 4.6 : 5.0;
   if (d->mode == KVQ_INT4_TOKEN_HEAD) crowded = 2.9;

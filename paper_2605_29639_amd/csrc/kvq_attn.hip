@@ -95,7 +95,16 @@ __device__ inline int range_of(const Split& s, int f) {
 // EVEN: the launch has no more wavefronts than are resident at PER_SIMD of them.
 // TEAM > 0: not a range of the flat list but a workgroup of TEAM wavefronts for one pair, each a slice of its
 // groups, put together in LDS: one launch instead of two (see pair_waves in kvq_api.hip).
-template <int MODE, int D, int NT, bool CEIL, int DEPTH, bool CLOCK, int PER_SIMD, bool EVEN, int TEAM = 0>
+// BANKS: group-scaled int4 with at most four query rows.  A tile has 16 columns, so each row gets four, one for
+// each channel group: q is zero outside a column's group, and one accumulator holds what took four.
+// The columns' logits are added up and dealt out so that each keeps a quarter of the tokens, with a
+// maximum and sums of its own: a lane has 4 exponentials to a group instead of 16, of which 12 were of
+// empty rows.  4 rows, us a call: 64 sequences of 512 to 4096 tokens 45.1 -> 41.5, 128 of 1000 36.9 -> 35.0; as
+// workgroups of a pair 60 of 1500 24.3 -> 22.4, 32 of 600 11.5 -> 10.4.  (A second register set for the next
+// group, 44.3 us at the first size, and nibbles of K taken as subnormals, which cancel 8 times the sum of q,
+// 40.6 us, were not worth it.)
+template <int MODE, int D, int NT, bool CEIL, int DEPTH, bool CLOCK, int PER_SIMD, bool EVEN, int TEAM = 0,
+          bool BANKS = false>
 __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stream_kernel(const AttnArgs p) {
   constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN;  // unquantized cache: 2-byte elements
   // e4m3 codes, one scale per lane and group: the block's, or the whole layer's
@@ -109,6 +118,7 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
   // fp32 scales per token and head, K and V
   constexpr bool TOKEN_SCALE = MODE == KVQ_INT8_TOKEN_HEAD || INT4;
   static_assert(!GROUPED || (NT == 1 && D == 128), "group scales: one row tile, head_dim 128");
+  static_assert(!BANKS || (GROUPED && PER_SIMD == 2), "banks of columns: group scales, from LDS");
   constexpr int NG = GROUPED ? 4 : 1;  // scale groups per token
   using ScaleT = std::conditional_t<GROUPED, floatx4, float>;  // a token's K (or V) scales
   constexpr int EB = PLAIN ? 2 : 1;                // bytes per cache element
@@ -331,7 +341,7 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
     const int h = c.pr / NRG, rg = c.pr - h * NRG;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-      const int r = (rg * NT + nt) * 16 + m16;
+      const int r = BANKS ? m16 & 3 : (rg * NT + nt) * 16 + m16;
       const bool live = r < p.rows;
       const int j = live ? r / p.group : 0;
       const int gi = live ? r - j * p.group : 0;
@@ -351,8 +361,9 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
           for (int e = 0; e < 4; ++e) {
             const _Float16 lo = (_Float16)__uint_as_float(raw[e] << 16);
             const _Float16 hi = (_Float16)__uint_as_float(raw[e] & 0xFFFF0000u);
-            qb[nt][s][2 * e] = live ? lo : (_Float16)0.0f;
-            qb[nt][s][2 * e + 1] = live ? hi : (_Float16)0.0f;
+            const bool mine = live && (!BANKS || s == m16 >> 2);
+            qb[nt][s][2 * e] = mine ? lo : (_Float16)0.0f;
+            qb[nt][s][2 * e + 1] = mine ? hi : (_Float16)0.0f;
           }
         }
       }
@@ -363,9 +374,31 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
     }
   };
 
+  // BANKS: a row's four columns become one (the same in all four)
+  auto join_banks = [&]() {
+    if constexpr (BANKS && !CEIL) {
+      float top = fmaxf(m_run[0], row_ror<8>(m_run[0]));
+      top = fmaxf(top, row_ror<4>(top));
+      const float scale = __builtin_amdgcn_exp2f(m_run[0] - (top == -INFINITY ? 0.0f : top));
+      m_run[0] = top;
+      l_run[0] *= scale;
+      l_run[0] += row_ror<8>(l_run[0]);
+      l_run[0] += row_ror<4>(l_run[0]);
+#pragma unroll
+      for (int tt = 0; tt < DT; ++tt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float x = acc[0][tt][i] * scale;
+          x += row_ror<8>(x);
+          acc[0][tt][i] = x + row_ror<4>(x);
+        }
+    }
+  };
+
   // leave a pair: final rows if this wave saw all of it, else a partial
   auto end_pair = [&](const Cursor& c, bool whole) {
     if constexpr (CEIL) return;
+    join_banks();
     const int h = c.pr / NRG, rg = c.pr - h * NRG;
     const size_t slot = (size_t)w + (size_t)c.b * Hp + c.pr;
     if (P > 0) whole = false;  // the pair's prefix is another partial, the prefix kernel's
@@ -408,7 +441,7 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
       for (int u = 0; u < 4; ++u) S[nt][u] = floatx4{0.f, 0.f, 0.f, 0.f};
-    if constexpr (GROUPED) {
+    if constexpr (GROUPED && !BANKS) {
 #pragma unroll
       for (int g = 0; g < 3; ++g)
 #pragma unroll
@@ -428,7 +461,9 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
 #pragma unroll
           for (int st = 0; st < 4; ++st) {
             const half8 a = cvt_int4(raw[st]);
-            if constexpr (GROUPED) {  // step st = channel group st: its own accumulator
+            if constexpr (BANKS) {
+              S[0][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, qb[0][st], S[0][u], 0, 0, 0);
+            } else if constexpr (GROUPED) {  // step st = channel group st: its own accumulator
               floatx4& dst = st == 0 ? S[0][u] : SG[st == 0 ? 0 : st - 1][u];
               dst = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, qb[0][st], dst, 0, 0, 0);
             } else {
@@ -458,6 +493,8 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
   constexpr bool GROUP_LDS = GROUPED && PER_SIMD == 2;
   __shared__ floatx4 sh_group_all[kWaves][GROUP_LDS ? 2 : 1][GROUP_LDS ? 64 : 1];  // K scales; V scales relative to the token's largest
   auto& sh_group = sh_group_all[wv];
+  __shared__ __align__(16) float sh_banks_all[BANKS ? kWaves : 1][BANKS ? 4 : 1][64];  // K scales by channel group
+  auto& sh_banks = sh_banks_all[BANKS ? wv : 0];
   float skp_lane = 0.0f, lsv_lane = 0.0f, rsv_lane = 0.0f;
   // (Group-scaled int4 at one wavefront per SIMD has nothing to cover 32 reads of LDS per group with: its K
   // scales and relative V scales stay in the lane of their token, and ride on the arithmetic as row
@@ -483,7 +520,12 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
         group_k = k;
         group_v = ratio;
       } else {
-        sh_group[0][lane] = k;
+        if constexpr (BANKS) {
+#pragma unroll
+          for (int g = 0; g < 4; ++g) sh_banks[g][lane] = k[g];
+        } else {
+          sh_group[0][lane] = k;
+        }
         sh_group[1][lane] = ratio;
       }
     } else {
@@ -504,8 +546,71 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
   // online_softmax in kvq_attn_common.h, shared with the many-row kernel.
   // TAIL = some row's causal length ends inside the group: positions past a row's length are
   // masked. ----
+  // (BANKS: the column's own quarter of the tokens, quad m16 / 4 of its sub-block)
+  auto softmax_banks = [&](auto TAILC, floatx4 (&S)[NT][4], const Cursor& c) {
+    constexpr bool TAIL = decltype(TAILC)::value;
+    const int bank = m16 >> 2, at = 16 * g4 + 4 * bank;
+    const floatx4 l4 = *(const floatx4*)&sh_scales[TOKEN_SCALE ? 1 : 0][at];
+    const floatx4 r4 = *(const floatx4*)&sh_scales[TOKEN_SCALE ? 2 : 0][at];
+    floatx4 half[2], z;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) S[0][u] *= *(const floatx4*)&sh_banks[BANKS ? bank : 0][16 * g4 + 4 * u];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float low = S[0][u][i] + row_ror<8>(S[0][u][i]), high = S[0][2 + u][i] + row_ror<8>(S[0][2 + u][i]);
+        half[u][i] = bank >= 2 ? high : low;
+      }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float even = half[0][i] + row_ror<12>(half[0][i]), odd = half[1][i] + row_ror<4>(half[1][i]);
+      z[i] = ((bank & 1) ? odd : even) + l4[i];
+      if constexpr (TAIL) z[i] = (c.g << 6) + at + i < nrow[0] ? z[i] : -INFINITY;
+      mx = fmaxf(mx, z[i]);
+    }
+    const float m_new = fmaxf(m_run[0], xor16_max(mx)), m_safe = m_new == -INFINITY ? 0.0f : m_new;
+    const float alpha = __builtin_amdgcn_exp2f(m_run[0] - m_safe);
+    m_run[0] = m_new;
+    float lsum = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      z[i] = __builtin_amdgcn_exp2f(z[i] - (m_safe - kPOffset));
+      lsum = __builtin_fmaf(z[i], r4[i], lsum);
+    }
+    l_run[0] = __builtin_fmaf(l_run[0], alpha, lsum);
+    // B operands of P.V: the column's probabilities in its own tokens' places, zero in the others'
+    floatx4 ratio[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ratio[i] = sh_group[GROUP_LDS ? 1 : 0][GROUP_LDS ? at + i : 0];
+    uint32_t keep[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) keep[k] = bank == k ? ~0u : 0u;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      uint32_t pair[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const half2v two = {(_Float16)(z[2 * k] * ratio[2 * k][g]), (_Float16)(z[2 * k + 1] * ratio[2 * k + 1][g])};
+        pair[k] = __builtin_bit_cast(uint32_t, two);
+      }
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf)
+        pbg[BANKS ? g : 0][hf] = __builtin_bit_cast(half8, uintx4{pair[0] & keep[2 * hf], pair[1] & keep[2 * hf],
+                                                                pair[0] & keep[2 * hf + 1], pair[1] & keep[2 * hf + 1]});
+    }
+    if (__any(alpha != 1.0f)) {
+#pragma unroll
+      for (int tt = 0; tt < DT; ++tt) acc[0][tt] *= alpha;
+    }
+  };
   auto softmax_impl = [&](auto TAILC, floatx4 (&S)[NT][4], const Cursor& c, Operand (&pb)[NT][2 * EB]) {
     constexpr bool TAIL = decltype(TAILC)::value;
+    if constexpr (BANKS) {
+      softmax_banks(TAILC, S, c);
+      return;
+    }
     const floatx4* scales = (const floatx4*)&sh_scales[0][TOKEN_SCALE ? 16 * g4 : 0];
     if constexpr (GROUP_ROWS) {
 #pragma clang fp contract(off)  // (a broadcast rides on a multiply or an add, not on both at once)
@@ -799,6 +904,7 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
     __shared__ floatx4 sh_sum[TEAM][RT][PITCH];
     const int h = cur.pr / NRG, rg = cur.pr - h * NRG, live = min(RT, p.rows - rg * RT);
     float l_all[NT];
+    join_banks();
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       l_all[nt] = xor16_sum(l_run[nt]);
@@ -975,7 +1081,9 @@ void launch_variant(const AttnArgs& a, hipStream_t stream) {
   // group-scaled 57, now 46.
   const bool granule = a.range_groups > 0;
   if constexpr (MODE == KVQ_INT4_GROUP32) {  // (the plan gives this format one row tile always)
-    if (granule ? !a.few_waves : a.slot_rows == 8)
+    if ((granule ? !a.few_waves : a.slot_rows == 8) && a.rows <= 4)
+      hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK, 2, true, 0, true>), grid, block, 0, stream, a);
+    else if (granule ? !a.few_waves : a.slot_rows == 8)
       hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK, 2, true>), grid, block, 0, stream, a);
     else
       hipLaunchKernelGGL((attn_stream_kernel<MODE, D, 1, CEIL, 1, CLOCK, 1, true>), grid, block, 0, stream, a);
@@ -997,15 +1105,15 @@ void launch_variant(const AttnArgs& a, hipStream_t stream) {
 
 // A workgroup for each pair, one launch for the call: as many wavefronts as a compute unit holds
 // (per_simd on each SIMD), or half of them.
-template <int MODE, int D, int NT, int DEPTH, int PER_SIMD>
+template <int MODE, int D, int NT, int DEPTH, int PER_SIMD, bool BANKS = false>
 void launch_team(const AttnArgs& a, hipStream_t stream) {
   constexpr int kWhole = 4 * PER_SIMD, kHalf = kWhole / 2;
   const dim3 grid((unsigned)(a.batch * a.pairs_per_seq));
   if (a.pair_waves == kWhole)
-    hipLaunchKernelGGL((attn_stream_kernel<MODE, D, NT, false, DEPTH, false, PER_SIMD, false, kWhole>), grid,
+    hipLaunchKernelGGL((attn_stream_kernel<MODE, D, NT, false, DEPTH, false, PER_SIMD, false, kWhole, BANKS>), grid,
                        dim3(64 * kWhole), 0, stream, a);
   else
-    hipLaunchKernelGGL((attn_stream_kernel<MODE, D, NT, false, DEPTH, false, PER_SIMD, false, kHalf>), grid,
+    hipLaunchKernelGGL((attn_stream_kernel<MODE, D, NT, false, DEPTH, false, PER_SIMD, false, kHalf, BANKS>), grid,
                        dim3(64 * kHalf), 0, stream, a);
 }
 template <int MODE, int D>
@@ -1018,7 +1126,10 @@ hipError_t launch_pairs(const AttnArgs& a, hipStream_t stream) {
       return hipGetLastError();
     }
   }
-  launch_team<MODE, D, 1, 1, kOneTile>(a, stream);
+  if (MODE == KVQ_INT4_GROUP32 && a.rows <= 4)
+    launch_team<MODE, D, 1, 1, kOneTile, MODE == KVQ_INT4_GROUP32>(a, stream);
+  else
+    launch_team<MODE, D, 1, 1, kOneTile>(a, stream);
   return hipGetLastError();
 }
 

@@ -65,6 +65,13 @@ __device__ inline float row_bcast(float x) {
       float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x150 + I, 0xF, 0xF, true));
 }
 
+// value of the lane I places before the caller's, around its 16-lane row
+template <int I>
+__device__ inline float row_ror(float x) {
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + I, 0xF, 0xF, true));
+}
+
 // Over the four lanes that share lane % 16: v_permlane32_swap_b32 and v_permlane16_swap_b32 of a value with
 // itself leave it beside the value 32 (16) lanes away, without the round trip through LDS of a shuffle,
 // which nothing hides where one or two wavefronts run on a SIMD.

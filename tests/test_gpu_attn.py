@@ -505,6 +505,23 @@ def test_group_scaled_int4_with_one_and_two_wavefronts_per_simd(hq, bound):
     assert np.isfinite(got).all() and attn_err(got, want) <= 5e-4
 
 
+@pytest.mark.parametrize("G,q_len", [(1, 1), (1, 3), (2, 2), (3, 1), (4, 1), (5, 1)])
+@pytest.mark.parametrize("seqs,bound", [(5, None), (5, 60000), (300, None)])
+def test_group_scaled_int4_with_four_rows_or_fewer(G, q_len, seqs, bound):
+    """Up to four rows take four columns of the tile each (five rows do not): a workgroup for each pair, an even
+    split with twice the wavefronts, and more pairs than wavefronts; contexts that end in each quarter
+    of a group, so that some of a row's columns see no token at all.  q is large, for
+    maxima that differ between a row's columns."""
+    lens = [(1100, 30, 64, 700, 415, 5, 17, 33, 49, 129)[i % 10] // (1 if seqs < 10 else 2) + q_len for i in range(seqs)]
+    wl = W.custom("banks", W.MODE_INT4_GROUP, lens, q_len, 2 * G, 2, 128, 16, seed=G + q_len)
+    scale = 4 * wl.sm_scale
+    wl.__class__ = type("Peaked", (type(wl),), {"sm_scale": scale})
+    oc, osc = oracle_fill(wl)
+    cache, scales, desc = upload_oracle_cache(wl, oc, osc)
+    got = gpu_attention(wl, cache, scales, desc, chunk_tokens=0, **({"max_len": bound} if bound else {}))
+    assert np.isfinite(got).all() and attn_err(got, oracle_out(wl, oc, osc)) <= 5e-4
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("q_len", [1, 4, 6, 20])
 def test_a_peaked_row_of_an_unquantized_cache(D, q_len):
