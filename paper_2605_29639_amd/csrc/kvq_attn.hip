@@ -1,6 +1,7 @@
 // paged_decode_attn kernels (gfx950): decode attention (Section 2) over the quantized paged
 // cache (Section 7.2.2).  Two launches: a streaming kernel that reads every K/V code from HBM
-// once, and a small log-sum-exp reduce over the pieces a (sequence, kv head) was cut into.
+// once, and a small log-sum-exp reduce over the pieces a (sequence, kv head) was cut into; or, for short
+// contexts, the streaming kernel alone with a workgroup for each pair (TEAM below).
 //
 // Work split.  All 64-token groups of all (sequence, kv head[, row group]) pairs form one flat
 // list (sequence-major).  It is cut into equal ranges, one per wavefront (one wavefront = one

@@ -1,5 +1,5 @@
 // Internal declarations shared by the library's translation units (host side).
-// The device kernels live in kvq_write.hip, kvq_attn.hip and kvq_repack.hip; kvq_api.hip
+// The device kernels live in kvq_write.hip, kvq_attn.hip, kvq_prefill.hip and kvq_repack.hip; kvq_api.hip
 // holds the extern "C" entry points, which validate on the host and then call these.
 #pragma once
 
