@@ -104,7 +104,7 @@ def over_the_flat_list(wl, cache, scales, desc, **kw):
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 def test_small_shapes_over_the_flat_list(mode, case):
     """Calls this small mostly give each (sequence, kv head) a workgroup; the flat list and its reduce must
-    give the same (the checker's bound; the two differ by the order of sums and by where f16 is exact)."""
+    give the same (the oracle's bound; the two differ by the order of sums and by where f16 is exact)."""
     name, lens, q_len, Hq, Hkv, D, bs = case
     skip_unsupported(mode, D)
     lens = [max(l, q_len) for l in lens]
@@ -122,7 +122,7 @@ def test_a_workgroup_for_each_pair(mode, D, G, q_len, seqs):
     """Contexts from one token to a few groups more than the workgroup has wavefronts, on and around the edges
     of groups (wavefronts without a group, with one, with one more than others); one and two row tiles, rows
     that fill neither, several row groups; up to one pair for each compute unit (whole workgroups)
-    and up to two (half ones); against the checker and the flat list."""
+    and up to two (half ones); against the oracle and the flat list."""
     import ctypes as C
     from paper_2605_29639_amd import kvq
     one_tile = G * q_len <= 16 or mode == W.MODE_INT4_GROUP
@@ -446,7 +446,7 @@ WIDE = {  # lengths, query tokens, query heads, kv heads, declared bound, whethe
 def test_workgroups_of_256_rows_against_the_streaming_kernels(mode, case):
     """Where contexts of max_seq_len would fill the chip with workgroups of 256 rows, the lengths decide on the
     device between that kernel and the one of 128 rows.  Either must agree with the streaming kernels,
-    also under a negative softmax scale.  Both sides are within the checker's bound elsewhere; f16
+    also under a negative softmax scale.  Both sides are within the oracle's bound elsewhere; f16
     probabilities differ by 2^-12 of a row's largest term at most (measured 1e-4)."""
     import ctypes as C
     from paper_2605_29639_amd import kvq
