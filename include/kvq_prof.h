@@ -41,13 +41,20 @@ void kvq_profile_prefill_kernel(int on);
 
 /* What paged_decode_attn (or, with shared_prefix_tokens, paged_decode_attn_prefix) would launch for
  * these host-side arguments; batch >= 1.  Host only.  plan_out: [0] 1 if the call goes to the
- * many-row kernel (2 where long contexts go to the one of 256 rows a workgroup), [1] cuts that kernel may make in the contexts of the batch, [2] wavefronts of the streaming
+ * many-row kernel (2 where long contexts go to the one of 256 rows a workgroup), [1] cuts that kernel (the
+ * one of 128 rows) may make in the contexts of the batch, [2] wavefronts of the streaming
  * kernel, [3] 64-token groups of the shared prefix that the prefix kernel takes, [4] rows of a row
  * group, and the reduce's [5] grid in x, [6] grid in y and [7] threads per workgroup ([2] and [5] to [7]
  * where the flat list is used). */
 int kvq_profile_plan(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,
                      int32_t max_seq_len, int32_t chunk_tokens, int32_t shared_prefix_tokens,
                      int64_t plan_out[8]);
+
+/* Where kvq_profile_plan says 2: wide_out [0] 64-token groups that the contexts of the batch have together where
+ * they go to the kernel of 256 rows a workgroup (0 in other calls), [1] cuts it may make ([1] of
+ * kvq_profile_plan are the other kernel's).  Host only. */
+int kvq_profile_wide(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,
+                     int32_t max_seq_len, int64_t wide_out[2]);
 
 /* Wavefronts of the workgroup that each (sequence, kv head, row group) would get, 0 where the call goes over
  * the flat list of groups (or to a many-row kernel).  Host only. */

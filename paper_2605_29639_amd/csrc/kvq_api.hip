@@ -125,13 +125,17 @@ void cut_contexts(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_
   const int64_t room = slot_rows / seq_rows;
   const int64_t per_seq = d->num_kv_heads * ((rows + kvq::kRowsPerWorkgroup - 1) / kvq::kRowsPerWorkgroup);
   double us, wide_us;
-  int64_t c = equal_pieces(slots, batch * per_seq, groups, room / batch + 1, false, &us);
+  const int64_t c = equal_pieces(slots, batch * per_seq, groups, room / batch + 1, false, &us);
   if (d->head_dim == 128 && rows > kvq::kRowsPerWorkgroup && groups * 64 <= (int64_t)kvq::kWideTable * d->block_size) {
     const int64_t wide_per_seq = d->num_kv_heads * ((rows + kvq::kWideRows - 1) / kvq::kWideRows);
     const int64_t wide_c = equal_pieces(slots / 2, batch * wide_per_seq, groups, room / batch + 1, true, &wide_us);
     if (wide_us < 0.93 * us) {
       plan->wide_groups = (int32_t)(batch * groups * 5 / 8);
-      c = wide_c;
+      // (of its own: a batch of which one context is at the bound and the others are short goes to the kernel
+      // for 128 rows, whose cuts it needs.  4 x 771 tokens, one over 8963 and three over 800, int8: 202 us where
+      // it has them, 229 where the other kernel's none stood for both; 14 x 115 tokens, 64 / 8 heads, one over
+      // 10649: 127 and 260.)
+      plan->wide_extra = (int32_t)(batch * (wide_c - 1));
     }
   }
   plan->piece_min = (int32_t)(per_seq < 32 ? 2 : per_seq / 16);
@@ -285,7 +289,7 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
   plan->few_waves = plan->num_waves <= waves / 2;
   // A many-row call has the same workspace as if it went through the streaming kernel; the pieces
   // of a cut context beyond the first (whose rows go to `out`) use it, a sequence's rows each.
-  plan->extra_pieces = 0;
+  plan->extra_pieces = plan->wide_extra = 0;
   plan->piece_min = 1;
   plan->piece_share = 0.0f;
   plan->many_rows = batch > 0 && many_rows(d, batch, rows, max_seq_len, chunk_tokens, slots_128);
@@ -569,6 +573,8 @@ int attn_call(const void* q, const void* cache, const float* scales,
   a.many_rows = plan.many_rows;
   a.wide_groups = plan.wide_groups;
   a.extra_pieces = plan.extra_pieces;
+  a.wide_extra = plan.wide_extra;
+  a.merge = plan.extra_pieces > 0 || plan.wide_extra > 0;
   a.piece_min = plan.piece_min;
   a.piece_share = plan.piece_share;
   const hipError_t e = kvq::launch_attn(a, (hipStream_t)stream);
@@ -682,6 +688,16 @@ int kvq_profile_plan(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len,
   const int64_t values[8] = {p.many_rows + (p.wide_groups > 0), p.extra_pieces, p.num_waves, p.shared_groups,
                              16 * p.row_tiles, r.pairs, r.parts, r.threads};
   for (int i = 0; i < 8; ++i) plan_out[i] = values[i];
+  return KVQ_OK;
+}
+
+int kvq_profile_wide(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,
+                     int32_t max_seq_len, int64_t wide_out[2]) {
+  kvq::AttnPlan p;
+  int err;
+  if (!make_plan(desc, batch, q_len, num_q_heads, max_seq_len, 0, 0, &p, &err)) return err;
+  wide_out[0] = p.wide_groups;
+  wide_out[1] = p.wide_extra;
   return KVQ_OK;
 }
 

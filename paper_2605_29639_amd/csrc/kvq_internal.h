@@ -137,6 +137,7 @@ struct AttnPlan {
   // many-row kernel: pieces beyond each sequence's first that the contexts may be cut into (0: no cut),
   // groups a piece holds at least, and the share of all groups that it holds at least
   int32_t extra_pieces, piece_min;
+  int32_t wide_extra;      // extra_pieces of the kernel with workgroups of kWideRows
   float piece_share;
 };
 
@@ -164,6 +165,8 @@ struct AttnArgs {
   int32_t many_rows;      // the call goes to a many-row kernel (kvq_prefill.hip)
   int32_t wide_groups;    // groups that give it to the one with workgroups of kWideRows, as in AttnPlan
   int32_t extra_pieces, piece_min;  // how the many-row kernel may cut the contexts, as in AttnPlan
+  int32_t wide_extra;     // the same for the other one (launch_prefill makes it that launch's extra_pieces)
+  int32_t merge;          // the merge is launched, for whichever kernel does the call
   float piece_share;
   unsigned long long* wave_clock;  // measurement build: 8 clock readings per wavefront; else null
 };

@@ -185,9 +185,12 @@ __device__ inline bool place_rows(const AttnArgs& p, int lane, int wv, Place& o)
     o.n_min = 0;  // (set below, from the rows' own causal lengths)
   } else {
     o.piece.b = pair / H;
-    if (p.extra_pieces > 0 &&
-        !context_piece(p, o.piece.b, __builtin_amdgcn_readfirstlane((int)(blockIdx.x == 0 && wv == 0)), o.piece))
-      return false;
+    const int leave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x == 0 && wv == 0));
+    if (p.extra_pieces > 0) {
+      if (!context_piece(p, o.piece.b, leave, o.piece)) return false;
+    } else if (CHOICE && p.merge && leave) {  // (a merge is launched for the other kernel's cuts)
+      for (int i = lane; i <= p.batch; i += 64) p.ws_prefix[i] = 0;
+    }
     o.b = o.piece.b;
     o.L = p.seq_lens[o.b];
     const int r_last = min(p.rows, (rb + 1) * ROWS) - 1;
@@ -1501,9 +1504,13 @@ hipError_t launch_wide(const AttnArgs& a, hipStream_t stream) {
 
 hipError_t launch_prefill(const AttnArgs& a, hipStream_t stream) {
   hipError_t e = hipSuccess;
-  if (a.wide_groups > 0) e = launch_wide(a, stream);  // (one of the two ends at once)
+  if (a.wide_groups > 0) {  // (one of the two ends at once)
+    AttnArgs wide = a;
+    wide.extra_pieces = a.wide_extra;
+    e = launch_wide(wide, stream);
+  }
   if (e == hipSuccess) e = launch_many_rows<false>(a, a.rows, a.batch + a.extra_pieces, stream);
-  if (e != hipSuccess || a.extra_pieces == 0) return e;
+  if (e != hipSuccess || !a.merge) return e;
   const int quads_shift = a.head_dim == 128 ? 5 : 4;
   const int64_t parts = ((((int64_t)a.q_len * a.num_q_heads) << quads_shift) + 255) / 256;
   hipLaunchKernelGGL(merge_kernel, dim3((unsigned)(a.batch * parts)), dim3(256), 0, stream, a, quads_shift,

@@ -118,6 +118,19 @@ def test_many_row_calls_may_always_cut_a_long_context(mode, D):
                 assert p["extra_pieces"] * q_len * 64 * D * 4 < held
 
 
+@pytest.mark.parametrize("H,hq,batch,q_len,max_len,cuts", [(8, 32, 4, 771, 8963, 4), (2, 16, 7, 300, 3000, 7),
+                                                           (8, 32, 4, 329, 4000, 4), (4, 32, 7, 200, 4000, 7)])
+def test_the_kernel_of_128_rows_keeps_its_cuts_beside_the_one_of_256(H, hq, batch, q_len, max_len, cuts):
+    """Which of the two does a call is decided by its lengths: a batch far below the bound goes to the kernel of
+    128 rows, with leave to cut its long contexts as if there were no other (c - 1 cuts a sequence where
+    batch * c workgroups fill the chip best), though the one of 256 rows may do without."""
+    desc = d(H=H, D=128, nblk=64)
+    p, wide = plan(desc, batch, q_len, hq, max_len), (C.c_int64 * 2)()
+    assert kvq.prof_lib().kvq_profile_wide(C.byref(desc), batch, q_len, hq, max_len, wide) == kvq.OK
+    assert p["many_rows"] == 2 and wide[0] > 0 and wide[1] == 0
+    assert p["extra_pieces"] == cuts
+
+
 @pytest.mark.parametrize("mode,D,q_len,prefix,used", [
     (0, 128, 4, 64, True), (0, 128, 5, 64, True),                                  # streaming calls: always
     (0, 128, 12, 64, False), (1, 128, 12, 6144, False), (2, 64, 15, 8192, False),   # above 64 rows: never

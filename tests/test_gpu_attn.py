@@ -438,6 +438,11 @@ WIDE = {  # lengths, query tokens, query heads, kv heads, declared bound, whethe
     "just too short": ([1300, 512, 1090, 768], 130, 64, 64, 1500, False),
     "just long enough": ([1300, 512, 1090, 769], 130, 64, 64, 1500, True),
     "short": ([130, 191, 257, 200], 130, 64, 64, 1500, False),
+    # one of the two kernels may cut contexts, the other may not; the merge is launched for both
+    "not cut, the other kernel would": ([3000, 2990, 2900, 3000, 2950, 2999, 2937], 300, 16, 2, 3000, True),
+    "one long, cut by the other kernel": ([3000, 301, 400, 310, 577, 300, 640], 300, 16, 2, 3000, False),
+    "cut, the other kernel would not": ([5000, 4990, 4950, 4999], 100, 64, 16, 5000, True),
+    "one long, not cut by the other kernel": ([5000, 300, 100, 700], 100, 64, 16, 5000, False),
 }
 
 
