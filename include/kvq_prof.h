@@ -52,9 +52,9 @@ int kvq_profile_plan(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len,
 
 /* Where kvq_profile_plan says 2: wide_out [0] 64-token groups that the contexts of the batch have together where
  * they go to the kernel of 256 rows a workgroup (0 in other calls), [1] cuts it may make ([1] of
- * kvq_profile_plan are the other kernel's).  Host only. */
+ * kvq_profile_plan are the other kernel's), [2] groups that the shortest has there.  Host only. */
 int kvq_profile_wide(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,
-                     int32_t max_seq_len, int64_t wide_out[2]);
+                     int32_t max_seq_len, int64_t wide_out[3]);
 
 /* Wavefronts of the workgroup that each (sequence, kv head, row group) would get, 0 where the call goes over
  * the flat list of groups (or to a many-row kernel).  Host only. */

@@ -115,22 +115,31 @@ int64_t equal_pieces(int64_t slots, int64_t walks, int64_t groups, int64_t room,
 // 2000 tokens: 414, 162 and 175 (the pieces are worked out, and none is needed).  A 512-token chunk
 // on its own under a bound of 32768: 21 us without leave to cut, 28 cut by the bound, 23 now (the
 // second launch finds nothing to do); over 4096 tokens, same bound: 117, 63 and 63.
-// Where the kernel for kWideRows should be faster for contexts of max_seq_len, both are launched, and the
-// lengths decide on the device which of them does the call: contexts much shorter than the bound are the
-// other's (an empty launch of about a microsecond is left).  Measured, kernel for 128 rows -> both: 8 x 512
-// tokens over 4608 int8 373 -> 345 us, fp8 305 -> 290, bf16 390 -> 375; 1 x 512 over 16896 183 -> 165,
-// 158 -> 145, 194 -> 183; 8 x 512 over 520 under a bound of 32768 53 -> 54, where the wide kernel takes 59.
-void cut_contexts(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t seq_rows,
+// The kernel for kWideRows gets int8 and e4m3 calls whose walks all take long and are much alike: both kernels
+// are launched then, and the lengths decide on the device which of them does the call, this one where the
+// contexts hold three quarters of what the bound allows and the shortest has half of it.  Over 1586
+// random calls with lengths near the bound, its time by that of the kernel for 128 rows: int8 0.91 and e4m3
+// 0.92 on average and 0.98 at most; without the lines at 60 us and at eight chunks to a context (a chunk's
+// first rows then see much less than its last) up to 1.08; bf16 0.95 and int4 0.96, up to 1.02, which is not
+// worth a second kernel.  With lengths as far apart as allowed 0.94, up to 1.04; with a quarter of the
+// sequences short 1.12.  The kernel for 128 rows alone -> both launched: 8 x 512 tokens over 4608 int8
+// 335 -> 319 us, e4m3 302 -> 290; 1 x 512 over 16896 171 -> 159, 157 -> 147.  The launch that ends at once takes
+// 2.1 us ahead of or behind the other (3 to 4 above 512 workgroups), also where the contexts are far
+// below the bound: 8 x 512 over 520 under a bound of 32768 52.1 -> 54.8 us, 1 x 512 over 512 21.8 -> 24.3.
+void cut_contexts(const kvq_cache_desc_t* d, int64_t batch, int64_t q_len, int64_t rows, int64_t seq_rows,
                   int64_t groups, int64_t slot_rows, int64_t slots, kvq::AttnPlan* plan) {
   const int64_t room = slot_rows / seq_rows;
   const int64_t per_seq = d->num_kv_heads * ((rows + kvq::kRowsPerWorkgroup - 1) / kvq::kRowsPerWorkgroup);
   double us, wide_us;
   const int64_t c = equal_pieces(slots, batch * per_seq, groups, room / batch + 1, false, &us);
-  if (d->head_dim == 128 && rows > kvq::kRowsPerWorkgroup && groups * 64 <= (int64_t)kvq::kWideTable * d->block_size) {
+  const bool codes = d->mode == KVQ_INT8_TOKEN_HEAD || d->mode == KVQ_FP8E4M3_BLOCK_HEAD || d->mode == KVQ_FP8E4M3_TENSOR;
+  if (codes && d->head_dim == 128 && rows > kvq::kRowsPerWorkgroup && us >= 60.0 && 8 * q_len <= 64 * groups &&
+      groups * 64 <= (int64_t)kvq::kWideTable * d->block_size) {
     const int64_t wide_per_seq = d->num_kv_heads * ((rows + kvq::kWideRows - 1) / kvq::kWideRows);
     const int64_t wide_c = equal_pieces(slots / 2, batch * wide_per_seq, groups, room / batch + 1, true, &wide_us);
     if (wide_us < 0.93 * us) {
-      plan->wide_groups = (int32_t)(batch * groups * 5 / 8);
+      plan->wide_groups = (int32_t)((3 * batch * groups + 3) / 4);
+      plan->wide_least = (int32_t)((groups + 1) / 2);
       // (of its own: a batch of which one context is at the bound and the others are short goes to the kernel
       // for 128 rows, whose cuts it needs.  4 x 771 tokens, one over 8963 and three over 800, int8: 202 us where
       // it has them, 229 where the other kernel's none stood for both; 14 x 115 tokens, 64 / 8 heads, one over
@@ -308,9 +317,9 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
   plan->pair_waves = plan->many_rows || chunk_tokens > 0
                          ? 0 : pair_waves(d, batch * pairs, ((int64_t)max_seq_len + 63) / 64, plan->row_tiles, waves);
   if (plan->pair_waves > 0) plan->shared_groups = 0;
-  plan->wide_groups = 0;
+  plan->wide_groups = plan->wide_least = 0;
   if (plan->many_rows)
-    cut_contexts(d, batch, rows, (int64_t)q_len * num_q_heads, ((int64_t)max_seq_len + 63) / 64,
+    cut_contexts(d, batch, q_len, rows, (int64_t)q_len * num_q_heads, ((int64_t)max_seq_len + 63) / 64,
                  (int64_t)slot_rows, slots_128, plan);
   return true;
 }
@@ -572,6 +581,7 @@ int attn_call(const void* q, const void* cache, const float* scales,
   a.pair_waves = plan.pair_waves;
   a.many_rows = plan.many_rows;
   a.wide_groups = plan.wide_groups;
+  a.wide_least = plan.wide_least;
   a.extra_pieces = plan.extra_pieces;
   a.wide_extra = plan.wide_extra;
   a.merge = plan.extra_pieces > 0 || plan.wide_extra > 0;
@@ -692,12 +702,13 @@ int kvq_profile_plan(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len,
 }
 
 int kvq_profile_wide(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,
-                     int32_t max_seq_len, int64_t wide_out[2]) {
+                     int32_t max_seq_len, int64_t wide_out[3]) {
   kvq::AttnPlan p;
   int err;
   if (!make_plan(desc, batch, q_len, num_q_heads, max_seq_len, 0, 0, &p, &err)) return err;
   wide_out[0] = p.wide_groups;
   wide_out[1] = p.wide_extra;
+  wide_out[2] = p.wide_least;
   return KVQ_OK;
 }
 

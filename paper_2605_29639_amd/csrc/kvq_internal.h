@@ -132,8 +132,9 @@ struct AttnPlan {
   int32_t prefix_chunks;   // pieces the prefix kernel cuts it into (>= 1)
   int32_t pair_waves;      // > 0: a workgroup of so many wavefronts for each pair, and no reduce
   int32_t many_rows;       // the call goes to a many-row kernel
-  int32_t wide_groups;     // to the one with workgroups of kWideRows where all contexts together have so many
-                           // groups (0: never)
+  // to the one with workgroups of kWideRows where all contexts together have so many groups (0: never) and
+  // the shortest has so many
+  int32_t wide_groups, wide_least;
   // many-row kernel: pieces beyond each sequence's first that the contexts may be cut into (0: no cut),
   // groups a piece holds at least, and the share of all groups that it holds at least
   int32_t extra_pieces, piece_min;
@@ -163,7 +164,7 @@ struct AttnArgs {
   int32_t prefix_chunks;  // pieces the prefix kernel cuts those groups into: one partial each
   int32_t pair_waves;     // > 0: a workgroup of so many wavefronts for each pair, and no reduce
   int32_t many_rows;      // the call goes to a many-row kernel (kvq_prefill.hip)
-  int32_t wide_groups;    // groups that give it to the one with workgroups of kWideRows, as in AttnPlan
+  int32_t wide_groups, wide_least;  // groups that give it to the one with workgroups of kWideRows, as in AttnPlan
   int32_t extra_pieces, piece_min;  // how the many-row kernel may cut the contexts, as in AttnPlan
   int32_t wide_extra;     // the same for the other one (launch_prefill makes it that launch's extra_pieces)
   int32_t merge;          // the merge is launched, for whichever kernel does the call

@@ -128,13 +128,17 @@ struct Place {
   Piece piece;
 };
 // Where the plan launches both kernels, which of them the lengths give the call to: the wide one where all
-// contexts together have p.wide_groups groups.
+// contexts together have p.wide_groups groups and the shortest p.wide_least.
 __device__ inline bool whole_wide(const AttnArgs& p, int lane) {
-  int total = 0;
-  for (int i = lane; i < p.batch; i += 64) total += (p.seq_lens[i] + 63) >> 6;
+  int total = 0, least = 0x7FFFFFFF;
+  for (int i = lane; i < p.batch; i += 64) {
+    const int groups = (p.seq_lens[i] + 63) >> 6;
+    total += groups;
+    least = min(least, groups);
+  }
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) total += __shfl_xor(total, d, 64);  // (shuffles: as in wave_min_int)
-  return total >= p.wide_groups;
+  return total >= p.wide_groups && wave_min_int(least) >= p.wide_least;
 }
 // Returns false for a workgroup that has nothing to do (the same in all its wavefronts).
 // CHOICE: the plan launches both kernels.
@@ -939,31 +943,23 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows64_kernel(con
 // K runs a phase ahead of V, so that a phase's first operands can be read before the barrier that opens it:
 // K is held in three buffers, V in two; 83 KB of operands and scales, 64 KB of table entries.  (V phases at
 // the higher priority: 318 -> 315 us int8, 295 -> 290 fp8; the matrix phases at the higher: 332 and 300.)
-// 8 x 512 tokens over 4608, 32 / 8 heads: int8 347 -> 315 us, fp8 312 -> 290, bf16 410 -> 367, int4 342 ->
-// 318.  What bounds it: a matrix phase takes 1700 to 2200 cycles beside a vector phase, 1024 of them matrix
+// 8 x 512 tokens over 4608, 32 / 8 heads, against the kernel above: int8 335 -> 319 us, fp8 302 -> 290.  (An
+// unquantized and a plain int4 cache, with 192 and 72 bytes of registers spilled, gained half of that.)  What bounds it: a matrix phase takes 1700 to 2200 cycles beside a vector phase, 1024 of them matrix
 // instructions; v_exp_f32 and matrix instructions of two wavefronts barely overlap (matched streams of
 // 125 us each take 176 together, multiply-adds 133).  head_dim 64 does better on the kernel above,
 // which runs three wavefronts per SIMD there (int8 230 us against 251).
 template <int MODE>
 __global__ __launch_bounds__(512, 2) void attn_wide_kernel(const AttnArgs p) {
-  constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN;  // unquantized cache: the operands are its bytes
   constexpr bool FP8 = MODE == KVQ_FP8E4M3_BLOCK_HEAD || MODE == KVQ_FP8E4M3_TENSOR;
-  constexpr bool INT4 = MODE == KVQ_INT4_TOKEN_HEAD;  // two codes per byte
-  constexpr bool TOKEN_SCALE = MODE == KVQ_INT8_TOKEN_HEAD || INT4;
+  constexpr bool TOKEN_SCALE = MODE == KVQ_INT8_TOKEN_HEAD;
+  static_assert(FP8 || TOKEN_SCALE, "the formats of one code per byte");
   constexpr int W = 8, D = 128, NT = 2;
-  constexpr int EB = PLAIN ? 2 : 1;  // bytes per cache element
-  constexpr int RB = INT4 ? D / 2 : D * EB;  // bytes per token row in a tile
+  constexpr int RB = D;            // bytes per token row in a tile
   constexpr int DT = D / 16;       // 16-channel tiles of V / of the output
   constexpr int KJ = RB / 64;      // 16-byte K pieces per lane and quad
   constexpr int KS = D / 32;       // matrix-instruction steps over the channels
-  // 16-byte pieces per lane that K (and V) of a group consist of, and how many of them a wavefront
-  // converts (BOTH: of K and of V; else team 0 has one of K each, team 1 one of V)
-  constexpr int NP = RB / 16;
-  constexpr bool BOTH = NP >= W;
-  constexpr int WP = BOTH ? NP / W : 1;
-  constexpr int kPace = INT4 ? 5 : 2;  // vector instructions behind a matrix instruction
-  // matrix-instruction operand of 8 values: f16 (from codes) or the cache's own bf16
-  using Operand = std::conditional_t<PLAIN, bf16x8, half8>;
+  static_assert(RB / 16 == W, "K (and V) of a group are eight 16-byte pieces per lane: a wavefront converts one of each");
+  constexpr int kPace = 2;  // vector instructions behind a matrix instruction
   __shared__ half8 k_ops[3][4][KS][64];  // [buffer][quad of the sub-block][step][lane]
   __shared__ half8 v_ops[2][DT][2][64];  // [half][channel tile][tokens 0-7 | 8-15][lane]
   // [buffer]: K scale * log2e / sqrt(D), log2 and reciprocal of the V scale of the 64 tokens
@@ -989,7 +985,7 @@ __global__ __launch_bounds__(512, 2) void attn_wide_kernel(const AttnArgs p) {
   const int last_sb = ((L - 1) >> 4) << 4;
 
   // ---- q as the B operand of QK^T, causal lengths, running state ----
-  Operand qb[NT][KS];
+  half8 qb[NT][KS];
   int nrow[NT];
   floatx4 acc[NT][DT];
   float m_run[NT], l_run[NT];
@@ -997,15 +993,13 @@ __global__ __launch_bounds__(512, 2) void attn_wide_kernel(const AttnArgs p) {
   const int n_min = at.n_min;
 
   // ---- producer side: this wavefront's share of a group's codes.  K runs a group ahead of V ----
-  const bool has_k = BOTH || wv < W / 2, has_v = BOTH || wv >= W / 2;
-  const int k_first = wv * WP, v_first = BOTH ? wv * WP : wv - W / 2;
   const uint32_t k_fixed = (uint32_t)h * tile_bytes + 64u * g4 + 16u * (m16 & 3);
   const uint32_t v_fixed = (uint32_t)(H + h) * tile_bytes + 16u * m16;
   const int blk0 = (g0 << 6) >> bs_shift;
   // (the table entries of the walk come from LDS: as loads they would have to be waited for, and every
   // load in flight behind them, before the addresses they give can be worked out)
   auto entry = [&](uint32_t pos) { return (uint64_t)(uint32_t)sh_table[min((int)(pos >> bs_shift) - blk0, kWideTable - 1)]; };
-  uintx4 rk[WP], rv[WP];
+  uintx4 rk, rv;
   float sk_next = 0.0f, sv_next = 0.0f;
   uint64_t k_from = 0, v_from = 0;  // byte offsets in the cache
   // K of group g0 + jk, V of group g0 + jv: where this lane's pieces lie
@@ -1026,73 +1020,32 @@ __global__ __launch_bounds__(512, 2) void attn_wide_kernel(const AttnArgs p) {
     const uint32_t t = (uint32_t)min((min(g0 + j, ng - 1) << 6) + 16 * g4, last_sb);
     request_scales_at(entry(t), t);
   };
-  auto request_k = [&]() {
-    if (has_k) {
-#pragma unroll
-      for (int x = 0; x < WP; ++x) {
-        const int pc = k_first + x;
-        rk[x] = *(const uintx4*)(cache + k_from + (pc / KJ) * (4 * RB) + 256 * (pc % KJ));
-      }
-    }
-  };
-  auto request_v = [&]() {
-    // (unquantized: piece 2 t + hf is channel tile t, tokens 8 hf .. 8 hf + 7)
-    if (has_v) {
-#pragma unroll
-      for (int x = 0; x < WP; ++x) {
-        const int pc = v_first + x;
-        rv[x] = *(const uintx4*)(cache + v_from + (PLAIN ? (pc & 1) * (16 * D) + 256 * (pc >> 1) : 256 * pc));
-      }
-    }
-  };
+  auto request_k = [&]() { rk = *(const uintx4*)(cache + k_from + (wv / KJ) * (4 * RB) + 256 * (wv % KJ)); };
+  auto request_v = [&]() { rv = *(const uintx4*)(cache + v_from + 256 * wv); };
   auto request = [&]() {
     request_k();
     request_v();
   };
-  auto publish_k = [&](uintx4& codes, int x, int buf) {
-    if (!has_k) return;
+  auto publish_k = [&](uintx4& codes, int buf) {
     asm volatile("" : "+v"(codes));  // (converted here, not earlier)
-    const int pc = k_first + x, u = pc / KJ, at = pc % KJ;
-    if constexpr (PLAIN) {  // bf16 rows are operands as they are; the LDS arrays hold their bits
-      k_ops[buf][u][at][lane] = __builtin_bit_cast(half8, codes);
-    } else if constexpr (INT4) {  // word st of the lane's piece holds the 8 channels of step st
-#pragma unroll
-      for (int st = 0; st < 4; ++st) k_ops[buf][u][st][lane] = cvt_int4(codes[st]);
-    } else {
-      k_ops[buf][u][2 * at][lane] = cvt8<MODE>(codes[0], codes[1]);
-      k_ops[buf][u][2 * at + 1][lane] = cvt8<MODE>(codes[2], codes[3]);
-    }
+    const int u = wv / KJ, at = wv % KJ;
+    k_ops[buf][u][2 * at][lane] = cvt8<MODE>(codes[0], codes[1]);
+    k_ops[buf][u][2 * at + 1][lane] = cvt8<MODE>(codes[2], codes[3]);
   };
-  auto publish_v = [&](int x, int half) {
-    if (!has_v) return;
-    asm volatile("" : "+v"(rv[x]));
-    const int pc = v_first + x;
-    if constexpr (PLAIN) {
-      v_ops[half][pc >> 1][pc & 1][lane] = __builtin_bit_cast(half8, rv[x]);
-    } else if constexpr (INT4) {
-#pragma unroll
-      for (int w4 = 0; w4 < 4; ++w4) v_ops[half][2 * pc + (w4 >> 1)][w4 & 1][lane] = cvt_int4(rv[x][w4]);
-    } else {
-      v_ops[half][pc][0][lane] = cvt8<MODE>(rv[x][0], rv[x][1]);
-      v_ops[half][pc][1][lane] = cvt8<MODE>(rv[x][2], rv[x][3]);
-    }
+  auto publish_v = [&](int half) {
+    asm volatile("" : "+v"(rv));
+    v_ops[half][wv][0][lane] = cvt8<MODE>(rv[0], rv[1]);
+    v_ops[half][wv][1][lane] = cvt8<MODE>(rv[2], rv[3]);
   };
   // V bits of tokens past the last position are cleared first: a NaN times 0 is NaN
   auto clear_missing = [&](int g) {
-    if (!(PLAIN || FP8) || (g << 6) + 64 <= L) return;
+    if (!FP8 || (g << 6) + 64 <= L) return;
     const int live = L - ((g << 6) + 16 * g4);  // tokens of this lane's sub-block below L
 #pragma unroll
-    for (int x = 0; x < WP; ++x)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if constexpr (PLAIN) {
-          const int n = live - (8 * ((v_first + x) & 1) + 2 * e);
-          rv[x][e] &= n >= 2 ? ~0u : n == 1 ? 0xFFFFu : 0u;
-        } else {
-          const int n = min(max(live - 4 * e, 0), 4);
-          rv[x][e] &= n == 4 ? ~0u : (1u << (8 * n)) - 1u;
-        }
-      }
+    for (int e = 0; e < 4; ++e) {
+      const int n = min(max(live - 4 * e, 0), 4);
+      rv[e] &= n == 4 ? ~0u : (1u << (8 * n)) - 1u;
+    }
   };
   auto publish_scales = [&](int j, float sk, float sv) {  // of group g0 + j
     const int g = min(g0 + j, ng - 1), buf = j % 3;
@@ -1111,27 +1064,20 @@ __global__ __launch_bounds__(512, 2) void attn_wide_kernel(const AttnArgs p) {
 
   // ---- consumer side ----
   floatx4 S[NT][4];
-  Operand pb[NT][2 * EB];  // unquantized: a probability goes in as two bf16 terms (hi, lo)
-  auto load_op = [&](const half8& bits) {
-    if constexpr (PLAIN) return __builtin_bit_cast(bf16x8, bits);
-    else return bits;
-  };
-  auto mma = [&](const Operand& a, const Operand& b, const floatx4& c) {
-    if constexpr (PLAIN) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-    else return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
-  };
+  half8 pb[NT][2];
+  auto mma = [&](const half8& a, const half8& b, const floatx4& c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); };
   float mx[NT];
   constexpr float skp = 0.0f, lsv = 0.0f;  // (the maxima of formats without token scales are those of S)
-  Operand op[2][4];  // operands of two chunks of eight matrix instructions
+  half8 op[2][4];  // operands of two chunks of eight matrix instructions
   floatx4 k4[2] = {}, l4[2] = {};
   constexpr int HS = KS / 2, QC = 2 * HS, PC = DT / 2;  // chunks of QK^T (two quads, two steps) and of P.V (two tiles)
   auto read_k = [&](int c, int buf) {
 #pragma unroll
-    for (int x = 0; x < 4; ++x) op[c & 1][x] = load_op(k_ops[buf][2 * (c / HS) + (x & 1)][2 * (c % HS) + (x >> 1)][lane]);
+    for (int x = 0; x < 4; ++x) op[c & 1][x] = k_ops[buf][2 * (c / HS) + (x & 1)][2 * (c % HS) + (x >> 1)][lane];
   };
   auto read_v = [&](int c, int half) {
 #pragma unroll
-    for (int x = 0; x < 4; ++x) op[(QC + c) & 1][x] = load_op(v_ops[half][2 * c + (x & 1)][x >> 1][lane]);
+    for (int x = 0; x < 4; ++x) op[(QC + c) & 1][x] = v_ops[half][2 * c + (x & 1)][x >> 1][lane];
   };
   auto read_scales = [&](int pair, int buf) {
     const floatx4* sc = (const floatx4*)&s_ops[buf][0][16 * g4];
@@ -1157,7 +1103,6 @@ __global__ __launch_bounds__(512, 2) void attn_wide_kernel(const AttnArgs p) {
       for (int nt = 0; nt < NT; ++nt) {
         floatx4& d = acc[nt][2 * c + (x & 1)];
         d = mma(op[(QC + c) & 1][x], pb[nt][x >> 1], d);
-        if constexpr (PLAIN) d = mma(op[(QC + c) & 1][x], pb[nt][2 + (x >> 1)], d);
       }
   };
   // N matrix instructions, with READS LDS reads dealt out between them and VALU vector ones behind each
@@ -1197,14 +1142,8 @@ __global__ __launch_bounds__(512, 2) void attn_wide_kernel(const AttnArgs p) {
         softmax_logits<MODE, NT, false>(S, 1, k4[1], l4[1], skp, lsv, 0, nrow, mx);
       }
       if constexpr (sc) read_scales(c / HS, kbuf);
-      if constexpr (c == 0) {
-#pragma unroll
-        for (int x = 0; x < WP; ++x) publish_k(rk[x], x, next_kbuf);
-      }
-      if constexpr (c == (QC > 2 ? 1 : 0)) {
-#pragma unroll
-        for (int x = 0; x < WP; ++x) publish_v(x, j & 1);
-      }
+      if constexpr (c == 0) publish_k(rk, next_kbuf);
+      if constexpr (c == 1) publish_v(j & 1);
       pace(std::integral_constant<int, 8>{}, std::integral_constant<int, (c + 1 < QC || PV ? 4 : 0) + (sc ? 4 : 0)>{}, std::integral_constant<int, kPace>{});
       if constexpr (c == QC - 1) {
         request();
@@ -1220,7 +1159,7 @@ __global__ __launch_bounds__(512, 2) void attn_wide_kernel(const AttnArgs p) {
           softmax_logits<MODE, NT, false>(S, 2, k4[0], l4[0], skp, lsv, 0, nrow, mx);
           softmax_logits<MODE, NT, false>(S, 3, k4[1], l4[1], skp, lsv, 0, nrow, mx);
         }
-        pace(std::integral_constant<int, PLAIN ? 16 : 8>{}, std::integral_constant<int, c + 1 < PC ? 4 : 0>{}, std::integral_constant<int, c == 0 ? kPace : 0>{});
+        pace(std::integral_constant<int, 8>{}, std::integral_constant<int, c + 1 < PC ? 4 : 0>{}, std::integral_constant<int, c == 0 ? kPace : 0>{});
       });
     } else {
       softmax_logits<MODE, NT, false>(S, 2, k4[0], l4[0], skp, lsv, 0, nrow, mx);
@@ -1238,7 +1177,7 @@ __global__ __launch_bounds__(512, 2) void attn_wide_kernel(const AttnArgs p) {
 #pragma unroll
       for (int u = 0; u < 4; ++u) r4[u] = sc[2 * kScalePitch + u];
     }
-    float skp = fabsf(p.scale_log2), lsv = 0.0f, rsv = 1.0f;
+    float skp = 0.0f, lsv = 0.0f, rsv = 1.0f;
     if constexpr (FP8) {
       skp = s_ops[sbuf][0][lane];
       lsv = s_ops[sbuf][1][lane];
@@ -1303,7 +1242,7 @@ __global__ __launch_bounds__(512, 2) void attn_wide_kernel(const AttnArgs p) {
     // (start: entries, then codes, then LDS, a round trip each and nothing twice; the entries of the first
     // groups do not go through LDS)
     const int blocks = min((min(last_sb, (ng << 6) - 1) >> bs_shift) - blk0 + 1, kWideTable);
-    uintx4 first_k[2][WP];  // K of groups 0 and (team 1) 1
+    uintx4 first_k[2];  // K of groups 0 and (team 1) 1
     {
       uint32_t e[3], ev, es;
 #pragma unroll
@@ -1318,14 +1257,11 @@ __global__ __launch_bounds__(512, 2) void attn_wide_kernel(const AttnArgs p) {
         const uint32_t tk = (uint32_t)min((min(g0 + j, ng - 1) << 6) + 16 * sbk, last_sb);
         k_from = (uint64_t)e[j] * block_stride + ((tk & (uint32_t)(bs - 1)) * RB + k_fixed);
         request_k();
-        if (j <= team) {
-#pragma unroll
-          for (int x = 0; x < WP; ++x) first_k[j & 1][x] = rk[x];
-        }
+        if (j <= team) first_k[j & 1] = rk;
       }
       v_from = (uint64_t)ev * block_stride + ((tv & (uint32_t)(bs - 1)) * RB + v_fixed);
       request_v();
-      if (!PLAIN && wv == 0) {
+      if (wv == 0) {
         request_scales_at(ev, tv);
         const float sk = sk_next, sv = sv_next;
         request_scales_at(es, ts);
@@ -1336,9 +1272,7 @@ __global__ __launch_bounds__(512, 2) void attn_wide_kernel(const AttnArgs p) {
     }
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int x = 0; x < WP; ++x)
-        if (j <= team) publish_k(first_k[j][x], x, j);
+      if (j <= team) publish_k(first_k[j], j);
     phase_end();
     locate(2 + team, 1);
     if (team == 1) phase_end_reads();
@@ -1354,7 +1288,7 @@ __global__ __launch_bounds__(512, 2) void attn_wide_kernel(const AttnArgs p) {
       else vector_phase(std::false_type{}, g0 + i, kbuf);
     };
     auto scales_part = [&](int i) {
-      if (!PLAIN && wv == 0) {
+      if (wv == 0) {
         publish_scales(i + 1, sk_next, sv_next);
         request_scales(i + 2);
       }
@@ -1389,11 +1323,8 @@ __global__ __launch_bounds__(512, 2) void attn_wide_kernel(const AttnArgs p) {
     } else {
       auto publish_all = [&](int j) {
         clear_missing(min(g0 + j, ng - 1));
-#pragma unroll
-        for (int x = 0; x < WP; ++x) {
-          publish_k(rk[x], x, team ? kb2 : kb1);
-          publish_v(x, j & 1);
-        }
+        publish_k(rk, team ? kb2 : kb1);
+        publish_v(j & 1);
         request();
       };
       publish_all(0);
@@ -1465,9 +1396,7 @@ hipError_t launch_many_rows(const AttnArgs& a, int all_rows, int walks, hipStrea
   const dim3 grid((unsigned)((size_t)walks * a.num_kv_heads * row_blocks));
   const dim3 block(64 * kWavesPerGroup);
 #define KVQ_LAUNCH_PREFILL(MODE, KERNEL_64)                                                   \
-  if (!PREFIX && a.wide_groups > 0)                                                           \
-    hipLaunchKernelGGL((attn_rows_kernel<MODE, 128, false, true>), grid, block, 0, stream, a); \
-  else if (a.head_dim == 128)                                                                 \
+  if (a.head_dim == 128)                                                                      \
     hipLaunchKernelGGL((attn_rows_kernel<MODE, 128, PREFIX, false>), grid, block, 0, stream, a); \
   else                                                                                        \
     hipLaunchKernelGGL(KERNEL_64, grid, block, 0, stream, a)
@@ -1478,10 +1407,7 @@ hipError_t launch_many_rows(const AttnArgs& a, int all_rows, int walks, hipStrea
   } else if (a.mode == KVQ_BF16_PLAIN) {
     KVQ_LAUNCH_PREFILL(KVQ_BF16_PLAIN, (attn_rows64_kernel<KVQ_BF16_PLAIN, PREFIX>));
   } else if (a.mode == KVQ_INT4_TOKEN_HEAD) {  // (head_dim 128 only)
-    if (!PREFIX && a.wide_groups > 0)
-      hipLaunchKernelGGL((attn_rows_kernel<KVQ_INT4_TOKEN_HEAD, 128, false, true>), grid, block, 0, stream, a);
-    else
-      hipLaunchKernelGGL((attn_rows_kernel<KVQ_INT4_TOKEN_HEAD, 128, PREFIX, false>), grid, block, 0, stream, a);
+    hipLaunchKernelGGL((attn_rows_kernel<KVQ_INT4_TOKEN_HEAD, 128, PREFIX, false>), grid, block, 0, stream, a);
   } else {
     KVQ_LAUNCH_PREFILL(KVQ_FP8E4M3_TENSOR, (attn_rows_kernel<KVQ_FP8E4M3_TENSOR, 64, PREFIX, false>));
   }
@@ -1489,27 +1415,27 @@ hipError_t launch_many_rows(const AttnArgs& a, int all_rows, int walks, hipStrea
   return hipGetLastError();
 }
 
-hipError_t launch_wide(const AttnArgs& a, hipStream_t stream) {
-  const int row_blocks = (a.rows + kWideRows - 1) / kWideRows;
-  const dim3 grid((unsigned)((size_t)(a.batch + a.extra_pieces) * a.num_kv_heads * row_blocks)), block(512);
-  switch (a.mode) {
-    case KVQ_INT8_TOKEN_HEAD: hipLaunchKernelGGL((attn_wide_kernel<KVQ_INT8_TOKEN_HEAD>), grid, block, 0, stream, a); break;
-    case KVQ_FP8E4M3_BLOCK_HEAD: hipLaunchKernelGGL((attn_wide_kernel<KVQ_FP8E4M3_BLOCK_HEAD>), grid, block, 0, stream, a); break;
-    case KVQ_BF16_PLAIN: hipLaunchKernelGGL((attn_wide_kernel<KVQ_BF16_PLAIN>), grid, block, 0, stream, a); break;
-    case KVQ_INT4_TOKEN_HEAD: hipLaunchKernelGGL((attn_wide_kernel<KVQ_INT4_TOKEN_HEAD>), grid, block, 0, stream, a); break;
-    default: hipLaunchKernelGGL((attn_wide_kernel<KVQ_FP8E4M3_TENSOR>), grid, block, 0, stream, a);
-  }
+// The kernel for 256 rows and, behind it, the one for 128: the lengths have one of them end at once.
+template <int MODE>
+hipError_t launch_either(const AttnArgs& a, hipStream_t stream) {
+  const int blocks = (a.rows + kRowsPerWorkgroup - 1) / kRowsPerWorkgroup, wide_blocks = (a.rows + kWideRows - 1) / kWideRows;
+  AttnArgs wide = a;
+  wide.extra_pieces = a.wide_extra;
+  hipLaunchKernelGGL((attn_wide_kernel<MODE>), dim3((unsigned)((size_t)(a.batch + a.wide_extra) * a.num_kv_heads * wide_blocks)),
+                     dim3(512), 0, stream, wide);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((attn_rows_kernel<MODE, 128, false, true>), dim3((unsigned)((size_t)(a.batch + a.extra_pieces) * a.num_kv_heads * blocks)),
+                     dim3(64 * kWavesPerGroup), 0, stream, a);
   return hipGetLastError();
 }
 
 hipError_t launch_prefill(const AttnArgs& a, hipStream_t stream) {
-  hipError_t e = hipSuccess;
-  if (a.wide_groups > 0) {  // (one of the two ends at once)
-    AttnArgs wide = a;
-    wide.extra_pieces = a.wide_extra;
-    e = launch_wide(wide, stream);
-  }
-  if (e == hipSuccess) e = launch_many_rows<false>(a, a.rows, a.batch + a.extra_pieces, stream);
+  hipError_t e;
+  if (a.wide_groups == 0) e = launch_many_rows<false>(a, a.rows, a.batch + a.extra_pieces, stream);
+  else if (a.mode == KVQ_INT8_TOKEN_HEAD) e = launch_either<KVQ_INT8_TOKEN_HEAD>(a, stream);
+  else if (a.mode == KVQ_FP8E4M3_BLOCK_HEAD) e = launch_either<KVQ_FP8E4M3_BLOCK_HEAD>(a, stream);
+  else e = launch_either<KVQ_FP8E4M3_TENSOR>(a, stream);
   if (e != hipSuccess || !a.merge) return e;
   const int quads_shift = a.head_dim == 128 ? 5 : 4;
   const int64_t parts = ((((int64_t)a.q_len * a.num_q_heads) << quads_shift) + 255) / 256;

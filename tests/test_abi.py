@@ -125,10 +125,22 @@ def test_the_kernel_of_128_rows_keeps_its_cuts_beside_the_one_of_256(H, hq, batc
     128 rows, with leave to cut its long contexts as if there were no other (c - 1 cuts a sequence where
     batch * c workgroups fill the chip best), though the one of 256 rows may do without."""
     desc = d(H=H, D=128, nblk=64)
-    p, wide = plan(desc, batch, q_len, hq, max_len), (C.c_int64 * 2)()
+    p, wide = plan(desc, batch, q_len, hq, max_len), (C.c_int64 * 3)()
     assert kvq.prof_lib().kvq_profile_wide(C.byref(desc), batch, q_len, hq, max_len, wide) == kvq.OK
     assert p["many_rows"] == 2 and wide[0] > 0 and wide[1] == 0
     assert p["extra_pieces"] == cuts
+
+
+@pytest.mark.parametrize("mode,H,hq,batch,q_len,max_len,wide", [
+    (0, 8, 32, 8, 512, 4608, True), (1, 8, 32, 1, 512, 16896, True), (3, 8, 32, 8, 512, 4608, True),
+    (2, 8, 32, 8, 512, 4608, False), (4, 8, 32, 8, 512, 4608, False), (5, 8, 32, 8, 512, 4608, False),
+    (0, 8, 32, 8, 512, 4096, True), (0, 8, 32, 8, 512, 4032, False),      # eight chunks to a context
+    (0, 64, 64, 4, 130, 1409, True), (0, 64, 64, 4, 130, 1344, False),    # 60 us: 62.8 and 60.2 or 57.6 by the estimate
+    (0, 64, 64, 4, 128, 4096, False), (0, 8, 32, 8, 512, 2 ** 22 + 1, False)])
+def test_which_calls_may_go_to_the_kernel_of_256_rows(mode, H, hq, batch, q_len, max_len, wide):
+    """int8 and e4m3 codes, more than 128 rows, long walks that are much alike, a block table that fits in LDS."""
+    desc = d(mode=mode, H=H, D=128, nblk=64, bs=256 if max_len > 2 ** 20 else 16)
+    assert plan(desc, batch, q_len, hq, max_len)["many_rows"] == (0 if mode == 5 else 1 + wide)
 
 
 @pytest.mark.parametrize("mode,D,q_len,prefix,used", [

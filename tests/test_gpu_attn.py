@@ -434,9 +434,11 @@ WIDE = {  # lengths, query tokens, query heads, kv heads, declared bound, whethe
     "dead wavefronts": ([1500, 1337, 1100, 1499], 130, 64, 64, 1500, True),
     "a row block of one row": ([2200, 2113, 2049, 2200], 257, 32, 32, 2200, True),
     "cut": ([9000], 512, 32, 8, 9000, True),
-    "cut, no group for some rows": ([5700], 512, 32, 8, 9000, True),
-    "just too short": ([1300, 512, 1090, 768], 130, 64, 64, 1500, False),
-    "just long enough": ([1300, 512, 1090, 769], 130, 64, 64, 1500, True),
+    "cut, below the bound": ([7000], 512, 32, 8, 9000, True),
+    "just too short": ([1300, 1200, 1090, 832], 130, 64, 64, 1500, False),
+    "just long enough": ([1300, 1200, 1090, 833], 130, 64, 64, 1500, True),
+    "one just too short": ([1500, 1500, 1480, 704], 130, 64, 64, 1500, False),
+    "one just long enough": ([1500, 1500, 1480, 705], 130, 64, 64, 1500, True),
     "short": ([130, 191, 257, 200], 130, 64, 64, 1500, False),
     # one of the two kernels may cut contexts, the other may not; the merge is launched for both
     "not cut, the other kernel would": ([3000, 2990, 2900, 3000, 2950, 2999, 2937], 300, 16, 2, 3000, True),
@@ -450,18 +452,21 @@ WIDE = {  # lengths, query tokens, query heads, kv heads, declared bound, whethe
 @pytest.mark.parametrize("case", sorted(WIDE))
 def test_workgroups_of_256_rows_against_the_streaming_kernels(mode, case):
     """Where contexts of max_seq_len would fill the chip with workgroups of 256 rows, the lengths decide on the
-    device between that kernel and the one of 128 rows.  Either must agree with the streaming kernels,
+    device between that kernel and the one of 128 rows (for int8 and e4m3 codes).  Either must agree with the streaming kernels,
     also under a negative softmax scale.  Both sides are within the oracle's bound elsewhere; f16
     probabilities differ by 2^-12 of a row's largest term at most (measured 1e-4)."""
     import ctypes as C
     from paper_2605_29639_amd import kvq
     lens, q_len, hq, hkv, bound, long = WIDE[case]
     groups = [-(-l // 64) for l in lens]
-    assert (sum(groups) >= len(lens) * -(-bound // 64) * 5 // 8) == long
+    codes = mode in (W.MODE_INT8, W.MODE_FP8, W.MODE_FP8_TENSOR)
     wl = W.custom("wide", mode, lens, q_len, hq, hkv, 128, 16, seed=len(case))
     cache, scales, desc = gpu_fill(wl)
     prof, out = kvq.prof_lib(), (C.c_int64 * 8)()
-    assert prof.kvq_profile_plan(C.byref(desc), len(lens), q_len, hq, bound, 0, 0, out) == kvq.OK and out[0] == 2
+    assert prof.kvq_profile_plan(C.byref(desc), len(lens), q_len, hq, bound, 0, 0, out) == kvq.OK and out[0] == 1 + codes
+    if codes:
+        assert prof.kvq_profile_wide(C.byref(desc), len(lens), q_len, hq, bound, out) == kvq.OK
+        assert (sum(groups) >= out[0] and min(groups) >= out[2]) == long
     for sign in (1.0, -1.0):
         signed = type("Signed", (type(wl),), {"sm_scale": sign * abs(wl.sm_scale)})
         wl.__class__ = signed
