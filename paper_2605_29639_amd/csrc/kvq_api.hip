@@ -186,22 +186,26 @@ bool many_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t m
 // sums together in LDS, so a second launch and a round trip of partials through memory fall away; what it
 // costs is that a compute unit's share is whole pairs, however few there are and however long.  All in
 // units of microseconds and 64-token groups, fitted to measurements with 1 to 60 sequences of 40 to
-// 8000 tokens, 8 kv heads: a group takes a wavefront `alone` where few compute units have one and
+// 8000 tokens, 8 kv heads, equal lengths: a group takes a wavefront `alone` where few compute units have one and
 // `crowded` where all have (memory, or for int4 and two row tiles arithmetic); beside that a workgroup per
-// pair takes 3.7 and the flat list with its reduce 8.3.  Bounds looser than the contexts make this path
-// rarer, never slower.  At most 8 groups to a wavefront: beyond, uneven lengths cost more than the
-// reduce.  us a call, flat list -> workgroup per pair: 4 query heads per kv head, int8, 1 x 600 tokens 8.4 -> 7.7,
-// 12 x 1500 17.1 -> 12.9, 32 x 600 16.0 -> 10.7, 32 of 300 to 2500 23.5 -> 20.9; 32 query rows, 31 x 600
-// 26.5 -> 13.3; not taken: 12 x 4000 24.2 -> 27.4, 1 x 2500 9.9 -> 13.6.  With more pairs than compute
-// units a workgroup has half of the wavefronts, and two share one.
-int32_t pair_waves(const kvq_cache_desc_t* d, int64_t pairs, int64_t groups, int row_tiles, int64_t waves) {
+// pair takes 3.7 and the flat list with its reduce 8.3.  us a call, flat list -> workgroup per pair: 4 query heads
+// per kv head, int8, 1 x 600 tokens 8.4 -> 7.7, 12 x 1500 17.1 -> 12.9, 32 x 600 16.0 -> 10.7, 32 of 300 to
+// 2500 23.5 -> 20.9; 32 query rows, 31 x 600 26.5 -> 13.3; not taken: 12 x 4000 24.2 -> 27.4, 1 x 2500
+// 9.9 -> 13.6.  With more pairs than compute units a workgroup has half of the wavefronts, and two share one.
+// A long context among short ones keeps its own workgroup for as many `rounds` as a wavefront has groups, where
+// the flat list would spread it over the chip, so few rounds are allowed.  Of 67733 random calls with up to 5,
+// mixtures of long and short among them, 8 took more than 1.03 of the flat list's time, 1.08 at most; at 6
+// to 8 rounds it was 44 of 1170, up to 1.35 (e4m3, one query row, 63 sequences of 40 to
+// 1819 tokens, 16.5 -> 22.2).  Where a row's reduce costs the flat list least (bf16 with one row at head_dim
+// 128) and for group-scaled int4 the line lies at 3 rounds: 0.97 and 1.00 at most, at 4 and 5 up to 1.13.
+int32_t pair_waves(const kvq_cache_desc_t* d, int64_t pairs, int64_t rows, int64_t groups, int row_tiles, int64_t waves) {
   const int per_simd = kvq::waves_per_simd(d->mode, d->head_dim, row_tiles);
   const int64_t cus = waves / 8;
   if (pairs < 1 || pairs > 2 * cus || groups < 1) return 0;
   const int64_t team = pairs <= cus ? 4 * per_simd : 2 * per_simd, slots = pairs <= cus ? cus : 2 * cus;
   const int64_t rounds = (groups + team - 1) / team;
-  if (rounds > 8) return 0;
   const bool small = d->head_dim == 64, bf16 = d->mode == KVQ_BF16_PLAIN;
+  if (rounds > ((bf16 && !small && rows == 1) || d->mode == KVQ_INT4_GROUP32 ? 3 : 5)) return 0;
   double alone = small ? 1.4 : 2.1, crowded = small ? 2.65 : bf16 ? 4.6 : 5.0;
   if (d->mode == KVQ_INT4_TOKEN_HEAD) crowded = 2.9;
   if (d->mode == KVQ_INT4_GROUP32) alone = 2.9, crowded = 3.2;
@@ -315,7 +319,7 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
   // (A call whose pairs get a workgroup each needs no prefix kernel either, and the same whether it has a
   // hint or not.)
   plan->pair_waves = plan->many_rows || chunk_tokens > 0
-                         ? 0 : pair_waves(d, batch * pairs, ((int64_t)max_seq_len + 63) / 64, plan->row_tiles, waves);
+                         ? 0 : pair_waves(d, batch * pairs, rows, ((int64_t)max_seq_len + 63) / 64, plan->row_tiles, waves);
   if (plan->pair_waves > 0) plan->shared_groups = 0;
   plan->wide_groups = plan->wide_least = 0;
   if (plan->many_rows)

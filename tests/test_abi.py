@@ -143,6 +143,19 @@ def test_which_calls_may_go_to_the_kernel_of_256_rows(mode, H, hq, batch, q_len,
     assert plan(desc, batch, q_len, hq, max_len)["many_rows"] == (0 if mode == 5 else 1 + wide)
 
 
+@pytest.mark.parametrize("mode,D,hq,batch,team,rounds", [
+    (0, 128, 32, 32, 8, 5), (1, 64, 8, 32, 8, 5), (4, 128, 32, 32, 8, 5), (2, 64, 8, 32, 4, 5), (2, 128, 32, 32, 4, 5),
+    (3, 128, 64, 40, 4, 5), (2, 128, 8, 32, 4, 3), (5, 128, 32, 32, 8, 3), (5, 128, 64, 40, 4, 3)])
+def test_a_workgroup_for_each_pair_walks_few_groups(mode, D, hq, batch, team, rounds):
+    """The plan knows a bound on the lengths and not their mixture: one long context among short ones would wait
+    for its own workgroup alone, so a wavefront never has more than five groups one after another (three where
+    the flat list is cheapest)."""
+    desc = d(mode=mode, H=8, D=D, nblk=64)
+    last = 64 * team * rounds
+    waves = [kvq.prof_lib().kvq_profile_pair_waves(C.byref(desc), batch, 1, hq, n, 0) for n in (last, last + 1, 2 * last)]
+    assert waves == [team, 0, 0]
+
+
 @pytest.mark.parametrize("mode,D,q_len,prefix,used", [
     (0, 128, 4, 64, True), (0, 128, 5, 64, True),                                  # streaming calls: always
     (0, 128, 12, 64, False), (1, 128, 12, 6144, False), (2, 64, 15, 8192, False),   # above 64 rows: never
