@@ -376,6 +376,8 @@ def blocks_export(cache, scales, desc, block_ids, packed_cache, packed_scales, s
     rc = (_fast_module or _fast()).move(True, cache, scales, desc, block_ids, packed_cache, packed_scales, stream)
     if rc == OK:
         return
+    if rc == E_HIP or rc == E_BAD_INDEX:
+        raise KvqError(rc, "kvq_blocks_export")
     import torch
     rc = lib().kvq_blocks_export(_dev(cache, torch.uint8, "cache"), _dev(scales, torch.float32, "scales"),
                                  C.byref(desc), _dev(block_ids, torch.int32, "block_ids"),
@@ -389,6 +391,8 @@ def blocks_import(packed_cache, packed_scales, desc, block_ids, cache, scales, s
     rc = (_fast_module or _fast()).move(False, cache, scales, desc, block_ids, packed_cache, packed_scales, stream)
     if rc == OK:
         return
+    if rc == E_HIP or rc == E_BAD_INDEX:
+        raise KvqError(rc, "kvq_blocks_import")
     import torch
     rc = lib().kvq_blocks_import(_any(packed_cache, torch.uint8, "packed_cache"),
                                  _any(packed_scales, torch.float32, "packed_scales"), C.byref(desc),
