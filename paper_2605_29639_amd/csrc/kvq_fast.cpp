@@ -25,6 +25,7 @@ decltype(&kvq_cache_bytes) g_cache_bytes = nullptr;
 decltype(&kvq_scales_bytes) g_scales_bytes = nullptr;
 PyObject* g_get_device = nullptr;  // torch._C._cuda_getDevice
 PyObject* g_get_stream = nullptr;  // torch._C._cuda_getCurrentRawStream
+PyObject* g_desc_type = nullptr;   // kvq.CacheDesc
 
 // A plain contiguous device tensor of the type, or nullptr.  (A subclass may stand for something else.)
 const at::Tensor* plain(PyObject* o, at::ScalarType type) {
@@ -36,9 +37,10 @@ const at::Tensor* plain(PyObject* o, at::ScalarType type) {
   return &t;
 }
 
+// (other objects that lend a buffer of a descriptor's size are none)
 bool get_desc(PyObject* o, kvq_cache_desc_t* desc) {
   Py_buffer view;
-  if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) {
+  if ((PyObject*)Py_TYPE(o) != g_desc_type || PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) {
     PyErr_Clear();
     return false;
   }
@@ -196,10 +198,10 @@ PyObject* fast_move(PyObject* const* a, Py_ssize_t n) {
   return PyLong_FromLong(rc);
 }
 
-// bind(addresses of the seven library functions, _cuda_getDevice, _cuda_getCurrentRawStream)
+// bind(addresses of the seven library functions, _cuda_getDevice, _cuda_getCurrentRawStream, CacheDesc)
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  if (n != 9) {
-    PyErr_SetString(PyExc_TypeError, "bind takes seven addresses and two callables");
+  if (n != 10) {
+    PyErr_SetString(PyExc_TypeError, "bind takes seven addresses, two callables and a type");
     return nullptr;
   }
   void* p[7];
@@ -215,8 +217,10 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
   g_import = (decltype(g_import))p[6];
   Py_INCREF(a[7]);
   Py_INCREF(a[8]);
+  Py_INCREF(a[9]);
   g_get_device = a[7];
   g_get_stream = a[8];
+  g_desc_type = a[9];
   g_write = (decltype(g_write))p[4];
   Py_RETURN_NONE;
 }

@@ -161,7 +161,7 @@ def _fast():
         address = [C.cast(f, C.c_void_p).value for f in (
             L.kvq_cache_bytes, L.kvq_scales_bytes, L.paged_decode_attn, L.paged_decode_attn_prefix,
             L.kv_quant_write, L.kvq_blocks_export, L.kvq_blocks_import)]
-        module.bind(*address, c._cuda_getDevice, c._cuda_getCurrentRawStream)
+        module.bind(*address, c._cuda_getDevice, c._cuda_getCurrentRawStream, CacheDesc)
         _fast_module = module
     return _fast_module
 
