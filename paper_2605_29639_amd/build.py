@@ -39,11 +39,21 @@ def _link(objs, lib):
 
 
 def _fast():
-    """The native half of the Python binding, on torch's headers and libraries."""
-    import torch
-    from torch.utils import cpp_extension
+    """The native half of the Python binding, on torch's headers and libraries (without them there is none,
+    and kvq.py does without)."""
+    if os.path.exists(LIB_FAST):
+        os.remove(LIB_FAST)   # (one of another torch would be worse than none)
+    try:
+        import torch
+        from torch.utils import cpp_extension
+        paths = cpp_extension.include_paths()
+    except ImportError:
+        paths = []
+    if not any(os.path.exists(os.path.join(p, "torch", "csrc", "autograd", "python_variable.h")) for p in paths):
+        print("no torch headers: %s is not built" % os.path.basename(LIB_FAST))
+        return
     tmp = LIB_FAST + ".tmp%d" % os.getpid()
-    include = [x for p in cpp_extension.include_paths() for x in ("-isystem", p)]
+    include = [x for p in paths for x in ("-isystem", p)]
     subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
                            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
                            "-I", sysconfig.get_paths()["include"], *include, os.path.join(CSRC, "kvq_fast.cpp"),

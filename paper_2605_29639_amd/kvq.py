@@ -147,17 +147,24 @@ _fast_module = None
 
 
 def _fast():
-    """The native module, bound to the library's functions by the first call that needs it."""
+    """The native module, bound to the library's functions by the first call that needs it.  It only saves time:
+    where it was not built, or does not fit this torch, all calls take the way through ctypes."""
     global _fast_module
     if _fast_module is None:
         c, L = _torch()._C, lib()
-        if not hasattr(c, "_cuda_getCurrentRawStream"):   # (as in _stream: all calls take the long way)
+        try:
+            if not hasattr(c, "_cuda_getCurrentRawStream"):   # (as in _stream)
+                raise ImportError("torch has no _cuda_getCurrentRawStream")
+            if not os.path.exists(FAST_PATH):
+                raise ImportError("it is not built: run `python -m paper_2605_29639_amd.build`")
+            from . import _kvq_fast as module
+        except ImportError as e:
             from types import SimpleNamespace
-            _fast_module = SimpleNamespace(write=lambda *a: None, attn=lambda *a: None, move=lambda *a: None)
+            import warnings
+            warnings.warn("calls take about 5 us longer each without %s: %s" % (os.path.basename(FAST_PATH), e),
+                          RuntimeWarning, stacklevel=3)
+            _fast_module = SimpleNamespace(**dict.fromkeys(("write", "attn", "move"), lambda *a: None))
             return _fast_module
-        if not os.path.exists(FAST_PATH):
-            raise RuntimeError("%s is not built: run `python -m paper_2605_29639_amd.build`" % FAST_PATH)
-        from . import _kvq_fast as module
         address = [C.cast(f, C.c_void_p).value for f in (
             L.kvq_cache_bytes, L.kvq_scales_bytes, L.paged_decode_attn, L.paged_decode_attn_prefix,
             L.kv_quant_write, L.kvq_blocks_export, L.kvq_blocks_import)]

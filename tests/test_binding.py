@@ -26,3 +26,22 @@ def test_a_call_that_reached_the_device_is_not_made_again(call, code, monkeypatc
     with pytest.raises(kvq.KvqError) as e:
         CALLS[call](kvq.make_desc(0, 8, 16, 2, 64))
     assert e.value.code == code and message in str(e.value)
+
+
+@pytest.mark.parametrize("why", ["not built", "does not load"])
+def test_without_the_native_module_calls_go_through_ctypes(why, tmp_path, monkeypatch):
+    """libkvq.so alone does: the module saves time and nothing else.  (CPU tensors of the right shapes get as far
+    as the device check of the route through ctypes.)"""
+    import sys
+    import torch
+    desc = kvq.make_desc(0, 4, 16, 2, 64)
+    cache, scales = kvq.alloc_cache(desc, device="cpu")
+    k, slots = torch.zeros((3, 2, 64), dtype=torch.bfloat16), torch.zeros(3, dtype=torch.int64)
+    monkeypatch.setattr(kvq, "_fast_module", None)
+    if why == "not built":
+        monkeypatch.setattr(kvq, "FAST_PATH", str(tmp_path / "_kvq_fast.so"))
+    else:
+        monkeypatch.delattr("paper_2605_29639_amd._kvq_fast", raising=False)
+        monkeypatch.setitem(sys.modules, "paper_2605_29639_amd._kvq_fast", None)
+    with pytest.warns(RuntimeWarning, match="_kvq_fast"), pytest.raises(TypeError, match="device tensor"):
+        kvq.kv_quant_write(k, k, slots, cache, scales, desc)
