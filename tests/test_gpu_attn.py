@@ -319,6 +319,7 @@ PREFIX_LENS = {
     "ragged": [700, 256, 1500, 333, 257],       # one sequence is nothing but the prefix
     "one": [1000],                              # a single pair per kv head
     "many": [256 + 37 * (i % 9) for i in range(70)],   # more sequences than a wavefront has lanes
+    "crowd": [256 + 29 * (i % 5) for i in range(260)],   # more pairs than get a workgroup each
 }
 
 
@@ -336,6 +337,8 @@ def test_shared_prefix_is_read_through_stacked_rows(mode, q_len, lens):
     sequences than a wavefront has lanes.  A prefix longer than the shortest sequence is dropped
     (on the host if it exceeds max_seq_len, else on the device), as is one below 64 tokens or
     with a single sequence: bit for bit paged_decode_attn's output then."""
+    import ctypes as C
+    from paper_2605_29639_amd import kvq
     wl = W.custom("prefix", mode, PREFIX_LENS[lens], q_len, 8, 2, 128, 16,
                   seed=90 + mode + q_len, shared_prefix=256)
     assert (wl.block_tables[:, :16] == wl.block_tables[0, :16]).all()
@@ -343,7 +346,11 @@ def test_shared_prefix_is_read_through_stacked_rows(mode, q_len, lens):
     want = oracle_out(wl, oc, osc)
     cache, scales, desc = upload_oracle_cache(wl, oc, osc)
     shortest = min(PREFIX_LENS[lens])
+    plan = (C.c_int64 * 8)()
     for chunk in (0, 128, 512):
+        assert kvq.prof_lib().kvq_profile_plan(C.byref(desc), wl.batch, q_len, 8, wl.max_seq_len, chunk, 256, plan) == kvq.OK
+        # (short contexts of few sequences have no use for it: a workgroup for each pair)
+        assert (plan[3] == 4) == (lens in ("ragged", "crowd") or lens == "many" and (chunk > 0 or mode == W.MODE_BF16))
         plain = gpu_attention(wl, cache, scales, desc, chunk_tokens=chunk)
         assert attn_err(plain, want) <= TOL
         for hint in (256, 200, 64, 63, 4096) + ((shortest + 64,) if lens != "one" else ()):
@@ -430,7 +437,7 @@ def test_contexts_are_cut_by_their_lengths(mode, D, G, q_len, lens):
         assert attn_err(got, want) <= 5e-4, bound
 
 
-WIDE = {  # lengths, query tokens, query heads, kv heads, declared bound, whether the lengths are long for it
+WIDE = {  # lengths, query tokens, query heads, kv heads, declared bound, whether the lengths are long for it[, block size]
     "dead wavefronts": ([1500, 1337, 1100, 1499], 130, 64, 64, 1500, True),
     "a row block of one row": ([2200, 2113, 2049, 2200], 257, 32, 32, 2200, True),
     "cut": ([9000], 512, 32, 8, 9000, True),
@@ -445,6 +452,11 @@ WIDE = {  # lengths, query tokens, query heads, kv heads, declared bound, whethe
     "one long, cut by the other kernel": ([3000, 301, 400, 310, 577, 300, 640], 300, 16, 2, 3000, False),
     "cut, the other kernel would not": ([5000, 4990, 4950, 4999], 100, 64, 16, 5000, True),
     "one long, not cut by the other kernel": ([5000, 300, 100, 700], 100, 64, 16, 5000, False),
+    "a walk of more table entries than threads": ([40000], 512, 32, 8, 40000, True),   # (four pieces of 626 entries)
+    "32-token blocks": ([2200, 2113, 2049, 2200], 257, 32, 32, 2200, True, 32),
+    "64-token blocks, a walk from inside a block": ([9000], 512, 32, 8, 9000, True, 64),
+    "128-token blocks, cut": ([8990], 512, 32, 8, 9000, True, 128),
+    "256-token blocks": ([1500, 1337, 1100, 1499], 130, 64, 64, 1500, True, 256),
 }
 
 
@@ -457,10 +469,10 @@ def test_workgroups_of_256_rows_against_the_streaming_kernels(mode, case):
     probabilities differ by 2^-12 of a row's largest term at most (measured 1e-4)."""
     import ctypes as C
     from paper_2605_29639_amd import kvq
-    lens, q_len, hq, hkv, bound, long = WIDE[case]
+    lens, q_len, hq, hkv, bound, long, bs = (*WIDE[case], 16)[:7]
     groups = [-(-l // 64) for l in lens]
     codes = mode in (W.MODE_INT8, W.MODE_FP8, W.MODE_FP8_TENSOR)
-    wl = W.custom("wide", mode, lens, q_len, hq, hkv, 128, 16, seed=len(case))
+    wl = W.custom("wide", mode, lens, q_len, hq, hkv, 128, bs, seed=len(case))
     cache, scales, desc = gpu_fill(wl)
     prof, out = kvq.prof_lib(), (C.c_int64 * 8)()
     assert prof.kvq_profile_plan(C.byref(desc), len(lens), q_len, hq, bound, 0, 0, out) == kvq.OK and out[0] == 1 + codes
