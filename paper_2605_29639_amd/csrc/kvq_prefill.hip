@@ -391,14 +391,14 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_kernel(const
     v_from = (uint64_t)entry_v * block_stride + ((tv & (uint32_t)(bs - 1)) * RB + v_fixed);
     asm volatile("" : "+v"(k_from), "+v"(v_from));  // (here, not where they are used)
   };
-  auto request_scales = [&](int g) {  // the same; lane = token
+  auto request_scales = [&](int g, float& sk, float& sv) {  // the same; lane = token
     uint32_t tk, tv;
     positions(g, tk, tv);
     const float* from = scales + ((uint64_t)entry_v * s_block_stride + (TOKEN_SCALE ? (uint32_t)(h * bs + m16) + (tv & (uint32_t)(bs - 1)) : (MODE == KVQ_FP8E4M3_TENSOR ? 0u : (uint32_t)h)));
-    sk_next = from[0];
-    sv_next = from[s_kv];
+    sk = from[0];
+    sv = from[s_kv];
   };
-  auto request = [&]() {
+  auto request = [&](uintx4 (&rk)[WP], uintx4 (&rv)[WP]) {
 #pragma unroll
     for (int x = 0; x < WP; ++x) {
       const int pc = first + x;
@@ -411,34 +411,34 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_kernel(const
       rv[x] = *(const uintx4*)(cache + v_from + (PLAIN ? (pc & 1) * (16 * D) + 256 * (pc >> 1) : 256 * pc));
     }
   };
-  auto publish_k = [&](int x, int buf) {
-    asm volatile("" : "+v"(rk[x]));  // (converted here, not earlier)
+  auto publish_k = [&](uintx4& codes, int x, int buf) {
+    asm volatile("" : "+v"(codes));  // (converted here, not earlier)
     const int pc = first + x, u = pc / KJ, at = pc % KJ;
     if constexpr (PLAIN) {  // bf16 rows are operands as they are; the LDS arrays hold their bits
-      k_ops[buf][u][at][lane] = __builtin_bit_cast(half8, rk[x]);
+      k_ops[buf][u][at][lane] = __builtin_bit_cast(half8, codes);
     } else if constexpr (INT4) {  // word st of the lane's piece holds the 8 channels of step st
 #pragma unroll
-      for (int st = 0; st < 4; ++st) k_ops[buf][u][st][lane] = cvt_int4(rk[x][st]);
+      for (int st = 0; st < 4; ++st) k_ops[buf][u][st][lane] = cvt_int4(codes[st]);
     } else {
-      k_ops[buf][u][2 * at][lane] = cvt8<MODE>(rk[x][0], rk[x][1]);
-      k_ops[buf][u][2 * at + 1][lane] = cvt8<MODE>(rk[x][2], rk[x][3]);
+      k_ops[buf][u][2 * at][lane] = cvt8<MODE>(codes[0], codes[1]);
+      k_ops[buf][u][2 * at + 1][lane] = cvt8<MODE>(codes[2], codes[3]);
     }
   };
-  auto publish_v = [&](int x, int half) {
-    asm volatile("" : "+v"(rv[x]));
+  auto publish_v = [&](uintx4& codes, int x, int half) {
+    asm volatile("" : "+v"(codes));
     const int pc = first + x;
     if constexpr (PLAIN) {
-      v_ops[half][pc >> 1][pc & 1][lane] = __builtin_bit_cast(half8, rv[x]);
+      v_ops[half][pc >> 1][pc & 1][lane] = __builtin_bit_cast(half8, codes);
     } else if constexpr (INT4) {
 #pragma unroll
-      for (int w4 = 0; w4 < 4; ++w4) v_ops[half][2 * pc + (w4 >> 1)][w4 & 1][lane] = cvt_int4(rv[x][w4]);
+      for (int w4 = 0; w4 < 4; ++w4) v_ops[half][2 * pc + (w4 >> 1)][w4 & 1][lane] = cvt_int4(codes[w4]);
     } else {
-      v_ops[half][pc][0][lane] = cvt8<MODE>(rv[x][0], rv[x][1]);
-      v_ops[half][pc][1][lane] = cvt8<MODE>(rv[x][2], rv[x][3]);
+      v_ops[half][pc][0][lane] = cvt8<MODE>(codes[0], codes[1]);
+      v_ops[half][pc][1][lane] = cvt8<MODE>(codes[2], codes[3]);
     }
   };
   // V bits of tokens past the last position are cleared first: a NaN times 0 is NaN
-  auto clear_missing = [&](int g) {
+  auto clear_missing = [&](int g, uintx4 (&rv)[WP]) {
     if (!(PLAIN || FP8) || (g << 6) + 64 <= L) return;
     const int live = L - ((g << 6) + 16 * g4);  // tokens of this lane's sub-block below L
 #pragma unroll
@@ -480,6 +480,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_kernel(const
     if constexpr (PLAIN) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
     else return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
   };
+  float scales_here[3] = {};  // e4m3: the lane's scales of the group in hand
   float mx[NT];
   constexpr float skp = 0.0f, lsv = 0.0f;  // (the maxima of formats without token scales are those of S)
   Operand op[2][4];  // operands of two chunks of eight matrix instructions
@@ -520,12 +521,14 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_kernel(const
         if constexpr (PLAIN) d = mma(op[(QC + c) & 1][x], pb[nt][2 + (x >> 1)], d);
       }
   };
-  // N matrix instructions, with READS LDS reads dealt out between them and VALU vector ones behind each
+  // N matrix instructions, an LDS read behind each of the first READS and VALU vector ones behind all.  (The reads
+  // dealt out over all N came too late for the next chunk where a workgroup has its compute unit to itself:
+  // 3 x 1000 tokens over 3000 int8 173.5 -> 171 us, int4 180 -> 177.)
   auto pace = [&](auto N, auto READS, auto VALU) {
     static_for<decltype(N)::value>([&](auto X) {
       constexpr int x = decltype(X)::value, n = decltype(N)::value, r = decltype(READS)::value;
       __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-      constexpr int now = (x + 1) * r / n - x * r / n;
+      constexpr int now = x < r ? 1 : 0;
       if constexpr (now > 0) __builtin_amdgcn_sched_group_barrier(0x100, now, 0);
       if constexpr (decltype(VALU)::value > 0) __builtin_amdgcn_sched_group_barrier(0x2, decltype(VALU)::value, 0);
       __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
@@ -546,9 +549,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_kernel(const
     }
     float skp = fabsf(p.scale_log2), lsv = 0.0f, rsv = 1.0f;
     if constexpr (FP8) {
-      skp = s_ops[sbuf][0][lane];
-      lsv = s_ops[sbuf][1][lane];
-      rsv = s_ops[sbuf][2][lane];
+      skp = scales_here[0];
+      lsv = scales_here[1];
+      rsv = scales_here[2];
     }
     if constexpr (TAIL) {
 #pragma unroll
@@ -590,6 +593,10 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_kernel(const
   // maxima (unmasked) worked out while the last ones' are contracted; and P.V, the next group's codes
   // converted into the other half under it.
   auto contract_k = [&](int half) {
+    if constexpr (FP8) {
+#pragma unroll
+      for (int x = 0; x < 3; ++x) scales_here[x] = s_ops[half][x][lane];
+    }
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       mx[nt] = -INFINITY;
@@ -614,9 +621,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_kernel(const
     softmax_logits<MODE, NT, false>(S, 3, k4[1], l4[1], skp, lsv, 0, nrow, mx);
   };
   constexpr int PIECES = 2 * WP;
-  auto publish = [&](int x, int half) {
-    if (x < WP) publish_k(x, half);
-    else publish_v(x - WP, half);
+  auto publish = [&](uintx4 (&rk)[WP], uintx4 (&rv)[WP], int x, int half) {
+    if (x < WP) publish_k(rk[x], x, half);
+    else publish_v(rv[x - WP], x - WP, half);
   };
   auto contract_v = [&](int half) {
     static_for<PC>([&](auto C) {
@@ -624,7 +631,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_kernel(const
       mm_v(c);
       if constexpr (c + 1 < PC) read_v(c + 1, half);
 #pragma unroll
-      for (int x = c * PIECES / PC; x < (c + 1) * PIECES / PC; ++x) publish(x, half ^ 1);
+      for (int x = c * PIECES / PC; x < (c + 1) * PIECES / PC; ++x) publish(rk, rv, x, half ^ 1);
       pace(std::integral_constant<int, PLAIN ? 16 : 8>{}, std::integral_constant<int, c + 1 < PC ? 4 : 0>{}, std::integral_constant<int, PLAIN ? 0 : kPace>{});
     });
   };
@@ -633,33 +640,44 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_kernel(const
   const bool live = __builtin_amdgcn_readfirstlane((int)at.wave_live) != 0;
   const int n = ng - g0;
   if (n > 0) {  // (a chunk's first rows see fewer groups than there may be pieces)
+    // (start: the entries of three groups, then the codes of two, a round trip each.  Asked for group by group
+    // they took contexts of one group two round trips more: 113 x 64 tokens over 64, 64 / 8 heads, int8 102 -> 90 us,
+    // e4m3 100 -> 90.)
     const bool scale_wave = !PLAIN && wv == 0;
+    uintx4 first_k[WP], first_v[WP];
+    float sk = 0.0f, sv = 0.0f;
     fetch_entries(g0);
-    locate(g0);
-    request();
-    if (scale_wave) {
-      request_scales(g0);
-      publish_scales(0, sk_next, sv_next);
-    }
-    clear_missing(g0);
-#pragma unroll
-    for (int x = 0; x < PIECES; ++x) publish(x, 0);
+    const uint32_t k0 = entry_k, v0 = entry_v;
     fetch_entries(g0 + 1);
-    locate(g0 + 1);
-    if (scale_wave) request_scales(g0 + 1);
+    const uint32_t k1 = entry_k, v1 = entry_v;
     fetch_entries(g0 + 2);
-    request();
+    const uint32_t k2 = entry_k, v2 = entry_v;
+    entry_k = k0, entry_v = v0;
+    locate(g0);
+    request(first_k, first_v);
+    if (scale_wave) request_scales(g0, sk, sv);
+    entry_k = k1, entry_v = v1;
+    locate(g0 + 1);
+    request(rk, rv);
+    if (scale_wave) {
+      request_scales(g0 + 1, sk_next, sv_next);
+      publish_scales(0, sk, sv);
+    }
+    entry_k = k2, entry_v = v2;
+    clear_missing(g0, first_v);
+#pragma unroll
+    for (int x = 0; x < PIECES; ++x) publish(first_k, first_v, x, 0);
     __syncthreads();
     auto prepare = [&](int i) {  // scales of group i + 1 published, of i + 2 requested, its codes located
       if (scale_wave) {
         publish_scales(i + 1, sk_next, sv_next);
-        request_scales(g0 + i + 2);
+        request_scales(g0 + i + 2, sk_next, sv_next);
       }
       locate(g0 + i + 2);
     };
     auto advance = [&](int i) {
       fetch_entries(g0 + i + 3);
-      request();
+      request(rk, rv);
       __syncthreads();
     };
     if (live) {
@@ -670,16 +688,16 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_kernel(const
         if ((g << 6) + 64 > n_min) vector_phase(std::true_type{}, g, half);
         else vector_phase(std::false_type{}, g, half);
         read_v(0, half);
-        clear_missing(min(g + 1, ng - 1));
+        clear_missing(min(g + 1, ng - 1), rv);
         contract_v(half);
         advance(i);
       }
     } else {
       for (int i = 0; i < n; ++i) {
         prepare(i);
-        clear_missing(min(g0 + i + 1, ng - 1));
+        clear_missing(min(g0 + i + 1, ng - 1), rv);
 #pragma unroll
-        for (int x = 0; x < PIECES; ++x) publish(x, ~i & 1);
+        for (int x = 0; x < PIECES; ++x) publish(rk, rv, x, ~i & 1);
         advance(i);
       }
     }
