@@ -117,13 +117,14 @@ int64_t equal_pieces(int64_t slots, int64_t walks, int64_t groups, int64_t room,
 // second launch finds nothing to do); over 4096 tokens, same bound: 117, 63 and 63.
 // The kernel for kWideRows gets int8 and e4m3 calls whose walks all take long and are much alike: both kernels
 // are launched then, and the lengths decide on the device which of them does the call, this one where the
-// contexts hold three quarters of what the bound allows and the shortest has half of it.  Over 1586
-// random calls with lengths near the bound, its time by that of the kernel for 128 rows: int8 0.91 and e4m3
-// 0.92 on average and 0.98 at most; without the lines at 60 us and at eight chunks to a context (a chunk's
-// first rows then see much less than its last) up to 1.08; bf16 0.95 and int4 0.96, up to 1.02, which is not
-// worth a second kernel.  With lengths as far apart as allowed 0.94, up to 1.04; with a quarter of the
-// sequences short 1.12.  The kernel for 128 rows alone -> both launched: 8 x 512 tokens over 4608 int8
-// 335 -> 319 us, e4m3 302 -> 290; 1 x 512 over 16896 171 -> 159, 157 -> 147.  The launch that ends at once takes
+// contexts hold three quarters of what the bound allows and the shortest has half of it.  In 3915 random
+// calls, those the rule takes with lengths near the bound: its time by that of the kernel for 128 rows 0.924
+// (int8) and 0.932 (e4m3) on average, 0.97 and 1.01 at most; with lengths as far apart as allowed 0.965, up to
+// 1.05.  Below 100 us the launch that ends at once takes back what it gains (4 x 256 tokens over 3000: int8
+// 80 -> 75, e4m3 71.7 -> 70.8 without that launch), with chunks of more than an eighth of the context (whose first
+// rows see much less than their last) it loses up to 8 %, with a quarter of the sequences short 12 %; bf16 and
+// int4 gain half as much.  The kernel for 128 rows alone -> both launched: 8 x 512 tokens over 4608 int8
+// 346 -> 333 us, e4m3 309 -> 298; 1 x 512 over 16896 175 -> 163, 158 -> 149.  The launch that ends at once takes
 // 2.1 us ahead of or behind the other (3 to 4 above 512 workgroups), also where the contexts are far
 // below the bound: 8 x 512 over 520 under a bound of 32768 52.1 -> 54.8 us, 1 x 512 over 512 21.8 -> 24.3.
 void cut_contexts(const kvq_cache_desc_t* d, int64_t batch, int64_t q_len, int64_t rows, int64_t seq_rows,
@@ -133,11 +134,11 @@ void cut_contexts(const kvq_cache_desc_t* d, int64_t batch, int64_t q_len, int64
   double us, wide_us;
   const int64_t c = equal_pieces(slots, batch * per_seq, groups, room / batch + 1, false, &us);
   const bool codes = d->mode == KVQ_INT8_TOKEN_HEAD || d->mode == KVQ_FP8E4M3_BLOCK_HEAD || d->mode == KVQ_FP8E4M3_TENSOR;
-  if (codes && d->head_dim == 128 && rows > kvq::kRowsPerWorkgroup && us >= 60.0 && 8 * q_len <= 64 * groups &&
+  if (codes && d->head_dim == 128 && rows > kvq::kRowsPerWorkgroup && us >= 100.0 && 8 * q_len <= 64 * groups &&
       groups * 64 <= (int64_t)kvq::kWideTable * d->block_size) {
     const int64_t wide_per_seq = d->num_kv_heads * ((rows + kvq::kWideRows - 1) / kvq::kWideRows);
     const int64_t wide_c = equal_pieces(slots / 2, batch * wide_per_seq, groups, room / batch + 1, true, &wide_us);
-    if (wide_us < 0.93 * us) {
+    if (wide_us < 0.92 * us) {
       plan->wide_groups = (int32_t)((3 * batch * groups + 3) / 4);
       plan->wide_least = (int32_t)((groups + 1) / 2);
       // (of its own: a batch of which one context is at the bound and the others are short goes to the kernel

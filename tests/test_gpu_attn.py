@@ -438,25 +438,23 @@ def test_contexts_are_cut_by_their_lengths(mode, D, G, q_len, lens):
 
 
 WIDE = {  # lengths, query tokens, query heads, kv heads, declared bound, whether the lengths are long for it[, block size]
-    "dead wavefronts": ([1500, 1337, 1100, 1499], 130, 64, 64, 1500, True),
-    "a row block of one row": ([2200, 2113, 2049, 2200], 257, 32, 32, 2200, True),
-    "cut": ([9000], 512, 32, 8, 9000, True),
-    "cut, below the bound": ([7000], 512, 32, 8, 9000, True),
-    "just too short": ([1300, 1200, 1090, 832], 130, 64, 64, 1500, False),
-    "just long enough": ([1300, 1200, 1090, 833], 130, 64, 64, 1500, True),
-    "one just too short": ([1500, 1500, 1480, 704], 130, 64, 64, 1500, False),
-    "one just long enough": ([1500, 1500, 1480, 705], 130, 64, 64, 1500, True),
-    "short": ([130, 191, 257, 200], 130, 64, 64, 1500, False),
+    "dead wavefronts": ([2500, 2337, 2100, 2499], 130, 64, 64, 2500, True),
+    "a row block of one row": ([2500, 2433, 2369, 2500], 257, 32, 32, 2500, True),
+    "cut": ([12000], 512, 32, 8, 12000, True),
+    "cut, below the bound": ([9500], 512, 32, 8, 12000, True),
+    "just too short": ([2100, 2000, 1800, 1600], 130, 64, 64, 2500, False),
+    "just long enough": ([2100, 2000, 1800, 1601], 130, 64, 64, 2500, True),
+    "one just too short": ([2500, 2500, 2480, 1216], 130, 64, 64, 2500, False),
+    "one just long enough": ([2500, 2500, 2480, 1217], 130, 64, 64, 2500, True),
+    "short": ([130, 191, 257, 200], 130, 64, 64, 2500, False),
     # one of the two kernels may cut contexts, the other may not; the merge is launched for both
     "not cut, the other kernel would": ([3000, 2990, 2900, 3000, 2950, 2999, 2937], 300, 16, 2, 3000, True),
     "one long, cut by the other kernel": ([3000, 301, 400, 310, 577, 300, 640], 300, 16, 2, 3000, False),
-    "cut, the other kernel would not": ([5000, 4990, 4950, 4999], 100, 64, 16, 5000, True),
-    "one long, not cut by the other kernel": ([5000, 300, 100, 700], 100, 64, 16, 5000, False),
     "a walk of more table entries than threads": ([40000], 512, 32, 8, 40000, True),   # (four pieces of 626 entries)
-    "32-token blocks": ([2200, 2113, 2049, 2200], 257, 32, 32, 2200, True, 32),
-    "64-token blocks, a walk from inside a block": ([9000], 512, 32, 8, 9000, True, 64),
-    "128-token blocks, cut": ([8990], 512, 32, 8, 9000, True, 128),
-    "256-token blocks": ([1500, 1337, 1100, 1499], 130, 64, 64, 1500, True, 256),
+    "32-token blocks": ([2500, 2433, 2369, 2500], 257, 32, 32, 2500, True, 32),
+    "64-token blocks, cut": ([12000], 512, 32, 8, 12000, True, 64),
+    "128-token blocks, walks from inside a block": ([11990], 512, 32, 8, 12000, True, 128),
+    "256-token blocks": ([2500, 2337, 2100, 2499], 130, 64, 64, 2500, True, 256),
 }
 
 
