@@ -194,11 +194,12 @@ bool many_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t m
 // 2500 23.5 -> 20.9; 32 query rows, 31 x 600 26.5 -> 13.3; not taken: 12 x 4000 24.2 -> 27.4, 1 x 2500
 // 9.9 -> 13.6.  With more pairs than compute units a workgroup has half of the wavefronts, and two share one.
 // A long context among short ones keeps its own workgroup for as many `rounds` as a wavefront has groups, where
-// the flat list would spread it over the chip, so few rounds are allowed.  Of 67733 random calls with up to 5,
-// mixtures of long and short among them, 8 took more than 1.03 of the flat list's time, 1.08 at most; at 6
-// to 8 rounds it was 44 of 1170, up to 1.35 (e4m3, one query row, 63 sequences of 40 to
-// 1819 tokens, 16.5 -> 22.2).  Where a row's reduce costs the flat list least (bf16 with one row at head_dim
-// 128) and for group-scaled int4 the line lies at 3 rounds: 0.97 and 1.00 at most, at 4 and 5 up to 1.13.
+// the flat list would spread it over the chip; so its walk may not take longer than the reduce and the partials
+// are worth, which is more the more rows they have (a wavefront's accumulators hold 16 rows, or 32, whose halves it
+// works on one after the other).  Of 16335 random calls with four to eight rounds, mixtures of long and short
+// among them: 15281 inside these lines, 0.57 of the flat list's time on average, 15 above 1.03 of it and none
+// above 1.08; 1054 beyond them, 86 above 1.03, up to 1.35 (e4m3, one row, 63 sequences of 40 to 1819 tokens,
+// 16.5 -> 22.2 us).
 int32_t pair_waves(const kvq_cache_desc_t* d, int64_t pairs, int64_t rows, int64_t groups, int row_tiles, int64_t waves) {
   const int per_simd = kvq::waves_per_simd(d->mode, d->head_dim, row_tiles);
   const int64_t cus = waves / 8;
@@ -206,11 +207,12 @@ int32_t pair_waves(const kvq_cache_desc_t* d, int64_t pairs, int64_t rows, int64
   const int64_t team = pairs <= cus ? 4 * per_simd : 2 * per_simd, slots = pairs <= cus ? cus : 2 * cus;
   const int64_t rounds = (groups + team - 1) / team;
   const bool small = d->head_dim == 64, bf16 = d->mode == KVQ_BF16_PLAIN;
-  if (rounds > ((bf16 && !small && rows == 1) || d->mode == KVQ_INT4_GROUP32 ? 3 : 5)) return 0;
   double alone = small ? 1.4 : 2.1, crowded = small ? 2.65 : bf16 ? 4.6 : 5.0;
   if (d->mode == KVQ_INT4_TOKEN_HEAD) crowded = 2.9;
   if (d->mode == KVQ_INT4_GROUP32) alone = 2.9, crowded = 3.2;
   if (row_tiles == 2 && !bf16) alone = small ? 1.9 : 2.1, crowded = 2.65;
+  const double longest = (double)rounds * (bf16 && !small ? 2.7 : alone);
+  if (rounds > 8 || longest > (rows == 1 ? 8.8 : rows < 4 ? 10.5 : rows <= 8 ? 13.5 : rows <= 16 ? 17.0 : 15.0)) return 0;
   const double here = 3.7 + (double)rounds * (alone + (crowded - alone) * (double)pairs / (double)slots);
   const double flat = 8.3 + crowded * (double)(pairs * groups) / (double)(4 * cus * per_simd);
   return here <= flat ? (int32_t)team : 0;

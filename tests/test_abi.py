@@ -143,16 +143,17 @@ def test_which_calls_may_go_to_the_kernel_of_256_rows(mode, H, hq, batch, q_len,
     assert plan(desc, batch, q_len, hq, max_len)["many_rows"] == (0 if mode == 5 else 1 + wide)
 
 
-@pytest.mark.parametrize("mode,D,hq,batch,team,rounds", [
-    (0, 128, 32, 32, 8, 5), (1, 64, 8, 32, 8, 5), (4, 128, 32, 32, 8, 5), (2, 64, 8, 32, 4, 5), (2, 128, 32, 32, 4, 5),
-    (3, 128, 64, 40, 4, 5), (2, 128, 8, 32, 4, 3), (5, 128, 32, 32, 8, 3), (5, 128, 64, 40, 4, 3)])
-def test_a_workgroup_for_each_pair_walks_few_groups(mode, D, hq, batch, team, rounds):
+@pytest.mark.parametrize("mode,D,hq,team,rounds", [
+    (0, 128, 8, 8, 4), (0, 128, 24, 8, 5), (0, 128, 32, 8, 6), (0, 128, 128, 8, 8), (0, 128, 256, 4, 7),
+    (1, 64, 8, 8, 6), (1, 64, 32, 8, 8), (4, 128, 32, 8, 6), (2, 64, 8, 4, 6), (2, 128, 8, 4, 3), (2, 128, 32, 4, 5),
+    (5, 128, 8, 8, 3), (5, 128, 32, 8, 4)])
+def test_a_workgroup_for_each_pair_walks_few_groups(mode, D, hq, team, rounds):
     """The plan knows a bound on the lengths and not their mixture: one long context among short ones would wait
-    for its own workgroup alone, so a wavefront never has more than five groups one after another (three where
-    the flat list is cheapest)."""
+    for its own workgroup alone, so the groups a wavefront takes one after another are limited, the more the
+    fewer rows a reduce would have had to put together."""
     desc = d(mode=mode, H=8, D=D, nblk=64)
     last = 64 * team * rounds
-    waves = [kvq.prof_lib().kvq_profile_pair_waves(C.byref(desc), batch, 1, hq, n, 0) for n in (last, last + 1, 2 * last)]
+    waves = [kvq.prof_lib().kvq_profile_pair_waves(C.byref(desc), 32, 1, hq, n, 0) for n in (last, last + 1, 2 * last)]
     assert waves == [team, 0, 0]
 
 
