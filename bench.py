@@ -415,7 +415,7 @@ def extras(res, lay, out_main, args, ev, prof):
     tflops = 4.0 * D * Hq * cB * visible / chunk_us / 1e6
     res["chunk_prefill"] = {"sequences": cB, "chunk_tokens": cq, "context": cL, "us": chunk_us,
                             "us_through_streaming_kernels": chunk_stream_us,
-                            "roofline": {"bound": "mfma", "kernel": "attn_wide_kernel" if D == 128 else "attn_rows_kernel",
+                            "roofline": {"bound": "mfma", "kernel": "attn_wide_kernel" if D == 128 and wl.mode in (0, 1, 3) else "attn_rows_kernel",
                                          "achieved": tflops, "peak": MFMA_F16_PEAK_TFLOPS,
                                          "unit": "TFLOP/s", "frac": tflops / MFMA_F16_PEAK_TFLOPS}}
     if wl.mode != 2 and not args.no_bf16_baseline:   # the same chunk over an unquantized cache

@@ -19,8 +19,10 @@
 // is free.  So the conversions of the next group's codes are dealt out under P.V and the logits of the first
 // tokens under the contraction of the last ones (sched_group_barrier; the conversions are pinned by an
 // empty asm, and the loop has no branch around a matrix phase: code that two branches share is moved ahead
-// of both, and the wait for its loads with it).  8 x 512 tokens over 4608, 32 / 8 heads: int8 381 -> 373 us,
-// bf16 411 -> 390; 16 x 33 tokens over 2000: int8 61.8 -> 57.6, bf16 69 -> 62.5.
+// of both, and the wait for its loads with it).  Against a kernel that did one after the other, 32 / 8 heads:
+// 3 x 1000 tokens over 3000 int8 180 -> 170 us, e4m3 163 -> 148, bf16 208 -> 192, int4 183 -> 176; 16 x 33 over
+// 2000 61.5 -> 56.6, 56.2 -> 51.6, 68.8 -> 61.8, 63.0 -> 58.9.  (What is left behind that kernel: one workgroup alone with
+// the last, long context of a batch, 398 x 64 tokens, one over 9807 and the rest over 180, e4m3 250 -> 266, int8 275 -> 285.)
 //
 // The arithmetic (logits in base 2 with the K scale applied after the contraction, V scale
 // folded into the probability, f16 probabilities scaled by 2^10, masks) is the streaming
@@ -708,8 +710,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_kernel(const
 
 // The same at head_dim 64 for the int8 and the unquantized cache, a phase after the other: in 164 registers,
 // so that three wavefronts run on a SIMD, which is worth more there than logits and conversions under the
-// matrix instructions (175 and 183 registers; 3 x 1000 tokens over 3000: int8 117 us here and 122 above,
-// bf16 129 and 133; the e4m3 formats fit either way and take 104 us above, 106 here).
+// matrix instructions (175 and 169 registers) unless there are few workgroups.  int8 and bf16, here and above:
+// 3 x 1000 tokens over 3000 122 and 132 us, 128 and 130; 40 x 64 over 300 22.0 and 24.5, 23.0 and 26.3; 16 x 33 over
+// 2000 46.0 and 43.2, 46.9 and 44.1.  The e4m3 formats fit either way and are faster above (105.7 -> 103.3).
 template <int MODE, bool PREFIX>
 __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows64_kernel(const AttnArgs p) {
   constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN;  // unquantized cache: the operands are its bytes
@@ -961,11 +964,12 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows64_kernel(con
 // K runs a phase ahead of V, so that a phase's first operands can be read before the barrier that opens it:
 // K is held in three buffers, V in two; 83 KB of operands and scales, 64 KB of table entries.  (V phases at
 // the higher priority: 318 -> 315 us int8, 295 -> 290 fp8; the matrix phases at the higher: 332 and 300.)
-// 8 x 512 tokens over 4608, 32 / 8 heads, against the kernel above: int8 335 -> 319 us, fp8 302 -> 290.  (An
-// unquantized and a plain int4 cache, with 192 and 72 bytes of registers spilled, gained half of that.)  What bounds it: a matrix phase takes 1700 to 2200 cycles beside a vector phase, 1024 of them matrix
-// instructions; v_exp_f32 and matrix instructions of two wavefronts barely overlap (matched streams of
-// 125 us each take 176 together, multiply-adds 133).  head_dim 64 does better on the kernel above,
-// which runs three wavefronts per SIMD there (int8 230 us against 251).
+// 8 x 512 tokens over 4608, 32 / 8 heads, against the kernel above: int8 338 -> 323 us, fp8 303 -> 294.  (An
+// unquantized and a plain int4 cache, with 192 and 72 bytes of registers spilled, gained half of that.)  What
+// bounds it: a wavefront is resident about 5000 cycles for a group, of which it waits 26 % (barriers and loads)
+// and 33 % to issue; its 1024 cycles of matrix and 1600 of vector instructions are 2600 of the 3000 that its SIMD
+// spends on a wavefront's group, so the teams' phases follow each other more than they overlap.  Each phase lasts as
+// long as the slower team's: the two barriers of a group are the next thing to take out.
 template <int MODE>
 __global__ __launch_bounds__(512, 2) void attn_wide_kernel(const AttnArgs p) {
   constexpr bool FP8 = MODE == KVQ_FP8E4M3_BLOCK_HEAD || MODE == KVQ_FP8E4M3_TENSOR;
