@@ -21,8 +21,8 @@
 // empty asm, and the loop has no branch around a matrix phase: code that two branches share is moved ahead
 // of both, and the wait for its loads with it).  Against a kernel that did one after the other, 32 / 8 heads:
 // 3 x 1000 tokens over 3000 int8 180 -> 170 us, e4m3 163 -> 148, bf16 208 -> 192, int4 183 -> 176; 16 x 33 over
-// 2000 61.5 -> 56.6, 56.2 -> 51.6, 68.8 -> 61.8, 63.0 -> 58.9.  (What is left behind that kernel: one workgroup alone with
-// the last, long context of a batch, 398 x 64 tokens, one over 9807 and the rest over 180, e4m3 250 -> 266, int8 275 -> 285.)
+// 2000 61.5 -> 56.6, 56.2 -> 51.6, 68.8 -> 61.8, 63.0 -> 58.9; one workgroup alone with the last, long context of a batch,
+// 398 x 64 tokens, one over 9807 and the rest over 180: 274 -> 249, 249 -> 233, 311 -> 282, 278 -> 258.
 //
 // The arithmetic (logits in base 2 with the K scale applied after the contraction, V scale
 // folded into the probability, f16 probabilities scaled by 2^10, masks) is the streaming
@@ -670,12 +670,16 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_kernel(const
 #pragma unroll
     for (int x = 0; x < PIECES; ++x) publish(first_k, first_v, x, 0);
     __syncthreads();
-    auto prepare = [&](int i) {  // scales of group i + 1 published, of i + 2 requested, its codes located
+    // codes of group i + 2 located, scales of i + 1 published, of i + 2 requested.  (Behind the matrix instructions: both
+    // wait for loads that were requested at the end of the last iteration.  Ahead of the softmax, a lone workgroup
+    // waited there for every group: 398 x 64 tokens, one over 9807 and the rest over 180, int8 285 -> 249 us, e4m3
+    // 267 -> 233, bf16 317 -> 282, int4 284 -> 258.)
+    auto prepare = [&](int i) {
+      locate(g0 + i + 2);
       if (scale_wave) {
         publish_scales(i + 1, sk_next, sv_next);
         request_scales(g0 + i + 2, sk_next, sv_next);
       }
-      locate(g0 + i + 2);
     };
     auto advance = [&](int i) {
       fetch_entries(g0 + i + 3);
@@ -686,12 +690,12 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_kernel(const
       for (int i = 0; i < n; ++i) {
         const int g = g0 + i, half = i & 1;
         contract_k(half);
-        prepare(i);
         if ((g << 6) + 64 > n_min) vector_phase(std::true_type{}, g, half);
         else vector_phase(std::false_type{}, g, half);
         read_v(0, half);
         clear_missing(min(g + 1, ng - 1), rv);
         contract_v(half);
+        prepare(i);
         advance(i);
       }
     } else {
