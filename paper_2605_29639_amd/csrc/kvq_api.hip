@@ -80,7 +80,7 @@ int ilog2(int x) {
 // of them on a compute unit, 0.6 of that with one, about 3 until a workgroup's first group is
 // consumed; splitting adds the second launch and writes and reads 64 KB per workgroup.  One
 // sequence's 512 tokens over 16384 cached ones (fp8, 32 / 8 heads): 427 us in one piece, 178 in
-// four with the merge (156 with the present kernels); eight such chunks over 4096 (1024 workgroups, two full rounds) stay whole.
+// four with the merge (159 with the present kernels); eight such chunks over 4096 (1024 workgroups, two full rounds) stay whole.
 // (wide: the kernel for kWideRows, one workgroup of 256 rows on a compute unit where the other kernel has two
 // of 128: 2.3 us per group, the same for the last round, 5 until a first group is consumed and 9 from one
 // workgroup of a compute unit to the next, which nothing overlaps.)
@@ -124,9 +124,9 @@ int64_t equal_pieces(int64_t slots, int64_t walks, int64_t groups, int64_t room,
 // 80 -> 75, e4m3 71.7 -> 70.8 without that launch), with chunks of more than an eighth of the context (whose first
 // rows see much less than their last) it loses up to 8 %, with a quarter of the sequences short 12 %; bf16 and
 // int4 gain half as much.  The kernel for 128 rows alone -> both launched: 8 x 512 tokens over 4608 int8
-// 338 -> 323 us, e4m3 303 -> 294; 1 x 512 over 16896 173 -> 159, 156 -> 146.  The launch that ends at once takes
+// 343 -> 330 us, e4m3 309 -> 298; 1 x 512 over 16896 175 -> 164, 159 -> 148.  The launch that ends at once takes
 // 2.1 us ahead of or behind the other (3 to 4 above 512 workgroups; 4.6 as a profiler sees it), also where the contexts are far
-// below the bound: 8 x 512 over 520 under a bound of 32768 51.0 -> 54.8 us, 1 x 512 over 512 21.5 -> 24.4.
+// below the bound: 8 x 512 over 520 under a bound of 32768 49.6 -> 53.0 us, 1 x 512 over 512 21.3 -> 24.0.
 void cut_contexts(const kvq_cache_desc_t* d, int64_t batch, int64_t q_len, int64_t rows, int64_t seq_rows,
                   int64_t groups, int64_t slot_rows, int64_t slots, kvq::AttnPlan* plan) {
   const int64_t room = slot_rows / seq_rows;
@@ -190,8 +190,8 @@ bool many_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t m
 // 8000 tokens, 8 kv heads, equal lengths: a group takes a wavefront `alone` where few compute units have one and
 // `crowded` where all have (memory, or for int4 and two row tiles arithmetic); beside that a workgroup per
 // pair takes 3.7 and the flat list with its reduce 8.3.  us a call, flat list -> workgroup per pair: 4 query heads
-// per kv head, int8, 1 x 600 tokens 8.4 -> 7.7, 12 x 1500 16.9 -> 12.9, 32 x 600 16.0 -> 10.7, 32 of 300 to
-// 2500 23.6 -> 20.7; 32 query rows, 31 x 600 26.3 -> 13.1; not taken: 12 x 4000 24.2 -> 27.4, 1 x 2500
+// per kv head, int8, 1 x 600 tokens 8.4 -> 7.7, 12 x 1500 17.2 -> 12.7, 32 x 600 16.2 -> 10.1, 32 of 300 to
+// 2500 23.6 -> 20.5; 32 query rows, 31 x 600 26.2 -> 13.1; not taken: 12 x 4000 24.2 -> 27.4, 1 x 2500
 // 9.9 -> 13.6.  With more pairs than compute units a workgroup has half of the wavefronts, and two share one.
 // A long context among short ones keeps its own workgroup for as many `rounds` as a wavefront has groups, where
 // the flat list would spread it over the chip; so its walk may not take longer than the reduce and the partials

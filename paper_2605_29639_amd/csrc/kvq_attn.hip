@@ -100,8 +100,8 @@ __device__ inline int range_of(const Split& s, int f) {
 // each channel group: q is zero outside a column's group, and one accumulator holds what took four.
 // The columns' logits are added up and dealt out so that each keeps a quarter of the tokens, with a
 // maximum and sums of its own: a lane has 4 exponentials to a group instead of 16, of which 12 were of
-// empty rows.  4 rows, us a call: 64 sequences of 512 to 4096 tokens 42.6 -> 41.3, 128 of 1000 37.4 -> 35.4; as
-// workgroups of a pair 32 of 600 11.5 -> 10.3.  (A second register set for the next
+// empty rows.  4 rows, us a call: 64 sequences of 512 to 4096 tokens 42.8 -> 41.9, 128 of 1000 38.0 -> 35.8,
+// 60 of 1500 31.2 -> 29.4.  (A second register set for the next
 // group, 44.3 us at the first size, and nibbles of K taken as subnormals, which cancel 8 times the sum of q,
 // 40.6 us, were not worth it.)
 template <int MODE, int D, int NT, bool CEIL, int DEPTH, bool CLOCK, int PER_SIMD, bool EVEN, int TEAM = 0,

@@ -20,9 +20,9 @@
 // tokens under the contraction of the last ones (sched_group_barrier; the conversions are pinned by an
 // empty asm, and the loop has no branch around a matrix phase: code that two branches share is moved ahead
 // of both, and the wait for its loads with it).  Against a kernel that did one after the other, 32 / 8 heads:
-// 3 x 1000 tokens over 3000 int8 180 -> 170 us, e4m3 163 -> 148, bf16 208 -> 192, int4 183 -> 176; 16 x 33 over
-// 2000 61.5 -> 56.6, 56.2 -> 51.6, 68.8 -> 61.8, 63.0 -> 58.9; one workgroup alone with the last, long context of a batch,
-// 398 x 64 tokens, one over 9807 and the rest over 180: 274 -> 249, 249 -> 233, 311 -> 282, 278 -> 258.
+// 3 x 1000 tokens over 3000 int8 183 -> 170 us, e4m3 163 -> 154, bf16 212 -> 197, int4 183 -> 175; 16 x 33 over
+// 2000 61.8 -> 55.5, 56.2 -> 52.2, 69.2 -> 63.1, 62.9 -> 58.5; one workgroup alone with the last, long context of a batch,
+// 398 x 64 tokens, one over 9807 and the rest over 180: 273 -> 249, 248 -> 235, 309 -> 281, 277 -> 257.
 //
 // The arithmetic (logits in base 2 with the K scale applied after the contraction, V scale
 // folded into the probability, f16 probabilities scaled by 2^10, masks) is the streaming
@@ -528,10 +528,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_kernel(const
   // 3 x 1000 tokens over 3000 int8 173.5 -> 171 us, int4 180 -> 177.)
   auto pace = [&](auto N, auto READS, auto VALU) {
     static_for<decltype(N)::value>([&](auto X) {
-      constexpr int x = decltype(X)::value, n = decltype(N)::value, r = decltype(READS)::value;
+      constexpr int x = decltype(X)::value, r = decltype(READS)::value;
       __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-      constexpr int now = x < r ? 1 : 0;
-      if constexpr (now > 0) __builtin_amdgcn_sched_group_barrier(0x100, now, 0);
+      if constexpr (x < r) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       if constexpr (decltype(VALU)::value > 0) __builtin_amdgcn_sched_group_barrier(0x2, decltype(VALU)::value, 0);
       __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
     });
@@ -714,9 +713,10 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_kernel(const
 
 // The same at head_dim 64 for the int8 and the unquantized cache, a phase after the other: in 164 registers,
 // so that three wavefronts run on a SIMD, which is worth more there than logits and conversions under the
-// matrix instructions (175 and 169 registers) unless there are few workgroups.  int8 and bf16, here and above:
-// 3 x 1000 tokens over 3000 122 and 132 us, 128 and 130; 40 x 64 over 300 22.0 and 24.5, 23.0 and 26.3; 16 x 33 over
-// 2000 46.0 and 43.2, 46.9 and 44.1.  The e4m3 formats fit either way and are faster above (105.7 -> 103.3).
+// matrix instructions unless there are few workgroups.  Here and above, int8 (175 registers): 3 x 1000 tokens over 3000
+// 119 and 125 us, 40 x 64 over 300 21.9 and 24.0, 16 x 33 over 2000 45.8 and 41.7; bf16 (167, but 188 for a shared
+// prefix) 128.6 and 127.8, 23.2 and 22.8, 46.7 and 43.9, 60 sequences of 1451 tokens that share 704, 28 rows, 45.3 and 47.8.  The e4m3
+// formats fit either way and are faster above (105.9 -> 104.8).
 template <int MODE, bool PREFIX>
 __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows64_kernel(const AttnArgs p) {
   constexpr bool PLAIN = MODE == KVQ_BF16_PLAIN;  // unquantized cache: the operands are its bytes
@@ -968,7 +968,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows64_kernel(con
 // K runs a phase ahead of V, so that a phase's first operands can be read before the barrier that opens it:
 // K is held in three buffers, V in two; 83 KB of operands and scales, 64 KB of table entries.  (V phases at
 // the higher priority: 318 -> 315 us int8, 295 -> 290 fp8; the matrix phases at the higher: 332 and 300.)
-// 8 x 512 tokens over 4608, 32 / 8 heads, against the kernel above: int8 338 -> 323 us, fp8 303 -> 294.  (An
+// 8 x 512 tokens over 4608, 32 / 8 heads, against the kernel above: int8 343 -> 330 us, fp8 309 -> 298.  (An
 // unquantized and a plain int4 cache, with 192 and 72 bytes of registers spilled, gained half of that.)  What
 // bounds it: a wavefront is resident about 5000 cycles for a group, of which it waits 26 % (barriers and loads)
 // and 33 % to issue; its 1024 cycles of matrix and 1600 of vector instructions are 2600 of the 3000 that its SIMD
