@@ -66,3 +66,36 @@ def test_no_blocks_is_a_no_op():
     kvq.blocks_export(cache, scales, desc, empty, torch.empty(0, dtype=torch.uint8, device="cuda"),
                       torch.empty(0, dtype=torch.float32, device="cuda"))
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("mode,H,D,bs,num", [
+    (W.MODE_INT8, 8, 128, 16, 31), (W.MODE_INT8, 8, 128, 16, 33),          # 248 and 264 pieces of 4 KiB around 256
+    (W.MODE_INT8, 8, 128, 16, 256), (W.MODE_INT8, 8, 128, 16, 257),        # 2048 and 2056
+    (W.MODE_FP8, 3, 64, 16, 1100), (W.MODE_INT4_GROUP, 3, 128, 128, 90)])  # blocks of one piece and a half; many scales
+@pytest.mark.parametrize("host", [False, True], ids=["device", "pinned_host"])
+def test_more_pieces_than_are_in_flight_from_host_memory(mode, H, D, bs, num, host):
+    """Moves of around and beyond the pieces that a move from (256) or to (2048) host memory has in flight, by
+    the bytes of the blocks."""
+    import torch
+    from paper_2605_29639_amd import kvq
+    pool = num + 7
+    desc = kvq.make_desc(mode, pool, bs, H, D)
+    cache, scales = kvq.alloc_cache(desc)
+    g = torch.Generator(device="cuda").manual_seed(num)
+    codes, floats = cache.view(torch.uint8).view(pool, -1), scales.view(pool, -1)
+    codes.copy_(torch.randint(0, 256, codes.shape, generator=g, device="cuda", dtype=torch.uint8))
+    floats.copy_(torch.rand(floats.shape, generator=g, device="cuda"))
+    ids = torch.randperm(pool, generator=g, device="cuda")[:num].to(torch.int32)
+    nbytes, nscales = kvq.packed_sizes(desc, num)
+    where = dict(pin_memory=True) if host else dict(device="cuda")
+    pc, ps = torch.zeros(nbytes, dtype=torch.uint8, **where), torch.zeros(nscales, **where)
+    kvq.blocks_export(cache, scales, desc, ids, pc, ps)
+    torch.cuda.synchronize()
+    assert torch.equal(pc.cuda().view(num, -1), codes[ids.long()])
+    assert torch.equal(ps.cuda().view(num, -1), floats[ids.long()])
+    want_c, want_s = codes.clone(), floats.clone()
+    to = torch.randperm(pool, generator=g, device="cuda")[:num].to(torch.int32)
+    want_c[to.long()], want_s[to.long()] = pc.cuda().view(num, -1), ps.cuda().view(num, -1)
+    kvq.blocks_import(pc, ps, desc, to, cache, scales)
+    torch.cuda.synchronize()
+    assert torch.equal(codes, want_c) and torch.equal(floats, want_s)
