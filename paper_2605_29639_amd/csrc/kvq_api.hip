@@ -200,6 +200,13 @@ bool many_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t m
 // among them: 15281 inside these lines, 0.57 of the flat list's time on average, 15 above 1.03 of it and none
 // above 1.08; 1054 beyond them, 86 above 1.03, up to 1.35 (e4m3, one row, 63 sequences of 40 to 1819 tokens,
 // 16.5 -> 22.2 us).
+double crowded_us(const kvq_cache_desc_t* d, int row_tiles) {  // (a group of a wavefront where all compute units have theirs)
+  const bool small = d->head_dim == 64, bf16 = d->mode == KVQ_BF16_PLAIN;
+  if (row_tiles == 2 && !bf16) return 2.65;
+  if (d->mode == KVQ_INT4_TOKEN_HEAD) return 2.9;
+  if (d->mode == KVQ_INT4_GROUP32) return 3.2;
+  return small ? 2.65 : bf16 ? 4.6 : 5.0;
+}
 int32_t pair_waves(const kvq_cache_desc_t* d, int64_t pairs, int64_t rows, int64_t groups, int row_tiles, int64_t waves) {
   const int per_simd = kvq::waves_per_simd(d->mode, d->head_dim, row_tiles);
   const int64_t cus = waves / 8;
@@ -207,15 +214,56 @@ int32_t pair_waves(const kvq_cache_desc_t* d, int64_t pairs, int64_t rows, int64
   const int64_t team = pairs <= cus ? 4 * per_simd : 2 * per_simd, slots = pairs <= cus ? cus : 2 * cus;
   const int64_t rounds = (groups + team - 1) / team;
   const bool small = d->head_dim == 64, bf16 = d->mode == KVQ_BF16_PLAIN;
-  double alone = small ? 1.4 : 2.1, crowded = small ? 2.65 : bf16 ? 4.6 : 5.0;
-  if (d->mode == KVQ_INT4_TOKEN_HEAD) crowded = 2.9;
-  if (d->mode == KVQ_INT4_GROUP32) alone = 2.9, crowded = 3.2;
-  if (row_tiles == 2 && !bf16) alone = small ? 1.9 : 2.1, crowded = 2.65;
+  const double crowded = crowded_us(d, row_tiles);
+  double alone = small ? 1.4 : 2.1;
+  if (d->mode == KVQ_INT4_GROUP32) alone = 2.9;
+  if (row_tiles == 2 && !bf16) alone = small ? 1.9 : 2.1;
   const double longest = (double)rounds * (bf16 && !small ? 2.7 : alone);
   if (rounds > 8 || longest > (rows == 1 ? 8.8 : rows < 4 ? 10.5 : rows <= 8 ? 13.5 : rows <= 16 ? 17.0 : 15.0)) return 0;
   const double here = 3.7 + (double)rounds * (alone + (crowded - alone) * (double)pairs / (double)slots);
   const double flat = 8.3 + crowded * (double)(pairs * groups) / (double)(4 * cus * per_simd);
   return here <= flat ? (int32_t)team : 0;
+}
+
+// Whether the prefix kernel is worth its launch for the plan's shared groups, and in how many pieces (plan->prefix_chunks
+// at most, for which the workspace has room).  In microseconds: what the streaming kernel is spared, (batch - 1)
+// times the shared groups of every pair, against a round of the many-row kernel's workgroups (3 and 2.6 a group, see
+// equal_pieces; 1.5 at head_dim 64, bf16 3.2), the partials of all stacked rows that it writes and the reduce reads (2.1 MB a
+// microsecond) and 2 of launch; a tenth and 5 us in doubt are the plain call's.  Cost (+) or gain, predicted and
+// measured, 8 kv heads, int8: 64 sequences of 2 k to 16 k tokens, 32 rows, prefix 1024 +9 and +9 of 234 us, of 8 k to
+// 16 k with 4096 -23 and -27 of 294; 128 of 2 k to 4 k, 8 rows, 1024 -15 and -16 of 143; 16 of them, 32 rows +8 and
+// +11 of 35; 9 of 2 k to 6 k, head_dim 64, +6 and +6 of 26.  Random hinted calls
+// took 1.15 of the plain call's time on average and up to 1.77 of it where every hint was followed (60 calls); now
+// 0.98 and 1.02 (240).
+// A call that is a many-row kernel's without a hint keeps it only where that kernel would take clearly longer than
+// the prefix and the rest together (bf16, 32 sequences of 8192 tokens, 40 rows: 203 us, 177 with 6144 shared; but
+// 29 of 2000 to 3300, 64 rows, 71 and 99 with 2048, 35 of 1600, 56 rows, 36 and 45 with 1536).
+bool prefix_pays(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t max_groups, int64_t slots, bool many,
+                 kvq::AttnPlan* plan) {
+  const int64_t groups = plan->shared_groups, stacked = batch * rows;
+  const int64_t walks = d->num_kv_heads * ((stacked + kvq::kRowsPerWorkgroup - 1) / kvq::kRowsPerWorkgroup);
+  const double partials = (double)stacked * d->num_kv_heads * d->head_dim * 4.0 / 2.1e6;
+  const double piece_us = d->mode == KVQ_BF16_PLAIN ? 3.2 : d->head_dim == 64 ? 1.5 : 2.6;
+  double least = 0.0;
+  for (int64_t c = 1, most = plan->prefix_chunks; c <= most; ++c) {
+    const int64_t n = walks * c, rest = n % slots;
+    const double rounds = (double)(n / slots) + (rest == 0 ? 0.0 : 2 * rest <= slots ? 0.6 : 1.0);
+    const double us = rounds * (3.0 + piece_us * (double)((groups + c - 1) / c)) + (double)c * partials + 2.0;
+    if (c == 1 || us < least) {
+      least = us;
+      plan->prefix_chunks = (int32_t)c;
+    }
+  }
+  const int per_simd = kvq::waves_per_simd(d->mode, d->head_dim, plan->row_tiles);
+  const double group_us = crowded_us(d, plan->row_tiles) / (double)(2 * slots * per_simd);
+  const double list = (double)batch * (double)plan->pairs_per_seq * group_us;  // (for one group of every context)
+  if (many) {
+    if (d->head_dim != 128 || groups < 64) return false;  // (of few groups the estimates are off by 10 us)
+    double alone;
+    equal_pieces(slots, batch * d->num_kv_heads, max_groups, kvq::kMaxContextSplits, false, &alone);
+    return least + 8.3 + list * (double)(max_groups - groups) < 0.85 * alone;
+  }
+  return list * (double)groups * (double)(batch - 1) / (double)batch >= 1.1 * least + 5.0;
 }
 
 // Everything the launch needs that depends only on host-side arguments.
@@ -318,6 +366,10 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
   plan->promised_groups = plan->shared_groups;
   if (plan->many_rows && (rows > 64 || 2 * (int64_t)plan->shared_groups < ((int64_t)max_seq_len + 63) / 64))
     plan->shared_groups = 0;
+  // (a caller's split-K granule keeps the prefix in as many pieces as there is room for)
+  plan->prefix_pays = plan->shared_groups > 0 &&
+                      (chunk_tokens > 0 || prefix_pays(d, batch, rows, ((int64_t)max_seq_len + 63) / 64, slots_128,
+                                                       plan->many_rows, plan));
   if (plan->shared_groups > 0) plan->many_rows = 0;
   // (A call whose pairs get a workgroup each needs no prefix kernel either, and the same whether it has a
   // hint or not.)
@@ -528,6 +580,11 @@ int attn_call(const void* q, const void* cache, const float* scales,
   // the kernels read q and the cache and write out in 16-byte pieces
   if ((((uintptr_t)q | (uintptr_t)cache | (uintptr_t)out) & 15) != 0) return KVQ_E_BAD_SHAPE;
   const size_t need = (plan.acc_floats + plan.ml_floats + plan.prefix_ints) * sizeof(float);
+  // (a prefix that is not worth its kernel: the call is paged_decode_attn's, in a workspace of the size asked for)
+  const int32_t promised = plan.promised_groups;
+  if (plan.shared_groups > 0 && !plan.prefix_pays &&
+      !make_plan(desc, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, 0, &plan, &err))
+    return err;
   if (own_scratch) {
     if (need > (size_t)KVQ_STATIC_WORKSPACE_BYTES) return KVQ_E_WORKSPACE;
     workspace = scratch_on_current_device();
@@ -546,8 +603,7 @@ int attn_call(const void* q, const void* cache, const float* scales,
                            0, (hipStream_t)stream, block_tables, seq_lens, batch,
                            max_blocks_per_seq, desc->num_blocks, desc->block_size, q_len,
                            max_seq_len,
-                           (plan.promised_groups * 64 + desc->block_size - 1) / desc->block_size,
-                           plan.promised_groups * 64, word);
+                           (promised * 64 + desc->block_size - 1) / desc->block_size, promised * 64, word);
       });
       if (rc != KVQ_OK) return rc;
     }
@@ -725,6 +781,14 @@ int kvq_profile_pair_waves(const kvq_cache_desc_t* desc, int32_t batch, int32_t 
   int err;
   if (!make_plan(desc, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, 0, &p, &err)) return err;
   return p.pair_waves;
+}
+
+int kvq_profile_prefix_pieces(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,
+                              int32_t max_seq_len, int32_t chunk_tokens, int32_t shared_prefix_tokens) {
+  kvq::AttnPlan p;
+  int err;
+  if (!make_plan(desc, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, shared_prefix_tokens, &p, &err)) return err;
+  return p.shared_groups > 0 && p.prefix_pays ? p.prefix_chunks : 0;
 }
 
 void kvq_profile_split_events(void* before, void* after) {

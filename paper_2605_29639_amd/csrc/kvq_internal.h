@@ -130,6 +130,7 @@ struct AttnPlan {
   int32_t shared_groups;   // shared prefix in 64-token groups, 0 where the prefix kernel is not used
   int32_t promised_groups; // the same also where the call does better without that kernel
   int32_t prefix_chunks;   // pieces the prefix kernel cuts it into (>= 1)
+  int32_t prefix_pays;     // else the call does better without the hint
   int32_t pair_waves;      // > 0: a workgroup of so many wavefronts for each pair, and no reduce
   int32_t many_rows;       // the call goes to a many-row kernel
   // to the one with workgroups of kWideRows where all contexts together have so many groups (0: never) and

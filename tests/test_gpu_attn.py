@@ -1,5 +1,6 @@
 """GPU parity, paged_decode_attn: within 2e-3 of the output's max norm of the CPU checker,
 both reading the same quantized bytes (the checker's cache, uploaded)."""
+import ctypes as C
 import zlib
 
 import numpy as np
@@ -362,6 +363,27 @@ def test_shared_prefix_is_read_through_stacked_rows(mode, q_len, lens):
             else:
                 assert attn_err(hinted, want) <= TOL, (chunk, hint)
                 assert attn_err(hinted, plain.astype(np.float64)) <= 2e-4, (chunk, hint)
+
+
+@pytest.mark.parametrize("mode", [W.MODE_INT8, W.MODE_FP8, W.MODE_BF16, W.MODE_INT4])
+def test_a_shared_prefix_is_used_where_it_is_worth_the_launch(mode):
+    """260 sequences behind 2048 shared tokens keep the hint, in fewer pieces than there is room for; of
+    16 sequences, or of 64 tokens, it is dropped on the host: bit for bit paged_decode_attn's output."""
+    from paper_2605_29639_amd import kvq
+    pieces = kvq.prof_lib().kvq_profile_prefix_pieces
+    for batch, hint, used in ((260, 2048, True), (260, 2000, True), (260, 64, False), (16, 2048, False)):
+        wl = W.custom("prefix_pays", mode, [2048 + 5 + 7 * (i % 9) for i in range(batch)], 2, 4, 2, 128, 16,
+                      seed=190 + mode, shared_prefix=2048)
+        oc, osc = oracle_fill(wl)
+        cache, scales, desc = upload_oracle_cache(wl, oc, osc)
+        assert (pieces(C.byref(desc), batch, 2, 4, wl.max_seq_len, 0, hint) > 0) == used
+        plain = gpu_attention(wl, cache, scales, desc)
+        hinted = gpu_attention(wl, cache, scales, desc, shared_prefix_tokens=hint)
+        if not used:
+            assert np.array_equal(hinted.view(np.uint32), plain.view(np.uint32))
+            continue
+        assert attn_err(hinted, oracle_out(wl, oc, osc)) <= TOL
+        assert attn_err(hinted, plain.astype(np.float64)) <= 2e-4
 
 
 @pytest.mark.parametrize("mode,D", [(m, 128) for m in MODES if m != W.MODE_INT4_GROUP] +
