@@ -168,7 +168,7 @@ size_t paged_decode_attn_workspace_bytes(const kvq_cache_desc_t* desc, int32_t b
  * seq_lens[b] counts the q_len current tokens, which must already be in the cache.
  *   q             device, bf16 [batch*q_len][num_q_heads][head_dim], read only, 16-byte aligned
  *   block_tables  device, int32 [batch][max_blocks_per_seq], read only; entries past a
- *                 sequence's last block are never dereferenced
+ *                 sequence's last block may be read and are never dereferenced
  *   seq_lens      device, int32 [batch], read only
  *   max_seq_len   host upper bound on seq_lens (sizes the launch grid)
  *   chunk_tokens  split-K granule: tokens of context per wavefront range, a multiple of 64;

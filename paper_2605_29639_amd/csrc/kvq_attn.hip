@@ -94,8 +94,12 @@ __device__ inline int range_of(const Split& s, int f) {
 // values in AGPRs and copying them back, 1-2 % faster.  At head_dim 64 the two-tile kernels,
 // double buffers included, fit 256 registers as well and run two per SIMD too.)
 // EVEN: the launch has no more wavefronts than are resident at PER_SIMD of them.
-// TEAM > 0: not a range of the flat list but a workgroup of TEAM wavefronts for one pair, each a slice of its
-// groups, put together in LDS: one launch instead of two (see pair_waves in kvq_api.hip).
+// TEAM > 0: not a range of the flat list but a workgroup of TEAM wavefronts for one pair, each every TEAM-th of its
+// groups, put together in LDS: one launch instead of two (see pair_waves in kvq_api.hip).  A chain of round trips
+// bounds it: a wavefront's first group does not depend on the sequence's length, so its table entries and q are
+// requested with the length and not behind it (4 rows of 8 kv heads, 600 tokens, us a call, one after the other
+// with slices of adjacent groups -> now: int8 7.8 -> 7.0, e4m3 7.2 -> 6.6, int4 8.5 -> 6.9; 31 sequences, 32 rows,
+// head_dim 64, 9.4 -> 7.9; 600 tokens of one sequence took 8.3 beside a step's write).
 // BANKS: group-scaled int4 with at most four query rows.  A tile has 16 columns, so each row gets four, one for
 // each channel group: q is zero outside a column's group, and one accumulator holds what took four.
 // The columns' logits are added up and dealt out so that each keeps a quarter of the tokens, with a
@@ -188,8 +192,9 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
     cur.pr = w - cur.b * Hp;
     cur.L = seq_lens[cur.b];
     cur.ng = (cur.L + 63) >> 6;
-    f0 = cur.g = cur.ng * wv / TEAM;
-    f1 = cur.ng * (wv + 1) / TEAM;
+    cur.g = wv;
+    f0 = 0;
+    f1 = max(cur.ng - wv + TEAM - 1, 0) / TEAM;
   } else if (B <= 64) {
     // lane i holds sequence i: one load and one scan give the list's length, the prefix sums
     // the reduce wants and, by a ballot, the sequence this wave's range starts in
@@ -251,6 +256,10 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
   }
   stamp(9);  // the range and its first group are known
   auto advance = [&](Cursor& c) {  // the next group of the list
+    if constexpr (TEAM > 0) {
+      c.g += TEAM;
+      return;
+    }
     if (++c.g < c.ng) return;
     c.g = P;
     if (++c.pr < Hp) return;
@@ -287,6 +296,21 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
     const int pos0 = c.g << 6, last_sb = ((c.L - 1) >> 4) << 4;
     blk_k = table[min(pos0 + 16 * sbk, last_sb) >> bs_shift];
     blk_v = table[min(pos0 + 16 * g4, last_sb) >> bs_shift];
+  };
+
+  // The entries of a team's first group, ahead of the sequence's length: in round with it, not behind it.  Where the group
+  // ends with the sequence they are another block's or nobody's, and usable_entries puts the group's first
+  // sub-block in their place (what it holds is masked, like all that is read past the end).
+  auto first_entries = [&](int g, int& blk_k, int& blk_v) {
+    const int32_t* __restrict__ table = p.block_tables + (size_t)cur.b * p.max_blocks_per_seq;
+    const int last = p.max_blocks_per_seq - 1;
+    blk_k = table[min(((g << 6) + 16 * sbk) >> bs_shift, last)];
+    blk_v = table[min(((g << 6) + 16 * g4) >> bs_shift, last)];
+  };
+  auto usable_entries = [&](const Cursor& c, int& blk_k, int& blk_v) {
+    const int of_k = lane_value(blk_k, 0), of_v = lane_value(blk_v, 0);
+    if ((c.g << 6) + 16 * sbk >= c.L) blk_k = of_k;
+    if ((c.g << 6) + 16 * g4 >= c.L) blk_v = of_v;
   };
 
   // K codes and both scales of a group; also works out where the group's V codes are
@@ -762,28 +786,32 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
   int blk_k, blk_v;
   floatx4 S[NT][4];
   Operand pb[NT][2 * EB];
+  [[maybe_unused]] int team_k = 0, team_v = 0;
+  if constexpr (TEAM > 0) {  // (requested before anything asks for the sequence's length)
+    first_entries(wv, team_k, team_v);
+    begin_pair(cur);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   const int count = f1 - f0;
   Cursor nxt = cur;
   if (count > 1) advance(nxt);
   Cursor nn = nxt;
   bool from_start = cur.g == P;  // did this wave see the current pair from its first listed group
   if (TEAM > 0 && count == 0) {  // (a context of fewer groups than wavefronts)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      m_run[nt] = -INFINITY;
-      l_run[nt] = 0.0f;
-#pragma unroll
-      for (int tt = 0; tt < DT; ++tt) acc[nt][tt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
   } else if constexpr (DEPTH == 1) {
     uintx4 kt[4][KJ], vt[VW];
     ScaleT sk, sv;
     const uint8_t* vbase;
     {
-      int bk0, bv0;
-      fetch_entries(cur, bk0, bv0);
-      fetch_entries(nxt, blk_k, blk_v);
-      begin_pair(cur);  // q is requested ahead of the codes so that it is not queued behind them
+      int bk0 = team_k, bv0 = team_v;
+      if constexpr (TEAM > 0) {
+        usable_entries(cur, bk0, bv0);
+        fetch_entries(nxt, blk_k, blk_v);
+      } else {
+        fetch_entries(cur, bk0, bv0);
+        fetch_entries(nxt, blk_k, blk_v);
+        begin_pair(cur);  // q is requested ahead of the codes so that it is not queued behind them
+      }
       __builtin_amdgcn_sched_barrier(0);
       stamp(10, true);  // the first table entries (and q) have arrived
       load_k(kt, sk, sv, vbase, cur, bk0, bv0);
@@ -837,9 +865,16 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
     if (count > 2) advance(c2);
     c3 = c2;
     if (count > 3) advance(c3);
-    fetch_entries(cur, tk0, tv0);
-    fetch_entries(c1, tk1, tv1);
-    begin_pair(cur);
+    if constexpr (TEAM > 0) {
+      tk0 = team_k;
+      tv0 = team_v;
+      usable_entries(cur, tk0, tv0);
+      fetch_entries(c1, tk1, tv1);
+    } else {
+      fetch_entries(cur, tk0, tv0);
+      fetch_entries(c1, tk1, tv1);
+      begin_pair(cur);
+    }
     __builtin_amdgcn_sched_barrier(0);
     load_k(kta, ska, sva, vbase, cur, tk0, tv0);
     load_v(vta, vbase, cur);
@@ -1129,8 +1164,8 @@ hipError_t launch_pairs(const AttnArgs& a, hipStream_t stream) {
   }
   if (MODE == KVQ_INT4_GROUP32 && a.rows <= 4)
     launch_team<MODE, D, 1, 1, kOneTile, MODE == KVQ_INT4_GROUP32>(a, stream);
-  else
-    launch_team<MODE, D, 1, 1, kOneTile>(a, stream);
+  else  // (int4 has the registers for a second set, and 1 x 600 tokens takes 6.9 us with it, 7.5 without; the others +-3 %)
+    launch_team<MODE, D, 1, MODE == KVQ_INT4_TOKEN_HEAD ? 2 : 1, kOneTile>(a, stream);
   return hipGetLastError();
 }
 
