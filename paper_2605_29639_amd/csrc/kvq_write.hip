@@ -952,10 +952,12 @@ __global__ __launch_bounds__(kWaves * 64) void write_window_kernel(
 }
 
 // Decode steps and small chunks: unit = (token, kv head, K|V); the wavefront of a run's first token
-// does the run.  A decode step is a chain of round trips behind a launch: the token's row is
-// requested together with the slots (lane i holds the slot of token t0 - 1 + i).
+// does the run (block-scaled fp8, whose runs are longer than a sub-block: that of a sub-block's first does the sub-block).  A decode step is a chain of round trips behind a launch: the token's row is
+// requested together with the slots (lane i holds the slot of token t0 - 1 + i).  Most wavefronts of a chunk end
+// there, so what counts is how many are resident: eight to a SIMD (64 registers).  Block-scaled fp8 took 72: 225
+// runs of four tokens 16.9 us, now 11.6.
 template <int MODE, int D>
-__global__ __launch_bounds__(kWaves * 64) void write_run_kernel(
+__global__ __launch_bounds__(kWaves * 64, 8) void write_run_kernel(
     const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int64_t* __restrict__ slot_mapping, int32_t num_tokens, uint8_t* __restrict__ cache,
     float* __restrict__ scales, int32_t H, int32_t bs) {
@@ -988,7 +990,8 @@ __global__ __launch_bounds__(kWaves * 64) void write_run_kernel(
   }
   const int span = FP8_BLOCK ? bs : 16;  // a run ends with its block / sub-block
   const int at = (int)(slot0 & (span - 1));
-  if (at > 0 && lane_i64(slot, 0) == slot0 - 1) return;  // not a run's first token
+  const bool inside = at > 0 && lane_i64(slot, 0) == slot0 - 1;  // not a run's first token
+  if (inside && (!FP8_BLOCK || (at & 15) != 0)) return;
   const uint64_t same = __ballot(lane > 0 && lane <= span - at && slot == slot0 + (lane - 1)) >> 1;
   int run = __builtin_ctzll(~same);  // (63 where every lane's token belongs to it)
   if (FP8_BLOCK && run == 63) {      // block sizes reach 256
@@ -1005,36 +1008,62 @@ __global__ __launch_bounds__(kWaves * 64) void write_run_kernel(
   const int off = (int)(slot0 & (bs - 1));
   const size_t tstride = (size_t)H * D;
   if constexpr (FP8_BLOCK) {
+    int back = 0;  // tokens of the run before this one
+    if (inside) {
+      for (int base = 0; base < at; base += 64) {
+        const int j = base + lane + 1;
+        const uint64_t m = __ballot(j <= at && j <= t0 && slot_mapping[max(t0 - j, 0)] == slot0 - j);
+        const int n = m == ~0ull ? 64 : __builtin_ctzll(~m);
+        back += n;
+        if (n < 64) break;
+      }
+    }
+    run += back;
     if (run > 1) {
-      // by sub-block, unless the scale grows over older codes: the rows are read once for the run's
-      // absmax and once more to encode them
-      uint32_t amax = 0;
-      const int first_sb = off >> 4, last_sb = (off + run - 1) >> 4;
+      // A wavefront per sub-block of the run (that of the sub-block's first token), unless the scale grows over older
+      // codes.  The scale needs the absmax of the whole run, which each of them takes for itself, two sub-blocks requested at
+      // a time: all of it is small, and nobody waits for anybody.  A scale read when another of the run's
+      // wavefronts has stored the new one already gives the new one again.  (One wavefront for the run, sub-block
+      // after sub-block: 500 tokens of 8 heads x 128 in blocks of 32, 64 and 128 tokens 10.8, 18.6 and 24.5 us,
+      // now 9.5, 11.2 and 15.8; 120 tokens 5.8, 9.2 and 13.1, now 4.8, 5.4 and 7.4.  Four sub-blocks requested at a
+      // time are faster alone, 12.0 for 500 in blocks of 128, and take the registers of a third of the wavefronts: 900 in
+      // blocks of 32 10.4 -> 13.6.)
+      const int o_min = off - back, first_sb = o_min >> 4, last_sb = (o_min + run - 1) >> 4;
+      const uint16_t* run_src = src - (size_t)back * tstride;
       auto rows_of = [&](int sb, Piece<D> (&raw)[4], int& r_lo, int& r_hi) {
-        r_lo = max(off - 16 * sb, 0);
-        r_hi = min(off + run - 16 * sb, 16);
-        load_subblock<D>(src + (size_t)(16 * sb + r_lo - off) * tstride, tstride, kv, lane, r_lo, r_hi, raw);
+        r_lo = max(o_min - 16 * sb, 0);
+        r_hi = min(o_min + run - 16 * sb, 16);
+        const uint16_t* first = run_src + (size_t)(16 * sb + r_lo - o_min) * tstride;
+        load_subblock<D>(first, tstride, kv, lane, r_lo, r_hi, raw);
+        return first;
       };
+      float* sp = scales_of<MODE>(scales, blk, kv, h, H, bs, off);
+      const float s_prev = o_min > 0 ? *sp : 0.0f;  // (a run from offset 0 starts the block afresh)
       Piece<D> raw[4];
       int r_lo, r_hi;
-      for (int sb = last_sb; sb >= first_sb; --sb) {  // (a run of one sub-block stays in registers)
-        rows_of(sb, raw, r_lo, r_hi);
+      const int sb = off >> 4;
+      const uint16_t* first = rows_of(sb, raw, r_lo, r_hi);
+      uint32_t amax = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) amax = max(amax, piece_absmax<D>(raw[i]));
+      for (int i = 0; i < 4; ++i) amax = max(amax, piece_absmax<D>(raw[i]));
+      for (int x = first_sb; x <= last_sb && first_sb < last_sb; x += 2) {
+        Piece<D> some[2][4];
+        int lo, hi;
+#pragma unroll
+        for (int n = 0; n < 2; ++n) rows_of(min(x + n, last_sb), some[n], lo, hi);
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) amax = max(amax, piece_absmax<D>(some[n][i]));
       }
-      float* sp = scales_of<MODE>(scales, blk, kv, h, H, bs, off);
-      const float s_prev = off > 0 ? *sp : 0.0f;
       const float s_new = grown_scale(s_prev, wave_max_u32(amax));
-      if (!(off > 0 && s_new > s_prev && s_prev > 0.0f)) {
-        uint8_t* tile = tile_of<MODE, D>(cache, blk, kv, h, H, bs);
-        for (int sb = first_sb; sb <= last_sb; ++sb) {
-          if (sb > first_sb) rows_of(sb, raw, r_lo, r_hi);
-          fp8_subblock<D, false>(raw, src + (size_t)(16 * sb + r_lo - off) * tstride, tstride, kv, tile, 16 * sb,
-                                 r_lo, r_hi, s_new, bs, lane);
-        }
-        if (lane == 0) *sp = s_new;
+      if (!(o_min > 0 && s_new > s_prev && s_prev > 0.0f)) {
+        fp8_subblock<D, false>(raw, first, tstride, kv, tile_of<MODE, D>(cache, blk, kv, h, H, bs), 16 * sb, r_lo, r_hi,
+                               s_new, bs, lane);
+        if (!inside && lane == 0) *sp = s_new;
         return;
       }
+      if (inside) return;  // (the run's first wavefront does all of it)
     }
     fp8_run<D>(k, v, cache, scales, H, bs, kv, h, t0, slot0, run, lane, table[wv]);
   } else {
