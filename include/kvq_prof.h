@@ -61,6 +61,11 @@ int kvq_profile_wide(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len,
 int kvq_profile_prefix_pieces(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,
                               int32_t max_seq_len, int32_t chunk_tokens, int32_t shared_prefix_tokens);
 
+/* Whether the call goes to the many-row kernel of group-scaled int4 (which kvq_profile_plan's many_rows does
+ * not count).  Host only. */
+int kvq_profile_group_rows(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,
+                           int32_t max_seq_len, int32_t chunk_tokens);
+
 /* Wavefronts of the workgroup that each (sequence, kv head, row group) would get, 0 where the call goes over
  * the flat list of groups (or to a many-row kernel).  Host only. */
 int kvq_profile_pair_waves(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,

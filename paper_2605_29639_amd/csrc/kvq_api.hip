@@ -151,7 +151,9 @@ void cut_contexts(const kvq_cache_desc_t* d, int64_t batch, int64_t q_len, int64
   plan->piece_min = (int32_t)(per_seq < 32 ? 2 : per_seq / 16);
   if (c > 1) {
     plan->extra_pieces = (int32_t)(batch * (c - 1));
-  } else if (rows < kvq::kRowsPerWorkgroup && groups > 2 * plan->piece_min) {
+  } else if ((rows < kvq::kRowsPerWorkgroup || d->mode == KVQ_INT4_GROUP32) && groups > 2 * plan->piece_min) {
+    // (group-scaled int4 with any number of rows, since its streaming kernel splits any mixture evenly: 5 x 266 tokens
+    // over 266 to 5000, 4 kv heads, 99 us streaming, 138 with the longest context uncut, 60 with it cut)
     const int64_t extra = (slots + per_seq - 1) / per_seq;
     plan->extra_pieces = (int32_t)(extra < room ? extra : room);
     plan->piece_share = 1.5f * (float)per_seq / (float)slots;
@@ -168,7 +170,7 @@ void cut_contexts(const kvq_cache_desc_t* d, int64_t batch, int64_t q_len, int64
 // 77 -> 41; bf16 40 rows 117 -> 118, 96 rows 180 -> 123.  With a workgroup for every slot of the chip
 // and short contexts (little to lose to uneven lengths) 33 rows are enough: 200 sequences of up to 300
 // tokens, 48 rows, 91 -> 49; 128 of up to 2000, 48 rows, 177 -> 138; but 60 of up to 6000, 56 rows,
-// 190 -> 204.  (The group-scaled int4 format has no many-row kernel.)
+// 190 -> 204.  (Group-scaled int4 has a kernel and a rule of its own: group_rows.)
 bool many_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t max_seq_len,
                int64_t chunk_tokens, int64_t slots) {
   if (d->mode == KVQ_INT4_GROUP32) return false;
@@ -180,6 +182,28 @@ bool many_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t m
   if (passes >= (d->head_dim == 128 ? 3 : 4)) return rows > 32;
   return rows > 32 && d->head_dim == 128 && max_seq_len <= 2048 &&
          batch * d->num_kv_heads >= slots;
+}
+
+// Whether a call goes to the many-row kernel of group-scaled int4 (one that a caller's granule does not keep on the
+// streaming kernel, and whose pairs do not get a workgroup each).  The streaming kernel takes 2.2 us for a wavefront's group of 16 rows, two wavefronts to a
+// SIMD's time, and 8.3 beside that; the other one 1.35 of what equal_pieces says, with no less for a row block of 33
+// rows than for one of 128.  A tenth in doubt is the streaming kernel's, whose ranges are even whatever the mixture of
+// lengths.  us a call by the estimates and measured, streaming and many-row, 8 kv heads: 64 sequences of 2000 to
+// 4000 tokens, 64 rows, 285 and 225 (bounds), 231 and 221; 20 of 500 to 1000, 96 rows, 41 and 36, 44.7 and 35.4; 2 x 128
+// tokens over 2500, 512 rows, 52 and 40, 54 and 42; not taken: 8 of 2000 to 8000, 64 rows, 77 and 85, 56 and 62; 1 x
+// 441 tokens over 469, 2 kv heads, 14 and 20, 22 and 25; 32 rows, of which one wavefront in four is busy, 147 and
+// 225, 126 and 153 at the first lengths.  Of 45 random calls that it takes, mixtures of long and short among them,
+// 0.64 of the streaming kernel's time on average and 1.00 at most; the error against 64 bits is no larger (1.67e-4 and
+// now 1.65e-4, 1.54e-4 and 1.52e-4, 1.64e-4 twice, 1.72e-4 twice).
+bool group_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t groups, int64_t slots) {
+  if (d->mode != KVQ_INT4_GROUP32 || rows <= 32 || batch < 1) return false;
+  const int64_t blocks = (rows + kvq::kRowsPerWorkgroup - 1) / kvq::kRowsPerWorkgroup;
+  // (a grid and its merge have fewer than 2^32 threads)
+  if (batch * d->num_kv_heads * blocks > 1 << 19) return false;
+  const double pairs = (double)(batch * d->num_kv_heads) * (double)((rows + 15) / 16);
+  double us;
+  equal_pieces(slots, batch * d->num_kv_heads * blocks, groups, kvq::kMaxContextSplits, false, &us);
+  return 1.35 * us <= 0.9 * (8.3 + 2.2 * pairs * (double)groups / (double)(2 * slots));
 }
 
 // Wavefronts of the workgroup that each (sequence, kv head, row group) pair gets in a call that does without the
@@ -375,9 +399,11 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
   // hint or not.)
   plan->pair_waves = plan->many_rows || chunk_tokens > 0
                          ? 0 : pair_waves(d, batch * pairs, rows, ((int64_t)max_seq_len + 63) / 64, plan->row_tiles, waves);
+  plan->group_rows = chunk_tokens == 0 && plan->pair_waves == 0 &&
+                     group_rows(d, batch, rows, ((int64_t)max_seq_len + 63) / 64, slots_128);
   if (plan->pair_waves > 0) plan->shared_groups = 0;
   plan->wide_groups = plan->wide_least = 0;
-  if (plan->many_rows)
+  if (plan->many_rows || plan->group_rows)
     cut_contexts(d, batch, q_len, rows, (int64_t)q_len * num_q_heads, ((int64_t)max_seq_len + 63) / 64,
                  (int64_t)slot_rows, slots_128, plan);
   return true;
@@ -642,7 +668,7 @@ int attn_call(const void* q, const void* cache, const float* scales,
   a.shared_groups = plan.shared_groups;
   a.prefix_chunks = plan.prefix_chunks;
   a.pair_waves = plan.pair_waves;
-  a.many_rows = plan.many_rows;
+  a.many_rows = plan.many_rows | plan.group_rows;
   a.wide_groups = plan.wide_groups;
   a.wide_least = plan.wide_least;
   a.extra_pieces = plan.extra_pieces;
@@ -789,6 +815,14 @@ int kvq_profile_prefix_pieces(const kvq_cache_desc_t* desc, int32_t batch, int32
   int err;
   if (!make_plan(desc, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, shared_prefix_tokens, &p, &err)) return err;
   return p.shared_groups > 0 && p.prefix_pays ? p.prefix_chunks : 0;
+}
+
+int kvq_profile_group_rows(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,
+                           int32_t max_seq_len, int32_t chunk_tokens) {
+  kvq::AttnPlan p;
+  int err;
+  if (!make_plan(desc, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, 0, &p, &err)) return err;
+  return p.group_rows;
 }
 
 void kvq_profile_split_events(void* before, void* after) {

@@ -133,6 +133,7 @@ struct AttnPlan {
   int32_t prefix_pays;     // else the call does better without the hint
   int32_t pair_waves;      // > 0: a workgroup of so many wavefronts for each pair, and no reduce
   int32_t many_rows;       // the call goes to a many-row kernel
+  int32_t group_rows;      // the call goes to that of group-scaled int4 (many_rows is 0)
   // to the one with workgroups of kWideRows where all contexts together have so many groups (0: never) and
   // the shortest has so many
   int32_t wide_groups, wide_least;

@@ -952,6 +952,188 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows64_kernel(con
   store_rows<D, PREFIX>(p, lane, at, acc, m_run, l_run);
 }
 
+// The same for group-scaled int4 (head_dim 128): a phase after the other, since the scales by channel group leave no
+// registers for more.  A step of QK^T contracts one group of 32 channels, and the logit is the four steps'
+// results weighted by the token's four K scales in fp32, as in the streaming kernel; P.V takes the
+// probabilities times the V scale of the group its channels belong to, worked out once a group for both of its channel
+// tiles.  Scales go to LDS by channel group, so that four tokens' come in one read.  Vector-bound: a logit
+// costs four multiply-adds, and four products and conversions behind the softmax, where the other formats have one and
+// half of one; what it spares is the conversion of all codes for every 16 rows.  One path behind the mask: with two copies of the
+// softmax, as above, 41 registers spilled and 8 x 512 tokens over 4608 took 630 us.  The same now 496, streaming
+// 1205; 1 x 512 over 16896 310 and 531, 64 sequences of 2000 to 4000, 128 rows, 225 and 433.
+__global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_group_kernel(const AttnArgs p) {
+  constexpr int NT = 2, D = 128, RB = D / 2, DT = D / 16, KS = D / 32;
+  constexpr int MODE = KVQ_INT4_GROUP32;
+  static_assert(kWavesPerGroup == 4, "a wavefront converts a quad of K and two channel tiles of V");
+  __shared__ half8 k_ops[2][4][KS][64];    // [half][quad of the sub-block][step][lane]
+  __shared__ half8 v_ops[2][DT][2][64];    // [half][channel tile][tokens 0-7 | 8-15][lane]
+  __shared__ __align__(16) float k_scales[2][KS][64];  // [half][channel group][token], times log2e / sqrt(D)
+  __shared__ __align__(16) float v_scales[2][KS][64];  // relative to the token's largest
+  __shared__ __align__(16) float s_ops[2][3][64];      // (unused,) log2 and reciprocal of the largest V scale
+
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int m16 = lane & 15, g4 = lane >> 4;
+  const int H = p.num_kv_heads, bs = p.block_size, bs_shift = p.bs_shift;
+  Place at;
+  if (!place_rows<false, kRowsPerWorkgroup, false>(p, lane, wv, at)) return;
+  const int h = at.h, b = at.b, L = at.L, g0 = at.g0, ng = at.ng;
+  const bool wave_live = at.wave_live;
+
+  const uint8_t* __restrict__ cache = p.cache;
+  const float* __restrict__ scales = p.scales;
+  const int32_t* __restrict__ table = p.block_tables + (size_t)b * p.max_blocks_per_seq;
+  const uint32_t tile_bytes = (uint32_t)bs * RB;
+  const uint32_t block_stride = 2u * (uint32_t)H * tile_bytes;
+  const int sbk = m16 >> 2;  // sub-block this lane reads K from
+  const int last_sb = ((L - 1) >> 4) << 4;
+
+  half8 qb[NT][KS];
+  int nrow[NT];
+  floatx4 acc[NT][DT];
+  float m_run[NT], l_run[NT];
+  load_queries<KVQ_INT4_TOKEN_HEAD, D, false>(p, lane, at, qb, nrow, acc, m_run, l_run);  // (the same words)
+  const int n_min = at.n_min;
+
+  // ---- producer side: quad wv of K, channel tiles 2 wv and 2 wv + 1 of V, the scales of K or of V ----
+  struct Entries {
+    uint32_t k, v, k_at, v_at;
+  };
+  const uint32_t k_fixed = (uint32_t)h * tile_bytes + 64u * g4 + 16u * (m16 & 3) + (uint32_t)wv * (4 * RB);
+  const uint32_t v_fixed = (uint32_t)(H + h) * tile_bytes + 16u * m16 + 256u * wv;
+  auto fetch_entries = [&](int g, Entries& e) {  // g is clamped by the caller
+    const uint32_t tk = (uint32_t)min((g << 6) + 16 * sbk, last_sb), tv = (uint32_t)min((g << 6) + 16 * g4, last_sb);
+    e.k = (uint32_t)table[tk >> bs_shift];
+    e.v = (uint32_t)table[tv >> bs_shift];
+    e.k_at = (tk & (uint32_t)(bs - 1)) * RB + k_fixed;
+    e.v_at = tv & (uint32_t)(bs - 1);
+  };
+  uintx4 rk, rv;
+  floatx4 rs = {};
+  auto issue_loads = [&](const Entries& e) {
+    rk = *(const uintx4*)(cache + ((uint64_t)e.k * block_stride + e.k_at));
+    rv = *(const uintx4*)(cache + ((uint64_t)e.v * block_stride + (e.v_at * RB + v_fixed)));
+    if (wv < 2)  // lane = token: wavefront 0 the K scales, 1 the V scales
+      rs = ((const floatx4*)scales)[(uint64_t)e.v * (2u * H * bs) + ((uint32_t)((wv * H + h) * bs + m16) + e.v_at)];
+  };
+  auto publish = [&](int g, int half) {  // convert the loaded codes and put them in LDS
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+      k_ops[half][wv][st][lane] = cvt_int4(rk[st]);
+      v_ops[half][2 * wv + (st >> 1)][st & 1][lane] = cvt_int4(rv[st]);
+    }
+    const bool dead = (g << 6) + lane >= L;  // a slot that was never written: its scales are not data
+    if (wv == 0) {
+#pragma unroll
+      for (int s = 0; s < KS; ++s) k_scales[half][s][lane] = dead ? 0.0f : rs[s] * p.scale_log2;
+    } else if (wv == 1) {
+      const float top = fmaxf(fmaxf(rs[0], rs[1]), fmaxf(rs[2], rs[3]));
+      const float lsv = dead ? 0.0f : __builtin_amdgcn_logf(fmaxf(top, kMinVScale));
+      const float rsv = dead ? 0.0f : __builtin_amdgcn_exp2f(-lsv);
+#pragma unroll
+      for (int s = 0; s < KS; ++s) v_scales[half][s][lane] = dead ? 0.0f : rs[s] * rsv;
+      s_ops[half][1][lane] = lsv;
+      s_ops[half][2][lane] = rsv;
+    }
+  };
+
+  // ---- consumer side ----
+  floatx4 S[NT][4];
+  auto qk = [&](int half) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      half8 a[KS];
+      floatx4 k4[KS];
+#pragma unroll
+      for (int s = 0; s < KS; ++s) a[s] = k_ops[half][u][s][lane];
+      const floatx4 l4 = *(const floatx4*)&s_ops[half][1][16 * g4 + 4 * u];
+#pragma unroll
+      for (int s = 0; s < KS; ++s) k4[s] = *(const floatx4*)&k_scales[half][s][16 * g4 + 4 * u];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        floatx4 part[KS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+          part[s] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[s], qb[nt][s], floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float z = __builtin_fmaf(part[0][i], k4[0][i], l4[i]);
+#pragma unroll
+          for (int s = 1; s < KS; ++s) z = __builtin_fmaf(part[s][i], k4[s][i], z);
+          S[nt][u][i] = z;
+        }
+      }
+    }
+  };
+  half8 none[NT][2];  // (not written: the softmax leaves group-scaled probabilities in S)
+  auto softmax = [&](int g, int half) {
+    // some row's causal length ends inside the group: positions past it are masked here, one path for all that follows
+    if ((g << 6) + 64 > n_min) {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            S[nt][u][i] = (g << 6) + 16 * g4 + 4 * u + i < nrow[nt] ? S[nt][u][i] : -INFINITY;
+    }
+    online_softmax<MODE, NT, DT, false>(S, (const floatx4*)&s_ops[half][0][16 * g4], 0.0f, 0.0f, 0.0f, 0, nrow, m_run,
+                                        l_run, acc, none);
+  };
+  auto pv = [&](int half) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      half8 a[2][2];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) a[x >> 1][x & 1] = v_ops[half][2 * s + (x >> 1)][x & 1][lane];
+      half8 pb[NT][2];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const floatx4 r4 = *(const floatx4*)&v_scales[half][s][16 * g4 + 4 * u];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) pb[nt][u >> 1][4 * (u & 1) + i] = (_Float16)__builtin_fmaf(S[nt][u][i], r4[i], 0.0f);
+      }
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt)
+            acc[nt][2 * s + x] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[x][hf], pb[nt][hf], acc[nt][2 * s + x], 0, 0, 0);
+    }
+  };
+
+  // ---- the walk: group g is consumed from half g % 2 while group g + 1 is converted into the
+  // other half and group g + 2 is requested (indices past the end repeat the last group) ----
+  Entries e_next, e_after;
+  if (g0 < ng) {  // (a chunk's first rows see fewer groups than there may be pieces)
+    Entries e0;
+    fetch_entries(g0, e0);
+    fetch_entries(min(g0 + 1, ng - 1), e_next);
+    fetch_entries(min(g0 + 2, ng - 1), e_after);
+    issue_loads(e0);
+    publish(g0, 0);
+    issue_loads(e_next);
+  }
+  __syncthreads();
+  for (int g = g0; g < ng; ++g) {
+    const int half = (g - g0) & 1;
+    if (wave_live) {
+      qk(half);
+      softmax(g, half);
+      pv(half);
+    }
+    // group g + 1 (requested one iteration ago) into the other half; request group g + 2
+    publish(min(g + 1, ng - 1), half ^ 1);
+    issue_loads(e_after);
+    fetch_entries(min(g + 3, ng - 1), e_after);
+    __syncthreads();
+  }
+  store_rows<D, false>(p, lane, at, acc, m_run, l_run);
+}
+
 // The kernel for more than kRowsPerWorkgroup rows at head_dim 128: eight wavefronts own 256 rows, one such
 // workgroup runs on a compute unit, two wavefronts on a SIMD.  The matrix unit and the vector unit of a SIMD
 // work side by side only for different wavefronts or for independent instructions of one, and two
@@ -1434,6 +1616,8 @@ hipError_t launch_many_rows(const AttnArgs& a, int all_rows, int walks, hipStrea
     KVQ_LAUNCH_PREFILL(KVQ_BF16_PLAIN, (attn_rows64_kernel<KVQ_BF16_PLAIN, PREFIX>));
   } else if (a.mode == KVQ_INT4_TOKEN_HEAD) {  // (head_dim 128 only)
     hipLaunchKernelGGL((attn_rows_kernel<KVQ_INT4_TOKEN_HEAD, 128, PREFIX, false>), grid, block, 0, stream, a);
+  } else if (a.mode == KVQ_INT4_GROUP32) {  // (and never with a shared prefix)
+    if constexpr (!PREFIX) hipLaunchKernelGGL(attn_rows_group_kernel, grid, block, 0, stream, a);
   } else {
     KVQ_LAUNCH_PREFILL(KVQ_FP8E4M3_TENSOR, (attn_rows_kernel<KVQ_FP8E4M3_TENSOR, 64, PREFIX, false>));
   }

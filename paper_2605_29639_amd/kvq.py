@@ -29,7 +29,8 @@ EXPORTS = ("kvq_cache_bytes", "kvq_scales_bytes", "kv_quant_write",
 # what the measurement build (libkvq_prof.so, include/kvq_prof.h) exports on top
 PROF_EXPORTS = ("kvq_profile_split_events", "kvq_profile_read_ceiling", "kvq_profile_skip_reduce",
                 "kvq_profile_prefill_kernel", "kvq_profile_plan", "kvq_profile_wide",
-                "kvq_profile_pair_waves", "kvq_profile_prefix_pieces", "kvq_profile_wave_clock")
+                "kvq_profile_pair_waves", "kvq_profile_prefix_pieces", "kvq_profile_group_rows",
+                "kvq_profile_wave_clock")
 PROF_LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libkvq_prof.so")
 
 
@@ -113,6 +114,8 @@ def _load(path, prof):
         L.kvq_profile_wide.argtypes = [D, I32, I32, I32, I32, C.POINTER(C.c_int64)]
         L.kvq_profile_pair_waves.restype = C.c_int
         L.kvq_profile_pair_waves.argtypes = [D, I32, I32, I32, I32, I32]
+        L.kvq_profile_group_rows.restype = C.c_int
+        L.kvq_profile_group_rows.argtypes = [D, I32, I32, I32, I32, I32]
         L.kvq_profile_prefix_pieces.restype = C.c_int
         L.kvq_profile_prefix_pieces.argtypes = [D, I32, I32, I32, I32, I32, I32]
         L.kvq_profile_read_ceiling.restype = None

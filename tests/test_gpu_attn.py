@@ -459,6 +459,33 @@ def test_contexts_are_cut_by_their_lengths(mode, D, G, q_len, lens):
         assert attn_err(got, want) <= 5e-4, bound
 
 
+@pytest.mark.parametrize("lens,q_len,G,H,bs", [
+    ([700, 655, 799] * 42, 13, 4, 4, 16),                 # 52 rows: a second row tile of four, two wavefronts without any
+    ([900, 64, 65, 1, 959] * 40, 1, 65, 2, 64),           # 65 rows, contexts of one token and of whole groups
+    ([640] * 60 + [4100], 16, 8, 2, 32),                  # 128 rows, one long context, cut alone
+    ([300, 1025, 513] * 4, 290, 4, 4, 16), ([4097], 129, 8, 4, 128), ([3000, 2990] * 2, 257, 8, 1, 256)])
+def test_many_rows_of_group_scaled_int4(lens, q_len, G, H, bs):
+    """The many-row kernel of group-scaled int4, against the oracle on sequences of every length and against the
+    streaming kernel on all (either rounds f16 probabilities: 2^-12 of a row's largest term), under a bound
+    far above the lengths, and with a negative softmax scale."""
+    from paper_2605_29639_amd import kvq
+    lens = [max(l, q_len) for l in lens]
+    wl = W.custom("group rows", W.MODE_INT4_GROUP, lens, q_len, G * H, H, 128, bs, seed=q_len + bs)
+    cache, scales, desc = gpu_fill(wl)
+    prof = kvq.prof_lib()
+    assert prof.kvq_profile_group_rows(C.byref(desc), len(lens), q_len, G * H, max(lens), 0) == 1
+    assert prof.kvq_profile_group_rows(C.byref(desc), len(lens), q_len, G * H, max(lens), 256) == 0
+    for sign, bound in ((1.0, max(lens)), (-1.0, max(lens)), (1.0, 8 * max(lens))):
+        wl.__class__ = type("Signed", (type(wl),), {"sm_scale": sign * abs(wl.sm_scale)})
+        got = gpu_attention(wl, cache, scales, desc, chunk_tokens=0, max_len=bound)
+        want = gpu_attention(wl, cache, scales, desc, chunk_tokens=256, max_len=bound)
+        assert np.isfinite(got).all()
+        assert attn_err(got, want.astype(np.float64)) <= 5e-4
+    if sum(lens) * q_len < 1 << 21:
+        wl.__class__ = type("Signed", (type(wl),), {"sm_scale": abs(wl.sm_scale)})
+        assert attn_err(gpu_attention(wl, cache, scales, desc, chunk_tokens=0), oracle_out(wl, *oracle_fill(wl))) <= 5e-4
+
+
 WIDE = {  # lengths, query tokens, query heads, kv heads, declared bound, whether the lengths are long for it[, block size]
     "dead wavefronts": ([2500, 2337, 2100, 2499], 130, 64, 64, 2500, True),
     "a row block of one row": ([2500, 2433, 2369, 2500], 257, 32, 32, 2500, True),
