@@ -96,10 +96,12 @@ __device__ inline int range_of(const Split& s, int f) {
 // EVEN: the launch has no more wavefronts than are resident at PER_SIMD of them.
 // TEAM > 0: not a range of the flat list but a workgroup of TEAM wavefronts for one pair, each every TEAM-th of its
 // groups, put together in LDS: one launch instead of two (see pair_waves in kvq_api.hip).  A chain of round trips
-// bounds it: a wavefront's first group does not depend on the sequence's length, so its table entries and q are
-// requested with the length and not behind it (4 rows of 8 kv heads, 600 tokens, us a call, one after the other
-// with slices of adjacent groups -> now: int8 7.8 -> 7.0, e4m3 7.2 -> 6.6, int4 8.5 -> 6.9; 31 sequences, 32 rows,
-// head_dim 64, 9.4 -> 7.9; 600 tokens of one sequence took 8.3 beside a step's write).
+// bounds it: a wavefront's first group does not depend on the sequence's length, so its table entries are
+// requested with the length, and q right behind them, by the wavefronts that have a group.  (q requested by all with
+// the length kept the few that had one waiting in short contexts: e4m3, 32 rows, 25 sequences of 32 tokens, 7.0 us
+// for 6.5; behind the codes, 1.015 of this order's time on average.)  4 rows of 8 kv heads, 600 tokens, us a call, one step
+// behind the other with slices of adjacent groups -> now: int8 7.7 -> 6.7, e4m3 7.0 -> 6.1, int4 8.4 -> 6.8; 31
+// sequences, 32 rows, head_dim 64, 8.9 -> 7.6.
 // BANKS: group-scaled int4 with at most four query rows.  A tile has 16 columns, so each row gets four, one for
 // each channel group: q is zero outside a column's group, and one accumulator holds what took four.
 // The columns' logits are added up and dealt out so that each keeps a quarter of the tokens, with a
@@ -361,6 +363,15 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
   float m_run[NT], l_run[NT];
   uint32_t ceil_x = 0;
   const uint32_t q_sign = PLAIN && p.scale_log2 < 0.0f ? 0x80008000u : 0u;
+  auto clear_sums = [&]() {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      m_run[nt] = -INFINITY;
+      l_run[nt] = 0.0f;
+#pragma unroll
+      for (int tt = 0; tt < DT; ++tt) acc[nt][tt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
   auto begin_pair = [&](const Cursor& c) {
     if constexpr (CEIL) return;
     const int h = c.pr / NRG, rg = c.pr - h * NRG;
@@ -392,11 +403,8 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
           }
         }
       }
-      m_run[nt] = -INFINITY;
-      l_run[nt] = 0.0f;
-#pragma unroll
-      for (int tt = 0; tt < DT; ++tt) acc[nt][tt] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
+    clear_sums();
   };
 
   // BANKS: a row's four columns become one (the same in all four)
@@ -789,7 +797,6 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
   [[maybe_unused]] int team_k = 0, team_v = 0;
   if constexpr (TEAM > 0) {  // (requested before anything asks for the sequence's length)
     first_entries(wv, team_k, team_v);
-    begin_pair(cur);
     __builtin_amdgcn_sched_barrier(0);
   }
   const int count = f1 - f0;
@@ -798,6 +805,7 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
   Cursor nn = nxt;
   bool from_start = cur.g == P;  // did this wave see the current pair from its first listed group
   if (TEAM > 0 && count == 0) {  // (a context of fewer groups than wavefronts)
+    clear_sums();
   } else if constexpr (DEPTH == 1) {
     uintx4 kt[4][KJ], vt[VW];
     ScaleT sk, sv;
@@ -805,6 +813,7 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
     {
       int bk0 = team_k, bv0 = team_v;
       if constexpr (TEAM > 0) {
+        begin_pair(cur);
         usable_entries(cur, bk0, bv0);
         fetch_entries(nxt, blk_k, blk_v);
       } else {
@@ -812,7 +821,7 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
         fetch_entries(nxt, blk_k, blk_v);
         begin_pair(cur);  // q is requested ahead of the codes so that it is not queued behind them
       }
-      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (TEAM == 0) __builtin_amdgcn_sched_barrier(0);
       stamp(10, true);  // the first table entries (and q) have arrived
       load_k(kt, sk, sv, vbase, cur, bk0, bv0);
       load_v(vt, vbase, cur);
@@ -868,6 +877,7 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
     if constexpr (TEAM > 0) {
       tk0 = team_k;
       tv0 = team_v;
+      begin_pair(cur);
       usable_entries(cur, tk0, tv0);
       fetch_entries(c1, tk1, tv1);
     } else {
@@ -875,7 +885,7 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
       fetch_entries(c1, tk1, tv1);
       begin_pair(cur);
     }
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (TEAM == 0) __builtin_amdgcn_sched_barrier(0);
     load_k(kta, ska, sva, vbase, cur, tk0, tv0);
     load_v(vta, vbase, cur);
     auto leave = [&](const Cursor& next) {  // after a group: does the next one open another pair

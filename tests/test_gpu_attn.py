@@ -117,7 +117,8 @@ def test_small_shapes_over_the_flat_list(mode, case):
 
 @pytest.mark.parametrize("mode,D,G,q_len", [(m, 128, 4, 1) for m in MODES] + [(W.MODE_INT8, 64, 2, 3), (W.MODE_FP8, 64, 8, 4),
                                             (W.MODE_BF16, 64, 1, 1), (W.MODE_INT8, 128, 8, 4), (W.MODE_INT4, 128, 7, 3),
-                                            (W.MODE_BF16, 128, 8, 3), (W.MODE_INT4_GROUP, 128, 8, 3), (W.MODE_FP8, 128, 5, 7)])
+                                            (W.MODE_BF16, 128, 8, 3), (W.MODE_INT4_GROUP, 128, 8, 3), (W.MODE_FP8, 128, 5, 7),
+                                            (W.MODE_INT8, 64, 8, 4), (W.MODE_BF16, 64, 8, 4), (W.MODE_FP8_TENSOR, 128, 8, 4)])
 @pytest.mark.parametrize("seqs", [1, 40, 130])
 def test_a_workgroup_for_each_pair(mode, D, G, q_len, seqs):
     """Contexts from one token to a few groups more than the workgroup has wavefronts, on and around the edges
