@@ -92,7 +92,7 @@ __device__ inline int range_of(const Split& s, int f) {
 // took 268, and 56 -> 49 us a call for 195 MB; one where its partials need the room): they
 // fit either way, but told so the compiler keeps everything in 200-224 VGPRs instead of parking
 // values in AGPRs and copying them back, 1-2 % faster.  At head_dim 64 the two-tile kernels,
-// double buffers included, fit 256 registers as well and run two per SIMD too.)
+// double buffers included, fit 256 registers as well and run two per SIMD too; not those of an unquantized cache.)
 // EVEN: the launch has no more wavefronts than are resident at PER_SIMD of them.
 // TEAM > 0: not a range of the flat list but a workgroup of TEAM wavefronts for one pair, each every TEAM-th of its
 // groups, put together in LDS: one launch instead of two (see pair_waves in kvq_api.hip).  A chain of round trips
@@ -160,7 +160,10 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
   // the even split, and then whatever fits runs: capped like the even split's they take 74 us instead of
   // 63 (bf16, head_dim 64, 64-token granules, 110k tokens), 48 instead of 43 (fp8).
   if constexpr (EVEN && PER_SIMD == 2) asm volatile("" ::: "v175");
-  else if constexpr (EVEN && ((PLAIN && D == 64) || INT4)) asm volatile("" ::: "v255", "a7");
+  // (Two workgroups of two wavefronts are put on the same two SIMDs where the registers let them: bf16, head_dim 64, 60
+  // sequences of 224 tokens, 32 rows, 9.3 us, kept apart 8.1.)
+  else if constexpr ((EVEN && ((PLAIN && D == 64) || INT4)) || (TEAM > 0 && PLAIN && D == 64 && NT == 2))
+    asm volatile("" ::: "v255", "a7");
   stamp(6);
   stamp(0);
   const int32_t* __restrict__ seq_lens = p.seq_lens;
@@ -846,7 +849,7 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
       softmax(S, sk_cur, sv_cur, cur, pb);
       pv(vt, pb, cur);
       load_v(vt, vbase, nxt);
-      if (nxt.g == P) {  // the next group opens another pair
+      if (TEAM == 0 && nxt.g == P) {  // the next group opens another pair
         end_pair(cur, from_start);
         begin_pair(nxt);
         from_start = true;
@@ -889,7 +892,7 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
     load_k(kta, ska, sva, vbase, cur, tk0, tv0);
     load_v(vta, vbase, cur);
     auto leave = [&](const Cursor& next) {  // after a group: does the next one open another pair
-      if (next.g == P) {
+      if (TEAM == 0 && next.g == P) {
         end_pair(cur, from_start);
         begin_pair(next);
         from_start = true;
