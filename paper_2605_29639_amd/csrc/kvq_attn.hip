@@ -140,6 +140,10 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
   const int wv = TEAM > 0 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) : 0;
   const int m16 = lane & 15, g4 = lane >> 4;
   const int w = blockIdx.x;
+  // The wavefront's first group.  Of two workgroups on a compute unit the second one's wavefronts sit one SIMD further
+  // on, so two groups each go to SIMDs 0, 2 and 1, 3 (with groups 0 and 1 in wavefronts 0 and 1: int8, head_dim 64, 44
+  // sequences of 94 tokens, 32 rows, 6.6 us for 5.7).
+  const int first = TEAM == 4 && PER_SIMD == 2 ? (wv & 1) * 2 + (wv >> 1) : wv;
   const int B = p.batch, Hp = p.pairs_per_seq;
   auto stamp = [&](int k, bool drain = false) {  // measurement build only
     if constexpr (CLOCK) {
@@ -197,9 +201,9 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
     cur.pr = w - cur.b * Hp;
     cur.L = seq_lens[cur.b];
     cur.ng = (cur.L + 63) >> 6;
-    cur.g = wv;
+    cur.g = first;
     f0 = 0;
-    f1 = max(cur.ng - wv + TEAM - 1, 0) / TEAM;
+    f1 = max(cur.ng - first + TEAM - 1, 0) / TEAM;
   } else if (B <= 64) {
     // lane i holds sequence i: one load and one scan give the list's length, the prefix sums
     // the reduce wants and, by a ballot, the sequence this wave's range starts in
@@ -799,7 +803,7 @@ __global__ __launch_bounds__(TEAM > 0 ? 64 * TEAM : 64, PER_SIMD) void attn_stre
   Operand pb[NT][2 * EB];
   [[maybe_unused]] int team_k = 0, team_v = 0;
   if constexpr (TEAM > 0) {  // (requested before anything asks for the sequence's length)
-    first_entries(wv, team_k, team_v);
+    first_entries(first, team_k, team_v);
     __builtin_amdgcn_sched_barrier(0);
   }
   const int count = f1 - f0;
