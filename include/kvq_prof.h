@@ -56,8 +56,8 @@ int kvq_profile_plan(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len,
 int kvq_profile_wide(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,
                      int32_t max_seq_len, int64_t wide_out[3]);
 
-/* Pieces that the prefix kernel would cut a shared prefix into, 0 where the call does without that kernel: where
- * kvq_profile_plan's shared_groups is 0, and where the prefix is not worth the launch.  Host only. */
+/* Pieces that the prefix kernel would cut a shared prefix into, 0 where the call does without that kernel (where
+ * plan_out[3] of kvq_profile_plan is 0).  Host only. */
 int kvq_profile_prefix_pieces(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,
                               int32_t max_seq_len, int32_t chunk_tokens, int32_t shared_prefix_tokens);
 

@@ -409,6 +409,23 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
   return true;
 }
 
+size_t workspace_bytes(const kvq::AttnPlan& plan) {
+  return (plan.acc_floats + plan.ml_floats + plan.prefix_ints) * sizeof(float);
+}
+
+// The plan that a call launches, and the workspace it asks for.  A prefix that is not worth its kernel leaves the call
+// paged_decode_attn's, in a workspace of the hint's size; the promise stays, for the checks.
+bool call_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t num_q_heads, int32_t max_seq_len,
+               int32_t chunk_tokens, int32_t shared_prefix_tokens, kvq::AttnPlan* plan, size_t* need, int* err) {
+  if (!make_plan(d, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, shared_prefix_tokens, plan, err)) return false;
+  *need = workspace_bytes(*plan);
+  if (plan->shared_groups == 0 || plan->prefix_pays) return true;
+  const int32_t promised = plan->promised_groups;
+  if (!make_plan(d, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, 0, plan, err)) return false;
+  plan->promised_groups = promised;
+  return true;
+}
+
 }  // namespace
 
 extern "C" {
@@ -458,7 +475,7 @@ size_t paged_decode_attn_workspace_bytes(const kvq_cache_desc_t* desc, int32_t b
   int err;
   if (!make_plan(desc, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, 0, &plan, &err))
     return 0;
-  return (plan.acc_floats + plan.ml_floats + plan.prefix_ints) * sizeof(float);
+  return workspace_bytes(plan);
 }
 
 size_t paged_decode_attn_prefix_workspace_bytes(const kvq_cache_desc_t* desc, int32_t batch,
@@ -470,7 +487,7 @@ size_t paged_decode_attn_prefix_workspace_bytes(const kvq_cache_desc_t* desc, in
   if (!make_plan(desc, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, shared_prefix_tokens,
                  &plan, &err))
     return 0;
-  return (plan.acc_floats + plan.ml_floats + plan.prefix_ints) * sizeof(float);
+  return workspace_bytes(plan);
 }
 
 }  // extern "C"
@@ -592,9 +609,10 @@ int attn_call(const void* q, const void* cache, const float* scales,
               int32_t shared_prefix_tokens, float* out, void* workspace, size_t workspace_bytes,
               bool own_scratch, void* stream) {
   kvq::AttnPlan plan;
+  size_t need;
   int err;
-  if (!make_plan(desc, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, shared_prefix_tokens,
-                 &plan, &err))
+  if (!call_plan(desc, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, shared_prefix_tokens,
+                 &plan, &need, &err))
     return err;
   if (max_blocks_per_seq < 0 ||
       (int64_t)max_blocks_per_seq * desc->block_size < (int64_t)max_seq_len)
@@ -605,12 +623,6 @@ int attn_call(const void* q, const void* cache, const float* scales,
   if (!scales && desc->mode != KVQ_BF16_PLAIN) return KVQ_E_NULLPTR;
   // the kernels read q and the cache and write out in 16-byte pieces
   if ((((uintptr_t)q | (uintptr_t)cache | (uintptr_t)out) & 15) != 0) return KVQ_E_BAD_SHAPE;
-  const size_t need = (plan.acc_floats + plan.ml_floats + plan.prefix_ints) * sizeof(float);
-  // (a prefix that is not worth its kernel: the call is paged_decode_attn's, in a workspace of the size asked for)
-  const int32_t promised = plan.promised_groups;
-  if (plan.shared_groups > 0 && !plan.prefix_pays &&
-      !make_plan(desc, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, 0, &plan, &err))
-    return err;
   if (own_scratch) {
     if (need > (size_t)KVQ_STATIC_WORKSPACE_BYTES) return KVQ_E_WORKSPACE;
     workspace = scratch_on_current_device();
@@ -629,7 +641,8 @@ int attn_call(const void* q, const void* cache, const float* scales,
                            0, (hipStream_t)stream, block_tables, seq_lens, batch,
                            max_blocks_per_seq, desc->num_blocks, desc->block_size, q_len,
                            max_seq_len,
-                           (promised * 64 + desc->block_size - 1) / desc->block_size, promised * 64, word);
+                           (plan.promised_groups * 64 + desc->block_size - 1) / desc->block_size,
+                           plan.promised_groups * 64, word);
       });
       if (rc != KVQ_OK) return rc;
     }
@@ -778,8 +791,9 @@ int kvq_profile_plan(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len,
                      int32_t max_seq_len, int32_t chunk_tokens, int32_t shared_prefix_tokens,
                      int64_t plan_out[8]) {
   kvq::AttnPlan p;
+  size_t need;
   int err;
-  if (!make_plan(desc, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, shared_prefix_tokens, &p, &err))
+  if (!call_plan(desc, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, shared_prefix_tokens, &p, &need, &err))
     return err;
   if (batch == 0) return KVQ_E_BAD_SHAPE;
   const kvq::ReduceLaunch r =
@@ -812,9 +826,11 @@ int kvq_profile_pair_waves(const kvq_cache_desc_t* desc, int32_t batch, int32_t 
 int kvq_profile_prefix_pieces(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,
                               int32_t max_seq_len, int32_t chunk_tokens, int32_t shared_prefix_tokens) {
   kvq::AttnPlan p;
+  size_t need;
   int err;
-  if (!make_plan(desc, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, shared_prefix_tokens, &p, &err)) return err;
-  return p.shared_groups > 0 && p.prefix_pays ? p.prefix_chunks : 0;
+  if (!call_plan(desc, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, shared_prefix_tokens, &p, &need, &err))
+    return err;
+  return p.shared_groups > 0 ? p.prefix_chunks : 0;
 }
 
 int kvq_profile_group_rows(const kvq_cache_desc_t* desc, int32_t batch, int32_t q_len, int32_t num_q_heads,

@@ -158,17 +158,23 @@ def test_a_workgroup_for_each_pair_walks_few_groups(mode, D, hq, team, rounds):
 
 
 @pytest.mark.parametrize("mode,D,q_len,prefix,used", [
-    (0, 128, 4, 64, True), (0, 128, 5, 64, True),                                  # streaming calls: always
+    (0, 128, 1, 4096, True), (0, 128, 8, 4096, True), (0, 64, 8, 8192, True),       # streaming calls: where it is worth it
+    (0, 128, 4, 64, False), (0, 128, 5, 64, False), (0, 64, 12, 64, False),
     (0, 128, 12, 64, False), (1, 128, 12, 6144, False), (2, 64, 15, 8192, False),   # above 64 rows: never
-    (2, 128, 5, 64, False), (2, 128, 8, 4032, False), (2, 128, 8, 4096, True),      # up to 64: from half on
-    (0, 64, 12, 64, True), (0, 64, 13, 64, False)])
+    (2, 128, 5, 64, False), (2, 128, 8, 4032, False), (2, 128, 5, 6144, True), (0, 64, 13, 64, False)])
 def test_a_shared_prefix_does_not_keep_a_call_from_the_many_row_kernel(mode, D, q_len, prefix, used):
     """A hint is never slower than none by more than the prefix is worth, and asks for the same workspace
-    whether the prefix is used or not."""
+    whether the prefix is used or not.  The plan is what is launched: that of the call without a hint where
+    the prefix is not used (with more room for cuts in a many-row call)."""
     desc = d(mode=mode, H=8, D=D, nblk=64)
-    p = plan(desc, 32, q_len, 64, 8192, prefix=prefix)
+    p, without = plan(desc, 32, q_len, 64, 8192, prefix=prefix), plan(desc, 32, q_len, 64, 8192)
     assert p["shared_groups"] == (prefix // 64 if used else 0)
-    assert bool(p["many_rows"]) == (bool(plan(desc, 32, q_len, 64, 8192)["many_rows"]) and not used)
+    pieces = kvq.prof_lib().kvq_profile_prefix_pieces(C.byref(desc), 32, q_len, 64, 8192, 0, prefix)
+    assert (pieces > 0) == used
+    assert bool(p["many_rows"]) == (bool(without["many_rows"]) and not used)
+    if not used:
+        assert p["extra_pieces"] >= without["extra_pieces"]
+        assert dict(p, extra_pieces=0) == dict(without, extra_pieces=0)
     plain = kvq.workspace_bytes(desc, 32, q_len, 64, 8192, 0)
     assert kvq.workspace_bytes(desc, 32, q_len, 64, 8192, 0, prefix) > plain
 

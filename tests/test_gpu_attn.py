@@ -334,11 +334,12 @@ def test_shared_prefix_is_read_through_stacked_rows(mode, q_len, lens):
     through the streaming kernel, and the reduce merges the two: the output stays within the
     bound of the checker and close to paged_decode_attn's (other order of the fp32 merges; the
     probabilities are rounded to 16 bits against a running maximum that depends on the order),
-    also with ranges given by chunk_tokens, with a prefix that is not a multiple of 64, with a
-    sequence that is nothing but the prefix (its query rows then mask part of it) and with more
-    sequences than a wavefront has lanes.  A prefix longer than the shortest sequence is dropped
-    (on the host if it exceeds max_seq_len, else on the device), as is one below 64 tokens or
-    with a single sequence: bit for bit paged_decode_attn's output then."""
+    with a prefix that is not a multiple of 64, with a sequence that is nothing but the prefix (its
+    query rows then mask part of it) and with more sequences than a wavefront has lanes.  A prefix
+    longer than the shortest sequence is dropped (on the host if it exceeds max_seq_len, else on the
+    device), as is one below 64 tokens or with a single sequence: bit for bit paged_decode_attn's output
+    then.  The ranges are given by chunk_tokens, which keeps the prefix; with the automatic split all
+    these hints are dropped on the host (the next test has those that are not)."""
     import ctypes as C
     from paper_2605_29639_amd import kvq
     wl = W.custom("prefix", mode, PREFIX_LENS[lens], q_len, 8, 2, 128, 16,
@@ -351,14 +352,14 @@ def test_shared_prefix_is_read_through_stacked_rows(mode, q_len, lens):
     plan = (C.c_int64 * 8)()
     for chunk in (0, 128, 512):
         assert kvq.prof_lib().kvq_profile_plan(C.byref(desc), wl.batch, q_len, 8, wl.max_seq_len, chunk, 256, plan) == kvq.OK
-        # (short contexts of few sequences have no use for it: a workgroup for each pair)
-        assert (plan[3] == 4) == (lens in ("ragged", "crowd") or lens == "many" and (chunk > 0 or mode == W.MODE_BF16))
+        # (with the automatic split so short a prefix is not worth its kernel)
+        assert (plan[3] == 4) == (chunk > 0 and lens != "one")
         plain = gpu_attention(wl, cache, scales, desc, chunk_tokens=chunk)
         assert attn_err(plain, want) <= TOL
         for hint in (256, 200, 64, 63, 4096) + ((shortest + 64,) if lens != "one" else ()):
             hinted = gpu_attention(wl, cache, scales, desc, chunk_tokens=chunk,
                                    shared_prefix_tokens=hint)
-            used = 64 <= hint and hint // 64 * 64 <= shortest and len(PREFIX_LENS[lens]) > 1
+            used = chunk > 0 and 64 <= hint and hint // 64 * 64 <= shortest and len(PREFIX_LENS[lens]) > 1
             if not used:
                 assert np.array_equal(hinted.view(np.uint32), plain.view(np.uint32)), hint
             else:
