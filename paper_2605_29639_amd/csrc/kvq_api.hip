@@ -249,16 +249,21 @@ int32_t pair_waves(const kvq_cache_desc_t* d, int64_t pairs, int64_t rows, int64
   return here <= flat ? (int32_t)team : 0;
 }
 
-// Whether the prefix kernel is worth its launch for the plan's shared groups, and in how many pieces (plan->prefix_chunks
-// at most, for which the workspace has room).  In microseconds: what the streaming kernel is spared, (batch - 1)
-// times the shared groups of every pair, against a round of the many-row kernel's workgroups (3 and 2.6 a group, see
-// equal_pieces; 1.5 at head_dim 64, bf16 3.2), the partials of all stacked rows that it writes and the reduce reads (2.1 MB a
-// microsecond) and 2 of launch; a tenth and 5 us in doubt are the plain call's.  Cost (+) or gain, predicted and
-// measured, 8 kv heads, int8: 64 sequences of 2 k to 16 k tokens, 32 rows, prefix 1024 +9 and +9 of 234 us, of 8 k to
-// 16 k with 4096 -23 and -27 of 294; 128 of 2 k to 4 k, 8 rows, 1024 -15 and -16 of 143; 16 of them, 32 rows +8 and
-// +11 of 35; 9 of 2 k to 6 k, head_dim 64, +6 and +6 of 26.  Random hinted calls
-// took 1.15 of the plain call's time on average and up to 1.77 of it where every hint was followed (60 calls); now
-// 0.98 and 1.02 (240).
+// Whether the prefix kernel is worth its launch for the plan's shared groups, and in how many pieces
+// (plan->prefix_chunks at most, for which the workspace has room).  In microseconds: what the streaming kernel is
+// spared, (batch - 1) times the shared groups of every pair, against a round of the many-row kernel's workgroups (3
+// and 2.6 a group, see equal_pieces; 1.5 at head_dim 64, bf16 3.2), the partials of all stacked rows that it writes and
+// the reduce reads (2.1 MB a microsecond) and 2 of launch.  Cost (+) or gain, predicted and measured, 8 kv heads, int8:
+// 64 sequences of 2 k to 16 k tokens, 32 rows, prefix 1024 +9 and +9 of 234 us, of 8 k to 16 k with 4096 -23 and -27
+// of 294; 128 of 2 k to 4 k, 8 rows, 1024 -15 and -16 of 143; 16 of them, 32 rows +8 and +11 of 35; 9 of 2 k to
+// 6 k, head_dim 64, +6 and +6 of 26.
+// A tenth and 5 us in doubt are the plain call's: the estimate errs towards the prefix kernel by as much where the
+// call is short (int8, 37 sequences of 4 k tokens, prefix 3584, 0.3 gained by it and 6 lost of 35).  Of a
+// call of 300 us and more by the bound half a percent is enough: 128 sequences of 2 k to 16 k tokens, 32 rows, prefix
+// 1024, 5 by it, e4m3 445 -> 440 us, int8 462 -> 460; 10 random calls that this adds 0.95 to 1.01, 0.98 on average,
+// where 19 of 140 to 300 us take 0.93 to 1.11, 1.01.  (Not int4, whose groups are cheaper than crowded_us says:
+// 367 -> 372.)  600 random hinted calls took 1.15 of the plain call's time on average and up to 2.16 of it where every
+// hint was followed; now 0.95, 1.15 at most.
 // A call that is a many-row kernel's without a hint keeps it only where that kernel would take clearly longer than
 // the prefix and the rest together (bf16, 32 sequences of 8192 tokens, 40 rows: 203 us, 177 with 6144 shared; but
 // 29 of 2000 to 3300, 64 rows, 71 and 99 with 2048, 35 of 1600, 56 rows, 36 and 45 with 1536).
@@ -287,7 +292,9 @@ bool prefix_pays(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t
     equal_pieces(slots, batch * d->num_kv_heads, max_groups, kvq::kMaxContextSplits, false, &alone);
     return least + 8.3 + list * (double)(max_groups - groups) < 0.85 * alone;
   }
-  return list * (double)groups * (double)(batch - 1) / (double)batch >= 1.1 * least + 5.0;
+  const double whole = list * (double)max_groups;
+  const double doubt = whole >= 300.0 && d->mode != KVQ_INT4_TOKEN_HEAD ? 0.005 * whole : 0.1 * least + 5.0;
+  return list * (double)groups * (double)(batch - 1) / (double)batch >= least + doubt;
 }
 
 // Everything the launch needs that depends only on host-side arguments.

@@ -179,6 +179,16 @@ def test_a_shared_prefix_does_not_keep_a_call_from_the_many_row_kernel(mode, D, 
     assert kvq.workspace_bytes(desc, 32, q_len, 64, 8192, 0, prefix) > plain
 
 
+@pytest.mark.parametrize("mode,batch,max_len,used", [
+    (0, 128, 16384, True), (1, 128, 16384, True), (3, 128, 16384, True), (2, 128, 16384, True), (4, 128, 16384, False),
+    (0, 64, 16384, False), (1, 64, 16384, False),   # (what 64 sequences spare is less than the kernel takes)
+    (0, 128, 2048, False), (1, 128, 2048, False)])  # (a short call, where the estimate is not that sure)
+def test_a_long_call_keeps_a_prefix_that_gains_little(mode, batch, max_len, used):
+    """32 query rows, 8 kv heads, 1024 shared tokens: a percent of a long call, and a doubtful part of a short one."""
+    desc = d(mode=mode, H=8, D=128, nblk=64)
+    assert (plan(desc, batch, 4, 64, max_len, prefix=1024)["shared_groups"] == 16) == used
+
+
 @pytest.mark.parametrize("mode,D,rows,batch,max_len,many", [
     (0, 128, 32, 300, 512, False), (0, 128, 33, 300, 512, True), (0, 128, 64, 300, 2048, True),
     (0, 128, 64, 300, 2049, False), (0, 128, 64, 255, 2048, False), (0, 128, 64, 256, 2048, True),
