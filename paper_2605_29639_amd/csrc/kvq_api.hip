@@ -265,8 +265,12 @@ int32_t pair_waves(const kvq_cache_desc_t* d, int64_t pairs, int64_t rows, int64
 // 367 -> 372.)  600 random hinted calls took 1.15 of the plain call's time on average and up to 2.16 of it where every
 // hint was followed; now 0.95, 1.15 at most.
 // A call that is a many-row kernel's without a hint keeps it only where that kernel would take clearly longer than
-// the prefix and the rest together (bf16, 32 sequences of 8192 tokens, 40 rows: 203 us, 177 with 6144 shared; but
-// 29 of 2000 to 3300, 64 rows, 71 and 99 with 2048, 35 of 1600, 56 rows, 36 and 45 with 1536).
+// the prefix and the rest together: by 6 us and 15 %, with codes 40 % (whose kernel is faster than equal_pieces says
+// in the short contexts where it takes so few rows).  bf16, 32 sequences of 8192 tokens, 40 rows: 203 us, 177 with
+// 6144 shared; 91 of 4000, 48 rows, 4 kv heads, 154 and 120 with 3840; but 29 of 2000 to 3300, 64 rows, 71 and 99
+// with 2048, 35 of 1600, 56 rows, 36 and 45 with 1536; e4m3, 132 of 1100, 44 rows, 102 and 116 with 832.  160
+// random such calls: 0.91 of their time without a hint on average, 1.06 at most, and 0.77 of where every hint was
+// followed, 1.10 at most.
 bool prefix_pays(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t max_groups, int64_t slots, bool many,
                  kvq::AttnPlan* plan) {
   const int64_t groups = plan->shared_groups, stacked = batch * rows;
@@ -287,10 +291,11 @@ bool prefix_pays(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t
   const double group_us = crowded_us(d, plan->row_tiles) / (double)(2 * slots * per_simd);
   const double list = (double)batch * (double)plan->pairs_per_seq * group_us;  // (for one group of every context)
   if (many) {
-    if (d->head_dim != 128 || groups < 64) return false;  // (of few groups the estimates are off by 10 us)
+    if (d->head_dim != 128) return false;
     double alone;
     equal_pieces(slots, batch * d->num_kv_heads, max_groups, kvq::kMaxContextSplits, false, &alone);
-    return least + 8.3 + list * (double)(max_groups - groups) < 0.85 * alone;
+    return least + 8.3 + list * (double)(max_groups - groups) + 6.0 <
+           (d->mode == KVQ_BF16_PLAIN ? 0.85 : 0.6) * alone;
   }
   const double whole = list * (double)max_groups;
   const double doubt = whole >= 300.0 && d->mode != KVQ_INT4_TOKEN_HEAD ? 0.005 * whole : 0.1 * least + 5.0;

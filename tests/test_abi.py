@@ -189,6 +189,20 @@ def test_a_long_call_keeps_a_prefix_that_gains_little(mode, batch, max_len, used
     assert (plan(desc, batch, 4, 64, max_len, prefix=1024)["shared_groups"] == 16) == used
 
 
+@pytest.mark.parametrize("mode,batch,q_len,max_len,prefix,used", [
+    (2, 91, 3, 4199, 3840, True), (2, 157, 3, 3072, 2752, True), (0, 280, 3, 2000, 1920, True),
+    (2, 141, 3, 7300, 6592, True),
+    (2, 20, 3, 1700, 1600, False), (2, 29, 4, 3300, 2048, False), (2, 7, 3, 1024, 960, False), (0, 132, 3, 1095, 832, False)])
+def test_a_many_row_call_keeps_a_prefix_that_gains_much(mode, batch, q_len, max_len, prefix, used):
+    """33 to 64 rows of a crowd behind one prompt, whatever the prompt's length: the many-row kernel alone would read
+    the prompt's keys and values for every sequence."""
+    desc = d(mode=mode, H=4, D=128, nblk=64)
+    without = plan(desc, batch, q_len, 64, max_len)
+    p = plan(desc, batch, q_len, 64, max_len, prefix=prefix)
+    assert without["many_rows"] == 1
+    assert (p["shared_groups"], p["many_rows"]) == ((prefix // 64, 0) if used else (0, 1))
+
+
 @pytest.mark.parametrize("mode,D,rows,batch,max_len,many", [
     (0, 128, 32, 300, 512, False), (0, 128, 33, 300, 512, True), (0, 128, 64, 300, 2048, True),
     (0, 128, 64, 300, 2049, False), (0, 128, 64, 255, 2048, False), (0, 128, 64, 256, 2048, True),
