@@ -185,25 +185,31 @@ bool many_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t m
 }
 
 // Whether a call goes to the many-row kernel of group-scaled int4 (one that a caller's granule does not keep on the
-// streaming kernel, and whose pairs do not get a workgroup each).  The streaming kernel takes 2.2 us for a wavefront's group of 16 rows, two wavefronts to a
-// SIMD's time, and 8.3 beside that; the other one 1.35 of what equal_pieces says, with no less for a row block of 33
-// rows than for one of 128.  A tenth in doubt is the streaming kernel's, whose ranges are even whatever the mixture of
-// lengths.  us a call by the estimates and measured, streaming and many-row, 8 kv heads: 64 sequences of 2000 to
-// 4000 tokens, 64 rows, 285 and 225 (bounds), 231 and 221; 20 of 500 to 1000, 96 rows, 41 and 36, 44.7 and 35.4; 2 x 128
-// tokens over 2500, 512 rows, 52 and 40, 54 and 42; not taken: 8 of 2000 to 8000, 64 rows, 77 and 85, 56 and 62; 1 x
-// 441 tokens over 469, 2 kv heads, 14 and 20, 22 and 25; 32 rows, of which one wavefront in four is busy, 147 and
-// 225, 126 and 153 at the first lengths.  Of 45 random calls that it takes, mixtures of long and short among them,
-// 0.64 of the streaming kernel's time on average and 1.00 at most; the error against 64 bits is no larger (1.67e-4 and
-// now 1.65e-4, 1.54e-4 and 1.52e-4, 1.64e-4 twice, 1.72e-4 twice).
-bool group_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t groups, int64_t slots) {
+// streaming kernel, and whose pairs do not get a workgroup each).  The streaming kernel takes 2.2 us for a wavefront's
+// group of 16 rows, two wavefronts to a SIMD's time, and 8.3 beside that; the other one 1.35 of what equal_pieces says,
+// with no less for a row block of 33 rows than for one of 128.  A tenth in doubt is the streaming kernel's, whose
+// ranges are even whatever the mixture of lengths, and a twentieth beside as many pieces as the workspace has room for
+// (34 random calls that the second line leaves to the streaming kernel: many-row 1.00 of its time on average, up to
+// 1.28, 22 of 2300 to 9300 tokens, 160 rows, 4 kv heads, 196 and 252; as strict as the first it would leave 32 more,
+// of which it takes 0.96).  us a call by the estimates and measured, streaming and many-row, 8 kv heads: 64 sequences
+// of 2000 to 4000 tokens, 64 rows, 285 and 225
+// (bounds), 231 and 221; 20 of 500 to 1000, 96 rows, 41 and 36, 44.7 and 35.4; 2 x 128 tokens over 2500, 512 rows, 52
+// and 40, 54 and 42; 1 x 512 over 16896, 2048 rows, 590 and 297, 531 and 310; not taken: 8 of 2000 to 8000, 64 rows,
+// 77 and 85, 56 and 62; 1 x 441 tokens over 469, 2 kv heads, 14 and 20, 22 and 25; 32 rows, of which one wavefront in
+// four is busy, 147 and 225, 126 and 153 at the first lengths.  Of 45 random calls that it takes, mixtures of long
+// and short among them, 0.64 of the streaming kernel's time on average and 1.00 at most; the error against 64 bits is
+// no larger (1.67e-4 and now 1.65e-4, 1.54e-4 and 1.52e-4, 1.64e-4 twice, 1.72e-4 twice).
+bool group_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t groups, int64_t slots, int64_t room) {
   if (d->mode != KVQ_INT4_GROUP32 || rows <= 32 || batch < 1) return false;
   const int64_t blocks = (rows + kvq::kRowsPerWorkgroup - 1) / kvq::kRowsPerWorkgroup;
   // (a grid and its merge have fewer than 2^32 threads)
   if (batch * d->num_kv_heads * blocks > 1 << 19) return false;
   const double pairs = (double)(batch * d->num_kv_heads) * (double)((rows + 15) / 16);
-  double us;
+  const double streaming = 8.3 + 2.2 * pairs * (double)groups / (double)(2 * slots);
+  double us, cut_us;
   equal_pieces(slots, batch * d->num_kv_heads * blocks, groups, kvq::kMaxContextSplits, false, &us);
-  return 1.35 * us <= 0.9 * (8.3 + 2.2 * pairs * (double)groups / (double)(2 * slots));
+  equal_pieces(slots, batch * d->num_kv_heads * blocks, groups, room, false, &cut_us);
+  return 1.35 * us <= 0.9 * streaming && 1.35 * cut_us <= 0.95 * streaming;
 }
 
 // Wavefronts of the workgroup that each (sequence, kv head, row group) pair gets in a call that does without the
@@ -271,8 +277,8 @@ int32_t pair_waves(const kvq_cache_desc_t* d, int64_t pairs, int64_t rows, int64
 // with 2048, 35 of 1600, 56 rows, 36 and 45 with 1536; e4m3, 132 of 1100, 44 rows, 102 and 116 with 832.  160
 // random such calls: 0.91 of their time without a hint on average, 1.06 at most, and 0.77 of where every hint was
 // followed, 1.10 at most.
-bool prefix_pays(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t max_groups, int64_t slots, bool many,
-                 kvq::AttnPlan* plan) {
+bool prefix_pays(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t max_groups, int64_t slots, int64_t room,
+                 bool many, kvq::AttnPlan* plan) {
   const int64_t groups = plan->shared_groups, stacked = batch * rows;
   const int64_t walks = d->num_kv_heads * ((stacked + kvq::kRowsPerWorkgroup - 1) / kvq::kRowsPerWorkgroup);
   const double partials = (double)stacked * d->num_kv_heads * d->head_dim * 4.0 / 2.1e6;
@@ -293,7 +299,7 @@ bool prefix_pays(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t
   if (many) {
     if (d->head_dim != 128) return false;
     double alone;
-    equal_pieces(slots, batch * d->num_kv_heads, max_groups, kvq::kMaxContextSplits, false, &alone);
+    equal_pieces(slots, batch * d->num_kv_heads, max_groups, room, false, &alone);
     return least + 8.3 + list * (double)(max_groups - groups) + 6.0 <
            (d->mode == KVQ_BF16_PLAIN ? 0.85 : 0.6) * alone;
   }
@@ -377,6 +383,10 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
   plan->acc_floats = slot_rows * d->head_dim;
   plan->ml_floats = slot_rows * 2;
   plan->prefix_ints = ((size_t)batch + 2 + 3) & ~(size_t)3;  // prefix sums, prefix length
+  // pieces of a context that a many-row kernel has room for in the workspace of a call without a hint
+  const int64_t room = batch == 0 ? 1
+                                  : (plan->num_waves + batch * pairs) * 16 * row_tiles /
+                                            ((int64_t)q_len * num_q_heads) / batch + 1;
   // The group-scaled int4 kernel runs two wavefronts per SIMD as well.  Its workspace is that of one, so
   // twice the wavefronts have room for their partials where a slot needs only eight rows; with
   // more the call keeps to one.  So do lists of less than four groups for each of the 2048, where a
@@ -405,14 +415,14 @@ bool make_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t 
   // (a caller's split-K granule keeps the prefix in as many pieces as there is room for)
   plan->prefix_pays = plan->shared_groups > 0 &&
                       (chunk_tokens > 0 || prefix_pays(d, batch, rows, ((int64_t)max_seq_len + 63) / 64, slots_128,
-                                                       plan->many_rows, plan));
+                                                       room, plan->many_rows, plan));
   if (plan->shared_groups > 0) plan->many_rows = 0;
   // (A call whose pairs get a workgroup each needs no prefix kernel either, and the same whether it has a
   // hint or not.)
   plan->pair_waves = plan->many_rows || chunk_tokens > 0
                          ? 0 : pair_waves(d, batch * pairs, rows, ((int64_t)max_seq_len + 63) / 64, plan->row_tiles, waves);
   plan->group_rows = chunk_tokens == 0 && plan->pair_waves == 0 &&
-                     group_rows(d, batch, rows, ((int64_t)max_seq_len + 63) / 64, slots_128);
+                     group_rows(d, batch, rows, ((int64_t)max_seq_len + 63) / 64, slots_128, room);
   if (plan->pair_waves > 0) plan->shared_groups = 0;
   plan->wide_groups = plan->wide_least = 0;
   if (plan->many_rows || plan->group_rows)

@@ -203,6 +203,17 @@ def test_a_many_row_call_keeps_a_prefix_that_gains_much(mode, batch, q_len, max_
     assert (p["shared_groups"], p["many_rows"]) == ((prefix // 64, 0) if used else (0, 1))
 
 
+@pytest.mark.parametrize("hkv,hq,batch,q_len,max_len,many", [
+    (8, 32, 8, 512, 4608, True), (8, 32, 1, 512, 16896, True), (8, 32, 1, 147, 4287, True), (8, 64, 64, 8, 4000, True),
+    (8, 64, 8, 8, 8000, False), (2, 12, 1, 441, 469, False),
+    (4, 64, 22, 10, 9297, False), (8, 32, 9, 19, 18117, False), (1, 64, 4, 5, 34831, False)])   # pieces without room
+def test_group_scaled_int4_counts_the_pieces_that_it_has_room_for(hkv, hq, batch, q_len, max_len, many):
+    """The workspace of one row tile holds few pieces of a context: a call that would need many to be the faster one
+    in the many-row kernel stays with the streaming kernel."""
+    desc = d(mode=5, H=hkv, D=128, nblk=64)
+    assert kvq.prof_lib().kvq_profile_group_rows(C.byref(desc), batch, q_len, hq, max_len, 0) == many
+
+
 @pytest.mark.parametrize("mode,D,rows,batch,max_len,many", [
     (0, 128, 32, 300, 512, False), (0, 128, 33, 300, 512, True), (0, 128, 64, 300, 2048, True),
     (0, 128, 64, 300, 2049, False), (0, 128, 64, 255, 2048, False), (0, 128, 64, 256, 2048, True),
