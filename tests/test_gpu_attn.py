@@ -465,7 +465,7 @@ def test_contexts_are_cut_by_their_lengths(mode, D, G, q_len, lens):
     ([700, 655, 799] * 42, 13, 4, 4, 16),                 # 52 rows: a second row tile of four, two wavefronts without any
     ([900, 64, 65, 1, 959] * 40, 1, 65, 2, 64),           # 65 rows, contexts of one token and of whole groups
     ([640] * 60 + [4100], 16, 8, 2, 32),                  # 128 rows, one long context, cut alone
-    ([300, 1025, 513] * 4, 290, 4, 4, 16), ([4097], 129, 8, 4, 128), ([3000, 2990] * 2, 257, 8, 1, 256)])
+    ([300, 1025, 513] * 4, 290, 4, 4, 16), ([4287], 147, 4, 8, 128), ([3000, 2990] * 2, 257, 8, 1, 256)])
 def test_many_rows_of_group_scaled_int4(lens, q_len, G, H, bs):
     """The many-row kernel of group-scaled int4, against the oracle on sequences of every length and against the
     streaming kernel on all (either rounds f16 probabilities: 2^-12 of a row's largest term), under a bound
