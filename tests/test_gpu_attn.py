@@ -367,14 +367,17 @@ def test_shared_prefix_is_read_through_stacked_rows(mode, q_len, lens):
                 assert attn_err(hinted, plain.astype(np.float64)) <= 2e-4, (chunk, hint)
 
 
-@pytest.mark.parametrize("mode", [W.MODE_INT8, W.MODE_FP8, W.MODE_BF16, W.MODE_INT4])
-def test_a_shared_prefix_is_used_where_it_is_worth_the_launch(mode):
+@pytest.mark.parametrize("mode,D", [(W.MODE_INT8, 128), (W.MODE_FP8, 128), (W.MODE_BF16, 128), (W.MODE_INT4, 128),
+                                    (W.MODE_INT8, 64), (W.MODE_FP8_TENSOR, 64), (W.MODE_BF16, 64)])
+def test_a_shared_prefix_is_used_where_it_is_worth_the_launch(mode, D):
     """260 sequences behind 2048 shared tokens keep the hint, in fewer pieces than there is room for; of
-    16 sequences, or of 64 tokens, it is dropped on the host: bit for bit paged_decode_attn's output."""
+    16 sequences, or of 64 tokens, it is dropped on the host: bit for bit paged_decode_attn's output.  A hint that
+    was kept is dropped on the device where one sequence is shorter than the prefix: the same results up to
+    the order of the merges."""
     from paper_2605_29639_amd import kvq
     pieces = kvq.prof_lib().kvq_profile_prefix_pieces
     for batch, hint, used in ((260, 2048, True), (260, 2000, True), (260, 64, False), (16, 2048, False)):
-        wl = W.custom("prefix_pays", mode, [2048 + 5 + 7 * (i % 9) for i in range(batch)], 2, 4, 2, 128, 16,
+        wl = W.custom("prefix_pays", mode, [2048 + 5 + 7 * (i % 9) for i in range(batch)], 2, 4, 2, D, 16,
                       seed=190 + mode, shared_prefix=2048)
         oc, osc = oracle_fill(wl)
         cache, scales, desc = upload_oracle_cache(wl, oc, osc)
@@ -386,6 +389,38 @@ def test_a_shared_prefix_is_used_where_it_is_worth_the_launch(mode):
             continue
         assert attn_err(hinted, oracle_out(wl, oc, osc)) <= TOL
         assert attn_err(hinted, plain.astype(np.float64)) <= 2e-4
+        short = wl.seq_lens.copy()
+        short[3] = 700
+        plain = gpu_attention(wl, cache, scales, desc, seq_lens=short, max_len=wl.max_seq_len)
+        dropped = gpu_attention(wl, cache, scales, desc, seq_lens=short, max_len=wl.max_seq_len,
+                                shared_prefix_tokens=hint)
+        assert np.isfinite(dropped).all()
+        assert attn_err(dropped, plain.astype(np.float64)) <= 2e-4
+
+
+@pytest.mark.parametrize("mode,batch,hkv,q_len,longest,prefix,pieces,many", [
+    (W.MODE_BF16, 91, 4, 3, 4199, 3840, 3, 1), (W.MODE_BF16, 80, 2, 5, 2200, 2048, 5, 1),
+    (W.MODE_INT8, 120, 2, 5, 2200, 2048, 3, 0), (W.MODE_FP8, 300, 1, 3, 2200, 2048, 2, 0)])
+def test_a_shared_prefix_under_33_to_64_rows(mode, batch, hkv, q_len, longest, prefix, pieces, many):
+    """Two row groups of stacked rows, in calls that are the many-row kernel's without the hint and in streaming ones,
+    against the oracle on a few sequences and the call without the hint on all."""
+    from paper_2605_29639_amd import kvq
+    hq = 16 * hkv if q_len == 3 else 8 * hkv
+    lens = [longest - 3 * (i % 40) for i in range(batch)]
+    wl = W.custom("prefix rows", mode, lens, q_len, hq, hkv, 128, 16, seed=230 + mode, shared_prefix=prefix)
+    cache, scales, desc = gpu_fill(wl)
+    prof, plan = kvq.prof_lib(), (C.c_int64 * 8)()
+    assert prof.kvq_profile_plan(C.byref(desc), batch, q_len, hq, longest, 0, 0, plan) == kvq.OK and plan[0] == many
+    assert prof.kvq_profile_prefix_pieces(C.byref(desc), batch, q_len, hq, longest, 0, prefix) == pieces
+    hinted = gpu_attention(wl, cache, scales, desc, chunk_tokens=0, shared_prefix_tokens=prefix)
+    assert attn_err(hinted, gpu_attention(wl, cache, scales, desc, chunk_tokens=0).astype(np.float64)) <= 2e-4
+    seqs = [0, 1, batch - 1]   # (the first one writes the prefix)
+    oc, osc = oracle_fill(wl, sequences=seqs)
+    rows = np.concatenate([np.arange(b * q_len, (b + 1) * q_len) for b in seqs])
+    want = oracle.paged_decode_attn(np.ascontiguousarray(wl.q[rows]), oc, osc, mode,
+                                    np.ascontiguousarray(wl.block_tables[seqs]),
+                                    np.ascontiguousarray(wl.seq_lens[seqs]), q_len, wl.sm_scale)
+    assert attn_err(hinted[rows], want) <= TOL
 
 
 @pytest.mark.parametrize("mode,D", [(m, 128) for m in MODES if m != W.MODE_INT4_GROUP] +

@@ -3,6 +3,8 @@ bench.py times.  The library writes and attends over the whole workload; the CPU
 writes and attends over a sample of sequences (it could do all of them, one by one, but
 that takes minutes), and the two are compared on those: cache bytes and scales bit for bit,
 attention within 2e-3 of the sampled output's max norm.  Every output must be finite."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -118,6 +120,9 @@ def test_verify_prefix_full_size(mode):
     wl = W.verify_prefix(mode=mode)
     assert wl.batch == 128 and wl.q_len == 4 and wl.group == 8 and wl.shared_prefix == 1024
     assert np.all(wl.block_tables[:, :64] == wl.block_tables[0, :64])
+    from paper_2605_29639_amd import kvq
+    from paper_2605_29639_amd.fill import gpu_desc
+    assert kvq.prof_lib().kvq_profile_prefix_pieces(C.byref(gpu_desc(wl)), 128, 4, 64, wl.max_seq_len, 0, 1024) > 0
     compare_on_sample(wl, chunks=(0,), seqs=sample_sequences(wl, extra=1))
 
 

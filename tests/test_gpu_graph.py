@@ -3,6 +3,8 @@ validation, so a decode step (kv_quant_write of the newest tokens + paged_decode
 captured in a HIP graph once and replayed: the sequence lengths, tables, queries and new rows
 are read on the device at every replay.  Each replay is checked bit for bit against the same
 calls made eagerly on the same inputs, with eager work and synchronisations in between."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -81,9 +83,9 @@ def test_a_captured_verify_step_with_a_shared_prefix_replays_like_eager_calls():
     sequence has become shorter than the prefix falls back by itself."""
     import torch
     from paper_2605_29639_amd import kvq
-    q_len, prefix = 4, 256
-    wl = W.custom("graph_prefix", W.MODE_INT8, [700, 300, 1030, 260], q_len, 8, 2, 128, 16, seed=6,
-                  shared_prefix=prefix)
+    q_len, prefix = 2, 2048
+    wl = W.custom("graph_prefix", W.MODE_INT8, [2100 + 7 * (i % 9) for i in range(260)], q_len, 4, 2, 128, 16,
+                  seed=6, shared_prefix=prefix)
     B, Hq, D, H = wl.batch, wl.num_q_heads, wl.head_dim, wl.num_kv_heads
     max_len = int(wl.seq_lens.max())
     bt = torch.from_numpy(wl.block_tables).cuda()
@@ -105,6 +107,7 @@ def test_a_captured_verify_step_with_a_shared_prefix_replays_like_eager_calls():
                               shared_prefix_tokens=prefix)
 
     cache_g, scales_g, desc = gpu_fill(wl)
+    assert kvq.prof_lib().kvq_profile_prefix_pieces(C.byref(desc), B, q_len, Hq, max_len, 0, prefix) > 1
     cache_e, scales_e = cache_g.clone(), scales_g.clone()
     ws_g = kvq.alloc_workspace(desc, B, q_len, Hq, max_len, 0, shared_prefix_tokens=prefix)
     ws_e = kvq.alloc_workspace(desc, B, q_len, Hq, max_len, 0, shared_prefix_tokens=prefix)
@@ -129,11 +132,11 @@ def test_a_captured_verify_step_with_a_shared_prefix_replays_like_eager_calls():
     for replay in range(4):
         if replay == 1:      # other decode positions, every sequence still holds the prefix
             lens[0] -= 37
-            lens[2] -= 500
+            lens[2] -= 50
         if replay == 2:      # sequence 3 shorter than the prefix: the prefix is not used
-            lens[3] = 200
+            lens[3] = 1000
         if replay == 3:
-            lens[3] = 256    # exactly the prefix: nothing but shared positions
+            lens[3] = 2048   # exactly the prefix: nothing but shared positions
         new = fresh_inputs(lens)
         for dst, src in zip(static, new):
             dst.copy_(src)
