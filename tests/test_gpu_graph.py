@@ -188,3 +188,50 @@ def test_a_captured_many_row_call_cuts_the_contexts_of_each_replay(mode, D, q_le
         torch.cuda.synchronize()
         assert torch.equal(out[0], out[1]), lens
         assert torch.isfinite(out[0]).all()
+
+
+@pytest.mark.parametrize("to_packed", [True, False], ids=["export", "import"])
+@pytest.mark.parametrize("host", [False, True], ids=["device", "pinned_host"])
+def test_a_captured_block_move_replays_like_an_eager_one(host, to_packed):
+    """Moves of more pieces than a move from or to host memory has in flight, which ask where the packed area
+    lies: a capture takes that like any other call, and every replay moves what is there at the time."""
+    import torch
+    from paper_2605_29639_amd import kvq
+    num = 300                                   # 8 pieces of 4 KiB a block
+    desc = kvq.make_desc(W.MODE_INT8, num + 50, 16, 8, 128)
+    cache, scales = kvq.alloc_cache(desc)
+    nbytes, nscales = kvq.packed_sizes(desc, num)
+    where = dict(pin_memory=True) if host else dict(device="cuda")
+    pc, ps = torch.zeros(nbytes, dtype=torch.uint8, **where), torch.zeros(nscales, **where)
+    ids = torch.randperm(num + 50, device="cuda")[:num].to(torch.int32)
+    codes, floats = cache.view(torch.uint8).view(num + 50, -1), scales.view(num + 50, -1)
+
+    def move():
+        if to_packed:
+            kvq.blocks_export(cache, scales, desc, ids, pc, ps)
+        else:
+            kvq.blocks_import(pc, ps, desc, ids, cache, scales)
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        move()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        move()
+    for replay in range(3):
+        g = torch.Generator(device="cuda").manual_seed(replay)
+        ids.copy_(torch.randperm(num + 50, generator=g, device="cuda")[:num])
+        codes.copy_(torch.randint(0, 256, codes.shape, generator=g, device="cuda", dtype=torch.uint8))
+        floats.copy_(torch.rand(floats.shape, generator=g, device="cuda"))
+        pc.copy_(torch.randint(0, 256, pc.shape, generator=g, device="cuda", dtype=torch.uint8))
+        ps.copy_(torch.rand(ps.shape, generator=g, device="cuda"))
+        want_c, want_s = (codes[ids.long()], floats[ids.long()]) if to_packed else (pc.cuda(), ps.cuda())
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got_c, got_s = (pc.cuda(), ps.cuda()) if to_packed else (codes[ids.long()], floats[ids.long()])
+        assert torch.equal(got_c.view(num, -1), want_c.view(num, -1)), replay
+        assert torch.equal(got_s.view(num, -1), want_s.view(num, -1)), replay
