@@ -9,8 +9,9 @@ namespace {
 
 typedef uint32_t uintx4v __attribute__((ext_vector_type(4)));
 
-constexpr uint32_t kHostReadUnits = 256;    // 4 KiB pieces in flight from host memory
-constexpr uint32_t kHostWriteUnits = 2048;  // and those of a move to it that may all be in flight
+constexpr uint32_t kHostUnits = 256;        // 4 KiB pieces in flight from or to host memory, where they are bounded:
+constexpr uint32_t kHostReadAll = 320;      // in a move from it of more pieces than this
+constexpr uint32_t kHostWriteAll = 2048;    // and in one to it
 
 __global__ __launch_bounds__(256) void repack_kernel(const uint8_t* __restrict__ src,
                                                      uint8_t* __restrict__ dst, size_t total,
@@ -146,12 +147,14 @@ hipError_t launch_block_copy(const void* pool_cache, const float* pool_scales,
   uint32_t grid = units;
   // Read from host memory, more than about 1 MiB of requests at once slows the link down: 8.65 MB with a workgroup
   // for every unit (2112) 198 us, 1024 workgroups 181, 256 158, 64 with four requests a lane 161; a copy engine 160.
+  // (A few units more than are in flight cost a second round trip: 1.1 MB 28.1 us all at once and 29.4, 1.2 MB 30.3 and
+  // 31.7, 1.3 MB 32.7 both, 1.5 MB 37.7 and 35.5.)
   // Writes to host memory: up to 8 MiB the same (256 blocks of int8, 161 us and 165), above it 327 -> 309 us
   // (500 blocks of e4m3), 314 -> 300 (60 of bf16, 64 tokens).  Device memory needs all of them in flight.
-  if (units > (to_packed ? kHostWriteUnits : kHostReadUnits)) {
+  if (units > (to_packed ? kHostWriteAll : kHostReadAll)) {
     hipPointerAttribute_t where;
     if (hipPointerGetAttributes(&where, packed_cache) != hipSuccess) (void)hipGetLastError();  // (memory HIP does not know)
-    else if (where.type == hipMemoryTypeHost) grid = kHostReadUnits;
+    else if (where.type == hipMemoryTypeHost) grid = kHostUnits;
   }
 #define KVQ_LAUNCH_COPY(TO_PACKED, STRIDED)                                                               \
   hipLaunchKernelGGL((block_copy_kernel<TO_PACKED, STRIDED>), dim3(grid), dim3(256), 0, stream,           \

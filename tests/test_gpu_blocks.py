@@ -69,13 +69,14 @@ def test_no_blocks_is_a_no_op():
 
 
 @pytest.mark.parametrize("mode,H,D,bs,num", [
-    (W.MODE_INT8, 8, 128, 16, 31), (W.MODE_INT8, 8, 128, 16, 33),          # 248 and 264 pieces of 4 KiB around 256
+    (W.MODE_INT8, 8, 128, 16, 31), (W.MODE_INT8, 8, 128, 16, 33),          # 248 and 264 pieces of 4 KiB around 256,
+    (W.MODE_INT8, 8, 128, 16, 40), (W.MODE_INT8, 8, 128, 16, 41),          # 320 and 328
     (W.MODE_INT8, 8, 128, 16, 256), (W.MODE_INT8, 8, 128, 16, 257),        # 2048 and 2056
     (W.MODE_FP8, 3, 64, 16, 1100), (W.MODE_INT4_GROUP, 3, 128, 128, 90)])  # blocks of one piece and a half; many scales
 @pytest.mark.parametrize("host", [False, True], ids=["device", "pinned_host"])
 def test_more_pieces_than_are_in_flight_from_host_memory(mode, H, D, bs, num, host):
-    """Moves of around and beyond the pieces that a move from (256) or to (2048) host memory has in flight, by
-    the bytes of the blocks."""
+    """Moves of around and beyond the pieces that may all be in flight from (320) or to (2048) host memory, and the
+    256 that are in larger moves, by the bytes of the blocks."""
     import torch
     from paper_2605_29639_amd import kvq
     pool = num + 7
