@@ -1179,10 +1179,12 @@ hipError_t launch_pairs(const AttnArgs& a, hipStream_t stream) {
       return hipGetLastError();
     }
   }
-  if (MODE == KVQ_INT4_GROUP32 && a.rows <= 4)
-    launch_team<MODE, D, 1, 1, kOneTile, MODE == KVQ_INT4_GROUP32>(a, stream);
-  else  // (int4 has the registers for a second set, and 1 x 600 tokens takes 6.9 us with it, 7.5 without; the others +-3 %)
+  if constexpr (MODE == KVQ_INT4_GROUP32) {
+    if (a.rows <= 4) launch_team<MODE, D, 1, 1, kOneTile, true>(a, stream);
+    else launch_team<MODE, D, 1, 1, kOneTile>(a, stream);
+  } else {  // (int4 has the registers for a second set, and 1 x 600 tokens takes 6.8 us with it, 7.5 without; the others +-3 %)
     launch_team<MODE, D, 1, MODE == KVQ_INT4_TOKEN_HEAD ? 2 : 1, kOneTile>(a, stream);
+  }
   return hipGetLastError();
 }
 
