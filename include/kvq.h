@@ -186,10 +186,10 @@ size_t paged_decode_attn_workspace_bytes(const kvq_cache_desc_t* desc, int32_t b
  * hundreds for a chunk of a prompt attending over its quantized prefix and itself.  With 128
  * and more query rows per kv head ((num_q_heads / num_kv_heads) * q_len), and with fewer where
  * that is faster, the call runs a kernel of its own that dequantizes every K/V tile once for 128
- * rows (or another, for 256, where max_seq_len and the lengths are long; KVQ_INT4_GROUP32 has one of its own, used
- * where it is the faster one and chunk_tokens is 0); calls with too few such row blocks to fill the GPU split the context and merge the pieces
- * in a second kernel.  Otherwise the rows are taken 32 at a time, each such group streaming the
- * keys and values again.  Many rows are bound by arithmetic, not by HBM.
+ * rows (or another, for 256, where max_seq_len and the lengths are long; KVQ_INT4_GROUP32 has one
+ * of its own, used where it is the faster one and chunk_tokens is 0); calls with too few such row
+ * blocks to fill the GPU split the context and merge the pieces in a second kernel.  Otherwise the
+ * rows are taken 32 at a time, each such group streaming the keys and values again.  Many rows are bound by arithmetic, not by HBM.
  * Requires 1 <= q_len <= KVQ_MAX_Q_LEN and num_q_heads % num_kv_heads == 0. */
 int paged_decode_attn(const void* q, const void* cache, const float* scales,
                       const kvq_cache_desc_t* desc, const int32_t* block_tables,
@@ -217,11 +217,13 @@ int paged_decode_attn(const void* q, const void* cache, const float* scales,
  * from seq_lens), for every format but KVQ_INT4_GROUP32, with batch >= 2 and up to 32 query rows
  * per kv head; with 33 to 127 only where paged_decode_attn would not run its many-row kernel or,
  * up to 64, the prefix is at least half of max_seq_len (that kernel is faster without it).  Where
- * paged_decode_attn gives each (sequence, kv head) pair a workgroup, or the prefix is too small a part of the call's
- * work to be worth the first kernel (by an estimate from the host's arguments; not with a chunk_tokens of the
- * caller's), it is not used either.
- * Otherwise, and with shared_prefix_tokens < 64, the call is paged_decode_attn.  (Where the
- * device finds a sequence too short, the call has the same results up to the order of the merges.)
+ * paged_decode_attn gives each (sequence, kv head) pair a workgroup, or the prefix is too small a
+ * part of the call's work to be worth the first kernel (by an estimate from the host's arguments;
+ * not with a chunk_tokens of the caller's), it is not used either.
+ * Otherwise, and with shared_prefix_tokens < 64, the call is paged_decode_attn.  (The same results up
+ * to the order of the merges where the device finds a sequence too short, and where the many-row
+ * kernel runs with more than 64 rows or a prefix of less than half of max_seq_len, for which the
+ * larger workspace has room for more pieces; else bit for bit.)
  * shared_prefix_tokens < 0 is KVQ_E_BAD_SHAPE.
  *
  * workspace_bytes must be at least paged_decode_attn_prefix_workspace_bytes() for the same

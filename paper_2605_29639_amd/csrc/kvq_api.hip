@@ -212,32 +212,37 @@ bool group_rows(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t 
   return 1.35 * us <= 0.9 * streaming && 1.35 * cut_us <= 0.95 * streaming;
 }
 
-// Wavefronts of the workgroup that each (sequence, kv head, row group) pair gets in a call that does without the
-// flat list and the reduce, or 0.  The wavefronts of a pair take equal slices of its context and put their
-// sums together in LDS, so a second launch and a round trip of partials through memory fall away; what it
-// costs is that a compute unit's share is whole pairs, however few there are and however long.  All in
-// units of microseconds and 64-token groups, fitted to measurements with 1 to 60 sequences of 40 to
-// 8000 tokens, 8 kv heads, equal lengths: a group takes a wavefront `alone` where few compute units have one and
-// `crowded` where all have (memory, or for int4 and two row tiles arithmetic); beside that a workgroup per
-// pair takes 3.7 and the flat list with its reduce 8.3.  us a call, flat list -> workgroup per pair: 4 query heads
-// per kv head, int8, 1 x 600 tokens 8.4 -> 7.7, 12 x 1500 17.2 -> 12.7, 32 x 600 16.2 -> 10.1, 32 of 300 to
-// 2500 23.6 -> 20.5; 32 query rows, 31 x 600 26.2 -> 13.1; not taken: 12 x 4000 24.2 -> 27.4, 1 x 2500
-// 9.9 -> 13.6.  With more pairs than compute units a workgroup has half of the wavefronts, and two share one.
-// A long context among short ones keeps its own workgroup for as many `rounds` as a wavefront has groups, where
-// the flat list would spread it over the chip; so its walk may not take longer than the reduce and the partials
-// are worth, which is more the more rows they have (a wavefront's accumulators hold 16 rows, or 32, whose halves it
-// works on one after the other).  Of 16335 random calls with four to eight rounds, mixtures of long and short
-// among them: 15281 inside these lines, 0.57 of the flat list's time on average, 15 above 1.03 of it and none
-// above 1.08; 1054 beyond them, 86 above 1.03, up to 1.35 (e4m3, one row, 63 sequences of 40 to 1819 tokens,
-// 16.5 -> 22.2 us).
-double crowded_us(const kvq_cache_desc_t* d, int row_tiles) {  // (a group of a wavefront where all compute units have theirs)
+// Microseconds that a 64-token group takes a wavefront of the streaming kernel where all compute units have theirs
+// (bound by memory, for int4 and two row tiles by arithmetic).
+double crowded_us(const kvq_cache_desc_t* d, int row_tiles) {
   const bool small = d->head_dim == 64, bf16 = d->mode == KVQ_BF16_PLAIN;
   if (row_tiles == 2 && !bf16) return 2.65;
   if (d->mode == KVQ_INT4_TOKEN_HEAD) return 2.9;
   if (d->mode == KVQ_INT4_GROUP32) return 3.2;
   return small ? 2.65 : bf16 ? 4.6 : 5.0;
 }
-int32_t pair_waves(const kvq_cache_desc_t* d, int64_t pairs, int64_t rows, int64_t groups, int row_tiles, int64_t waves) {
+
+// Wavefronts of the workgroup that each (sequence, kv head, row group) pair gets in a call that does without the flat
+// list and the reduce, or 0.  The wavefronts of a pair take its groups in turn and put their sums together in LDS, so
+// a second launch and a round trip of partials through memory fall away; what it costs is that a compute unit's share
+// is whole pairs, however few there are and however long.  All in units of microseconds and 64-token groups, fitted
+// to measurements with 1 to 60 sequences of 40 to 8000 tokens, 8 kv heads, equal lengths, when a wavefront had a
+// slice of adjacent groups and began behind the sequence's length (the chain is up to 1 us shorter now, the lines are
+// where they were): a group takes a wavefront `alone` where few compute units have one and `crowded` where all have;
+// beside that a workgroup per pair takes 3.7 and the flat list with its reduce 8.3.  us a call, flat list ->
+// workgroup per pair: 4 query heads per kv head, int8, 1 x 600 tokens 8.6 -> 6.8, 12 x 1500 17.3 -> 12.8, 32 x 600
+// 16.1 -> 9.3, 32 of 300 to 2500 23.6 -> 20.8; 32 query rows, 31 x 600 26.6 -> 12.3; not taken: 12 x 4000 24.2 ->
+// 27.4, 1 x 2500 9.9 -> 13.6.  With more pairs than compute units a workgroup has half of the wavefronts, and two
+// share one.
+// A long context among short ones keeps its own workgroup for as many `rounds` as a wavefront has groups, where
+// the flat list would spread it over the chip; so its walk may not take longer than the reduce and the partials
+// are worth, which is more the more rows they have (a wavefront's accumulators hold 16 rows, or 32, whose halves it
+// works on one after the other).  Of 16335 random calls with four to eight rounds, mixtures of long and short among
+// them, measured with slices: 15281 inside these lines, 0.57 of the flat list's time on average, 15 above 1.03 of it
+// and none above 1.08; 1054 beyond them, 86 above 1.03, up to 1.35 (e4m3, one row, 63 sequences of 40 to 1819
+// tokens, 16.5 -> 22.2 us).  500 random calls of up to 2500 tokens with the present kernels: 0.65, 1.01 at most.
+int32_t pair_waves(const kvq_cache_desc_t* d, int64_t pairs, int64_t rows, int64_t groups, int row_tiles,
+                   int64_t waves) {
   const int per_simd = kvq::waves_per_simd(d->mode, d->head_dim, row_tiles);
   const int64_t cus = waves / 8;
   if (pairs < 1 || pairs > 2 * cus || groups < 1) return 0;
@@ -277,8 +282,8 @@ int32_t pair_waves(const kvq_cache_desc_t* d, int64_t pairs, int64_t rows, int64
 // with 2048, 35 of 1600, 56 rows, 36 and 45 with 1536; e4m3, 132 of 1100, 44 rows, 102 and 116 with 832.  160
 // random such calls: 0.91 of their time without a hint on average, 1.06 at most, and 0.77 of where every hint was
 // followed, 1.10 at most.
-bool prefix_pays(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t max_groups, int64_t slots, int64_t room,
-                 bool many, kvq::AttnPlan* plan) {
+bool prefix_pays(const kvq_cache_desc_t* d, int64_t batch, int64_t rows, int64_t max_groups, int64_t slots,
+                 int64_t room, bool many, kvq::AttnPlan* plan) {
   const int64_t groups = plan->shared_groups, stacked = batch * rows;
   const int64_t walks = d->num_kv_heads * ((stacked + kvq::kRowsPerWorkgroup - 1) / kvq::kRowsPerWorkgroup);
   const double partials = (double)stacked * d->num_kv_heads * d->head_dim * 4.0 / 2.1e6;
@@ -439,7 +444,8 @@ size_t workspace_bytes(const kvq::AttnPlan& plan) {
 // paged_decode_attn's, in a workspace of the hint's size; the promise stays, for the checks.
 bool call_plan(const kvq_cache_desc_t* d, int32_t batch, int32_t q_len, int32_t num_q_heads, int32_t max_seq_len,
                int32_t chunk_tokens, int32_t shared_prefix_tokens, kvq::AttnPlan* plan, size_t* need, int* err) {
-  if (!make_plan(d, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, shared_prefix_tokens, plan, err)) return false;
+  if (!make_plan(d, batch, q_len, num_q_heads, max_seq_len, chunk_tokens, shared_prefix_tokens, plan, err))
+    return false;
   *need = workspace_bytes(*plan);
   if (plan->shared_groups == 0 || plan->prefix_pays) return true;
   const int32_t promised = plan->promised_groups;

@@ -953,14 +953,15 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows64_kernel(con
 }
 
 // The same for group-scaled int4 (head_dim 128): a phase after the other, since the scales by channel group leave no
-// registers for more.  A step of QK^T contracts one group of 32 channels, and the logit is the four steps'
-// results weighted by the token's four K scales in fp32, as in the streaming kernel; P.V takes the
-// probabilities times the V scale of the group its channels belong to, worked out once a group for both of its channel
-// tiles.  Scales go to LDS by channel group, so that four tokens' come in one read.  Vector-bound: a logit
-// costs four multiply-adds, and four products and conversions behind the softmax, where the other formats have one and
-// half of one; what it spares is the conversion of all codes for every 16 rows.  One path behind the mask: with two copies of the
-// softmax, as above, 41 registers spilled and 8 x 512 tokens over 4608 took 630 us.  The same now 502, streaming
-// 1204; 1 x 512 over 16896 309 and 534, 64 sequences of 2000 to 4000, 128 rows, 231 and 433.
+// registers for more.  A step of QK^T contracts one group of 32 channels, and the logit is the four steps' results
+// weighted by the token's four K scales in fp32, as in the streaming kernel; P.V takes the probabilities times the V
+// scale of the group its channels belong to, worked out once a group for both of its channel tiles.  Scales go to LDS
+// by channel group, so that four tokens' come in one read.  Vector-bound: a logit costs four multiply-adds, and four
+// products and conversions behind the softmax, where the other formats have one and half of one; what it spares is
+// the conversion of all codes for every 16 rows.  One path behind the mask: with two copies of the softmax, as above,
+// 41 registers spilled and 8 x 512 tokens over 4608 took 630 us.  The same now 502, streaming 1204; 1 x 512 over
+// 16896, in the two pieces that the workspace has room for, 256 workgroups of the 512 that fit, 309 and 534; 64
+// sequences of 2000 to 4000, 128 rows, 231 and 433.
 __global__ __launch_bounds__(64 * kWavesPerGroup, 2) void attn_rows_group_kernel(const AttnArgs p) {
   constexpr int NT = 2, D = 128, RB = D / 2, DT = D / 16, KS = D / 32;
   constexpr int MODE = KVQ_INT4_GROUP32;

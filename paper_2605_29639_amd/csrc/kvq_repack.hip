@@ -102,10 +102,10 @@ __global__ __launch_bounds__(256) void repack16_kernel(const uint16_t* __restric
   }
 }
 
-// Whole blocks between the pool and a packed staging area.  A unit is one 4 KiB piece of one block's codes
-// (16 bytes per lane) and, as far as there are any, 256 of the block's scales (one a lane: no format has more than
-// four bytes of scales to 16 of codes), both requested before either is stored.  Non-temporal on both sides: every byte is touched
-// once.  (With a block's scales in a loop of its first workgroup, 47 blocks of 128 tokens under group-scaled
+// Whole blocks between the pool and a packed staging area.  A unit is one 4 KiB piece of one block's codes (16 bytes
+// per lane) and, as far as there are any, 256 of the block's scales (one a lane: no format has more than four bytes
+// of scales to 16 of codes), both requested before either is stored.  Non-temporal on both sides: every byte is
+// touched once.  (With a block's scales in a loop of its first workgroup, 47 blocks of 128 tokens under group-scaled
 // int4, 4096 scales each, took 8.0 us, now 3.6.)
 // STRIDED: fewer workgroups than units.
 template <bool TO_PACKED, bool STRIDED>

@@ -88,8 +88,8 @@ __device__ inline float bf16_of(const Piece<D>& raw, int e) {  // element e of t
 // that each store instruction fills whole quads; for V rows 4 g + i, so that the lane's codes of a
 // channel are adjacent in that channel's 16-token row.
 // Rows r_lo .. r_hi - 1 of the sub-block are the run's tokens (all 16 for a whole sub-block);
-// `src` is where row r_lo's token lies; the other rows are not read.  (Every row is read once: the
-// loads are non-temporal, which makes the prompt kernels 3-4 % faster.)
+// `src` is where row r_lo's token lies; the other rows are not read.  (The prompt kernels read
+// every row once: the loads are non-temporal, which makes them 3-4 % faster.)
 template <int D>
 __device__ inline void load_subblock(const uint16_t* __restrict__ src, size_t tstride, int kv,
                                      int lane, int r_lo, int r_hi, Piece<D> (&raw)[4]) {
@@ -951,11 +951,11 @@ __global__ __launch_bounds__(kWaves * 64) void write_window_kernel(
   }
 }
 
-// Decode steps and small chunks: unit = (token, kv head, K|V); the wavefront of a run's first token
-// does the run (block-scaled fp8, whose runs are longer than a sub-block: that of a sub-block's first does the sub-block).  A decode step is a chain of round trips behind a launch: the token's row is
-// requested together with the slots (lane i holds the slot of token t0 - 1 + i).  Most wavefronts of a chunk end
-// there, so what counts is how many are resident: eight to a SIMD (64 registers).  Block-scaled fp8 took 72: 225
-// runs of four tokens 16.9 us, now 11.6.
+// Decode steps and small chunks: unit = (token, kv head, K|V); the wavefront of a run's first token does the run
+// (block-scaled fp8, whose runs are longer than a sub-block: that of a sub-block's first does the sub-block).  A
+// decode step is a chain of round trips behind a launch: the token's row is requested together with the slots (lane i
+// holds the slot of token t0 - 1 + i).  Most wavefronts of a chunk end there, so what counts is how many are
+// resident: eight to a SIMD (64 registers).  Block-scaled fp8 took 72: 225 runs of four tokens 16.9 us, now 11.6.
 template <int MODE, int D>
 __global__ __launch_bounds__(kWaves * 64, 8) void write_run_kernel(
     const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -1020,14 +1020,14 @@ __global__ __launch_bounds__(kWaves * 64, 8) void write_run_kernel(
     }
     run += back;
     if (run > 1) {
-      // A wavefront per sub-block of the run (that of the sub-block's first token), unless the scale grows over older
-      // codes.  The scale needs the absmax of the whole run, which each of them takes for itself, two sub-blocks requested at
-      // a time: all of it is small, and nobody waits for anybody.  A scale read when another of the run's
-      // wavefronts has stored the new one already gives the new one again.  (One wavefront for the run, sub-block
-      // after sub-block: 500 tokens of 8 heads x 128 in blocks of 32, 64 and 128 tokens 10.8, 18.6 and 24.5 us,
-      // now 9.5, 11.2 and 15.8; 120 tokens 5.8, 9.2 and 13.1, now 4.8, 5.4 and 7.4.  Four sub-blocks requested at a
-      // time are faster alone, 12.0 for 500 in blocks of 128, and take the registers of a third of the wavefronts: 900 in
-      // blocks of 32 10.4 -> 13.6.)
+      // A wavefront per sub-block of the run (that of the sub-block's first token), unless the scale grows
+      // over older codes.  The scale needs the absmax of the whole run, which each of them takes for itself,
+      // two sub-blocks requested at a time: all of it is small, and nobody waits for anybody.  A scale read
+      // when another of the run's wavefronts has stored the new one already gives the new one again.  (One
+      // wavefront for the run, sub-block after sub-block: 500 tokens of 8 heads x 128 in blocks of 32, 64 and
+      // 128 tokens 10.8, 18.6 and 24.5 us, now 9.5, 11.2 and 15.8; 120 tokens 5.8, 9.2 and 13.1, now 4.8, 5.4
+      // and 7.4.  Four sub-blocks requested at a time are faster alone, 12.0 for 500 in blocks of 128, and
+      // take the registers of a third of the wavefronts: 900 in blocks of 32 10.4 -> 13.6.)
       const int o_min = off - back, first_sb = o_min >> 4, last_sb = (o_min + run - 1) >> 4;
       const uint16_t* run_src = src - (size_t)back * tstride;
       auto rows_of = [&](int sb, Piece<D> (&raw)[4], int& r_lo, int& r_hi) {
